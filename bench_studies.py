@@ -17,7 +17,7 @@ def ablations(torch, spqt, use_graph, cpu):
     half of K), three kernels: list-balanced (spqt_gather + spqt_gemv), static column ranges
     with in-kernel test and compaction (spqt_gemv_fused), the same without compaction, and the one-launch
     kernel that counts the kept columns first and splits them evenly (SPQT_CFG_EVEN_SHARES).  Also the
-    list-balanced kernel with one-group passes instead of row-aligned ones (SPQT_CFG_GROUP_PASSES)."""
+    list-balanced kernel with one-group passes (SPQT_CFG_GROUP_PASSES)."""
     import numpy as np
     from workloads import CONFIG_SCALE_RANGE
     M, K, s = 28672, 8192, 0.5

@@ -164,11 +164,10 @@ typedef struct {
 #define SPQT_CFG_Y_FP16 4
 
 /* spqt_gemv_ex with an index list and one activation row only - an ablation of how the list is
- * consumed.  By default a pass of 64 column slots is 8 rows of 8 slots and only a ROW must hold
- * columns of one quantization group, so a group boundary wastes the rest of a row.  With this flag
- * the kernel that serves several activation rows is used: a whole pass holds columns of ONE group
- * (its 8 column-lanes are folded before the scale is applied), so a group boundary wastes the rest
- * of a pass - at 50 % sparsity nearly half of the slots.  Same results up to rounding order. */
+ * consumed.  By default a pass of 64 column slots takes the next entries of the list from up to 4
+ * quantization groups.  With this flag a whole pass holds columns of ONE group, so a group boundary
+ * wastes the rest of a pass - at 50 % sparsity nearly half of the slots.  Same results up to
+ * rounding order. */
 #define SPQT_CFG_GROUP_PASSES 8
 
 /* DEVICE, async.  y[b][m] = sum over the listed columns k of scale[m][k/group] * q[m][k] *
@@ -255,7 +254,8 @@ int spqt_gemv_fused_rows(const void *packed_dev, int64_t M, int64_t K, int group
                          size_t workspace_bytes, void *stream, const spqt_launch_cfg *cfg);
 
 /* The launch shape spqt_gemv would pick for this shape (host only, no device access): sparse != 0
- * for a call with an index list, 0 for the dense kernel. */
+ * for a call with an index list, 0 for the dense kernel.  (With 3 or 4 activation rows a shape of more
+ * than 256 workgroups runs as at most 256 workgroups of 8 wavefronts, which needs no more exchange words.) */
 int spqt_default_cfg(int64_t M, int64_t K, int batch, int sparse, spqt_launch_cfg *out);
 
 #ifdef __cplusplus

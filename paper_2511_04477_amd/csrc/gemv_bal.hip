@@ -16,18 +16,19 @@
 //      them, into a ring of (column, x) pairs in LDS: an exclusive scan of the lanes' kept counts ranks the
 //      kept columns, and an entry whose rank falls inside the share is written at rank - share start.
 //      The next step's x is requested one refill ahead, so no pass ever waits on a dependent global read.
-//   4. GEMV.  Row-aligned passes over the ring exactly as gemv_list.hip forms them over idx (rowpass.hpp),
+//   4. GEMV.  Passes over the ring exactly as gemv_list.hip forms them over idx (pass.hpp),
 //      same two-stage pipeline, same exchange between the workgroups of a block-row; for the same launch
 //      shape the two kernels perform the same arithmetic in the same order.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "rowpass.hpp"
+#include "pass.hpp"
 
 namespace {
 
 using namespace spqt;
 
+constexpr int kGroups = groups_per_pass(1);
 constexpr int kStepCols = 512;            // columns one wavefront step thresholds: 8 per lane
 constexpr int kXsSteps = 64;              // steps of x kept in LDS: K <= 32768 (larger K: static column ranges)
 constexpr int kPackSteps = 3;             // step counts packed in one 32-bit word (10 bits each, a count is <= 512)
@@ -93,9 +94,7 @@ template <int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
     const uint8_t *__restrict__ packed, const uint16_t *__restrict__ x, float thr, float *__restrict__ y,
     void *partials, int32_t *ws_flags, int K, int NG, int S, int T, int M) {
-    __shared__ __attribute__((aligned(16))) uint32_t stage_off[WAVES][2][kPassCols];   // byte offset of each slot's column in the block-row
-    __shared__ __attribute__((aligned(16))) uint16_t stage_x[WAVES][2][8][8];          // x of each slot, [row][slot in row]
-    __shared__ int32_t stage_grp[WAVES][2][8];                                         // group of each row
+    __shared__ __attribute__((aligned(16))) StagedX staged[WAVES];
     __shared__ __attribute__((aligned(16))) float red[WAVES][1][kTileRows];
     // kept columns per step: word [w][q][row of 16 lanes] holds, 10 bits each, that row's counts of the steps
     // w + WAVES * (3 q + r), r = 0..2 (the steps wavefront w thresholds, three at a time)
@@ -107,17 +106,11 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int cg = lane >> 3;      // row of the pass this lane reads
-    const int seg = lane & 7;      // 32-row segment of the tile this lane reads
-    const int cgr = ((cg & 1) << 2) | (cg & 2) | (cg >> 2);   // cg with its three bits reversed
-    const uint32_t seg16 = (uint32_t)seg * 16u;
-    const uint64_t upto = (2ull << lane) - 1ull;              // bits 0..lane
-    // all S workgroups of a block-row on one XCD (same index mod 8), as in gemv.hip
-    const int xcd = blockIdx.x & 7;
-    const int slot_x = blockIdx.x >> 3;
-    const int t = xcd + 8 * (slot_x / S);
-    const int s = slot_x % S;
-    if (t >= T) return;
+    const int n = lane & 15;       // 16-row segment of the block-row this lane reads
+    const uint32_t n8 = (uint32_t)n * 8u;
+    const uint32_t out4 = (uint32_t)(4 * n + (lane >> 4));    // the lane's 4 outputs: rows 4 out4 .. 4 out4 + 3
+    int t, s;
+    if (!block_of((int)blockIdx.x, S, T, t, s)) return;
 
     // 1. COUNT: x into LDS, then the kept columns of every 512-column step (every workgroup does all of x).
     const int nsteps = (K + kStepCols - 1) / kStepCols;      // <= kXsSteps (checked on the host)
@@ -169,12 +162,10 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
     const int total = (int)(((uint32_t)n_ns * (uint32_t)(part + 1)) / (uint32_t)parts) - begin;
 
     const int log2g = (NG << 7) == K ? 7 : 6;
-    const int chunk_b = kScaleBytes + (kColBytes << log2g);
+    const uint32_t chunk_b = (uint32_t)(kScaleBytes + (kColBytes << log2g));
     const uint8_t *row_base = packed + (size_t)t * NG * chunk_b;
 
-    float acc[32];   // rows 32 seg + i of the block-row, this lane's rows of the passes, scaled, in units of 2^-24 (even i) or 2^-20 (odd i)
-#pragma unroll
-    for (int i = 0; i < 32; ++i) acc[i] = 0.0f;
+    float acc[1][4] = {{0.0f, 0.0f, 0.0f, 0.0f}};   // rows 4 out4 + p of the block-row, scaled, in the products' units
 
     if (total > 0) {
         // the step in which rank `begin` lies, and the kept columns before that step
@@ -216,92 +207,72 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
             return e < total ? (int)(v & 0xFFFFu) : -1;
         };
 
-        // FETCH stage of the pass that starts at entry p < total: deal the entries to rows, request the
-        // pass's weights and its rows' scales.
-        auto fetch = [&](int p, int slot, u32x4(&w)[8], u32x4(&sc)[4], int &n_out, bool &hi_out, uint32_t &xraw,
-                         int &where) {
-            const int kk = fetch_k(p, xraw);
-            const RowDeal d = deal_rows(kk, log2g, lane, upto);
-            where = d.take ? d.row * 8 + d.col : -1;
-            hi_out = d.hi;
-            const uint32_t off_own = (uint32_t)d.g * (uint32_t)chunk_b + (uint32_t)(kk & ((1 << log2g) - 1)) * kColBytes;
-            // Slots no entry lands in point at the pass's first column (a line that is fetched anyway)
-            // and carry x = 0; rows no entry lands in take the first row's group.
+        uint32_t off;              // the same state and stages as in gemv_list.hip, with the ring in the place of idx
+        uint64_t starts;
+        int g, j;
+        uint32_t xraw[1];
+        auto head = [&](int p) -> int {
+            const int kk = fetch_k(p, xraw[0]);
+            g = kk >> log2g;
+            const Deal d = deal_groups<kGroups>(kk, g, lane);
+            const uint32_t off_own = (uint32_t)g * chunk_b + (uint32_t)(kk & ((1 << log2g) - 1)) * kColBytes;
             const uint32_t off_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)off_own);
-            const int g_first = __builtin_amdgcn_readfirstlane(d.g);
-            stage_off[wave][slot][lane] = off_first;
-            if (lane < 8) stage_grp[wave][slot][lane] = g_first;
-            __builtin_amdgcn_wave_barrier();
-            if (d.take) {
-                stage_off[wave][slot][where] = off_own;
-                if (d.col == 0) stage_grp[wave][slot][d.row] = d.g;
-            }
-            __builtin_amdgcn_wave_barrier();
-            const u32x4 o0 = *reinterpret_cast<const u32x4 *>(&stage_off[wave][slot][cg * 8]);
-            const u32x4 o1 = *reinterpret_cast<const u32x4 *>(&stage_off[wave][slot][cg * 8 + 4]);
-            const int grow = stage_grp[wave][slot][cg];
-            const uint8_t *wp = row_base + kScaleBytes + seg16;
-            w[0] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(wp + (size_t)o0.x));
-            w[1] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(wp + (size_t)o0.y));
-            w[2] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(wp + (size_t)o0.z));
-            w[3] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(wp + (size_t)o0.w));
-            w[4] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(wp + (size_t)o1.x));
-            w[5] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(wp + (size_t)o1.y));
-            w[6] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(wp + (size_t)o1.z));
-            w[7] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(wp + (size_t)o1.w));
-            // the 32 scales of rows 32 seg .. 32 seg + 31 for this lane's row of the pass
-            const u32x4 *scp = reinterpret_cast<const u32x4 *>(row_base + (size_t)grow * chunk_b + (size_t)seg * 64);
+            off = d.take ? off_own : off_first;
+            starts = d.starts;
+            j = d.take ? d.j : -1;
+            return p + d.n;
+        };
+        auto load_scales = [&](u32x2(&sc)[kGroups]) {
+            uint64_t left = starts;
+            int at = 0;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) sc[i] = scp[i];
-            n_out = d.n;
+            for (int i = 0; i < kGroups; ++i) {
+                at = left ? (int)__builtin_ctzll(left) : at;
+                left &= left - 1ull;
+                const uint32_t gi = (uint32_t)__builtin_amdgcn_readlane(g, at);
+                sc[i] = *reinterpret_cast<const u32x2 *>(row_base + (size_t)(gi * chunk_b) + (size_t)(out4 * 8u));
+            }
         };
 
-        // MULTIPLY stage of a fetched pass: x goes to its slots, then the shared row-pass multiply.
-        auto multiply = [&](int slot, u32x4(&w)[8], u32x4(&sc)[4], bool hi, uint32_t xraw, int where) {
-            if (lane < 32) reinterpret_cast<uint32_t *>(&stage_x[wave][slot][0][0])[lane] = 0u;
-            __builtin_amdgcn_wave_barrier();
-            if (where >= 0) (&stage_x[wave][slot][0][0])[where] = (uint16_t)xraw;
-            __builtin_amdgcn_wave_barrier();
-            const u32x4 xa = *reinterpret_cast<const u32x4 *>(&stage_x[wave][slot][cg][0]);
-            multiply_row_pass(w, sc, xa, hi, lane, acc);
-            __builtin_amdgcn_wave_barrier();
-        };
-
-        // 4. GEMV: two-stage software pipeline over the passes, buffers A and B alternating.
-        u32x4 wA[8], wB[8], scA[4], scB[4];
-        uint32_t xrA, xrB;
-        int nA, nB, whA, whB;
-        bool hiA, hiB;
-        int pos = 0;
-        fetch(pos, 0, wA, scA, nA, hiA, xrA, whA);
+        // 4. GEMV: the passes of gemv_list.hip
+        const uint8_t *columns = row_base + kScaleBytes;
+        u32x2 w[16], sc[kGroups];
+        u32x4 x0, x1;
+        f32x4 d[4];
+        int turn = part;
+        int pos = head(0);
         SPQT_TL(2);
+        load_columns<0, 16>(columns, off, n8, w);
+        load_scales(sc);
         SPQT_TL_WAIT(3);
-        for (;;) {
-            const int posB = pos + nA;
-            if (posB >= total) {
-                multiply(0, wA, scA, hiA, xrA, whA);
-                break;
-            }
-            fetch(posB, 1, wB, scB, nB, hiB, xrB, whB);
-            multiply(0, wA, scA, hiA, xrA, whA);
-            const int posA = posB + nB;
-            if (posA >= total) {
-                multiply(1, wB, scB, hiB, xrB, whB);
-                break;
-            }
-            fetch(posA, 0, wA, scA, nA, hiA, xrA, whA);
-            multiply(1, wB, scB, hiB, xrB, whB);
-            pos = posA;
+        while (pos < total) {
+            stage_x<1, kGroups>(staged[wave], lane, lane, j, j >= 0, negated(turn), xraw);
+            pos = head(pos);
+            keep_order();
+            start_products(staged[wave], lane, x0, x1, d);
+            half_pass<0>(w, x0, lane, d);
+            keep_order();
+            load_columns<0, 8>(columns, off, n8, w);
+            keep_order();
+            half_pass<1>(w, x1, lane, d);
+            keep_order();
+            load_columns<8, 16>(columns, off, n8, w);
+            keep_order();
+            add_scaled<1, kGroups>(d, sc, negated(turn), acc);
+            load_scales(sc);
+            ++turn;
+            keep_order();
         }
+        stage_x<1, kGroups>(staged[wave], lane, lane, j, j >= 0, negated(turn), xraw);
+        start_products(staged[wave], lane, x0, x1, d);
+        half_pass<0>(w, x0, lane, d);
+        half_pass<1>(w, x1, lane, d);
+        add_scaled<1, kGroups>(d, sc, negated(turn), acc);
     }
     SPQT_TL(4);
 
-    // the 8 column-lanes are folded: lane (cg, seg) ends with rows 32 seg + 4 rev(cg) + j (the fold only adds
-    // rows whose index is equal mod 4, so odd and even rows stay apart), then back to true units
-    float r4[4];
-    fold_columns(acc, r4);
-    reinterpret_cast<f32x4 *>(red[wave][0])[8 * seg + cgr] =
-        f32x4{r4[0] * kTwo24, r4[1] * (kTwo24 * 0.0625f), r4[2] * kTwo24, r4[3] * (kTwo24 * 0.0625f)};
+    reinterpret_cast<f32x4 *>(red[wave][0])[out4] = f32x4{acc[0][0] * kEvenUnit, acc[0][1] * kOddUnit,
+                                                         acc[0][2] * kEvenUnit, acc[0][3] * kOddUnit};
     __syncthreads();
     SPQT_TL(5);
     combine_block_row<WAVES, 1>(&red[0][0][0], tid, t, s, S, partials, ws_flags, y, M);

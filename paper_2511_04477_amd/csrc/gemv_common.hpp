@@ -1,6 +1,6 @@
-// Device helpers shared by the GEMV kernels (gemv.hip, gemv_cb.hip): the int4 multiply step,
-// the transposing lane folds, wave sums, and the exchange of partial sums between the
-// workgroups of a block-row.  Not part of the C ABI.
+// Device helpers shared by the GEMV kernels: the int4 multiply step and the transposing lane folds of the
+// column-block kernels, the placement of workgroups, and the exchange of partial sums between the workgroups of a
+// block-row.  Not part of the C ABI.
 #ifndef SPQT_GEMV_COMMON_HPP
 #define SPQT_GEMV_COMMON_HPP
 
@@ -12,12 +12,11 @@
 namespace spqt {
 
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kPassCols = 64;                  // most columns one pass covers (8 steps)
+constexpr int kPassCols = 64;                  // most columns one pass covers
 constexpr float kTwo24 = 16777216.0f;          // 2^24: undoes the fp16 subnormal exponent
 constexpr int kHalfOutputBit = 1 << 30;        // in the kernels' M argument: y is fp16, not fp32
 constexpr int kOwnSetsBit = 1 << 29;           // in the kernels' M argument: every activation row keeps its own set
@@ -73,7 +72,6 @@ __device__ __forceinline__ float half_bits_to_float(uint32_t h16) {
 __device__ __forceinline__ float as_float(uint32_t bits) { return __builtin_bit_cast(float, bits); }
 __device__ __forceinline__ uint32_t as_u32(float f) { return __builtin_bit_cast(uint32_t, f); }
 __device__ __forceinline__ f16x2 as_f16x2(uint32_t bits) { return __builtin_bit_cast(f16x2, bits); }
-__device__ __forceinline__ f16x4 as_f16x4(u32x2 bits) { return __builtin_bit_cast(f16x4, bits); }
 
 // Eight codes of one dword: acc[i] (+)= n_i * x for nibble i (row 8d+i of the lane's 32 rows).
 // xlo = x * 2^24 pairs with nibbles sitting at bits 0..3 of a half, xhi = x * 2^20 with
@@ -172,18 +170,6 @@ __device__ __forceinline__ float dpp_move(float v) {
     return as_float(__builtin_amdgcn_update_dpp(0u, as_u32(v), CTRL, 0xf, 0xf, false));
 }
 
-// Sum over the 64 lanes, returned in every lane: xor-butterfly inside rows of 16 with DPP
-// (quad permutes, half-row and row mirrors), then across rows with the permlane swaps.
-__device__ __forceinline__ float wave_sum(float v) {
-    v += dpp_move<0xB1>(v);    // quad_perm [1,0,3,2]: lane ^ 1
-    v += dpp_move<0x4E>(v);    // quad_perm [2,3,0,1]: lane ^ 2
-    v += dpp_move<0x141>(v);   // row_half_mirror: the other quad of the 8
-    v += dpp_move<0x140>(v);   // row_mirror: the other half of the row
-    v = fold16(v, v);
-    v = fold32(v, v);
-    return v;
-}
-
 // Sum over the 8 lanes that read the same rows of a column run (lanes seg, seg + 8, ..., seg + 56).
 __device__ __forceinline__ float sum_over_columns(float v) {
     v += dpp_move<0x128>(v);   // row_ror:8 - the lane 8 further inside the row of 16
@@ -192,30 +178,45 @@ __device__ __forceinline__ float sum_over_columns(float v) {
     return v;
 }
 
-// Matrix-core B operands for 4 consecutive rows of W at 4 columns.  w0..w3 are the same dword of 4
-// steps (4 columns, 8 rows each); HALF picks rows 0..3 or 4..7 of the dword.  One v_perm_b32 puts the
-// same 16 bits of two columns side by side; masked in place, b[p] holds row p's code at the 4
-// columns as fp16 subnormals: code * 2^-24 for p = 0, 2 and 16 * code * 2^-24 for p = 1, 3.
-template <int HALF>
-__device__ __forceinline__ void code_rows(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, u32x2 (&b)[4]) {
-    constexpr uint32_t sel = HALF ? 0x07060302u : 0x05040100u;
-    const uint32_t t01 = __builtin_amdgcn_perm(w1, w0, sel);
-    const uint32_t t23 = __builtin_amdgcn_perm(w3, w2, sel);
-    const uint32_t s01 = t01 >> 8, s23 = t23 >> 8;
-    b[0] = u32x2{t01 & 0x000F000Fu, t23 & 0x000F000Fu};
-    b[1] = u32x2{t01 & 0x00F000F0u, t23 & 0x00F000F0u};
-    b[2] = u32x2{s01 & 0x000F000Fu, s23 & 0x000F000Fu};
-    b[3] = u32x2{s01 & 0x00F000F0u, s23 & 0x00F000F0u};
-}
-
 // The one-launch kernel for one activation row: list built in the kernel, even shares (gemv_bal.hip).
 hipError_t launch_gemv_bal(int waves, int grid, hipStream_t stream, const uint8_t *packed, const uint16_t *x, float thr,
                            float *y, void *partials, int32_t *ws_flags, int K, int NG, int S, int T, int m_and_flags);
 
-// The index-list kernel for one activation row with row-aligned passes (gemv_list.hip).
-hipError_t launch_gemv_list(int waves, int grid, hipStream_t stream, const uint8_t *packed, const uint16_t *x,
-                            const int32_t *idx, const int32_t *count, float *y, void *partials, int32_t *ws_flags,
-                            int K, int NG, int S, int T, int m_and_flags);
+// The index-list and dense kernels (gemv_list.hip); idx == nullptr: dense.  one_group: passes of one quantization group.
+struct ListLaunch {
+    const uint8_t *packed;
+    const uint16_t *x;
+    const int32_t *idx, *count;
+    float *y;
+    void *partials;
+    int32_t *ws_flags;
+    int K, NG, S, T, m_and_flags;
+};
+hipError_t launch_gemv_list(int waves, int batch, bool one_group, int grid, hipStream_t stream, const ListLaunch &a);
+
+// Which workgroup of which block-row a launch index is.  Workgroups go to the 8 XCDs round-robin by index; the S workgroups
+// of a block-row are kept on ONE XCD as far as that leaves the XCDs equally loaded: block-rows in multiples of 8 go to the
+// XCDs whole, and the workgroups of the T % 8 that are left are spread over the XCDs evenly (with 20 block-rows, whole
+// ones would give four XCDs 3 and four 2: 5120 x 13824 dense, 12 workgroups per block-row, 13.1 us, evenly 10.4).  A
+// spread block-row's reducer may run before producers on another XCD are dispatched; there are at most 8 such rows, and
+// every other workgroup of the launch finishes without them, so they always get their turn.
+// Returns false for the padding of the grid (grid_blocks).
+__device__ __forceinline__ bool block_of(int index, int S, int T, int &t, int &s) {
+    const int xcd = index & 7;
+    const int slot = index >> 3;               // position among this XCD's workgroups
+    const int whole = (T >> 3) * S;            // workgroups of whole block-rows per XCD
+    if (slot < whole) {
+        t = xcd + 8 * (slot / S);
+        s = slot % S;
+        return true;
+    }
+    const int left = (T & 7) * S;
+    const int per_xcd = (left + 7) >> 3;
+    const int r = xcd * per_xcd + slot - whole;
+    t = (T & ~7) + r / S;
+    s = r % S;
+    return slot - whole < per_xcd && r < left;
+}
 
 // Combine the S workgroups of block-row t (paper Section 4.2.2: the partial sums of the
 // threadgroups that share a superblock row are reduced once at the end, without atomics on y).

@@ -1,0 +1,176 @@
+// One pass of the group-layout GEMV kernels: up to 64 columns of a block-row, 128 bytes each, multiplied on the
+// matrix cores for 1..4 activation rows.  Shared by gemv_list.hip (index list, dense), gemv.hip (one launch, static
+// column ranges) and gemv_bal.hip (one launch, even shares).
+//
+// Slots: entry e of a pass sits in slot (c, u) = (e / 16, e % 16).  In step u the 16 lanes of quarter c of the
+// wavefront read the 128-byte run of column (c, u), 8 bytes each: lane l holds rows 16 n .. 16 n + 15 of the block-row,
+// n = l % 16, at the 16 columns of its quarter.  The lane that owns entry e is lane e, i.e. a column's offset is
+// known in the very quarter that reads it, so it reaches the other 15 lanes by DPP (row_newbcast), not through LDS.
+//
+// Products: v_mfma_f32_16x16x32_f16 computes D[m][n] += sum over 32 k of A[m][k] * B[k][n]; lane l brings A[l % 16] and
+// B[..][l % 16] at the 8 k of quarter l / 16, i.e. at 8 of the 16 columns of its quarter.  B is ONE row's codes at those
+// columns (fp16 subnormals, code * 2^-22 or 2^-18, shifted and masked after one v_perm_b32), A the raw fp16 x.
+// The sum over k is the sum over all columns of the pass, so nothing is left to fold across lanes.
+// The 16 rows of A are 4 v + j: v (four variants of A, zero in the other rows) says which four of the lane's 16 rows of
+// W the product belongs to, so that all 16 rows end up in FOUR accumulator tuples D[p], and j = 0..3 separates
+// activation rows and quantization groups (j = group of the pass * rows + activation row): one activation row takes
+// columns of up to 4 groups per pass, two rows 2 groups, three or four rows one.  Lane (v, n) = (l / 16, l % 16) ends
+// up with rows 16 n + 4 v + p, p = 0..3, in D[p][j]; the group's scale is applied there and the lane's 4 outputs per
+// activation row are all that is carried from pass to pass.
+//
+// Why this form: with 4-wide products (v_mfma_f32_4x4x4) a lane keeps 32 sums per activation row that must be folded
+// over 8 lanes - per pass, when a pass is one group, or once per slice at the price of 32 scales per lane and pass.
+// That took 244 VGPRs for 4 rows and 218 for one (two wavefronts per SIMD) and made the kernels issue-bound.  Measured before
+// and after (us, HIP graph, weights cold): index list at 50 %, one row 14336 x 4096 9.0 / 7.8, 28672 x 8192 16.6 / 15.6; 4 rows
+// at 70 % 14336 x 4096 18.3 / 13.5, 28672 x 8192 32.9 / 27.0; one launch, 2 rows at 65 %, 28672 x 8192 25.1 / 20.0; dense
+// 5120 x 13824 13.3 / 10.0 (half of that from the launch shape).  What bounds them now: the fixed cost of a launch (start,
+// first weights, exchange: about 5 us) on small matrices, HBM on large ones (28672 x 8192 dense: 5.3 TB/s).
+#ifndef SPQT_PASS_HPP
+#define SPQT_PASS_HPP
+
+#include "gemv_common.hpp"
+
+namespace spqt {
+
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ f16x8 as_f16x8(u32x4 bits) { return __builtin_bit_cast(f16x8, bits); }
+
+// What undoes the units of the products: a code at bits 2..5 of an fp16 half is code * 2^-22, at bits 6..9 code * 2^-18.
+constexpr float kEvenUnit = 4194304.0f, kOddUnit = 262144.0f;
+
+// activation rows as the passes count them (3 is treated as 4 with a zero row), and quantization groups per pass
+constexpr int padded_rows(int batch) { return batch == 3 ? 4 : batch; }
+constexpr int groups_per_pass(int batch) { return 4 / padded_rows(batch); }
+
+// x of the 64 slots of a pass as fp16, [j][slot] with j as above; row 4 takes what no product reads.
+struct StagedX {
+    uint16_t v[5][kPassCols];
+    uint16_t pad[8];   // a multiple of 16 bytes per wavefront
+};
+
+// Keeps the compiler from moving instructions across: it would gather the refills behind the products.
+__device__ __forceinline__ void keep_order() { __builtin_amdgcn_sched_barrier(0); }
+
+// v of lane U of the caller's row of 16 lanes, in every lane of the row.
+template <int U>
+__device__ __forceinline__ uint32_t row_lane(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + U, 0xf, 0xf, true);
+}
+
+// Requests the weights of slots u = FROM .. TO - 1 of a pass: off = byte offset (from base) of the column run of the entry
+// this lane owns, n8 = 8 * (lane % 16).
+template <int FROM, int TO>
+__device__ __forceinline__ void load_columns(const uint8_t *base, uint32_t off, uint32_t n8, u32x2 (&w)[16]) {
+    w[FROM] = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(base + (size_t)(row_lane<FROM>(off) + n8)));
+    if constexpr (FROM + 1 < TO) load_columns<FROM + 1, TO>(base, off, n8, w);
+}
+
+// Products of the 32 slots (c, u), u = 8 SET .. 8 SET + 7: d[p][j] += sum of code(row 16 n + 4 v + p, slot) * x(j, slot)
+// in units of kEvenUnit (even p) or kOddUnit (odd p).  xa = the lane's x of those slots: row j = lane % 4 of the staged x,
+// quarter lane / 16.
+// A code sits at bits 2..5 or 6..9 of its half, not at 0..3 or 4..7 (which would save one shift in six instructions): the
+// matrix cores align products by the exponent FIELDS, so bits that a subnormal has above its code are bits of
+// precision lost in every product.
+template <int SET>
+__device__ __forceinline__ void half_pass(const u32x2 (&w)[16], u32x4 xa, int lane, f32x4 (&d)[4]) {
+    const int variant = (lane >> 2) & 3;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const bool mine = variant == v;
+        const f16x8 a = as_f16x8(u32x4{mine ? xa.x : 0u, mine ? xa.y : 0u, mine ? xa.z : 0u, mine ? xa.w : 0u});
+        const uint32_t sel = (v & 1) ? 0x07060302u : 0x05040100u;   // which 16 bits of the dword: rows 0..3 or 4..7 of it
+        uint32_t t[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            t[k] = __builtin_amdgcn_perm(w[8 * SET + 2 * k + 1][v >> 1], w[8 * SET + 2 * k][v >> 1], sel);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const uint32_t m = (p & 1) ? 0x03C003C0u : 0x003C003Cu;
+            u32x4 b;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) b[k] = (p < 2 ? t[k] << 2 : t[k] >> 6) & m;
+            d[p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, as_f16x8(b), d[p], 0, 0, 0);
+        }
+    }
+}
+
+// The bias of the offset-binary codes (stored = q + 8) enters as the accumulators' initial value: the product of x with
+// the constant -8 in the codes' own units.  x0, x1 = the lane's x of slots u < 8 and u >= 8.
+__device__ __forceinline__ void start_products(const StagedX &xs, int lane, u32x4 &x0, u32x4 &x1, f32x4 (&d)[4]) {
+    const u32x4 *src = reinterpret_cast<const u32x4 *>(&xs.v[lane & 3][lane & 48]);
+    x0 = src[0];
+    x1 = src[1];
+    const f16x8 even = as_f16x8(u32x4{0x80208020u, 0x80208020u, 0x80208020u, 0x80208020u});
+    const f16x8 odd = as_f16x8(u32x4{0x82008200u, 0x82008200u, 0x82008200u, 0x82008200u});
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    d[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(x0), even, zero, 0, 0, 0);
+    d[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(x0), odd, zero, 0, 0, 0);
+    d[2] = d[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(x1), even, d[0], 0, 0, 0);
+    d[3] = d[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(x1), odd, d[1], 0, 0, 0);
+}
+
+// Whether a pass is computed with -x (and its sums subtracted).  The matrix cores round the terms of a product DOWN, so a
+// sum over many passes carries a negative bias, relative to the result in proportion to sqrt(K).  With x negated the bias
+// changes sign.  One pass in eight is negated, which leaves three quarters of the bias: on 1024 x 28672 dense the error against
+// 64-bit arithmetic (relative 2-norm) is 3.2e-6 for Laplace x and 9.7e-6 for SiLU products.  The 4-wide products of
+// v_mfma_f32_4x4x4 give 1.1e-5 and 2.7e-5, a bias of the same sign; with that much of it left the results also stay
+// within 2e-5 of theirs.  `turn` counts passes, from another start in every wavefront of a block-row.
+__device__ __forceinline__ bool negated(int turn) { return (turn & 7) == 7; }
+
+// Applies the scales of a pass's groups (sc[g] = the fp16 scales of the lane's 4 rows in group g of the pass) and adds to
+// the lane's running sums, which stay in the products' units.
+template <int BATCH, int GROUPS>
+__device__ __forceinline__ void add_scaled(const f32x4 (&d)[4], const u32x2 (&sc)[GROUPS], bool neg, float (&acc)[BATCH][4]) {
+    constexpr int kRows = padded_rows(BATCH);
+    const uint32_t sign = neg ? 0x80008000u : 0u;
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g) {
+        const f16x2 h01 = as_f16x2(sc[g].x ^ sign), h23 = as_f16x2(sc[g].y ^ sign);
+        const float s[4] = {(float)h01.x, (float)h01.y, (float)h23.x, (float)h23.y};
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b)
+#pragma unroll
+            for (int p = 0; p < 4; ++p) acc[b][p] = __builtin_fmaf(s[p], d[p][g * kRows + b], acc[b][p]);
+    }
+}
+
+// The entries of a pass, dealt to its groups: lane e holds candidate column kk (or -1 past the slice), candidates are
+// consecutive list entries, and a run of entries of one quantization group is one group of the pass.  A run that would
+// be group GROUPS (counted from 0) waits for the next pass.
+struct Deal {
+    bool take;      // this lane's candidate belongs to the pass
+    int j;          // its group inside the pass
+    int n;          // entries the pass takes (wave-uniform): the next pass starts n entries further
+    uint64_t starts;   // lanes at which the pass's groups start (wave-uniform)
+};
+template <int GROUPS>
+__device__ __forceinline__ Deal deal_groups(int kk, int g, int lane) {
+    Deal d;
+    const bool cand = kk >= 0;
+    const int gprev = __builtin_amdgcn_update_dpp(-1, g, 0x138, 0xf, 0xf, false);   // wave_shr:1; lane 0 keeps -1
+    const uint64_t starts = __ballot(cand && (lane == 0 || g != gprev));
+    const int before = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(starts >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)starts, 0u));
+    d.j = before - 1 + (int)((starts >> lane) & 1ull);
+    d.take = cand && d.j < GROUPS;
+    d.n = __builtin_amdgcn_readfirstlane((int)__popcll(__ballot(d.take)));
+    d.starts = starts;
+    return d;
+}
+
+// Stages the x of a pass: entry `slot` of lane `lane` carries x[b] for group j of the pass.
+template <int BATCH, int GROUPS>
+__device__ __forceinline__ void stage_x(StagedX &xs, int lane, int slot, int j, bool take, bool neg, const uint32_t (&xraw)[BATCH]) {
+    constexpr int kRows = padded_rows(BATCH);
+    {   // slots that no entry writes must read as zero
+        reinterpret_cast<u32x2 *>(&xs.v[0][0])[lane] = u32x2{0u, 0u};
+        __builtin_amdgcn_wave_barrier();
+    }
+    // no branch on `take`: a divergent one inside the pipeline's loop makes the compiler join the loop's exits with its
+    // entry and wait for all loads there
+#pragma unroll
+    for (int b = 0; b < BATCH; ++b) xs.v[take ? j * kRows + b : 4][slot] = (uint16_t)(xraw[b] ^ (neg ? 0x8000u : 0u));
+    __builtin_amdgcn_wave_barrier();
+}
+
+}  // namespace spqt
+#endif

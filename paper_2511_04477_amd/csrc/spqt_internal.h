@@ -38,29 +38,28 @@ inline int check_shape(int64_t M, int64_t K, int group) {
     return SPQT_OK;
 }
 
-enum class Kernel { dense, list_rows, list_groups, fused };
+// Workgroups in the grid of a group-layout launch (block_of in gemv_common.hpp says which is which).
+inline int grid_blocks(int64_t T, int S) { return 8 * (int)((T / 8) * S + ((T % 8) * S + 7) / 8); }
 
-// Launch shape per kernel, measured on MI355X over the benchmark shapes at 50 % sparsity and dense.
+enum class Kernel { group_layout, colblock_list, colblock_dense };
+
+// Launch shape, measured on MI355X over the benchmark's matrices at 50 % sparsity and dense.
+// Group layout, one or two activation rows: about one workgroup of 4 wavefronts per CU - at most 256 in total - and S any
+// integer up to 16.  More workgroups only shorten every wavefront's slice, and the fixed cost per wavefront (dependent
+// prologue loads, pipeline fill, exchange of partial sums) outweighs the extra parallelism: dense 13824 x 5120 with 4 / 8
+// / 16 workgroups per block-row 9.7 / 11.0 / 12.3 us, index list at 50 % 28672 x 8192 with 2 / 4 / 6 15.5 / 17.0 / 17.0.
+// Three or four rows, and the column-block layouts: about 512 (dense with one row: 1024) workgroups, S a power of two.
 inline void choose_cfg(int64_t M, int64_t K, int batch, Kernel kind, spqt_launch_cfg *out) {
     const int64_t T = tiles(M), NG = K / kGroup;
     const int waves = 4;
     int64_t S = 1;
-    if (kind == Kernel::list_rows) {
-        // Row-aligned passes (one activation row): fastest with about one workgroup of 4 wavefronts per
-        // CU - at most 256 in total - and S any integer up to 16.  More workgroups only shorten every
-        // wavefront's slice, and the fixed cost per wavefront (dependent prologue loads, pipeline fill,
-        // fold, exchange of partial sums) outweighs the extra parallelism.
+    if (kind == Kernel::group_layout && batch <= 2) {
         S = 256 / T;
         S = S < 1 ? 1 : (S > 16 ? 16 : S);
         while (S > 1 && S * waves > 4 * NG) --S;
     } else {
-        // The others: about 512 (sparse) / 1024 (dense) workgroups in total, S a power of two and at
-        // most 16.  Several activation rows need enough accumulator registers that two wavefronts fit per
-        // SIMD instead of three: 512 workgroups of 4 wavefronts is then the whole chip, once.
-        // The dense batch-1 kernel on matrices large enough to be bandwidth-bound (>= 64 MB packed) is
-        // fastest with one wavefront per SIMD: about 256 workgroups.
         const bool big = (size_t)M * (size_t)K / 2 >= ((size_t)64 << 20);
-        const int64_t target = batch >= 2 ? 512 : (kind != Kernel::dense ? 512 : (big ? 256 : 1024));
+        const int64_t target = batch >= 2 ? 512 : (kind != Kernel::colblock_dense ? 512 : (big ? 256 : 1024));
         while (S * 2 <= 16 && S * 2 * T <= target) S *= 2;
         // keep at least a quarter of a quantization group per wavefront
         while (S > 1 && S * waves > 4 * NG) S /= 2;
@@ -68,6 +67,18 @@ inline void choose_cfg(int64_t M, int64_t K, int batch, Kernel kind, spqt_launch
     out->splits = (int)S;
     out->waves = waves;
     out->flags = 0;
+}
+
+// Three or four activation rows: where choose_cfg's shape is more than one workgroup of 4 wavefronts per CU, the kernels run
+// one workgroup of 8 per CU instead.  The exchange grows with rows times workgroups per block-row: index list at 70 %
+// sparsity, 4 rows, 14336 x 4096 with 8 x 4 / 4 x 8 wavefronts per block-row 16.2 / 13.1 us, 28672 x 8192 with 4 x 4 / 2 x 8
+// 30.3 / 26.7.  (spqt_default_cfg and the limit of spqt_gemv_static go by choose_cfg's shape, which never needs fewer
+// exchange words.)
+inline void wide_workgroups(int64_t M, int batch, spqt_launch_cfg *c) {
+    const int64_t T = tiles(M);
+    if (batch < 3 || T * c->splits <= 256) return;
+    c->splits = T < 256 ? (int)(256 / T) : 1;
+    c->waves = 8;
 }
 
 }  // namespace spqt

@@ -48,7 +48,7 @@ def main(argv=None) -> int:
     M, K, s = args.M, args.K, args.sparsity
     dev = torch.device("cuda:0")
     L = spqt.lib()
-    setter = {"list": "spqt_timeline_set_list", "fused": "spqt_timeline_set_bal", "dense": "spqt_timeline_set_gemv",
+    setter = {"list": "spqt_timeline_set_list", "fused": "spqt_timeline_set_bal", "dense": "spqt_timeline_set_list",
               "fused_static": "spqt_timeline_set_gemv"}[args.kernel]
     set_buf = getattr(L, setter)
     set_buf.argtypes = [ctypes.c_void_p]

@@ -1,0 +1,110 @@
+"""GPU parity of the passes shared by the group-layout kernels (pass.hpp) where they can go wrong: entries around the 64 slots
+of a pass and the groups a pass takes, stretches that keep nothing longer than one refill of the one-launch kernel (256
+columns), block-rows that do not divide evenly over the 8 XCDs, workgroups of 8 wavefronts for 3 and 4 rows - against the
+oracle, |y_gpu - y_ref| <= 1e-2 + 2e-3 * |y_ref| - and the rounding of the matrix-core sums against 64-bit arithmetic."""
+import numpy as np
+import pytest
+
+import oracle
+from workloads import make_weights, make_x, quantile_threshold
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    import paper_2511_04477_amd as spqt
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    spqt.lib()
+    return torch, spqt, torch.device("cuda:0")
+
+
+def run(gpu, w, x_np, thr, mode, group=128, splits=0, own=False):
+    torch, spqt, dev = gpu
+    M, K = w["q_rowmajor"].shape[0], w["q_rowmajor"].shape[1] * 2
+    packed = torch.from_numpy(spqt.spqt_pack(w["q_rowmajor"], w["scales"], group)).to(dev)
+    x = torch.from_numpy(np.ascontiguousarray(x_np)).to(dev)
+    rows = x.shape[0]
+    y = torch.full((rows, M), float("nan"), dtype=torch.float32, device=dev)
+    ws = spqt.new_workspace(M, K, rows)
+    xx, yy = (x, y) if rows > 1 else (x[0], y[0])
+    if mode == "fused":
+        if rows > 1:
+            spqt.spqt_gemv_fused_rows(packed, M, K, xx, thr, yy, ws, own_sets=own, group=group, splits=splits)
+        else:
+            spqt.spqt_gemv_fused(packed, M, K, xx, thr, yy, ws, group=group, splits=splits)
+    else:
+        idx = torch.empty(K, dtype=torch.int32, device=dev)
+        cnt = torch.zeros(1, dtype=torch.int32, device=dev)
+        if mode == "list":
+            spqt.spqt_gather(xx, thr, idx, cnt)
+        else:
+            idx = cnt = None
+        spqt.spqt_gemv(packed, M, K, xx, idx, cnt, yy, ws, group=group, splits=splits)
+    torch.cuda.synchronize()
+    return y.cpu().numpy()
+
+
+def check(got, ref, what):
+    err = np.abs(got.astype(np.float64) - ref)
+    assert np.all(err <= 1e-2 + 2e-3 * np.abs(ref)), f"{what}: max err {np.nanmax(err):.3e}"
+
+
+@pytest.mark.parametrize("rows", [1, 2, 3, 4])
+@pytest.mark.parametrize("group", [128, 64])
+def test_pass_edges(gpu, rows, group):
+    """One workgroup walks the whole matrix, so a wavefront sees every pass length: n kept columns spread over the columns
+    (many groups per pass), in one run (one group per pass), and behind a stretch that keeps nothing."""
+    M, K = 256, 2048
+    w = make_weights(M, K, 5100 + rows, group=group)
+    base = make_x(K, "normal", 5101, batch=rows)
+    base = np.where(np.abs(base) < 0.25, np.float16(0.25), base).astype(np.float16)
+    for n in (0, 1, 63, 64, 65, 129, 257, 600):
+        spread = np.unique(np.linspace(0, K - 1, n).astype(int)) if n else np.zeros(0, int)
+        for name, cols in (("spread", spread), ("run", np.arange(n)), ("tail", np.arange(K - n, K))):
+            x = np.zeros_like(base)
+            x[:, cols] = base[:, cols]
+            ref = oracle.gemv(w["q_rowmajor"], w["scales"], x, 0.125, group=group)
+            for mode in ("list", "fused"):
+                print(f"pass edges rows={rows} group={group} n={n} {name} {mode}", flush=True)
+                check(run(gpu, w, x, 0.125, mode, group, splits=1), ref, f"n={n} {name} {mode}")
+
+
+@pytest.mark.parametrize("T,K", [(9, 1024), (12, 1024), (20, 2048), (33, 1024), (300, 256)])
+@pytest.mark.parametrize("rows", [1, 3])
+def test_block_rows_over_xcds(gpu, T, K, rows):
+    """Block-rows that do not divide by 8, with the default launch shape (33 block-rows and 3 rows: workgroups of 8
+    wavefronts) and with odd numbers of workgroups per block-row."""
+    M = 256 * T - 19
+    w = make_weights(256 * T, K, 5200 + T)
+    w = {"q_rowmajor": w["q_rowmajor"][:M].copy(), "scales": w["scales"][:M].copy()}
+    x = make_x(K, "laplace", 5201, batch=rows)
+    thr = quantile_threshold(x, 0.5)
+    sparse = oracle.gemv(w["q_rowmajor"], w["scales"], x, thr)
+    dense = oracle.gemv(w["q_rowmajor"], w["scales"], x, 0.0)
+    for splits in (0, 3, 5):
+        for mode in ("list", "fused", "dense"):
+            print(f"block-rows T={T} K={K} rows={rows} splits={splits} {mode}", flush=True)
+            check(run(gpu, w, x, thr, mode, splits=splits), dense if mode == "dense" else sparse, f"splits={splits} {mode}")
+
+
+@pytest.mark.parametrize("rows", [1, 4])
+def test_rounding_of_the_sums(gpu, rows):
+    """SiLU products (many small activations beside few large ones) through all 28672 columns: the matrix cores round
+    products down relative to the largest one.  32 products summed with 2^-24 of the largest lost per product, codes one
+    to five bits below their exponent field, biased: below 2e-5 of the result in the 2-norm."""
+    M, K = 256, 28672
+    w = make_weights(M, K, 5300)
+    r = np.random.default_rng(5301)
+    g, u = r.standard_normal((2, rows, K))
+    x = (g / (1 + np.exp(-g)) * u).astype(np.float16)
+    q = w["q_rowmajor"]
+    codes = np.stack([q & 15, q >> 4], -1).reshape(M, K).astype(np.int64)
+    codes = np.where(codes > 7, codes - 16, codes)
+    W = codes * np.repeat(w["scales"].view(np.float16).astype(np.float64), 128, axis=1)
+    ref = x.astype(np.float64) @ W.T
+    got = run(gpu, w, x, 0.0, "dense").astype(np.float64)
+    rel = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    print(f"rounding rows={rows}: {rel:.2e}", flush=True)
+    assert rel < 2e-5
