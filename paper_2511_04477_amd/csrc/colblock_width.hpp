@@ -8,7 +8,7 @@
 // Everything else follows spqt_cb_gemv_kernel: even split of the index list over the S x WAVES
 // wavefronts of a block-row (Section 4.2.3), the scales folded into x by the lane that owns the list
 // entry, two-stage software pipeline with unpredicated clamped loads, one fold of the 8 column-lanes at
-// the end, reduction through LDS and the tagged-word exchange.  Three modes: list-driven, dense (every
+// the end, reduction through LDS and the workspace.  Three modes: list-driven, dense (every
 // column, no list), and ONE-LAUNCH (FUSED, one activation row): the kernel applies the sparsity test of
 // Section 2 itself on static 64-column units - lane l tests column 64 u + l, a ballot gives the kept set,
 // mbcnt the rank, and the kept columns are staged in rank order - so no index list exists.

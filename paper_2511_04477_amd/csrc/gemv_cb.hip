@@ -20,7 +20,7 @@
 //     the end, and the offset-binary bias (stored = q + 8) is removed there as -8 * (sum of
 //     x * s of the lane's block over the slice).
 //   - two-stage software pipeline, unpredicated clamped loads, reduction through LDS and the
-//     tagged-word workspace exactly as in gemv.hip.
+//     workspace exactly as in gemv_list.hip.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -7,6 +7,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "spqt_internal.h"
 
 namespace spqt {
@@ -222,108 +224,139 @@ __device__ __forceinline__ bool block_of(int index, int S, int T, int &t, int &s
 // threadgroups that share a superblock row are reduced once at the end, without atomics on y).
 // `red` holds this workgroup's [WAVES][BATCH][ROWS] partial sums in LDS (already synchronised);
 // ROWS is the height of a block-row (256 for the 4-bit layouts).
-// Every workgroup but the last (s == S-1) publishes its ROWS partial sums as 64-bit words
-// {value, kWordTag} with device-scope stores and is done: no wait, no counter.  The last one adds
-// the others' words in index order, polling a word until it carries the tag, then its own sums,
-// writes y, and stores zero back into every word it consumed - so between calls the exchange area
-// is all zeros whatever M, launch shape or kernel the calls had, and a word with the tag is always
-// one of THIS call.  A 64-bit store is a single access: value and tag arrive together.  The
-// reducer has the highest index of its block-row and workgroups are dispatched in index order, so
+// Every workgroup but the last (s == S-1) publishes its ROWS partial sums as 32-bit words with device-scope stores
+// (two adjacent rows per store where a thread owns more than one) and is done: no wait, no counter.  A word is the COMPLEMENT of the sum's bits (never 0: the
+// one pattern that would give 0 is a NaN and is replaced by another NaN), and 0 means "not there yet".  The last
+// workgroup adds the others' words in index order, polling until none is 0, then its own sums, writes y, and stores zero
+// back into every word it consumed - so between calls the exchange area is all zeros whatever M, launch shape or kernel
+// the calls had, and a word that is not 0 is always one of THIS call.  (A tag beside every value would double the bytes:
+// four activation rows, 1024 x 4096, 16 workgroups per block-row: 9.8 us with tagged 64-bit words, 7.4 without;
+// one row, 4096 x 4096: 5.6 and 5.2.)
+// The reducer has the highest index of its block-row and workgroups are dispatched in index order, so
 // everything it waits for is running or finished; the wait is bounded anyway, and a give-up
 // poisons y with NaN instead of hanging and raises the workspace's poison flag (word 0 of its
 // head): a late word of the abandoned call could otherwise be taken for a later call's, so from
 // then on every call on that workspace yields NaN until spqt_workspace_init clears it.
-constexpr uint32_t kWordTag = 0x5B07C0DEu;
+__device__ __forceinline__ uint32_t exchange_word(float v) {
+    const uint32_t w = ~as_u32(v);
+    return w ? w : 1u;
+}
 template <int WAVES, int BATCH, int ROWS = kTileRows>
 __device__ __forceinline__ void combine_block_row(const float *red, int tid, int t, int s, int S, void *partials,
                                                   int32_t *ws_flags, float *__restrict__ y, int m_and_flags) {
-    // One kernel argument carries both (M <= 2^24): every extra scalar argument costs the
-    // four-row kernels, which sit at the register limit, a spill.
+    // One kernel argument carries both (M <= 2^24).
     const int M = m_and_flags & kRowsMask;
     const bool y_half = (m_and_flags & kHalfOutputBit) != 0;
     constexpr int kOut = BATCH * ROWS;           // values one workgroup contributes: [BATCH][ROWS]
     constexpr int kThreads = WAVES * 64;
-    constexpr int kPerThread = (kOut + kThreads - 1) / kThreads;
-    // A thread that owns several values handles 2 of them together, so that the reducer's loads for
-    // all of them are in flight at once (one round trip instead of one per value).
+    constexpr int kVals = kOut > kThreads ? 2 : 1;     // adjacent values a thread moves at once: 64-bit or 32-bit accesses
+    typedef std::conditional_t<kVals == 2, unsigned long long, uint32_t> Word;
+    constexpr int kUnits = kOut / kVals;         // unit i = values kVals i ..
+    constexpr int kPerThread = (kUnits + kThreads - 1) / kThreads;
+    // A thread that owns several units handles 2 of them together, so that the reducer's loads for
+    // all of them are in flight at once (one round trip instead of one per unit).
     constexpr int kTogether = kPerThread < 2 ? kPerThread : 2;
-    unsigned long long *slots = reinterpret_cast<unsigned long long *>(partials) + (size_t)t * S * kOut;
+    Word *slots = reinterpret_cast<Word *>(partials) + (size_t)t * S * kUnits;    // [S - 1][kUnits]
     const bool reducer = S > 1 && s == S - 1;
     uint32_t poisoned = 0u;
     if (reducer) poisoned = __hip_atomic_load(reinterpret_cast<uint32_t *>(ws_flags), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (int r0 = tid; r0 < kOut; r0 += kTogether * kThreads) {
-        int r[kTogether];
-        bool real[kTogether];
-        float sum[kTogether];
+    for (int i0 = tid; i0 < kUnits; i0 += kTogether * kThreads) {
+        uint32_t at[kTogether];
+        float sum[kTogether][kVals];
 #pragma unroll
         for (int i = 0; i < kTogether; ++i) {
-            const bool have = r0 + i * kThreads < kOut;
-            r[i] = have ? r0 + i * kThreads : r0;
-            real[i] = have && t * ROWS + (r[i] % ROWS) < M;   // rows past M are the last block-row's zero padding
-            sum[i] = 0.0f;
+            at[i] = (uint32_t)(i0 + i * kThreads < kUnits ? i0 + i * kThreads : i0);
 #pragma unroll
-            for (int w2 = 0; w2 < WAVES; ++w2) sum[i] += red[w2 * kOut + r[i]];
+            for (int q = 0; q < kVals; ++q) {
+                sum[i][q] = 0.0f;
+#pragma unroll
+                for (int w2 = 0; w2 < WAVES; ++w2) sum[i][q] += red[w2 * kOut + kVals * at[i] + q];
+            }
         }
-        // fp32 output, or the same value rounded to fp16 (nearest even) when the caller asked for it
-        auto store_y = [&](int i, float v) {
-            const size_t y_at = (size_t)(r[i] / ROWS) * M + t * ROWS + (r[i] % ROWS);
-            if (y_half) reinterpret_cast<_Float16 *>(y)[y_at] = (_Float16)v;
-            else y[y_at] = v;
+        // fp32 output, or the same value rounded to fp16 (nearest even) when the caller asked for it;
+        // rows past M are the last block-row's zero padding
+        auto store_y = [&](int i, int q, float v) {
+            const int r = (int)(kVals * at[i]) + q;
+            const int row = t * ROWS + r % ROWS;
+            const size_t y_at = (size_t)(r / ROWS) * M + row;
+            if (row < M) {
+                if (y_half) reinterpret_cast<_Float16 *>(y)[y_at] = (_Float16)v;
+                else y[y_at] = v;
+            }
         };
         if (S == 1) {
 #pragma unroll
             for (int i = 0; i < kTogether; ++i)
-                if (real[i]) store_y(i, sum[i]);
+#pragma unroll
+                for (int q = 0; q < kVals; ++q) store_y(i, q, sum[i][q]);
         } else if (!reducer) {
 #pragma unroll
             for (int i = 0; i < kTogether; ++i) {
-                if (i > 0 && r[i] == r[0]) continue;   // a clamped duplicate: already published
+                if (i > 0 && at[i] == at[0]) continue;   // a clamped duplicate: already published
                 if (kMuteProducers) continue;
-                const unsigned long long word = ((unsigned long long)kWordTag << 32) | as_u32(sum[i]);
-                __hip_atomic_store(slots + (size_t)s * kOut + r[i], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                Word word = exchange_word(sum[i][0]);
+                if (kVals == 2) word |= (Word)((unsigned long long)exchange_word(sum[i][kVals - 1]) << 32);
+                __hip_atomic_store(slots + (size_t)s * kUnits + at[i], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         } else {
-            float total[kTogether];
-#pragma unroll
-            for (int i = 0; i < kTogether; ++i) total[i] = 0.0f;
-            bool gave_up = false;
-            for (int p0 = 0; p0 < S - 1; p0 += 16) {
-                unsigned long long v[kTogether][16];
-                int polls = 0;
-                bool all_here;
-                do {
-                    // unconditional loads back to back (clamped index), then one check
-#pragma unroll
-                    for (int i = 0; i < kTogether; ++i)
-#pragma unroll
-                        for (int j = 0; j < 16; ++j) {
-                            const int p = p0 + j < S - 1 ? p0 + j : S - 2;
-                            v[i][j] = __hip_atomic_load(slots + (size_t)p * kOut + r[i], __ATOMIC_RELAXED,
-                                                        __HIP_MEMORY_SCOPE_AGENT);
-                        }
-                    uint32_t missing = 0u;
-#pragma unroll
-                    for (int i = 0; i < kTogether; ++i)
-#pragma unroll
-                        for (int j = 0; j < 16; ++j) missing |= (uint32_t)(v[i][j] >> 32) ^ kWordTag;
-                    all_here = missing == 0u;
-                } while (!all_here && ++polls < kMaxPolls);
-                gave_up = gave_up || !all_here;
-#pragma unroll
-                for (int i = 0; i < kTogether; ++i)
-#pragma unroll
-                    for (int j = 0; j < 16; ++j)
-                        if (p0 + j < S - 1) {
-                            total[i] += as_float((uint32_t)v[i][j]);
-                            // consumed: the word goes back to zero for whatever call comes next
-                            __hip_atomic_store(slots + (size_t)(p0 + j) * kOut + r[i], 0ull, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
-                        }
-            }
-            if (gave_up) __hip_atomic_store(reinterpret_cast<uint32_t *>(ws_flags), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            float total[kTogether][kVals];
 #pragma unroll
             for (int i = 0; i < kTogether; ++i)
-                if (real[i]) store_y(i, (gave_up || poisoned) ? __builtin_nanf("") : total[i] + sum[i]);
+#pragma unroll
+                for (int q = 0; q < kVals; ++q) total[i][q] = 0.0f;
+            bool gave_up = false;
+            // N partial sums per round; with few workgroups per block-row the larger N would read some of them many times
+            auto collect = [&](auto count) {
+                constexpr int N = decltype(count)::value;
+                for (int p0 = 0; p0 < S - 1; p0 += N) {
+                    Word v[kTogether][N];
+                    int polls = 0;
+                    bool all_here;
+                    do {
+                        // unconditional loads back to back (clamped index), then one check
+#pragma unroll
+                        for (int j = 0; j < N; ++j) {
+                            const Word *from = slots + (size_t)(p0 + j < S - 1 ? p0 + j : S - 2) * kUnits;   // wave-uniform
+#pragma unroll
+                            for (int i = 0; i < kTogether; ++i)
+                                v[i][j] = __hip_atomic_load(from + at[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        }
+                        uint32_t least = ~0u;   // one running minimum: a comparison per word costs 0.5 us here
+#pragma unroll
+                        for (int i = 0; i < kTogether; ++i)
+#pragma unroll
+                            for (int j = 0; j < N; ++j)
+#pragma unroll
+                                for (int q = 0; q < kVals; ++q) {
+                                    const uint32_t word = (uint32_t)((unsigned long long)v[i][j] >> (32 * q));
+                                    least = word < least ? word : least;
+                                }
+                        all_here = least != 0u;
+                    } while (!all_here && ++polls < kMaxPolls);
+                    gave_up = gave_up || !all_here;
+#pragma unroll
+                    for (int j = 0; j < N; ++j)
+                        if (p0 + j < S - 1) {
+                            Word *from = slots + (size_t)(p0 + j) * kUnits;
+#pragma unroll
+                            for (int i = 0; i < kTogether; ++i) {
+#pragma unroll
+                                for (int q = 0; q < kVals; ++q)
+                                    total[i][q] += as_float(~(uint32_t)((unsigned long long)v[i][j] >> (32 * q)));
+                                // consumed: the words go back to zero for whatever call comes next
+                                __hip_atomic_store(from + at[i], (Word)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            }
+                        }
+                }
+            };
+            if (S <= 5) collect(std::integral_constant<int, 4>{});
+            else collect(std::integral_constant<int, 16>{});
+            if (gave_up) __hip_atomic_store(reinterpret_cast<uint32_t *>(ws_flags), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const bool bad = gave_up || poisoned;
+#pragma unroll
+            for (int i = 0; i < kTogether; ++i)
+#pragma unroll
+                for (int q = 0; q < kVals; ++q) store_y(i, q, bad ? __builtin_nanf("") : total[i][q] + sum[i][q]);
         }
     }
 }

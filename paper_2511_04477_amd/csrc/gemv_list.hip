@@ -10,7 +10,7 @@
 //   - one buffer of weights (16 loads of 8 bytes per lane), refilled half by half as a pass is multiplied: when the products
 //     of slots u < 8 are done, their registers receive the same slots of the next pass, whose HEAD (deal the entries,
 //     request its x and the entries of the pass after it) has run before the products.
-//   - WAVES wavefronts are combined through LDS, the S workgroups of a block-row through a workspace of tagged words
+//   - WAVES wavefronts are combined through LDS, the S workgroups of a block-row through words in a workspace
 //     (gemv_common.hpp).  No floating-point atomics, so results are reproducible.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
