@@ -5,149 +5,120 @@
 // to the position the scan gives it, so the list is contiguous.  The paper scans 1024-entry
 // segments with a Blelloch scan and orders the segments through a global atomic counter,
 // which makes the order depend on arrival.  Here the list must be ascending and
-// reproducible, so there are no atomics: workgroup b owns the 4096-entry segment b of x,
-// ranks its kept entries with wave64 primitives (ballot + mbcnt inside a 512-entry wave
-// step, eight wave totals through LDS), and obtains its base offset by simply counting
-// the kept entries of all earlier segments itself (x is at most 128 KB and sits in L2 after
-// the first touch; counting needs no ballots, only popcounts).
+// reproducible, so there are no atomics: workgroup b owns the 4096-entry segment b of x, 4 entries per lane, ranks its
+// kept entries with wave64 primitives (ballot + mbcnt, the wavefronts' totals through LDS), and obtains its base offset by
+// counting the kept entries of all earlier segments itself (x is at most 128 KB per row and sits in L2; counting is
+// integer work on pairs of halves, the rows of a batch joined by a maximum before the test).
+//
+// What bounds it: the chain launch -> x -> ballot -> LDS -> list for one segment; for many, the last workgroup's read of
+// all of x through one CU (64 bytes a clock).  Two entries per packed instruction and 16 wavefronts of 4 entries per
+// lane, against fp32 compares and 8 wavefronts of 8 before: added time per call in a chain of GEMVs (an empty kernel adds
+// 1.4 to 2.2 us) K = 4096 2.7 -> 2.4 us, 14336 3.7 -> 3.0, 28672 4.2 -> 3.6; 4 rows, 28672 10.0 -> 4.9.  (Requesting four
+// chunks of the earlier segments at once instead of two: 14336 3.4, 28672 3.8.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "keep.hpp"
 #include "spqt_internal.h"
 
 namespace {
 
-constexpr int kWaves = 8;
-constexpr int kThreads = kWaves * 64;
-constexpr int kPerLane = 8;                        // one 16-byte load of fp16 per lane
-constexpr int kStep = 64 * kPerLane;               // entries one wave covers
-constexpr int kSegment = kWaves * kStep;           // entries one workgroup ranks: 4096
+using namespace spqt;
 
+constexpr int kPerLane = 4;                        // own entries per lane: one 8-byte load of fp16 per row
+constexpr int kMaxWaves = 16;
+constexpr int kSegment = kMaxWaves * 64 * kPerLane;    // entries one workgroup ranks: 4096
+constexpr int kCountCols = kMaxWaves * 64 * 8;         // entries of earlier segments a workgroup counts at a time: 8192
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ float half_bits_to_float(uint32_t h16) {
-    return (float)__builtin_bit_cast(_Float16, (uint16_t)h16);
-}
-
-// Bit i of the result is set iff entry i of the eight fp16 values in v is kept:
-// kept == !(|x| < thr), evaluated in fp32 (Section 2: sparse iff |x_i| < threshold).
-__device__ __forceinline__ uint32_t keep_bits(u32x4 v, float thr) {
-    uint32_t m = 0;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        const uint32_t word = v[d];
-        const float lo = half_bits_to_float(word & 0xFFFFu);
-        const float hi = half_bits_to_float(word >> 16);
-        m |= (uint32_t)(!(__builtin_fabsf(lo) < thr)) << (2 * d);
-        m |= (uint32_t)(!(__builtin_fabsf(hi) < thr)) << (2 * d + 1);
-    }
-    return m;
-}
-
-// Keep mask of the eight entries starting at `first` (all rows of the batch OR-ed), or 0 past K.
-template <int BATCH>
-__device__ __forceinline__ uint32_t mask_at(const uint16_t *__restrict__ x, int K, int first, float thr) {
-    u32x4 v[BATCH];
-#pragma unroll
-    for (int b = 0; b < BATCH; ++b) v[b] = *reinterpret_cast<const u32x4 *>(x + (size_t)b * K + first);
-    uint32_t m = 0;
-#pragma unroll
-    for (int b = 0; b < BATCH; ++b) m |= keep_bits(v[b], thr);
-    return m;
-}
-
-// The eight fp16 values of v with the entries whose bit in `keep` is clear replaced by +0.
-__device__ __forceinline__ u32x4 zero_dropped(u32x4 v, uint32_t keep) {
-    u32x4 out;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        const uint32_t lo = (keep >> (2 * d)) & 1u ? 0x0000FFFFu : 0u;
-        const uint32_t hi = (keep >> (2 * d + 1)) & 1u ? 0xFFFF0000u : 0u;
-        out[d] = v[d] & (lo | hi);
-    }
-    return out;
-}
 
 // MASKED: besides the union list, write a copy of x in which every row has ITS OWN dropped
 // entries set to zero.  A GEMV over the union list fed this copy gives each row the sum over
 // that row's kept columns only (a dropped entry of a listed column contributes 0 * w).
-template <int BATCH, bool MASKED = false>
-__global__ __launch_bounds__(kThreads) void spqt_gather_kernel(const uint16_t *__restrict__ x, int K,
-                                                               float thr, int32_t *__restrict__ idx,
-                                                               int32_t *__restrict__ count,
-                                                               uint16_t *__restrict__ x_masked = nullptr) {
-    __shared__ int wave_total[kWaves];
-    __shared__ int wave_before[kWaves];
+// One workgroup of 1024 lanes per segment; a single segment may have fewer lanes (K <= 4 * lanes).
+template <int BATCH, bool MASKED>
+__global__ __launch_bounds__(kMaxWaves * 64) void spqt_gather_kernel(const uint16_t *__restrict__ x, int K, float thr,
+                                                                     int32_t *__restrict__ idx, int32_t *__restrict__ count,
+                                                                     uint16_t *__restrict__ x_masked) {
+    __shared__ int wave_kept[kMaxWaves];
+    __shared__ int wave_before[kMaxWaves];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
+    const int waves = blockDim.x >> 6;
     const int seg = blockIdx.x;
-    const int lane_first = wave * kStep + lane * kPerLane;   // inside a segment
+    const int first = seg * kSegment + (int)threadIdx.x * kPerLane;
+    const bool inside = first < K;                 // K % 8 == 0: a lane's entries are all inside x or all past its end
 
-    // This workgroup's own segment: lane l of wave w owns entries 8l..8l+7 of wave step w, so
-    // ranks follow (wave, lane, bit) order = ascending index.
-    const int first = seg * kSegment + lane_first;
-    // K % 8 == 0, so a lane's eight entries are all inside x or all past its end
-    uint32_t m = 0u;
-    if (MASKED) {
-        if (first < K) {
+    u32x2 v[BATCH];
 #pragma unroll
-            for (int b = 0; b < BATCH; ++b) {
-                const u32x4 v = *reinterpret_cast<const u32x4 *>(x + (size_t)b * K + first);
-                const uint32_t kb = keep_bits(v, thr);
-                *reinterpret_cast<u32x4 *>(x_masked + (size_t)b * K + first) = zero_dropped(v, kb);
-                m |= kb;
-            }
-        }
-    } else {
-        m = first < K ? mask_at<BATCH>(x, K, first, thr) : 0u;
-    }
+    for (int b = 0; b < BATCH; ++b) v[b] = *reinterpret_cast<const u32x2 *>(x + (size_t)b * K + (inside ? first : 0));
 
     // Kept entries of all earlier segments, counted by this workgroup itself.
-    // (Earlier segments are complete - only the last one can be ragged - so these loads need no
-    // bounds test and can all be in flight together.)
+    const uint32_t c2 = threshold_bits(thr);
     int before = 0;
-#pragma unroll 4
-    for (int p = 0; p < seg; ++p) before += __popc(mask_at<BATCH>(x, K, p * kSegment + lane_first, thr));
+    const int upto = seg * kSegment;
+#pragma unroll 2
+    for (int p = (int)threadIdx.x * 8; p < upto; p += kCountCols) {
+        u32x4 m = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int s = 1; s < 64; s <<= 1) before += __shfl_xor(before, s);
+        for (int b = 0; b < BATCH; ++b) {
+            const u32x4 e = *reinterpret_cast<const u32x4 *>(x + (size_t)b * K + p);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) m[d] = b == 0 ? magnitude_bits(e[d]) : larger_bits(m[d], magnitude_bits(e[d]));
+        }
+        before += 8 - (int)__popc(dropped_signs(m.x, c2) | (dropped_signs(m.y, c2) >> 1) | (dropped_signs(m.z, c2) >> 2) |
+                                  (dropped_signs(m.w, c2) >> 3));
+    }
 
-    int rank = 0, total = 0;
+    uint32_t m0 = 0u, m1 = 0u;
+#pragma unroll
+    for (int b = 0; b < BATCH; ++b) {
+        const uint32_t a0 = magnitude_bits(v[b].x), a1 = magnitude_bits(v[b].y);
+        m0 = b == 0 ? a0 : larger_bits(m0, a0);
+        m1 = b == 0 ? a1 : larger_bits(m1, a1);
+        if (MASKED && inside) {
+            // a dropped half's sign bit, brought down to bit 0 of its half, times 0xFFFF covers the half
+            const uint32_t t0 = dropped_signs(a0, c2) >> 15, t1 = dropped_signs(a1, c2) >> 15;
+            *reinterpret_cast<u32x2 *>(x_masked + (size_t)b * K + first) = u32x2{v[b].x & ~((t0 << 16) - t0), v[b].y & ~((t1 << 16) - t1)};
+        }
+    }
+    const uint32_t d0 = dropped_signs(m0, c2), d1 = dropped_signs(m1, c2);
+    const bool kept[kPerLane] = {inside && !(d0 & 0x8000u), inside && !(d0 >> 31), inside && !(d1 & 0x8000u), inside && !(d1 >> 31)};
+    int rank = 0, total = 0;     // entries kept by lower lanes, and by the whole wavefront
 #pragma unroll
     for (int j = 0; j < kPerLane; ++j) {
-        const uint64_t ballot = __ballot((m >> j) & 1u);
-        rank += __builtin_amdgcn_mbcnt_hi((uint32_t)(ballot >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ballot, 0u));
+        const uint64_t ballot = __ballot(kept[j]);
+        rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(ballot >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ballot, (uint32_t)rank));
         total += __popcll(ballot);
     }
+    if (seg > 0) before = wave_total(before);
     if (lane == 0) {
-        wave_total[wave] = total;
+        wave_kept[wave] = total;
         wave_before[wave] = before;
     }
     __syncthreads();
-    int base = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        const int t = wave_total[w];
-        base += wave_before[w] + ((w < wave) ? t : 0);
-        all += wave_before[w] + t;
-    }
-    if (seg == (int)gridDim.x - 1 && threadIdx.x == 0) *count = all;
+    const int w = lane < waves ? lane : 0;
+    const int wk = lane < waves ? wave_kept[w] : 0, wb = lane < waves ? wave_before[w] : 0;
+    const int base = wave_total(wb + (lane < wave ? wk : 0));
+    if (seg == (int)gridDim.x - 1 && wave == waves - 1 && lane == 0) *count = base + total;
 
     int pos = base + rank;
 #pragma unroll
     for (int j = 0; j < kPerLane; ++j)
-        if ((m >> j) & 1u) idx[pos++] = first + j;
+        if (kept[j]) idx[pos++] = first + j;
 }
 
 int run_gather(const void *x_dev, int64_t K, int batch, float threshold, int32_t *idx_out_dev,
                int32_t *count_out_dev, void *x_masked_dev, void *stream) {
     if (!x_dev || !idx_out_dev || !count_out_dev) return SPQT_EINVAL;
-    if (K <= 0 || K % spqt::kGroup != 0 || K > SPQT_GATHER_MAX_K) return SPQT_ESHAPE;
+    if (K <= 0 || K % kGroup != 0 || K > SPQT_GATHER_MAX_K) return SPQT_ESHAPE;
     if (batch < 1 || batch > SPQT_MAX_BATCH) return SPQT_ESHAPE;
     if (threshold != threshold) return SPQT_EINVAL;   // NaN threshold has no meaning
     if ((uintptr_t)x_dev % 16 != 0 || (uintptr_t)idx_out_dev % 4 != 0) return SPQT_EALIGN;
     if ((uintptr_t)x_masked_dev % 16 != 0) return SPQT_EALIGN;
     const int segments = (int)((K + kSegment - 1) / kSegment);
-    const dim3 grid(segments), block(kThreads);
+    const dim3 grid(segments), block(segments > 1 ? kMaxWaves * 64 : 64 * (int)((K + 64 * kPerLane - 1) / (64 * kPerLane)));
     hipStream_t st = (hipStream_t)stream;
     const uint16_t *x = (const uint16_t *)x_dev;
     if (x_masked_dev) {

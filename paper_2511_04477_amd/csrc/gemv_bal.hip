@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "keep.hpp"
 #include "pass.hpp"
 
 namespace {
@@ -34,35 +35,15 @@ constexpr int kXsSteps = 64;              // steps of x kept in LDS: K <= 32768 
 constexpr int kPackSteps = 3;             // step counts packed in one 32-bit word (10 bits each, a count is <= 512)
 constexpr int kRing = 1024;               // ring entries per wavefront; a refill adds at most 512 to at most 63 live ones
 
-typedef short s16x2 __attribute__((ext_vector_type(2)));
-
-// The sparsity test |x| < thr on fp16 bit patterns.  For an fp16 x and an fp32 thr, |x| < thr holds iff
-// |x| < c, c being the smallest fp16 value >= thr (c = 0 for thr <= 0: nothing is below it; c = +inf for
-// thr above the largest finite fp16), and for non-negative fp16 values the order of the values is the
-// order of their bit patterns, NaN patterns lying above +inf: so the test is (bits & 0x7FFF) < bits(c)
-// as 15-bit integers, two halves of a dword at a time - exactly the result of the fp32 comparison
-// (NaN and, at any finite threshold, Inf are kept; an entry equal to the threshold is kept).
-__device__ __forceinline__ uint32_t threshold_bits(float thr) {
-    if (!(thr > 0.0f)) return 0u;
-    const _Float16 h = (_Float16)thr;                       // round to nearest even
-    uint32_t b = __builtin_bit_cast(uint16_t, h);
-    if ((float)h < thr) b += 1u;                            // next fp16 up (from the largest finite one: +inf)
-    return b | (b << 16);
-}
-// Sign bits (bit 15 / bit 31) set where the half is DROPPED.
-__device__ __forceinline__ uint32_t dropped_signs(uint32_t two_halves, uint32_t c2) {
-    const s16x2 d = __builtin_bit_cast(s16x2, two_halves & 0x7FFF7FFFu) - __builtin_bit_cast(s16x2, c2);
-    return __builtin_bit_cast(uint32_t, d) & 0x80008000u;
-}
 // Number of dropped entries among the eight fp16 values of v.
 __device__ __forceinline__ int dropped_count8(u32x4 v, uint32_t c2) {
-    return (int)__popc(dropped_signs(v.x, c2) | (dropped_signs(v.y, c2) >> 1) | (dropped_signs(v.z, c2) >> 2) |
-                       (dropped_signs(v.w, c2) >> 3));
+    return (int)__popc(dropped_signs(magnitude_bits(v.x), c2) | (dropped_signs(magnitude_bits(v.y), c2) >> 1) | (dropped_signs(magnitude_bits(v.z), c2) >> 2) |
+                       (dropped_signs(magnitude_bits(v.w), c2) >> 3));
 }
 // Bit i set iff entry i of the eight fp16 values of v is KEPT.
 __device__ __forceinline__ uint32_t keep_bits8(u32x4 v, uint32_t c2) {
-    const uint32_t u = (dropped_signs(v.x, c2) >> 15) | (dropped_signs(v.y, c2) >> 13) | (dropped_signs(v.z, c2) >> 11) |
-                       (dropped_signs(v.w, c2) >> 9);
+    const uint32_t u = (dropped_signs(magnitude_bits(v.x), c2) >> 15) | (dropped_signs(magnitude_bits(v.y), c2) >> 13) | (dropped_signs(magnitude_bits(v.z), c2) >> 11) |
+                       (dropped_signs(magnitude_bits(v.w), c2) >> 9);
     return ~(u | (u >> 15)) & 0xFFu;
 }
 
@@ -80,16 +61,6 @@ __device__ __forceinline__ int wave_inclusive_scan(int v, int lane, int &total) 
     total = t0 + t1 + t2 + t3;
     return v + (row > 0 ? t0 : 0) + (row > 1 ? t1 : 0) + (row > 2 ? t2 : 0);
 }
-// Sum over the 64 lanes (wave-uniform).
-__device__ __forceinline__ int wave_total(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
-    return __builtin_amdgcn_readlane(v, 15) + __builtin_amdgcn_readlane(v, 31) + __builtin_amdgcn_readlane(v, 47) +
-           __builtin_amdgcn_readlane(v, 63);
-}
-
 template <int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
     const uint8_t *__restrict__ packed, const uint16_t *__restrict__ x, float thr, float *__restrict__ y,
