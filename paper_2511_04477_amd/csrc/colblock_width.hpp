@@ -48,12 +48,8 @@ __device__ __forceinline__ void colblock_width_gemv(const uint8_t *__restrict__ 
     const int seg = lane & 7;      // eighth of the block-row this lane reads
     const int cgr = ((cg & 1) << 2) | (cg & 2) | (cg >> 2);
     const uint32_t seg16 = (uint32_t)seg * 16u;
-    // all S workgroups of a block-row on one XCD (workgroups go to the 8 XCDs round-robin)
-    const int xcd = blockIdx.x & 7;
-    const int slot_id = blockIdx.x >> 3;
-    const int t = xcd + 8 * (slot_id / S);
-    const int s = slot_id % S;
-    if (t >= T) return;
+    int t, s;
+    if (!block_of((int)blockIdx.x, S, T, t, s)) return;
 
     // what is split evenly: the kept-column list, all columns, or (one launch) the 64-column units
     const int n_raw = FUSED ? K / kPassCols : (DENSE ? K : __builtin_amdgcn_readfirstlane(*count));
@@ -252,7 +248,7 @@ int colblock_width_run(int mode, int batch, int max_splits, int default_splits, 
         partials = (void *)((uint8_t *)workspace_dev + counter_bytes(M));
     }
     const int T = (int)T64, NC = (int)(K / kGroup);
-    const int grid = 8 * ((T + 7) / 8) * S;
+    const int grid = grid_blocks(T, S);
     const int m_and_flags = (int)M | (y_half ? kHalfOutputBit : 0);
     const hipError_t err = launch(waves, mode, grid, partials, ws_flags, NC, S, T, m_and_flags);
     return err == hipSuccess ? SPQT_OK : SPQT_EHIP;

@@ -260,7 +260,7 @@ extern "C" int spqt_default_cfg(int64_t M, int64_t K, int batch, int sparse, spq
     if (!out) return SPQT_EINVAL;
     if (int rc = check_shape(M, K, kGroup)) return rc;
     if (batch < 1 || batch > SPQT_MAX_BATCH) return SPQT_ESHAPE;
-    choose_cfg(M, K, batch, Kernel::group_layout, out);
+    choose_cfg(M, K, batch, out);
     return SPQT_OK;
 }
 
@@ -281,7 +281,7 @@ int gemv_run(const void *packed_dev, int64_t M, int64_t K, int group, const void
 
     const bool one_group = cfg && (cfg->flags & SPQT_CFG_GROUP_PASSES);
     spqt_launch_cfg c;
-    choose_cfg(M, K, batch, Kernel::group_layout, &c);
+    choose_cfg(M, K, batch, &c);
     if (cfg && (cfg->splits || cfg->waves)) {
         if (cfg->splits) c.splits = cfg->splits;
         if (cfg->waves) c.waves = cfg->waves;
@@ -358,7 +358,7 @@ extern "C" int spqt_gemv_static(const void *packed_dev, int64_t M, int64_t K, in
     if (int rc = check_shape(M, K, group)) return rc;
     if (batch < 1 || batch > SPQT_MAX_BATCH) return SPQT_ESHAPE;
     spqt_launch_cfg c;
-    choose_cfg(M, K, batch, Kernel::group_layout, &c);
+    choose_cfg(M, K, batch, &c);
     if (c.splits > 1 && exchange_bytes(tiles(M), kTileRows, c.splits, batch) > kStaticScratchBytes) return SPQT_ESIZE;
     void *ws = nullptr;
     if (int rc = static_scratch(&ws)) return rc;
@@ -381,7 +381,7 @@ extern "C" int spqt_gemv_fused(const void *packed_dev, int64_t M, int64_t K, int
     if (even_shares && ((cfg->flags & SPQT_CFG_NO_COMPACTION) || K > 32768 || (uintptr_t)x_dev % 16 != 0)) return SPQT_EINVAL;
     const bool static_ranges = !even_shares;
     spqt_launch_cfg c;
-    choose_cfg(M, K, 1, Kernel::group_layout, &c);
+    choose_cfg(M, K, 1, &c);
     if (cfg) {
         if (cfg->splits) c.splits = cfg->splits;
         if (cfg->waves) c.waves = cfg->waves;
@@ -429,7 +429,7 @@ extern "C" int spqt_gemv_fused_rows(const void *packed_dev, int64_t M, int64_t K
     if ((uintptr_t)packed_dev % 128 != 0 || (uintptr_t)x_dev % 2 != 0 || (uintptr_t)y_dev % (y_half ? 2 : 4) != 0)
         return SPQT_EALIGN;
     spqt_launch_cfg c;
-    choose_cfg(M, K, batch, Kernel::group_layout, &c);
+    choose_cfg(M, K, batch, &c);
     if (cfg) {
         if (cfg->splits) c.splits = cfg->splits;
         if (cfg->waves && cfg->waves != 4) return SPQT_EINVAL;   // callers get 4 wavefronts per workgroup

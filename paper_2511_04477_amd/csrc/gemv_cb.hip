@@ -66,12 +66,8 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
     const int seg = lane & 7;
     const int cgr = ((cg & 1) << 2) | (cg & 2) | (cg >> 2);
     const uint32_t seg16 = (uint32_t)seg * 16u;
-    // all S workgroups of a block-row on one XCD (workgroups go to the 8 XCDs round-robin)
-    const int xcd = blockIdx.x & 7;
-    const int slot_id = blockIdx.x >> 3;
-    const int t = xcd + 8 * (slot_id / S);
-    const int s = slot_id % S;
-    if (t >= T) return;
+    int t, s;
+    if (!block_of((int)blockIdx.x, S, T, t, s)) return;
 
     // (a count outside 0..K cannot come from spqt_gather; clamping keeps a corrupt one inside idx)
     const int n_raw = FUSED ? K / kPassCols : (DENSE ? K : __builtin_amdgcn_readfirstlane(*count));
@@ -348,15 +344,10 @@ int run_cb(int mode, int batch, const void *packed_dev, int64_t M, int64_t K, co
     if ((uintptr_t)packed_dev % 128 != 0 || (uintptr_t)x_dev % 2 != 0 || (uintptr_t)y_dev % (y_half ? 2 : 4) != 0)
         return SPQT_EALIGN;
     spqt_launch_cfg c;
-    choose_cfg(M, K, batch, (mode != 1 && mode != 4) ? Kernel::colblock_list : Kernel::colblock_dense, &c);
-    {
-        // Measured on MI355X (sweep of S per shape, 50 % and dense): this kernel has no per-group
-        // work, so on matrices large enough to be bandwidth-bound (>= 64 MB packed) fewer, longer
-        // slices win for the batch-1 list-driven and dense kernels: about 256 workgroups instead of 512 / 1024.
-        const int64_t T64 = tiles(M);
-        if (mode != 2 && mode != 5 && batch == 1 && (size_t)M * (size_t)K / 2 >= ((size_t)64 << 20))
-            while (c.splits > 1 && (int64_t)c.splits * T64 > 256) c.splits /= 2;
-    }
+    c.splits = colblock_splits(tiles(M), K, mode == 1 || mode == 4 ? Columns::dense : mode == 2 || mode == 5 ? Columns::units : Columns::list,
+                               batch, 3);
+    while (c.splits > K / kGroup) --c.splits;      // at least a quarter of a chunk per wavefront
+    c.waves = 4;
     if (cfg) {
         if (cfg->splits) c.splits = cfg->splits;
         if (cfg->waves) c.waves = cfg->waves;
@@ -375,7 +366,7 @@ int run_cb(int mode, int batch, const void *packed_dev, int64_t M, int64_t K, co
         partials = (void *)((uint8_t *)workspace_dev + counter_bytes(M));
     }
     const int T = (int)tiles(M), NC = (int)(K / kGroup);
-    const int grid = 8 * ((T + 7) / 8) * c.splits;
+    const int grid = grid_blocks(T, c.splits);
     hipStream_t st = (hipStream_t)stream;
     const uint8_t *pk = (const uint8_t *)packed_dev;
     const uint16_t *xp = (const uint16_t *)x_dev;

@@ -139,12 +139,14 @@ int run2(int mode, int batch, const void *packed_dev, int64_t M, int64_t K, cons
          const spqt_launch_cfg *cfg) {
     // a fourth activation row's 64 accumulators no longer fit the register file next to two stages of weights
     if (batch > kMaxRows2) return SPQT_ESHAPE;
-    // about one workgroup of 4 wavefronts per CU: the 64 accumulators per activation row and two stages
-    // of weights leave room for one wavefront per SIMD; S a power of two <= 16
+    // one workgroup of 4 wavefronts per CU: the 64 accumulators per activation row and two stages of weights leave
+    // room for one wavefront per SIMD
     const int64_t T64 = (M + W2::kRows - 1) / W2::kRows;
     int S0 = 1;
-    while (S0 * 2 <= kMaxSplits2 && (int64_t)S0 * 2 * T64 <= 256) S0 *= 2;
-    while (S0 > 1 && (int64_t)S0 * 4 * kPassCols > K) S0 /= 2;      // at least one full pass (or unit) per wavefront when dense
+    if (check_shape(M, K, kGroup) == SPQT_OK) {    // colblock_width_run refuses the others
+        S0 = colblock_splits(T64, K, mode == 1 ? Columns::dense : mode == 2 ? Columns::units : Columns::list, batch, 1);
+        while (S0 > 1 && (int64_t)S0 * 4 * kPassCols > K) --S0;      // at least one full pass (or unit) per wavefront when dense
+    }
     hipStream_t st = (hipStream_t)stream;
     const uint8_t *pk = (const uint8_t *)packed_dev;
     const uint16_t *xp = (const uint16_t *)x_dev;

@@ -111,14 +111,12 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb8_gemv_kernel(
 int run8(int mode, int batch, const void *packed_dev, int64_t M, int64_t K, const void *x_dev, const int32_t *idx_dev,
          const int32_t *count_dev, float thr, void *y_dev, void *workspace_dev, size_t workspace_bytes, void *stream,
          const spqt_launch_cfg *cfg) {
-    // same targets as the 4-bit column-block kernel: about 512 (list) / 1024 (dense) workgroups of
-    // 4 wavefronts, 256 on matrices large enough to be bandwidth-bound; S a power of two <= 16
     const int64_t T64 = (M + W8::kRows - 1) / W8::kRows;
-    const bool big = M > 0 && K > 0 && (size_t)M * (size_t)K >= ((size_t)64 << 20);
-    const int64_t target = big && batch == 1 ? 256 : (mode == 1 && batch == 1 ? 1024 : 512);
     int S0 = 1;
-    while (S0 * 2 <= 16 && (int64_t)S0 * 2 * T64 <= target) S0 *= 2;
-    while (mode == 2 && S0 > 1 && (int64_t)S0 * 4 * kPassCols > K) S0 /= 2;   // one launch: at least one unit per wavefront
+    if (check_shape(M, K, kGroup) == SPQT_OK) {    // colblock_width_run refuses the others
+        S0 = colblock_splits(T64, K, mode == 1 ? Columns::dense : mode == 2 ? Columns::units : Columns::list, batch, 3);
+        while (mode == 2 && S0 > 1 && (int64_t)S0 * 4 * kPassCols > K) --S0;   // one launch: at least one unit per wavefront
+    }
     hipStream_t st = (hipStream_t)stream;
     const uint8_t *pk = (const uint8_t *)packed_dev;
     const uint16_t *xp = (const uint16_t *)x_dev;

@@ -41,32 +41,75 @@ inline int check_shape(int64_t M, int64_t K, int group) {
 // Workgroups in the grid of a group-layout launch (block_of in gemv_common.hpp says which is which).
 inline int grid_blocks(int64_t T, int S) { return 8 * (int)((T / 8) * S + ((T % 8) * S + 7) / 8); }
 
-enum class Kernel { group_layout, colblock_list, colblock_dense };
-
-// Launch shape, measured on MI355X over the benchmark's matrices at 50 % sparsity and dense.
-// Group layout, one or two activation rows: about one workgroup of 4 wavefronts per CU - at most 256 in total - and S any
+// Launch shape of the group layout, measured on MI355X over the benchmark's matrices at 50 % sparsity and dense.
+// One or two activation rows: about one workgroup of 4 wavefronts per CU - at most 256 in total - and S any
 // integer up to 16.  More workgroups only shorten every wavefront's slice, and the fixed cost per wavefront (dependent
 // prologue loads, pipeline fill, exchange of partial sums) outweighs the extra parallelism: dense 13824 x 5120 with 4 / 8
 // / 16 workgroups per block-row 9.7 / 11.0 / 12.3 us, index list at 50 % 28672 x 8192 with 2 / 4 / 6 15.5 / 17.0 / 17.0.
-// Three or four rows, and the column-block layouts: about 512 (dense with one row: 1024) workgroups, S a power of two.
-inline void choose_cfg(int64_t M, int64_t K, int batch, Kernel kind, spqt_launch_cfg *out) {
+// Three or four rows: about 512 workgroups, S a power of two.
+inline void choose_cfg(int64_t M, int64_t K, int batch, spqt_launch_cfg *out) {
     const int64_t T = tiles(M), NG = K / kGroup;
     const int waves = 4;
     int64_t S = 1;
-    if (kind == Kernel::group_layout && batch <= 2) {
+    if (batch <= 2) {
         S = 256 / T;
         S = S < 1 ? 1 : (S > 16 ? 16 : S);
         while (S > 1 && S * waves > 4 * NG) --S;
     } else {
-        const bool big = (size_t)M * (size_t)K / 2 >= ((size_t)64 << 20);
-        const int64_t target = batch >= 2 ? 512 : (kind != Kernel::colblock_dense ? 512 : (big ? 256 : 1024));
-        while (S * 2 <= 16 && S * 2 * T <= target) S *= 2;
+        while (S * 2 <= 16 && S * 2 * T <= 512) S *= 2;
         // keep at least a quarter of a quantization group per wavefront
         while (S > 1 && S * waves > 4 * NG) S /= 2;
     }
     out->splits = (int)S;
     out->waves = waves;
     out->flags = 0;
+}
+
+// Workgroups (of 4 wavefronts) per block-row of the column-block kernels, any integer up to 16; T block-rows.  What counts is
+// how full the last round over the 256 CUs is: `depth` workgroups per CU leave T * S <= 256 * depth.  Power-of-two S
+// left it at 62 to 87 % of the CUs for most heights.  Swept per layout, mode and shape (us, at 50 % sparsity or dense):
+//   - one workgroup per CU is where every kernel starts: 4-bit, T = 20, list 5120 x 13824 S = 16 / 12 10.6 / 9.3, dense 14.3 / 11.5;
+//   - lists of 1 or 2 rows go deeper for a 3 % fuller last round (4-bit, T = 54, 13824 x 5120 S = 4 / 8 / 14 9.4 / 9.8 / 8.6; 8-bit,
+//     T = 86, 11008 x 4096 S = 2 / 5 / 8 9.7 / 9.2 / 8.5), the others only for a 20 % fuller one, since two workgroups on a CU cost them
+//     more than that (4-bit dense 13824 x 5120 S = 4 / 8 12.0 / 12.6, 4 rows 15.8 / 16.3);
+//   - a list slice of 112 to 256 columns (1 or 2 rows) is a pass and a bit: two workgroups per CU (8-bit 4096 x 4096 S = 8 / 16 6.6 / 6.0,
+//     but 4-bit 9000 x 2944 with 105 columns S = 7 / 14 6.0 / 6.2);
+//   - dense slices of at most one pass, if 3 workgroups per CU reach that without a less full round (4-bit 11008 x 4096 S = 5 / 16
+//     9.7 / 8.9, 9000 x 2944 S = 7 / 14 7.5 / 6.9);
+//   - one launch: passes are half full, so slices of more than 5 units want a second workgroup per CU (4-bit 28672 x 8192
+//     S = 2 / 4 23.0 / 19.4, 8-bit 4096 x 11008 S = 8 / 16 9.4 / 9.1, but 4-bit 13824 x 5120 with 5 units S = 4 / 7 9.8 / 10.0), and
+//     S is the smallest with the same number of units in the longest slice (4-bit 5120 x 5120 S = 12 / 10 6.6 / 6.4);
+//   - several rows with slices from 1024 columns on: two workgroups per CU (4-bit, 4 rows, 28672 x 8192 S = 2 / 4 36.7 / 34.0).
+// max_depth 1: one workgroup fills a CU's registers (2-bit: 28672 x 8192 S = 4 / 8 16.1 / 17.3).
+enum class Columns { list, dense, units };    // units: one launch, static ranges of 64-column units
+inline int colblock_splits(int64_t T, int64_t K, Columns from, int batch, int max_depth) {
+    auto deepest = [&](int64_t depth) {
+        const int64_t S = 256 * depth / T;
+        return (int)(S < 1 ? 1 : (S > 16 ? 16 : S));
+    };
+    auto fill = [&](int64_t S) {              // per cent of the CUs' slots, rounds up to the last one
+        const int64_t n = T * S, rounds = (n + 255) / 256;
+        return (int)(n * 100 / (256 * rounds));
+    };
+    auto slice = [&](int64_t S) { return K / (4 * S); };
+    const int64_t least_gain = from == Columns::list && batch <= 2 ? 103 : 120;
+    int64_t S = deepest(1), depth = 1;
+    const bool long_slices = from == Columns::units ? slice(S) > 5 * 64 : batch >= 2 && slice(S) >= 1024;
+    if (max_depth >= 2 && long_slices) S = deepest(depth = 2);
+    for (int64_t d = depth + 1; d <= max_depth; ++d) {
+        const int64_t gain = depth >= 2 ? 103 : least_gain;
+        if (fill(deepest(d)) * 100 >= fill(S) * gain) S = deepest(d);
+    }
+    if (max_depth >= 2 && from == Columns::list && batch <= 2 && slice(S) >= 112 && slice(S) <= 256 && T * S <= 256 && fill(deepest(2)) >= fill(S))
+        S = deepest(2);
+    if (from == Columns::dense && slice(S) > 64)
+        for (int64_t d = 2; d <= max_depth; ++d)
+            if (K <= 4 * 64 * deepest(d) && fill(deepest(d)) >= fill(S)) { S = deepest(d); break; }
+    if (from == Columns::units) {
+        const int64_t units = K / 64;
+        while (S > 1 && (units + 4 * S - 1) / (4 * S) == (units + 4 * (S - 1) - 1) / (4 * (S - 1))) --S;
+    }
+    return (int)S;
 }
 
 // Three or four activation rows: where choose_cfg's shape is more than one workgroup of 4 wavefronts per CU, the kernels run
