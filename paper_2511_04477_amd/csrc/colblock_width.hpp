@@ -125,7 +125,7 @@ __device__ __forceinline__ void colblock_width_gemv(const uint8_t *__restrict__ 
                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
                 {
                     const int c = (u + 1) * kPassCols + lane;
-                    xr_next = x[c < K ? c : K - 1];
+                    xr_next = __hip_atomic_load(x + (c < K ? c : K - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
                 }
                 const int uu = any ? u : 0;
                 const uint32_t chunk_off = (uint32_t)(uu >> 1) * (uint32_t)F::kChunkBytes;
@@ -156,10 +156,11 @@ __device__ __forceinline__ void colblock_width_gemv(const uint8_t *__restrict__ 
                 pos = uA;
             }
         } else {
+            // atomic loads (the same instructions): plain ones the compiler moves behind the weights, to their use
             auto fetch_k = [&](int p) -> int {
                 const int e = p + lane;
                 if (DENSE) return e < end ? e : 0;
-                return idx[e < end ? e : end - 1];
+                return __hip_atomic_load(idx + (e < end ? e : end - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
             };
             // FETCH stage of the pass at list position p: the next pass's entries, this pass's x, scales
             // and weights.  Lanes past the pass point at its first column and later carry x = 0.

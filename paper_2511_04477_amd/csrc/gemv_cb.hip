@@ -89,10 +89,12 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
     }
 
     if (pos < end) {
+        // Atomic loads (the same instructions): the compiler moves plain ones down to the use of their values, behind the
+        // weights, and then waits for those too (10240 x 18944, list, 4 rows: 42.4 us with plain loads, 39.0 with these).
         auto fetch_k = [&](int p) -> int {
             const int e = p + lane;
             if (DENSE) return e < end ? e : 0;
-            return idx[e < end ? e : end - 1];
+            return __hip_atomic_load(idx + (e < end ? e : end - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         };
 
         // FETCH stage of the pass at list position p (kk = its entries): request the next pass's
@@ -216,7 +218,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
                 {
                     const int c = (u + 1) * kPassCols + lane;
-                    xr_next = x[c < K ? c : K - 1];
+                    xr_next = __hip_atomic_load(x + (c < K ? c : K - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
                 }
                 const int uu = any ? u : 0;
                 const uint32_t chunk_off = (uint32_t)(uu >> 1) * (uint32_t)kCbChunkBytes;
