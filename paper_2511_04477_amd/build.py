@@ -32,7 +32,7 @@ HIPCC_FLAGS = [
     # keep the compiler from forming packed-fp32 VALU ops
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # matrix-core results stay in ordinary VGPRs: with a separate accumulator file the kernels that use
-    # v_mfma would hold their 128 sums twice (AGPRs + copies for the lane folds) and lose a wavefront
+    # v_mfma would copy their sums to scale and add them
     "-mllvm", "-amdgpu-mfma-vgpr-form",
     "-Wno-unused-command-line-argument",
 ]

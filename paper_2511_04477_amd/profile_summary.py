@@ -155,8 +155,8 @@ def main(argv=None) -> int:
         q = sq[k]
         L.append(f"| {k} | {rd:,.0f} | {wr:,.0f} | {(rd + wr) / b:.3f} | {q['SQ_INSTS_VALU']:,.0f} | {q['SQ_INSTS_VALU'] * 64 / weights:.2f} | "
                  f"{q['SQ_INSTS_SALU']:,.0f} | {q['SQ_INSTS_LDS']:,.0f} | {q['SQ_INSTS_VMEM_RD']:,.0f} | {q['SQ_WAVES']:,.0f} |")
-        traffic_rows[k.split("<")[0] + ("_dense" if is_dense(k) else "") + ("_one_launch" if "false, 1, 1>" in k else "")
-                     + ("_group_passes" if "false, 1, 0>" in k else "")] = int(rd + wr)
+        traffic_rows[k.split("<")[0] + ("_dense" if is_dense(k) else "")
+                     + ("_group_passes" if "list_kernel<4, false, 1, 1>" in k else "")] = int(rd + wr)
     L += ["", "VALU lane-ops per weight = VALU wave-instructions (matrix-core instructions included) x 64 / weights multiplied. "
           "The chip issues 39.3 T lane-ops/s (256 CUs x 4 SIMD x 16 lanes x 2.4 GHz)."]
     with open(args.out, "w") as fh:
