@@ -176,9 +176,10 @@ typedef struct {
  * on a block-row).
  *   packed_dev     device copy of spqt_pack's output, 128-byte aligned (else SPQT_EALIGN).
  *   x_dev          fp16[batch][K].
- *   idx_dev        int32 kept-column list from spqt_gather (distinct columns, ascending), or NULL for
- *                  the dense kernel, which visits every column and reads neither idx nor count.  With one
- *                  activation row a list of n_ns == K entries is taken to be 0..K-1 without being read.
+ *   idx_dev        int32 kept-column list (distinct columns, in any order; spqt_gather gives them
+ *                  ascending, which is fastest), or NULL for the dense kernel, which visits every column
+ *                  and reads neither idx nor count.  With one activation row a list of n_ns == K entries,
+ *                  which holds every column, is taken as 0..K-1.
  *   count_dev      int32[1] n_ns on the device (ignored when idx_dev == NULL).
  *   y_dev          fp32[batch][M], fully overwritten (zeros when n_ns == 0).
  *                  Non-finite activations: a kept NaN or +-Inf in x[b] makes EVERY output of row b NaN.

@@ -54,8 +54,9 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
         pos = (int)(((int64_t)n_ns * part) / parts);
         end = (int)(((int64_t)n_ns * (part + 1)) / parts);
     }
-    // One activation row: a list of all K columns is the identity (the entries are distinct columns in ascending order),
-    // so the FIRST pass does not wait for its entries, which takes a dependent memory access off the start.
+    // One activation row: a list of K entries holds every column once, so every pass takes columns 0, 1, 2, ... in its place
+    // whatever order the list has.  The FIRST pass then does not wait for its entries, which takes a dependent memory
+    // access off the start.
     const bool all_kept = DENSE || (BATCH == 1 && n_ns == K);
 
     const int log2g = (NG << 7) == K ? 7 : 6;
@@ -69,8 +70,9 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
         for (int p = 0; p < 4; ++p) acc[b][p] = 0.0f;
 
     if (pos < end) {
-        // List entry p + lane (clamped: the load is never predicated).  It is an atomic load (the same instruction) because
-        // the compiler moves a plain one down to the use of its value, behind the weights, and then waits for those too.
+        // List entry p + lane (clamped: the load is never predicated, so the number of loads in flight is the same on every
+        // path).  It is an atomic load (the same instruction) because the compiler moves a plain one down to the use of its
+        // value, behind the weights, and then waits for those too.
         auto fetch_k = [&](int p) -> int {
             const int e = p + lane;
             if (DENSE) return e;
@@ -87,7 +89,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
         // HEAD of the pass that starts at list position p < end: deal the entries to the pass's groups, request the
         // entries of the pass after it and its x.  Returns where the pass after it starts.
         auto head = [&](int p) -> int {
-            const int kk = p + lane < end ? k_next : -1;
+            const int kk = p + lane < end ? (BATCH == 1 && all_kept ? p + lane : k_next) : -1;
             g = kk >> log2g;
             const Deal d = deal_groups<GROUPS>(kk, g, lane);
             const int k_own = d.take ? kk : 0;

@@ -108,3 +108,26 @@ def test_rounding_of_the_sums(gpu, rows):
     rel = np.linalg.norm(got - ref) / np.linalg.norm(ref)
     print(f"rounding rows={rows}: {rel:.2e}", flush=True)
     assert rel < 2e-5
+
+
+@pytest.mark.parametrize("rows", [1, 2, 4])
+@pytest.mark.parametrize("order", ["reversed", "shuffled"])
+def test_full_list_in_any_order(gpu, rows, order):
+    """A list of all K columns that is not ascending, slices of several passes: every column counts exactly once."""
+    torch, spqt, dev = gpu
+    M, K = 256, 2048
+    w = make_weights(M, K, 5400)
+    x_np = make_x(K, "normal", 5401, batch=rows)
+    ref = oracle.gemv(w["q_rowmajor"], w["scales"], x_np, 0.0)
+    cols = np.arange(K)[::-1] if order == "reversed" else np.random.default_rng(5402).permutation(K)
+    packed = torch.from_numpy(spqt.spqt_pack(w["q_rowmajor"], w["scales"])).to(dev)
+    x = torch.from_numpy(x_np if rows > 1 else x_np[0].copy()).to(dev)
+    idx = torch.from_numpy(np.ascontiguousarray(cols, dtype=np.int32)).to(dev)
+    cnt = torch.full((1,), K, dtype=torch.int32, device=dev)
+    ws = spqt.new_workspace(M, K, rows)
+    for splits in (1, 3, 0):
+        print(f"full list {order} rows={rows} splits={splits}", flush=True)
+        y = torch.full((rows, M) if rows > 1 else (M,), float("nan"), dtype=torch.float32, device=dev)
+        spqt.spqt_gemv(packed, M, K, x, idx, cnt, y, ws, splits=splits)
+        torch.cuda.synchronize()
+        check(y.cpu().numpy().reshape(rows, M), ref, f"full list {order} splits={splits}")
