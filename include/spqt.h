@@ -77,8 +77,9 @@ const char *spqt_status_str(int status);
 int spqt_packed_bytes(int64_t M, int64_t K, int group, size_t *out_bytes);
 
 /* Size in bytes of the device workspace spqt_gemv needs for this shape: a 256-byte head plus, for
- * each of up to SPQT_MAX_SPLITS workgroups that may share a block-row, 256 x batch 64-bit words
- * {partial sum, tag} through which they hand their partial sums to the workgroup that writes y.
+ * each of up to SPQT_MAX_SPLITS workgroups that may share a block-row, 8 bytes for each of 256 x batch
+ * outputs, where they hand their partial sums to the workgroup that writes y (as 32-bit words, 0 = not
+ * there yet, so half of it is reserve).
  * The workspace must be prepared ONCE with spqt_workspace_init before its first use.  The workgroup
  * that consumes a word puts it back to zero, so every call leaves the workspace all zeros: calls on
  * one stream, or replays of one graph, may share one workspace whatever their M, K, batch, launch

@@ -26,6 +26,8 @@ TIMELINE_LIB = os.path.join(PKG, "libspqt_timeline.so")
 # what the tests use to run the give-up path of the exchange (NaN outputs, poison flag) without a stalled kernel.
 GIVEUP_LIB = os.path.join(PKG, "libspqt_giveup.so")
 GIVEUP_SOURCES = ["pack.cpp", "gemv.hip", "gemv_list.hip", "gemv_bal.hip"]
+# The library with reducers that never wait in a block-row spread over several XCDs: they hand the sum over at once.
+HANDOVER_LIB = os.path.join(PKG, "libspqt_handover.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -69,6 +71,7 @@ def build(verbose: bool = False) -> str:
     plan = [_jobs(CALIB_LIB, CALIB_SOURCES),
             _jobs(TIMELINE_LIB, SOURCES, defines=("SPQT_TIMELINE=1",), tag="tl_"),
             _jobs(GIVEUP_LIB, GIVEUP_SOURCES, defines=("SPQT_TEST_GIVE_UP=1",), tag="gu_"),
+            _jobs(HANDOVER_LIB, SOURCES, defines=("SPQT_TEST_HAND_OVER=1",), tag="ho_"),
             _jobs(LIB, SOURCES)]
     # every object of every library in one pool (longest first), then the links
     compiles = sorted((c for cs, _ in plan for c in cs), key=lambda c: -os.path.getsize(c[-1]))

@@ -212,7 +212,7 @@ __device__ __forceinline__ void colblock_width_gemv(const uint8_t *__restrict__ 
 #pragma unroll
     for (int b = 0; b < BATCH; ++b) F::finish(acc[b], bs[b], seg, cgr, red[wave][b]);
     __syncthreads();
-    combine_block_row<WAVES, BATCH, F::kRows>(&red[0][0][0], tid, t, s, S, partials, ws_flags, y, M);
+    combine_block_row<WAVES, BATCH, F::kRows>(&red[0][0][0], tid, t, s, S, T, partials, ws_flags, y, M);
 }
 
 // Host side shared by the entry points: argument checks, launch shape, workspace, grid.  `launch` starts the

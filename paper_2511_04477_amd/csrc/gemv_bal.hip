@@ -246,7 +246,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
                                                          acc[0][2] * kEvenUnit, acc[0][3] * kOddUnit};
     __syncthreads();
     SPQT_TL(5);
-    combine_block_row<WAVES, 1>(&red[0][0][0], tid, t, s, S, partials, ws_flags, y, M);
+    combine_block_row<WAVES, 1>(&red[0][0][0], tid, t, s, S, T, partials, ws_flags, y, M);
     SPQT_TL_END(WAVES, wave, lane, S > 1 && s == S - 1);
 }
 

@@ -290,7 +290,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
             f32x4{r4[0] - bias, r4[1] - bias, r4[2] - bias, r4[3] - bias};
     }
     __syncthreads();
-    combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, t, s, S, partials, ws_flags, y, M);
+    combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, t, s, S, T, partials, ws_flags, y, M);
 }
 
 template <int WAVES, int BATCH>

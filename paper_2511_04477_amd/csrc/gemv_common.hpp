@@ -33,6 +33,13 @@ constexpr bool kMuteProducers = true;
 constexpr int kMaxPolls = 1 << 18;             // bound on the reducer's wait for one batch of partials
 constexpr bool kMuteProducers = false;
 #endif
+constexpr int kHandOverPolls = 1 << 10;        // polls (about 1 ms) after which the reducer of a spread block-row hands over
+#ifdef SPQT_TEST_HAND_OVER
+// Test build (libspqt_handover.so): it hands over instead of waiting for the last of its words.
+constexpr bool kAlwaysHandOver = true;
+#else
+constexpr bool kAlwaysHandOver = false;
+#endif
 
 // Per-wavefront wall-clock stamps for the timeline build (-DSPQT_TIMELINE=1, libspqt_timeline.so): every
 // wavefront records when it started (0), knew its share of the list (1), had issued its first pass (2),
@@ -200,9 +207,9 @@ hipError_t launch_gemv_list(int waves, int batch, bool one_group, int grid, hipS
 // of a block-row are kept on ONE XCD as far as that leaves the XCDs equally loaded: block-rows in multiples of 8 go to the
 // XCDs whole, and the workgroups of the T % 8 that are left are spread over the XCDs evenly (with 20 block-rows, whole
 // ones would give four XCDs 3 and four 2: 5120 x 13824 dense, 12 workgroups per block-row, 13.1 us, evenly 10.4).  A
-// spread block-row's reducer may run before producers on another XCD are dispatched; there are at most 8 such rows, and
-// every other workgroup of the launch finishes without them, so they always get their turn.
+// spread block-row's reducer may run before producers on another XCD are dispatched, which combine_block_row allows for.
 // Returns false for the padding of the grid (grid_blocks).
+__device__ __forceinline__ bool is_spread(int t, int T) { return t >= (T & ~7); }
 __device__ __forceinline__ bool block_of(int index, int S, int T, int &t, int &s) {
     const int xcd = index & 7;
     const int slot = index >> 3;               // position among this XCD's workgroups
@@ -225,24 +232,33 @@ __device__ __forceinline__ bool block_of(int index, int S, int T, int &t, int &s
 // `red` holds this workgroup's [WAVES][BATCH][ROWS] partial sums in LDS (already synchronised);
 // ROWS is the height of a block-row (256 for the 4-bit layouts).
 // Every workgroup but the last (s == S-1) publishes its ROWS partial sums as 32-bit words with device-scope stores
-// (two adjacent rows per store where a thread owns more than one) and is done: no wait, no counter.  A word is the COMPLEMENT of the sum's bits (never 0: the
+// (two adjacent rows per store where a thread owns more than one).  A word is the COMPLEMENT of the sum's bits (never 0: the
 // one pattern that would give 0 is a NaN and is replaced by another NaN), and 0 means "not there yet".  The last
 // workgroup adds the others' words in index order, polling until none is 0, then its own sums, writes y, and stores zero
 // back into every word it consumed - so between calls the exchange area is all zeros whatever M, launch shape or kernel
 // the calls had, and a word that is not 0 is always one of THIS call.  (A tag beside every value would double the bytes:
 // four activation rows, 1024 x 4096, 16 workgroups per block-row: 9.8 us with tagged 64-bit words, 7.4 without;
 // one row, 4096 x 4096: 5.6 and 5.2.)
-// The reducer has the highest index of its block-row and workgroups are dispatched in index order, so
-// everything it waits for is running or finished; the wait is bounded anyway, and a give-up
-// poisons y with NaN instead of hanging and raises the workspace's poison flag (word 0 of its
-// head): a late word of the abandoned call could otherwise be taken for a later call's, so from
+//
+// Why the wait ends.  A whole block-row has all its workgroups on one XCD, where they are dispatched in index order: the
+// reducer has the highest index, so everything it waits for is running or finished.  The workgroups of a SPREAD block-row
+// (block_of) are on several XCDs, which take their shares of a launch independently: a kernel of another stream may hold
+// one XCD for any length of time while the reducer already runs on another.  There a reducer's wavefront that has polled
+// kHandOverPolls times hands its values over: it publishes its own sums too, in the slot that is otherwise unused, and
+// does not wait.  A producer's wavefront of a spread block-row looks at that slot once its own words are out.  A thread
+// exchanges words only with the threads of its own number, and whichever of them publishes last finds all words there and
+// does the sum, in the same order; should several find them, the one that takes the reducer's word out does.  (The look is
+// a round trip at the end of producers only: 1024 x 4096 to 5120 x 13824 take 0 to 0.1 us longer.  A counter of arrivals,
+// shared by the wavefronts of a launch, took 0.7 to 2.3 us.)
+// All waits are bounded anyway, and a give-up poisons y with NaN instead of hanging and raises the workspace's poison flag
+// (word 0 of its head): a late word of the abandoned call could otherwise be taken for a later call's, so from
 // then on every call on that workspace yields NaN until spqt_workspace_init clears it.
 __device__ __forceinline__ uint32_t exchange_word(float v) {
     const uint32_t w = ~as_u32(v);
     return w ? w : 1u;
 }
 template <int WAVES, int BATCH, int ROWS = kTileRows>
-__device__ __forceinline__ void combine_block_row(const float *red, int tid, int t, int s, int S, void *partials,
+__device__ __forceinline__ void combine_block_row(const float *red, int tid, int t, int s, int S, int T, void *partials,
                                                   int32_t *ws_flags, float *__restrict__ y, int m_and_flags) {
     // One kernel argument carries both (M <= 2^24).
     const int M = m_and_flags & kRowsMask;
@@ -256,8 +272,9 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, int
     // A thread that owns several units handles 2 of them together, so that the reducer's loads for
     // all of them are in flight at once (one round trip instead of one per unit).
     constexpr int kTogether = kPerThread < 2 ? kPerThread : 2;
-    Word *slots = reinterpret_cast<Word *>(partials) + (size_t)t * S * kUnits;    // [S - 1][kUnits]
+    Word *slots = reinterpret_cast<Word *>(partials) + (size_t)t * S * kUnits;    // [S][kUnits]; S - 1: handed over
     const bool reducer = S > 1 && s == S - 1;
+    const bool spread = is_spread(t, T) && !kMuteProducers;   // the build with silent producers is for give-ups only
     uint32_t poisoned = 0u;
     if (reducer) poisoned = __hip_atomic_load(reinterpret_cast<uint32_t *>(ws_flags), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (int i0 = tid; i0 < kUnits; i0 += kTogether * kThreads) {
@@ -284,19 +301,36 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, int
                 else y[y_at] = v;
             }
         };
+        auto word_of = [&](const float (&values)[kVals]) -> Word {
+            Word word = exchange_word(values[0]);
+            if (kVals == 2) word |= (Word)((unsigned long long)exchange_word(values[kVals - 1]) << 32);
+            return word;
+        };
+        auto publish = [&]() {
+#pragma unroll
+            for (int i = 0; i < kTogether; ++i) {
+                if (i > 0 && at[i] == at[0]) continue;   // a clamped duplicate: already published
+                if (kMuteProducers) continue;
+                __hip_atomic_store(slots + (size_t)s * kUnits + at[i], word_of(sum[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        };
+        bool handed_over = false;                // (wave-uniform) the reducer of a spread block-row has not waited for all
         if (S == 1) {
 #pragma unroll
             for (int i = 0; i < kTogether; ++i)
 #pragma unroll
                 for (int q = 0; q < kVals; ++q) store_y(i, q, sum[i][q]);
         } else if (!reducer) {
+            publish();
+            if (spread) {
+                // A device-scope store has reached every XCD when it is acknowledged: of two threads that publish and then look
+                // for each other's words one at least finds them.
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                Word there = 0;
 #pragma unroll
-            for (int i = 0; i < kTogether; ++i) {
-                if (i > 0 && at[i] == at[0]) continue;   // a clamped duplicate: already published
-                if (kMuteProducers) continue;
-                Word word = exchange_word(sum[i][0]);
-                if (kVals == 2) word |= (Word)((unsigned long long)exchange_word(sum[i][kVals - 1]) << 32);
-                __hip_atomic_store(slots + (size_t)s * kUnits + at[i], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                for (int i = 0; i < kTogether; ++i)
+                    there |= __hip_atomic_load(slots + (size_t)(S - 1) * kUnits + at[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                handed_over = __ballot(there != 0) != 0ull;
             }
         } else {
             float total[kTogether][kVals];
@@ -305,11 +339,13 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, int
 #pragma unroll
                 for (int q = 0; q < kVals; ++q) total[i][q] = 0.0f;
             bool gave_up = false;
+            int p0 = 0;                          // partial sums consumed so far
             // N partial sums per round; with few workgroups per block-row the larger N would read some of them many times
             auto collect = [&](auto count) {
                 constexpr int N = decltype(count)::value;
-                for (int p0 = 0; p0 < S - 1; p0 += N) {
+                for (; p0 < S - 1; p0 += N) {
                     Word v[kTogether][N];
+                    const bool at_once = kAlwaysHandOver && spread && p0 + N >= S - 1;
                     int polls = 0;
                     bool all_here;
                     do {
@@ -332,7 +368,11 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, int
                                     least = word < least ? word : least;
                                 }
                         all_here = least != 0u;
-                    } while (!all_here && ++polls < kMaxPolls);
+                    } while (!all_here && !at_once && ++polls < (spread ? kHandOverPolls : kMaxPolls));
+                    if (spread && (at_once || __ballot(!all_here) != 0ull)) {     // wave-uniform, like p0: the addresses stay scalar
+                        handed_over = true;
+                        return;
+                    }
                     gave_up = gave_up || !all_here;
 #pragma unroll
                     for (int j = 0; j < N; ++j)
@@ -351,12 +391,49 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, int
             };
             if (S <= 5) collect(std::integral_constant<int, 4>{});
             else collect(std::integral_constant<int, 16>{});
-            if (gave_up) __hip_atomic_store(reinterpret_cast<uint32_t *>(ws_flags), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const bool bad = gave_up || poisoned;
+            if (!handed_over) {
+                if (gave_up) __hip_atomic_store(reinterpret_cast<uint32_t *>(ws_flags), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const bool bad = gave_up || poisoned;
 #pragma unroll
-            for (int i = 0; i < kTogether; ++i)
+                for (int i = 0; i < kTogether; ++i)
 #pragma unroll
-                for (int q = 0; q < kVals; ++q) store_y(i, q, bad ? __builtin_nanf("") : total[i][q] + sum[i][q]);
+                    for (int q = 0; q < kVals; ++q) store_y(i, q, bad ? __builtin_nanf("") : total[i][q] + sum[i][q]);
+            } else {
+                // what was consumed in earlier rounds (no default launch shape has several) is handed over as the first word
+                for (int p = 0; p < p0; ++p)
+#pragma unroll
+                    for (int i = 0; i < kTogether; ++i)
+                        __hip_atomic_store(slots + (size_t)p * kUnits + at[i], p ? (Word)~0ull : word_of(total[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                publish();
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+        }
+        if (handed_over) {
+            // The sum of a handed-over block-row, by the thread that finds all words there.
+#pragma unroll 1
+            for (int i = 0; i < kTogether; ++i) {
+                if (i > 0 && at[i] == at[0]) continue;
+                Word *from = slots + at[i];
+                bool all_here = true;
+                for (int p = S - 1; p >= 0 && all_here; --p)
+                    all_here = __hip_atomic_load(from + (size_t)p * kUnits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+                if (!all_here) continue;         // whoever publishes the missing word comes by here too
+                const Word own = __hip_atomic_exchange(from + (size_t)(S - 1) * kUnits, (Word)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (own == 0) continue;          // another thread does it
+                const uint32_t bad = __hip_atomic_load(reinterpret_cast<uint32_t *>(ws_flags), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                float total[kVals];
+#pragma unroll
+                for (int q = 0; q < kVals; ++q) total[q] = 0.0f;
+#pragma unroll 1
+                for (int p = 0; p < S; ++p) {
+                    const Word v = p == S - 1 ? own : __hip_atomic_load(from + (size_t)p * kUnits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                    for (int q = 0; q < kVals; ++q) total[q] += as_float(~(uint32_t)((unsigned long long)v >> (32 * q)));
+                    if (p < S - 1) __hip_atomic_store(from + (size_t)p * kUnits, (Word)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+#pragma unroll
+                for (int q = 0; q < kVals; ++q) store_y(i, q, bad ? __builtin_nanf("") : total[q]);
+            }
         }
     }
 }

@@ -161,7 +161,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
                                                              acc[b][2] * kEvenUnit, acc[b][3] * kOddUnit};
     __syncthreads();
     SPQT_TL(5);
-    combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, t, s, S, partials, ws_flags, y, M);
+    combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, t, s, S, T, partials, ws_flags, y, M);
     SPQT_TL_END(WAVES, wave, lane, S > 1 && s == S - 1);
 }
 

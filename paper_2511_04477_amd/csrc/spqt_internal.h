@@ -22,8 +22,8 @@ inline int64_t tiles(int64_t M) { return (M + kTileRows - 1) / kTileRows; }
 // wait for partial sums is abandoned; the rest keeps the exchange words 256-byte aligned.
 inline size_t counter_bytes(int64_t) { return 256; }
 
-// Bytes of exchange words a launch with S workgroups per block-row really touches (64-bit words,
-// `rows` outputs per block-row and activation row), head included.
+// Bytes asked for where a launch with S workgroups per block-row brings just its exchange words (8 bytes for each of the
+// `rows` outputs per block-row and activation row; the words are 32-bit, so half of it stays unused), head included.
 inline size_t exchange_bytes(int64_t n_tiles, int rows, int S, int batch) {
     return 256 + (size_t)n_tiles * (size_t)rows * (size_t)S * (size_t)batch * 8;
 }
