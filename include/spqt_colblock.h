@@ -63,7 +63,8 @@ int spqt_cb_dequantize(const void *packed, int64_t M, int64_t K, float *w_out);
  *   count_dev      int32[1] n_ns on the device (ignored when idx_dev == NULL).
  *   y_dev          fp32[batch][M] (fp16 with SPQT_CFG_Y_FP16), fully overwritten.
  *   workspace_dev  as for spqt_gemv: >= spqt_workspace_bytes(M, K, batch), prepared once by
- *                  spqt_workspace_init.
+ *                  spqt_workspace_init.  (Matrices tall enough to keep the chip busy with one workgroup
+ *                  per block-row also run without one, somewhat slower; the others return SPQT_EINVAL.)
  *   cfg            launch shape or NULL (flags: 0 or SPQT_CFG_Y_FP16).
  * Deterministic; same bounded wait and NaN-on-give-up behaviour as spqt_gemv. */
 int spqt_cb_gemv(const void *packed_dev, int64_t M, int64_t K, const void *x_dev, int batch,

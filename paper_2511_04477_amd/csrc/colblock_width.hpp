@@ -216,9 +216,10 @@ __device__ __forceinline__ void colblock_width_gemv(const uint8_t *__restrict__ 
 }
 
 // Host side shared by the entry points: argument checks, launch shape, workspace, grid.  `launch` starts the
-// kernel for (waves, mode) with mode 0 = index list, 1 = dense, 2 = one launch (batch 1 only).
+// kernel for (waves, mode) with mode 0 = index list, 1 = dense, 2 = one launch (batch 1 only).  without_workspace: the
+// default shape is one workgroup per block-row if the call brings no usable workspace.
 template <class F, class Launch>
-int colblock_width_run(int mode, int batch, int max_splits, int default_splits, const void *packed_dev, int64_t M, int64_t K,
+int colblock_width_run(int mode, int batch, int max_splits, int default_splits, bool without_workspace, const void *packed_dev, int64_t M, int64_t K,
                        const void *x_dev, const int32_t *idx_dev, const int32_t *count_dev, void *y_dev,
                        void *workspace_dev, size_t workspace_bytes, const spqt_launch_cfg *cfg, Launch launch) {
     if (!packed_dev || !x_dev || !y_dev) return SPQT_EINVAL;
@@ -230,15 +231,16 @@ int colblock_width_run(int mode, int batch, int max_splits, int default_splits, 
     if ((uintptr_t)packed_dev % 128 != 0 || (uintptr_t)x_dev % 2 != 0 || (uintptr_t)y_dev % (y_half ? 2 : 4) != 0)
         return SPQT_EALIGN;
     const int64_t T64 = (M + F::kRows - 1) / F::kRows;
-    int S = default_splits, waves = 4;
+    size_t need = 0;
+    spqt_workspace_bytes(M, K, batch, &need);
+    int S = without_workspace && !usable_workspace(workspace_dev, workspace_bytes, need) ? 1 : default_splits;
+    int waves = 4;
     if (cfg) {
         if (cfg->splits) S = cfg->splits;
         if (cfg->waves) waves = cfg->waves;
     }
     if (S < 1 || S > max_splits) return SPQT_EINVAL;
     if (waves != 1 && waves != 2 && waves != 4) return SPQT_EINVAL;
-    size_t need = 0;
-    spqt_workspace_bytes(M, K, batch, &need);
     void *partials = nullptr;
     int32_t *ws_flags = nullptr;
     if (S > 1) {

@@ -346,18 +346,21 @@ int run_cb(int mode, int batch, const void *packed_dev, int64_t M, int64_t K, co
     if ((uintptr_t)packed_dev % 128 != 0 || (uintptr_t)x_dev % 2 != 0 || (uintptr_t)y_dev % (y_half ? 2 : 4) != 0)
         return SPQT_EALIGN;
     spqt_launch_cfg c;
-    c.splits = colblock_splits(tiles(M), K, mode == 1 || mode == 4 ? Columns::dense : mode == 2 || mode == 5 ? Columns::units : Columns::list,
-                               batch, 3);
+    const Columns from = mode == 1 || mode == 4 ? Columns::dense : mode == 2 || mode == 5 ? Columns::units : Columns::list;
+    c.splits = colblock_splits(tiles(M), K, from, batch, 3);
     while (c.splits > K / kGroup) --c.splits;      // at least a quarter of a chunk per wavefront
     c.waves = 4;
+    size_t need = 0;
+    spqt_workspace_bytes(M, K, batch, &need);
+    // (the one-launch kernel's limit is the same for matrices of any size)
+    const size_t code_bytes = from == Columns::units ? 0 : (size_t)M * (size_t)K / 2;
+    if (!usable_workspace(workspace_dev, workspace_bytes, need) && runs_without_workspace(tiles(M), code_bytes, from, batch)) c.splits = 1;
     if (cfg) {
         if (cfg->splits) c.splits = cfg->splits;
         if (cfg->waves) c.waves = cfg->waves;
     }
     if (c.splits < 1 || c.splits > SPQT_MAX_SPLITS) return SPQT_EINVAL;
     if (c.waves != 1 && c.waves != 2 && c.waves != 4) return SPQT_EINVAL;
-    size_t need = 0;
-    spqt_workspace_bytes(M, K, batch, &need);
     void *partials = nullptr;
     int32_t *ws_flags = nullptr;
     if (c.splits > 1) {

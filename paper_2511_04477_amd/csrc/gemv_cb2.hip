@@ -151,7 +151,7 @@ int run2(int mode, int batch, const void *packed_dev, int64_t M, int64_t K, cons
     const uint8_t *pk = (const uint8_t *)packed_dev;
     const uint16_t *xp = (const uint16_t *)x_dev;
     return colblock_width_run<W2>(
-        mode, batch, kMaxSplits2, S0, packed_dev, M, K, x_dev, idx_dev, count_dev, y_dev, workspace_dev, workspace_bytes, cfg,
+        mode, batch, kMaxSplits2, S0, false, packed_dev, M, K, x_dev, idx_dev, count_dev, y_dev, workspace_dev, workspace_bytes, cfg,
         [&](int waves, int md, int grid, void *partials, int32_t *ws_flags, int NC, int S, int T, int m_and_flags) {
             switch (waves) {
                 case 1: SPQT_CB2_ROWS(1); break;

@@ -113,15 +113,18 @@ int run8(int mode, int batch, const void *packed_dev, int64_t M, int64_t K, cons
          const spqt_launch_cfg *cfg) {
     const int64_t T64 = (M + W8::kRows - 1) / W8::kRows;
     int S0 = 1;
+    bool without_workspace = false;
     if (check_shape(M, K, kGroup) == SPQT_OK) {    // colblock_width_run refuses the others
-        S0 = colblock_splits(T64, K, mode == 1 ? Columns::dense : mode == 2 ? Columns::units : Columns::list, batch, 3);
+        const Columns from = mode == 1 ? Columns::dense : mode == 2 ? Columns::units : Columns::list;
+        S0 = colblock_splits(T64, K, from, batch, 3);
+        without_workspace = runs_without_workspace(T64, (size_t)M * (size_t)K, from, batch);
         while (mode == 2 && S0 > 1 && (int64_t)S0 * 4 * kPassCols > K) --S0;   // one launch: at least one unit per wavefront
     }
     hipStream_t st = (hipStream_t)stream;
     const uint8_t *pk = (const uint8_t *)packed_dev;
     const uint16_t *xp = (const uint16_t *)x_dev;
     return colblock_width_run<W8>(
-        mode, batch, SPQT_MAX_SPLITS, S0, packed_dev, M, K, x_dev, idx_dev, count_dev, y_dev, workspace_dev, workspace_bytes, cfg,
+        mode, batch, SPQT_MAX_SPLITS, S0, without_workspace, packed_dev, M, K, x_dev, idx_dev, count_dev, y_dev, workspace_dev, workspace_bytes, cfg,
         [&](int waves, int md, int grid, void *partials, int32_t *ws_flags, int NC, int S, int T, int m_and_flags) {
             switch (waves) {
                 case 1: SPQT_CB8_ROWS(1); break;

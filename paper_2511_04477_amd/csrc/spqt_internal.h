@@ -112,6 +112,19 @@ inline int colblock_splits(int64_t T, int64_t K, Columns from, int batch, int ma
     return (int)S;
 }
 
+// A workspace the exchange can use: calls with several workgroups per block-row refuse any other.
+inline bool usable_workspace(const void *ws, size_t bytes, size_t need) {
+    return ws && bytes >= need && (uintptr_t)ws % 256 == 0;
+}
+// Whether a column-block call that asks for no launch shape and brings no usable workspace runs with ONE workgroup per
+// block-row, which exchanges nothing.  Above these heights the block-rows alone keep the chip busy enough for that to be a
+// sensible shape (half the CUs for a matrix of 64 MB and more and one row, all of them otherwise, twice that for a
+// dense one, whose slices are shortest): 4-bit list at 50 % 33024 x 4096 without / with a workspace 13.8 / 13.0 us.
+inline bool runs_without_workspace(int64_t T, size_t code_bytes, Columns from, int batch) {
+    const bool large = batch == 1 && code_bytes >= (size_t)64 << 20;
+    return T > (large ? 128 : (from == Columns::dense && batch == 1 ? 512 : 256));
+}
+
 // Three or four activation rows: where choose_cfg's shape is more than one workgroup of 4 wavefronts per CU, the kernels run
 // one workgroup of 8 per CU instead.  The exchange grows with rows times workgroups per block-row: index list at 70 %
 // sparsity, 4 rows, 14336 x 4096 with 8 x 4 / 4 x 8 wavefronts per block-row 16.2 / 13.1 us, 28672 x 8192 with 4 x 4 / 2 x 8
