@@ -111,11 +111,11 @@ __device__ __forceinline__ void start_products(const StagedX &xs, int lane, u32x
 
 // Whether a pass is computed with -x (and its sums subtracted).  The matrix cores round the terms of a product DOWN, so a
 // sum over many passes carries a negative bias, relative to the result in proportion to sqrt(K).  With x negated the bias
-// changes sign.  One pass in eight is negated, which leaves three quarters of the bias: on 1024 x 28672 dense the error against
-// 64-bit arithmetic (relative 2-norm) is 3.2e-6 for Laplace x and 9.7e-6 for SiLU products.  The 4-wide products of
-// v_mfma_f32_4x4x4 give 1.1e-5 and 2.7e-5, a bias of the same sign; with that much of it left the results also stay
-// within 2e-5 of theirs.  `turn` counts passes, from another start in every wavefront of a block-row.
-__device__ __forceinline__ bool negated(int turn) { return (turn & 7) == 7; }
+// changes sign, so every other pass is negated and it cancels: against 64-bit arithmetic (relative 2-norm, 1024 x 28672
+// dense, one row) 4.4e-6 -> 4.6e-7 for Laplace x and 1.3e-5 -> 7.8e-7 for SiLU products.  (The 4-wide products of
+// v_mfma_f32_4x4x4 have a bias of the same sign, 1.1e-5 and 2.7e-5.)  `turn` counts passes, from another start in every
+// wavefront of a block-row, so slices of one pass cancel too.
+__device__ __forceinline__ bool negated(int turn) { return (turn & 1) != 0; }
 
 // Applies the scales of a pass's groups (sc[g] = the fp16 scales of the lane's 4 rows in group g of the pass) and adds to
 // the lane's running sums, which stay in the products' units.
