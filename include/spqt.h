@@ -138,7 +138,8 @@ int spqt_gather_rows(const void *x_dev, int64_t K, int batch, float threshold, i
  * many workgroups share a block-row, and how many wavefronts each holds).  0 = choose. */
 typedef struct {
     int splits; /* workgroups per block-row, 1..SPQT_MAX_SPLITS (any integer) */
-    int waves;  /* wavefronts per workgroup: 1, 2 or 4 */
+    int waves;  /* wavefronts per workgroup: 1, 2 or 4; 8 with 3 or 4 activation rows, or with an
+                 * index list and one row (spqt_gemv_ex) */
     int flags;  /* 0, or SPQT_CFG_* bits */
 } spqt_launch_cfg;
 
@@ -209,11 +210,11 @@ int spqt_gemv_ex(const void *packed_dev, int64_t M, int64_t K, int group, const 
  * Same arguments, kernels, launch shape and results as spqt_gemv; the exchange words live in a fixed
  * array of SPQT_STATIC_SCRATCH_BYTES inside the library's device image (every GPU the library runs on
  * holds its own copy until the process ends).  The call allocates and frees nothing.
- *   - SPQT_ESIZE when the default launch shape for (M, K, batch) needs more exchange words than the
- *     array holds: 256 + ceil(M/256) * 256 * splits * batch * 8 bytes, splits as spqt_default_cfg
- *     reports (a shape that runs with one workgroup per block-row needs none).  The default launch
- *     shapes keep block-rows x splits <= 512, so every shape fits with 1 or 2 activation rows; with
- *     3 or 4 rows the large ones (e.g. 8192 x 28672: 32 block-rows x 16 splits) do not.
+ *   - SPQT_ESIZE when 256 + ceil(M/256) * 256 * splits * batch * 8 bytes are more than the array holds,
+ *     splits counted for workgroups of 4 wavefronts: one per CU with 1 or 2 activation rows (every shape
+ *     fits), with 3 or 4 rows the largest power of two up to 16 that keeps block-rows x splits <= 512
+ *     (the large ones do not fit, e.g. 8192 x 28672: 32 block-rows x 16 splits).  A shape of one
+ *     workgroup per block-row needs none.
  *   - All calls on one GPU share that GPU's array: calls that may overlap in time (different streams,
  *     different host threads) race on it and must use spqt_gemv with workspaces of their own.  Every
  *     call leaves the array all zeros, so successive calls may differ in shape.
@@ -248,16 +249,16 @@ int spqt_gemv_fused(const void *packed_dev, int64_t M, int64_t K, int group, con
  *              non-zero: row b takes only the columns it keeps itself, |x[b][k]| >= threshold - the
  *              result spqt_gemv_fused gives for that row alone (as spqt_gather_rows + spqt_gemv do).
  *   y_dev      fp32 (or fp16 with SPQT_CFG_Y_FP16) [batch][M].
- *   cfg        NULL, or splits and SPQT_CFG_Y_FP16; this kernel always runs 4 wavefronts per
- *              workgroup (cfg->waves must be 0 or 4, else SPQT_EINVAL).
+ *   cfg        NULL, or splits, waves and SPQT_CFG_Y_FP16; cfg->waves must be 0 or 4, or 8 with 3
+ *              or 4 rows, else SPQT_EINVAL.
  * Workspace as for spqt_gemv with the same batch. */
 int spqt_gemv_fused_rows(const void *packed_dev, int64_t M, int64_t K, int group, const void *x_dev,
                          int batch, float threshold, int own_sets, void *y_dev, void *workspace_dev,
                          size_t workspace_bytes, void *stream, const spqt_launch_cfg *cfg);
 
-/* The launch shape spqt_gemv would pick for this shape (host only, no device access): sparse != 0
- * for a call with an index list, 0 for the dense kernel.  (With 3 or 4 activation rows a shape of more
- * than 256 workgroups runs as at most 256 workgroups of 8 wavefronts, which needs no more exchange words.) */
+/* The launch shape spqt_gemv picks for this shape (host only, no device access): sparse != 0
+ * for a call with an index list (spqt_gemv_fused and spqt_gemv_fused_rows pick the same), 0 for the
+ * dense kernel.  A call may ask for it and gets the same result. */
 int spqt_default_cfg(int64_t M, int64_t K, int batch, int sparse, spqt_launch_cfg *out);
 
 #ifdef __cplusplus

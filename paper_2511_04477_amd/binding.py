@@ -293,7 +293,7 @@ def spqt_gemv_fused(packed, M: int, K: int, x, threshold: float, y, workspace, s
 
 
 def spqt_gemv_fused_rows(packed, M: int, K: int, x, threshold: float, y, workspace, own_sets: bool = False, stream=None,
-                         group: int = GROUP, splits: int = 0) -> None:
+                         group: int = GROUP, splits: int = 0, waves: int = 0) -> None:
     """Threshold + compaction + GEMV in one launch for x fp16[batch, K], batch 1..4; y fp32 (or fp16) [batch, M].
     own_sets: every row sums over its own kept columns instead of the union."""
     import torch
@@ -306,7 +306,7 @@ def spqt_gemv_fused_rows(packed, M: int, K: int, x, threshold: float, y, workspa
     wp, wbytes = None, 0
     if workspace is not None:
         wp, wbytes = _dev(workspace, torch.uint8, "workspace"), workspace.numel()
-    cfg = _cfg(splits, 0, yflags)
+    cfg = _cfg(splits, waves, yflags)
     _check(lib().spqt_gemv_fused_rows(pp, M, K, group, xp, batch, float(threshold), int(bool(own_sets)), yp, wp, wbytes,
                                       _stream_ptr(stream), ctypes.byref(cfg)))
 

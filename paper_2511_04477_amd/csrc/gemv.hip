@@ -260,11 +260,20 @@ extern "C" int spqt_default_cfg(int64_t M, int64_t K, int batch, int sparse, spq
     if (!out) return SPQT_EINVAL;
     if (int rc = check_shape(M, K, kGroup)) return rc;
     if (batch < 1 || batch > SPQT_MAX_BATCH) return SPQT_ESHAPE;
-    choose_cfg(M, K, batch, out);
+    default_shape(M, K, batch, out);
     return SPQT_OK;
 }
 
 namespace {
+
+// Bytes of workspace a call with S workgroups per block-row asks for: what spqt_workspace_bytes reports, or just the exchange
+// words of this launch (`tight`).
+size_t needed_bytes(int64_t M, int64_t K, int batch, int S, bool tight) {
+    size_t need = 0;
+    if (tight) return exchange_bytes(tiles(M), kTileRows, S, batch);
+    spqt_workspace_bytes(M, K, batch, &need);
+    return need;
+}
 
 // spqt_gemv_ex, and the allocation-free variant: `tight` accepts a workspace that holds just the
 // exchange words this launch shape touches instead of the size spqt_workspace_bytes reports.
@@ -281,21 +290,19 @@ int gemv_run(const void *packed_dev, int64_t M, int64_t K, int group, const void
 
     const bool one_group = cfg && (cfg->flags & SPQT_CFG_GROUP_PASSES);
     spqt_launch_cfg c;
-    choose_cfg(M, K, batch, &c);
     if (cfg && (cfg->splits || cfg->waves)) {
+        choose_cfg(M, K, batch, &c);
         if (cfg->splits) c.splits = cfg->splits;
         if (cfg->waves) c.waves = cfg->waves;
-        // a caller may ask for 8 wavefronts per workgroup (two per SIMD) with an index list and one activation row only
-        if (c.waves == 8 && (!idx_dev || batch > 1 || one_group)) return SPQT_EINVAL;
+        // 8 wavefronts per workgroup (two per SIMD) exist for 3 and 4 activation rows and for an index list with one
+        if (c.waves == 8 && batch < 3 && (!idx_dev || batch > 1 || one_group)) return SPQT_EINVAL;
     } else {
-        wide_workgroups(M, batch, &c);
+        default_shape(M, K, batch, &c);
     }
     if (c.splits < 1 || c.splits > SPQT_MAX_SPLITS) return SPQT_EINVAL;
     if (c.waves != 1 && c.waves != 2 && c.waves != 4 && c.waves != 8) return SPQT_EINVAL;
 
-    size_t need = 0;
-    spqt_workspace_bytes(M, K, batch, &need);
-    if (tight) need = exchange_bytes(tiles(M), kTileRows, c.splits, batch);
+    const size_t need = needed_bytes(M, K, batch, c.splits, tight);
     void *partials = nullptr;
     int32_t *ws_flags = nullptr;
     if (c.splits > 1) {
@@ -381,15 +388,16 @@ extern "C" int spqt_gemv_fused(const void *packed_dev, int64_t M, int64_t K, int
     if (even_shares && ((cfg->flags & SPQT_CFG_NO_COMPACTION) || K > 32768 || (uintptr_t)x_dev % 16 != 0)) return SPQT_EINVAL;
     const bool static_ranges = !even_shares;
     spqt_launch_cfg c;
-    choose_cfg(M, K, 1, &c);
-    if (cfg) {
+    if (cfg && (cfg->splits || cfg->waves)) {
+        choose_cfg(M, K, 1, &c);
         if (cfg->splits) c.splits = cfg->splits;
         if (cfg->waves) c.waves = cfg->waves;
+    } else {
+        default_shape(M, K, 1, &c);
     }
     if (c.splits < 1 || c.splits > SPQT_MAX_SPLITS) return SPQT_EINVAL;
     if (c.waves != 1 && c.waves != 2 && c.waves != 4) return SPQT_EINVAL;
-    size_t need = 0;
-    spqt_workspace_bytes(M, K, 1, &need);
+    const size_t need = needed_bytes(M, K, 1, c.splits, false);
     void *partials = nullptr;
     int32_t *ws_flags = nullptr;
     if (c.splits > 1) {
@@ -429,15 +437,16 @@ extern "C" int spqt_gemv_fused_rows(const void *packed_dev, int64_t M, int64_t K
     if ((uintptr_t)packed_dev % 128 != 0 || (uintptr_t)x_dev % 2 != 0 || (uintptr_t)y_dev % (y_half ? 2 : 4) != 0)
         return SPQT_EALIGN;
     spqt_launch_cfg c;
-    choose_cfg(M, K, batch, &c);
-    if (cfg) {
+    if (cfg && (cfg->splits || cfg->waves)) {
+        choose_cfg(M, K, batch, &c);
         if (cfg->splits) c.splits = cfg->splits;
-        if (cfg->waves && cfg->waves != 4) return SPQT_EINVAL;   // callers get 4 wavefronts per workgroup
+        if (cfg->waves) c.waves = cfg->waves;
+    } else {
+        default_shape(M, K, batch, &c);
     }
-    if (!cfg || (!cfg->splits && !cfg->waves)) wide_workgroups(M, batch, &c);
+    if (c.waves != 4 && !(c.waves == 8 && batch >= 3)) return SPQT_EINVAL;
     if (c.splits < 1 || c.splits > SPQT_MAX_SPLITS) return SPQT_EINVAL;
-    size_t need = 0;
-    spqt_workspace_bytes(M, K, batch, &need);
+    const size_t need = needed_bytes(M, K, batch, c.splits, false);
     void *partials = nullptr;
     int32_t *ws_flags = nullptr;
     if (c.splits > 1) {

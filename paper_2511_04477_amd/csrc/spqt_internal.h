@@ -41,8 +41,9 @@ inline int check_shape(int64_t M, int64_t K, int group) {
 // Workgroups in the grid of a group-layout launch (block_of in gemv_common.hpp says which is which).
 inline int grid_blocks(int64_t T, int S) { return 8 * (int)((T / 8) * S + ((T % 8) * S + 7) / 8); }
 
-// Launch shape of the group layout, measured on MI355X over the benchmark's matrices at 50 % sparsity and dense.
-// One or two activation rows: about one workgroup of 4 wavefronts per CU - at most 256 in total - and S any
+// Launch shape of the group layout with workgroups of 4 wavefronts, measured on MI355X over the benchmark's matrices at
+// 50 % sparsity and dense.  default_shape below starts from it; a caller's own shape overrides it.
+// One or two activation rows: about one workgroup per CU - at most 256 in total - and S any
 // integer up to 16.  More workgroups only shorten every wavefront's slice, and the fixed cost per wavefront (dependent
 // prologue loads, pipeline fill, exchange of partial sums) outweighs the extra parallelism: dense 13824 x 5120 with 4 / 8
 // / 16 workgroups per block-row 9.7 / 11.0 / 12.3 us, index list at 50 % 28672 x 8192 with 2 / 4 / 6 15.5 / 17.0 / 17.0.
@@ -125,16 +126,18 @@ inline bool runs_without_workspace(int64_t T, size_t code_bytes, Columns from, i
     return T > (large ? 128 : (from == Columns::dense && batch == 1 ? 512 : 256));
 }
 
-// Three or four activation rows: where choose_cfg's shape is more than one workgroup of 4 wavefronts per CU, the kernels run
-// one workgroup of 8 per CU instead.  The exchange grows with rows times workgroups per block-row: index list at 70 %
+// The launch shape of the group layout where the caller asks for none.
+// Three or four activation rows, up to 256 block-rows: where choose_cfg's shape is more than one workgroup of 4 wavefronts per CU,
+// the kernels run one workgroup of 8 per CU instead.  The exchange grows with rows times workgroups per block-row: index list at 70 %
 // sparsity, 4 rows, 14336 x 4096 with 8 x 4 / 4 x 8 wavefronts per block-row 16.2 / 13.1 us, 28672 x 8192 with 4 x 4 / 2 x 8
-// 30.3 / 26.7.  (spqt_default_cfg and the limit of spqt_gemv_static go by choose_cfg's shape, which never needs fewer
-// exchange words.)
-inline void wide_workgroups(int64_t M, int batch, spqt_launch_cfg *c) {
+// 30.3 / 26.7.  Higher matrices have nothing to exchange: 76800 x 1024 1 x 4 / 1 x 8 14.3 / 15.6, one launch 14.2 / 16.4.
+inline void default_shape(int64_t M, int64_t K, int batch, spqt_launch_cfg *out) {
     const int64_t T = tiles(M);
-    if (batch < 3 || T * c->splits <= 256) return;
-    c->splits = T < 256 ? (int)(256 / T) : 1;
-    c->waves = 8;
+    choose_cfg(M, K, batch, out);
+    if (batch >= 3 && T <= 256 && T * out->splits > 256) {
+        out->splits = (int)(256 / T);
+        out->waves = 8;
+    }
 }
 
 }  // namespace spqt

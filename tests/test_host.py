@@ -320,7 +320,7 @@ def test_null_and_small_buffers_are_rejected_on_the_host():
     assert L.spqt_gemv(64, 256, 128, 128, 16, 1, None, None, 16, None, 0, None) == -3
     assert L.spqt_gemv(128, 256, 128, 128, 16, 1, 16, None, 16, None, 0, None) == -1  # idx without count
     assert L.spqt_gemv(128, 256, 128, 128, 16, 7, None, None, 16, None, 0, None) == -2
-    # one launch for several rows: same checks, and 4 wavefronts per workgroup only
+    # one launch for several rows: same checks, and 4 (or, from 3 rows on, 8) wavefronts per workgroup only
     fr = L.spqt_gemv_fused_rows
     assert fr(None, 256, 128, 128, 16, 2, ctypes.c_float(0.0), 0, 16, None, 0, None, None) == -1
     assert fr(128, 256, 100, 128, 16, 2, ctypes.c_float(0.0), 0, 16, None, 0, None, None) == -2
@@ -339,6 +339,31 @@ def test_default_launch_shape_is_valid(M, K):
     for sparse in (False, True):
         splits, waves = spqt.spqt_default_cfg(M, K, 1, sparse)
         assert 1 <= splits <= spqt.MAX_SPLITS and waves in (1, 2, 4)
+
+
+@pytest.mark.parametrize("M,K,batch,sparse,shape", [
+    (28672, 8192, 1, True, (2, 4)), (4096, 4096, 2, False, (16, 4)),                   # one workgroup per CU
+    (8192, 28672, 4, True, (8, 8)), (33 * 256, 1024, 3, False, (7, 8)),                # 3 and 4 rows: 8 wavefronts
+    (65536, 1024, 4, True, (1, 8)), (65792, 1024, 4, True, (1, 4)),                    # up to 256 block-rows
+    (22016, 6272, 1, True, (2, 4)), (33024, 3072, 4, False, (1, 8)), (49408, 5120, 1, True, (1, 4))])
+def test_default_launch_shape_can_be_asked_for(M, K, batch, sparse, shape):
+    """What spqt_default_cfg reports is a shape the entry points take: an error about the size of the workspace, not about
+    the shape (or none asked for: one workgroup per block-row needs no workspace, so nothing is called)."""
+    assert spqt.spqt_default_cfg(M, K, batch, sparse) == shape
+    if shape[0] > 1:
+        cfg = spqt.binding.LaunchCfg(*shape, 0)
+        L = spqt.lib()
+        assert L.spqt_gemv_ex(128, M, K, 128, 16, batch, 16 if sparse else None, 16 if sparse else None, 16, 256, 0, None, ctypes.byref(cfg)) == -4
+        assert L.spqt_gemv_fused_rows(128, M, K, 128, 16, batch, ctypes.c_float(0.0), 0, 16, 256, 0, None, ctypes.byref(cfg)) == -4
+
+
+def test_eight_wavefronts_are_refused_where_no_kernel_has_them():
+    cfg = spqt.binding.LaunchCfg(2, 8, 0)
+    L = spqt.lib()
+    for batch, idx in ((1, None), (2, None), (2, 16)):
+        assert L.spqt_gemv_ex(128, 4096, 4096, 128, 16, batch, idx, idx, 16, 256, 0, None, ctypes.byref(cfg)) == -1
+    for batch in (1, 2):
+        assert L.spqt_gemv_fused_rows(128, 4096, 4096, 128, 16, batch, ctypes.c_float(0.0), 0, 16, 256, 0, None, ctypes.byref(cfg)) == -1
 
 
 def test_bench_refuses_more_than_one_gpu():

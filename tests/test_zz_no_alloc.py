@@ -58,9 +58,9 @@ def test_static_scratch_rejects_what_does_not_fit():
     import torch
     import paper_2511_04477_amd as spqt
     dev = torch.device("cuda:0")
-    M, K = 8192, 28672            # 32 block-rows x 16 workgroups x 4 rows x 256 words of 8 bytes = 4 MiB > the array
-    splits, _ = spqt.spqt_default_cfg(M, K, 4, True)
-    assert 256 + (M // 256) * 256 * splits * 4 * 8 > (2 << 20) + 256
+    M, K = 8192, 28672            # 32 block-rows x 16 workgroups of 4 wavefronts x 4 rows x 256 outputs x 8 bytes = 4 MiB > the array
+    splits, waves = spqt.spqt_default_cfg(M, K, 4, True)
+    assert 256 + (M // 256) * 256 * (splits * waves // 4) * 4 * 8 > (2 << 20) + 256
     one = torch.zeros(16, dtype=torch.uint8, device=dev)
     p = one.data_ptr()
     assert spqt.lib().spqt_gemv_static(p, M, K, 128, p, 4, p, p, p, None) == -4       # SPQT_ESIZE, on the host, nothing launched
