@@ -116,7 +116,7 @@ int run8(int mode, int batch, const void *packed_dev, int64_t M, int64_t K, cons
     bool without_workspace = false;
     if (check_shape(M, K, kGroup) == SPQT_OK) {    // colblock_width_run refuses the others
         const Columns from = mode == 1 ? Columns::dense : mode == 2 ? Columns::units : Columns::list;
-        S0 = colblock_splits(T64, K, from, batch, 3);
+        S0 = colblock_splits(T64, K, from, batch, colblock8_depth(T64, K, from, batch));
         without_workspace = runs_without_workspace(T64, (size_t)M * (size_t)K, from, batch);
         while (mode == 2 && S0 > 1 && (int64_t)S0 * 4 * kPassCols > K) --S0;   // one launch: at least one unit per wavefront
     }

@@ -79,7 +79,10 @@ inline void choose_cfg(int64_t M, int64_t K, int batch, spqt_launch_cfg *out) {
 //     9.7 / 8.9, 9000 x 2944 S = 7 / 14 7.5 / 6.9);
 //   - one launch: passes are half full, so slices of more than 5 units want a second workgroup per CU (4-bit 28672 x 8192
 //     S = 2 / 4 23.0 / 19.4, 8-bit 4096 x 11008 S = 8 / 16 9.4 / 9.1, but 4-bit 13824 x 5120 with 5 units S = 4 / 7 9.8 / 10.0), and
-//     S is the smallest with the same number of units in the longest slice (4-bit 5120 x 5120 S = 12 / 10 6.6 / 6.4);
+//     S is the smallest with the same number of units in the longest slice (4-bit 5120 x 5120 S = 12 / 10 6.6 / 6.4).  A third
+//     workgroup per CU has to leave a fuller round after that, too (14848 x 10240, 4-bit S = 8 / 10 14.7 / 16.8, K-quant 15.2 / 17.4, 8-bit with
+//     58 block-rows 12.7 / 14.3).  More than 128 block-rows with slices of at most 5 units exchange nothing (S = 1): a fuller round is worth
+//     less than the exchange (22016 x 1024 8-bit S = 1 / 4 6.5 / 7.0, 44032 x 1280 4-bit S = 1 / 3 8.6 / 9.8, K-quant 9.2 / 10.0);
 //   - several rows with slices from 1024 columns on: two workgroups per CU (4-bit, 4 rows, 28672 x 8192 S = 2 / 4 36.7 / 34.0).
 // max_depth 1: one workgroup fills a CU's registers (2-bit: 28672 x 8192 S = 4 / 8 16.1 / 17.3).
 enum class Columns { list, dense, units };    // units: one launch, static ranges of 64-column units
@@ -96,21 +99,35 @@ inline int colblock_splits(int64_t T, int64_t K, Columns from, int batch, int ma
     const int64_t least_gain = from == Columns::list && batch <= 2 ? 103 : 120;
     int64_t S = deepest(1), depth = 1;
     const bool long_slices = from == Columns::units ? slice(S) > 5 * 64 : batch >= 2 && slice(S) >= 1024;
+    if (from == Columns::units && T > 128 && !long_slices) return 1;
     if (max_depth >= 2 && long_slices) S = deepest(depth = 2);
+    const int64_t units = K / 64;
+    auto fewest = [&](int64_t s) {            // the smallest S with the same number of units in the longest slice
+        while (s > 1 && (units + 4 * s - 1) / (4 * s) == (units + 4 * (s - 1) - 1) / (4 * (s - 1))) --s;
+        return s;
+    };
     for (int64_t d = depth + 1; d <= max_depth; ++d) {
         const int64_t gain = depth >= 2 ? 103 : least_gain;
-        if (fill(deepest(d)) * 100 >= fill(S) * gain) S = deepest(d);
+        bool fuller = fill(deepest(d)) * 100 >= fill(S) * gain;
+        if (from == Columns::units && depth >= 2) fuller = fuller && fill(fewest(deepest(d))) * 100 >= fill(fewest(S)) * gain;
+        if (fuller) S = deepest(d);
     }
     if (max_depth >= 2 && from == Columns::list && batch <= 2 && slice(S) >= 112 && slice(S) <= 256 && T * S <= 256 && fill(deepest(2)) >= fill(S))
         S = deepest(2);
     if (from == Columns::dense && slice(S) > 64)
         for (int64_t d = 2; d <= max_depth; ++d)
             if (K <= 4 * 64 * deepest(d) && fill(deepest(d)) >= fill(S)) { S = deepest(d); break; }
-    if (from == Columns::units) {
-        const int64_t units = K / 64;
-        while (S > 1 && (units + 4 * S - 1) / (4 * S) == (units + 4 * (S - 1) - 1) / (4 * (S - 1))) --S;
-    }
-    return (int)S;
+    return (int)(from == Columns::units ? fewest(S) : S);
+}
+
+// max_depth of the 8-bit layout.  Dense, one row, 129 to 256 block-rows, slices from 768 columns on: one workgroup per CU on two
+// thirds of the CUs already reads at the rate of the memory, so a third workgroup per CU only adds the exchange (22016 x 4096 S = 1 / 4
+// 18.2 / 19.1 us, 24576 x 8192 34.5 / 37.0; below two thirds two per CU pay, 16640 x 8192 S = 1 / 3 29.8 / 27.7, and short slices
+// gain from parallelism, 22016 x 1024 S = 1 / 4 7.6 / 7.5).  One launch, more than 256 block-rows, fewer than 40 units: S = 1 / 2
+// 33024 x 1536 10.4 / 10.8, 40960 x 1536 11.6 / 11.9, 36864 x 2304 13.3 / 13.6 (2816 columns 16.6 / 16.7 and 14.1 / 13.9; K-quant 66048 x 1536 14.0 / 13.4).
+inline int colblock8_depth(int64_t T, int64_t K, Columns from, int batch) {
+    if (from == Columns::units) return T > 256 && K < 2560 ? 2 : 3;
+    return from == Columns::dense && batch == 1 && T > 128 && T <= 256 && K >= 4 * 768 ? 2 : 3;
 }
 
 // A workspace the exchange can use: calls with several workgroups per block-row refuse any other.

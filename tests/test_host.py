@@ -357,6 +357,26 @@ def test_default_launch_shape_can_be_asked_for(M, K, batch, sparse, shape):
         assert L.spqt_gemv_fused_rows(128, M, K, 128, 16, batch, ctypes.c_float(0.0), 0, 16, 256, 0, None, ctypes.byref(cfg)) == -4
 
 
+def test_colblock_launch_shapes(tmp_path):
+    """Workgroups per block-row that were measured to be the faster ones where a fuller last round may not pay for the exchange it
+    brings in (8-bit dense from two thirds of the CUs on, one launch over few units) or is none once the slices are whole units."""
+    import subprocess
+    shapes = [("dense", 172, 4096, "8", 1), ("dense", 192, 8192, "8", 1), ("dense", 130, 8192, "8", 3), ("dense", 172, 1024, "8", 4),
+              ("dense", 258, 4096, "8", 2), ("dense", 192, 8192, "4", 4),
+              ("units", 172, 1024, "8", 1), ("units", 172, 1280, "4", 1), ("units", 258, 1280, "8", 1), ("units", 172, 1536, "8", 2),
+              ("units", 320, 2304, "8", 1), ("units", 320, 2816, "8", 2), ("units", 320, 1536, "4", 2), ("units", 192, 1536, "4", 2), ("units", 172, 1792, "4", 4),
+              ("units", 172, 2048, "8", 4), ("units", 130, 1536, "8", 3), ("units", 52, 6144, "8", 8), ("units", 58, 10240, "4", 8),
+              ("units", 86, 5120, "4", 5), ("units", 104, 4096, "8", 4), ("units", 130, 4096, "4", 3), ("units", 112, 8192, "4", 4)]
+    calls = "".join(f'    std::printf("%d ", colblock_splits({T}, {K}, Columns::{mode}, 1, '
+                    + (f"colblock8_depth({T}, {K}, Columns::{mode}, 1)" if bits == "8" else "3") + "));\n" for mode, T, K, bits, _ in shapes)
+    src = tmp_path / "splits.cpp"
+    src.write_text('#include <cstdio>\n#include "spqt_internal.h"\nusing namespace spqt;\nint main() {\n' + calls + "}\n")
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2511_04477_amd", "csrc"),
+                    "-o", str(tmp_path / "splits"), str(src)], check=True)
+    got = subprocess.run([str(tmp_path / "splits")], check=True, capture_output=True, text=True).stdout.split()
+    assert [int(v) for v in got] == [s[-1] for s in shapes]
+
+
 def test_eight_wavefronts_are_refused_where_no_kernel_has_them():
     cfg = spqt.binding.LaunchCfg(2, 8, 0)
     L = spqt.lib()
