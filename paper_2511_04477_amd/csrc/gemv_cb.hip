@@ -172,12 +172,12 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
                 float xb[8];     // what step u adds to the bias sum: the product itself, or x * minimum
 #pragma unroll
                 for (int u = 0; u < 8; ++u) xb[u] = KQ ? stage_xm[wave][0][u * 8 + cg][seg] : xl[u];
-                fma_step<false>(w[0], xl[0], acc[0]);
+                fma_step(w[0], xl[0], acc[0]);
                 bsum[0] += xb[0];
 #pragma unroll
                 for (int u = 1; u < 8; ++u)
                     if (u * 8 < n) {
-                        fma_step<false>(w[u], xl[u], acc[0]);
+                        fma_step(w[u], xl[u], acc[0]);
                         bsum[0] += xb[u];
                     }
             } else {
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
 #pragma unroll
                         for (int b = 0; b < BATCH; ++b) {
                             const float xl = stage_xs[wave][b][u * 8 + cg][seg];
-                            fma_step<false>(w[u], xl, acc[b]);
+                            fma_step(w[u], xl, acc[b]);
                             bsum[b] += KQ ? stage_xm[wave][b][u * 8 + cg][seg] : xl;
                         }
                     }

@@ -82,34 +82,31 @@ __device__ __forceinline__ float as_float(uint32_t bits) { return __builtin_bit_
 __device__ __forceinline__ uint32_t as_u32(float f) { return __builtin_bit_cast(uint32_t, f); }
 __device__ __forceinline__ f16x2 as_f16x2(uint32_t bits) { return __builtin_bit_cast(f16x2, bits); }
 
-// Eight codes of one dword: acc[i] (+)= n_i * x for nibble i (row 8d+i of the lane's 32 rows).
+// Eight codes of one dword: acc[i] += n_i * x for nibble i (row 8d+i of the lane's 32 rows).
 // xlo = x * 2^24 pairs with nibbles sitting at bits 0..3 of a half, xhi = x * 2^20 with
-// nibbles at bits 4..7 (value 16 n * 2^-24).  INIT overwrites the accumulators (first step of
-// a pass) instead of adding to them.
-template <bool INIT>
+// nibbles at bits 4..7 (value 16 n * 2^-24).
 __device__ __forceinline__ void fma_codes(uint32_t w, float xlo, float xhi, float *acc) {
     const uint32_t w8 = w >> 8;
     const f16x2 a = as_f16x2(w & 0x000F000Fu);    // nibbles 0, 4
     const f16x2 b = as_f16x2(w & 0x00F000F0u);    // nibbles 1, 5
     const f16x2 c = as_f16x2(w8 & 0x000F000Fu);   // nibbles 2, 6
     const f16x2 d = as_f16x2(w8 & 0x00F000F0u);   // nibbles 3, 7
-    acc[0] = __builtin_fmaf((float)a.x, xlo, INIT ? 0.0f : acc[0]);
-    acc[4] = __builtin_fmaf((float)a.y, xlo, INIT ? 0.0f : acc[4]);
-    acc[1] = __builtin_fmaf((float)b.x, xhi, INIT ? 0.0f : acc[1]);
-    acc[5] = __builtin_fmaf((float)b.y, xhi, INIT ? 0.0f : acc[5]);
-    acc[2] = __builtin_fmaf((float)c.x, xlo, INIT ? 0.0f : acc[2]);
-    acc[6] = __builtin_fmaf((float)c.y, xlo, INIT ? 0.0f : acc[6]);
-    acc[3] = __builtin_fmaf((float)d.x, xhi, INIT ? 0.0f : acc[3]);
-    acc[7] = __builtin_fmaf((float)d.y, xhi, INIT ? 0.0f : acc[7]);
+    acc[0] = __builtin_fmaf((float)a.x, xlo, acc[0]);
+    acc[4] = __builtin_fmaf((float)a.y, xlo, acc[4]);
+    acc[1] = __builtin_fmaf((float)b.x, xhi, acc[1]);
+    acc[5] = __builtin_fmaf((float)b.y, xhi, acc[5]);
+    acc[2] = __builtin_fmaf((float)c.x, xlo, acc[2]);
+    acc[6] = __builtin_fmaf((float)c.y, xlo, acc[6]);
+    acc[3] = __builtin_fmaf((float)d.x, xhi, acc[3]);
+    acc[7] = __builtin_fmaf((float)d.y, xhi, acc[7]);
 }
 
-template <bool INIT>
 __device__ __forceinline__ void fma_step(u32x4 w, float xl, float *acc) {
     const float xh = xl * 0.0625f;
-    fma_codes<INIT>(w.x, xl, xh, acc + 0);
-    fma_codes<INIT>(w.y, xl, xh, acc + 8);
-    fma_codes<INIT>(w.z, xl, xh, acc + 16);
-    fma_codes<INIT>(w.w, xl, xh, acc + 24);
+    fma_codes(w.x, xl, xh, acc + 0);
+    fma_codes(w.y, xl, xh, acc + 8);
+    fma_codes(w.z, xl, xh, acc + 16);
+    fma_codes(w.w, xl, xh, acc + 24);
 }
 
 // The three levels of the column fold are written as asm blocks: the lane swaps work in place

@@ -171,19 +171,24 @@ void start(int grid, hipStream_t stream, const ListLaunch &a) {
                        a.x, a.idx, a.count, a.y, a.partials, a.ws_flags, a.K, a.NG, a.S, a.T, a.m_and_flags);
 }
 
+// Which kernels have workgroups of 8 wavefronts: an index list with one row, and 3 and 4 rows (the callers refuse the others).
 template <int WAVES>
 void start_waves(int batch, bool one_group, int grid, hipStream_t stream, const ListLaunch &a) {
     const bool dense = a.idx == nullptr;
     switch (batch) {
         case 1:
             // dense shares are whole runs of columns: a pass of one group loses nothing there
-            if (dense) start<WAVES, true, 1, 1>(grid, stream, a);
-            else if (one_group) start<WAVES, false, 1, 1>(grid, stream, a);
-            else start<WAVES, false, 1, groups_per_pass(1)>(grid, stream, a);
+            if constexpr (WAVES < 8) {
+                if (dense) return start<WAVES, true, 1, 1>(grid, stream, a);
+                if (one_group) return start<WAVES, false, 1, 1>(grid, stream, a);
+            }
+            start<WAVES, false, 1, groups_per_pass(1)>(grid, stream, a);
             break;
         case 2:
-            if (dense) start<WAVES, true, 2, 1>(grid, stream, a);
-            else start<WAVES, false, 2, groups_per_pass(2)>(grid, stream, a);
+            if constexpr (WAVES < 8) {
+                if (dense) start<WAVES, true, 2, 1>(grid, stream, a);
+                else start<WAVES, false, 2, groups_per_pass(2)>(grid, stream, a);
+            }
             break;
         case 3:
             if (dense) start<WAVES, true, 3, 1>(grid, stream, a);
