@@ -116,10 +116,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
             __builtin_amdgcn_wave_barrier();
         };
 
-        uint32_t off;              // the same state and stages as in gemv_list.hip, with the ring in the place of idx
-        uint64_t starts;
-        int g, j;
-        uint32_t xraw[BATCH];
+        PassHead<BATCH> h;
         // HEAD of the pass that starts at entry p.  One refill at most, so a pass takes what is there (nothing, if kRefill
         // units keep nothing); the next units' x is requested every time, refilled or not, so that the number of loads in
         // flight is the same on every path.
@@ -130,63 +127,22 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
             const u32x2 v = ring[wave][e & (kRing - 1)];
             const uint32_t v23 = BATCH > 2 ? ring23[wave][e & (kRing - 1)] : 0u;
             const int kk = e < filled ? (int)v.x : -1;
-            g = kk >> log2g;
-            const Deal d = deal_groups<kGroups>(kk, g, lane);
-            const uint32_t off_own = (uint32_t)g * chunk_b + (uint32_t)(kk & ((1 << log2g) - 1)) * kColBytes;
+            h.g = kk >> log2g;
+            const Deal d = deal_groups<kGroups>(kk, h.g, lane);
+            const uint32_t off_own = (uint32_t)h.g * chunk_b + (uint32_t)(kk & ((1 << log2g) - 1)) * kColBytes;
             const uint32_t off_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)off_own);
-            off = d.take ? off_own : (d.n ? off_first : 0u);
-            starts = d.starts;
-            g = d.n ? g : 0;
-            j = d.take ? d.j : -1;
+            h.off = d.take ? off_own : (d.n ? off_first : 0u);
+            h.starts = d.starts;
+            h.g = d.n ? h.g : 0;
+            h.j = d.take ? d.j : -1;
             const uint32_t xv[4] = {v.y & 0xFFFFu, v.y >> 16, v23 & 0xFFFFu, v23 >> 16};
 #pragma unroll
-            for (int b = 0; b < BATCH; ++b) xraw[b] = xv[b];
+            for (int b = 0; b < BATCH; ++b) h.xraw[b] = xv[b];
             return p + d.n;
         };
-        auto load_scales = [&](u32x2(&sc)[kGroups]) {
-            uint64_t left = starts;
-            int at = 0;
-#pragma unroll
-            for (int i = 0; i < kGroups; ++i) {
-                at = left ? (int)__builtin_ctzll(left) : at;     // selects, no branch
-                left &= left - 1ull;
-                const uint32_t gi = (uint32_t)__builtin_amdgcn_readlane(g, at);
-                sc[i] = *reinterpret_cast<const u32x2 *>(row_base + (size_t)(gi * chunk_b) + (size_t)(out4 * 8u));
-            }
-        };
-
-        const uint8_t *columns = row_base + kScaleBytes;
-        u32x2 w[16], sc[kGroups];
-        u32x4 x0, x1;
-        f32x4 d[4];
-        int turn = part;
         fetch_x(u);
-        int pos = head(0);
-        load_columns<0, 16>(columns, off, n8, w);
-        load_scales(sc);
-        while (pos < filled || u < end) {
-            stage_x<BATCH, kGroups>(staged[wave], lane, lane, j, j >= 0, negated(turn), xraw);
-            pos = head(pos);
-            keep_order();
-            start_products(staged[wave], lane, x0, x1, d);
-            half_pass<0>(w, x0, lane, d);
-            keep_order();
-            load_columns<0, 8>(columns, off, n8, w);
-            keep_order();
-            half_pass<1>(w, x1, lane, d);
-            keep_order();
-            load_columns<8, 16>(columns, off, n8, w);
-            keep_order();
-            add_scaled<BATCH, kGroups>(d, sc, negated(turn), acc);
-            load_scales(sc);
-            ++turn;
-            keep_order();
-        }
-        stage_x<BATCH, kGroups>(staged[wave], lane, lane, j, j >= 0, negated(turn), xraw);
-        start_products(staged[wave], lane, x0, x1, d);
-        half_pass<0>(w, x0, lane, d);
-        half_pass<1>(w, x1, lane, d);
-        add_scaled<BATCH, kGroups>(d, sc, negated(turn), acc);
+        run_passes<BATCH, kGroups>(staged[wave], row_base, chunk_b, lane, n8, out4, part, 0, h, head,
+                                   [&](int p) { return p < filled || u < end; }, [&]() {}, [&]() {}, acc);
     }
 
     SPQT_TL(4);

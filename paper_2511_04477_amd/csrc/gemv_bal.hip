@@ -17,7 +17,7 @@
 //      kept columns, and an entry whose rank falls inside the share is written at rank - share start.
 //      The next step's x is requested one refill ahead, so no pass ever waits on a dependent global read.
 //   4. GEMV.  Passes over the ring exactly as gemv_list.hip forms them over idx (pass.hpp),
-//      same two-stage pipeline, same exchange between the workgroups of a block-row; for the same launch
+//      same loop, same exchange between the workgroups of a block-row; for the same launch
 //      shape the two kernels perform the same arithmetic in the same order.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -178,67 +178,21 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
             return e < total ? (int)(v & 0xFFFFu) : -1;
         };
 
-        uint32_t off;              // the same state and stages as in gemv_list.hip, with the ring in the place of idx
-        uint64_t starts;
-        int g, j;
-        uint32_t xraw[1];
+        PassHead<1> h;
         auto head = [&](int p) -> int {
-            const int kk = fetch_k(p, xraw[0]);
-            g = kk >> log2g;
-            const Deal d = deal_groups<kGroups>(kk, g, lane);
-            const uint32_t off_own = (uint32_t)g * chunk_b + (uint32_t)(kk & ((1 << log2g) - 1)) * kColBytes;
+            const int kk = fetch_k(p, h.xraw[0]);
+            h.g = kk >> log2g;
+            const Deal d = deal_groups<kGroups>(kk, h.g, lane);
+            const uint32_t off_own = (uint32_t)h.g * chunk_b + (uint32_t)(kk & ((1 << log2g) - 1)) * kColBytes;
             const uint32_t off_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)off_own);
-            off = d.take ? off_own : off_first;
-            starts = d.starts;
-            j = d.take ? d.j : -1;
+            h.off = d.take ? off_own : off_first;
+            h.starts = d.starts;
+            h.j = d.take ? d.j : -1;
             return p + d.n;
         };
-        auto load_scales = [&](u32x2(&sc)[kGroups]) {
-            uint64_t left = starts;
-            int at = 0;
-#pragma unroll
-            for (int i = 0; i < kGroups; ++i) {
-                at = left ? (int)__builtin_ctzll(left) : at;
-                left &= left - 1ull;
-                const uint32_t gi = (uint32_t)__builtin_amdgcn_readlane(g, at);
-                sc[i] = *reinterpret_cast<const u32x2 *>(row_base + (size_t)(gi * chunk_b) + (size_t)(out4 * 8u));
-            }
-        };
-
-        // 4. GEMV: the passes of gemv_list.hip
-        const uint8_t *columns = row_base + kScaleBytes;
-        u32x2 w[16], sc[kGroups];
-        u32x4 x0, x1;
-        f32x4 d[4];
-        int turn = part;
-        int pos = head(0);
-        SPQT_TL(2);
-        load_columns<0, 16>(columns, off, n8, w);
-        load_scales(sc);
-        SPQT_TL_WAIT(3);
-        while (pos < total) {
-            stage_x<1, kGroups>(staged[wave], lane, lane, j, j >= 0, negated(turn), xraw);
-            pos = head(pos);
-            keep_order();
-            start_products(staged[wave], lane, x0, x1, d);
-            half_pass<0>(w, x0, lane, d);
-            keep_order();
-            load_columns<0, 8>(columns, off, n8, w);
-            keep_order();
-            half_pass<1>(w, x1, lane, d);
-            keep_order();
-            load_columns<8, 16>(columns, off, n8, w);
-            keep_order();
-            add_scaled<1, kGroups>(d, sc, negated(turn), acc);
-            load_scales(sc);
-            ++turn;
-            keep_order();
-        }
-        stage_x<1, kGroups>(staged[wave], lane, lane, j, j >= 0, negated(turn), xraw);
-        start_products(staged[wave], lane, x0, x1, d);
-        half_pass<0>(w, x0, lane, d);
-        half_pass<1>(w, x1, lane, d);
-        add_scaled<1, kGroups>(d, sc, negated(turn), acc);
+        // 4. GEMV
+        run_passes<1, kGroups>(staged[wave], row_base, chunk_b, lane, n8, out4, part, 0, h, head, [&](int p) { return p < total; },
+                               [&]() { SPQT_TL(2); }, [&]() { SPQT_TL_WAIT(3); }, acc);
     }
     SPQT_TL(4);
 

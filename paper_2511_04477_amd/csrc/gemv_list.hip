@@ -80,77 +80,30 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
         };
 
         int k_next;                // the lane's list entry for the pass whose HEAD comes next
-        uint32_t off;              // byte offset of the column this lane owns in the pass whose weights are requested next
-        uint64_t starts;           // where the groups of that pass start
-        int g;                     // group of the lane's candidate of that pass
-        int j;                     // group of the lane's entry inside that pass, or -1: not part of it
-        uint32_t xraw[BATCH];      // its x
+        PassHead<BATCH> h;
 
         // HEAD of the pass that starts at list position p < end: deal the entries to the pass's groups, request the
         // entries of the pass after it and its x.  Returns where the pass after it starts.
         auto head = [&](int p) -> int {
             const int kk = p + lane < end ? (BATCH == 1 && all_kept ? p + lane : k_next) : -1;
-            g = kk >> log2g;
-            const Deal d = deal_groups<GROUPS>(kk, g, lane);
+            h.g = kk >> log2g;
+            const Deal d = deal_groups<GROUPS>(kk, h.g, lane);
             const int k_own = d.take ? kk : 0;
-            const uint32_t off_own = (uint32_t)g * chunk_b + (uint32_t)(kk & ((1 << log2g) - 1)) * kColBytes;
+            const uint32_t off_own = (uint32_t)h.g * chunk_b + (uint32_t)(kk & ((1 << log2g) - 1)) * kColBytes;
             // slots past the pass point at its first column (a line that is fetched anyway) and carry x = 0
             const uint32_t off_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)off_own);
-            off = d.take ? off_own : off_first;
-            starts = d.starts;
-            j = d.take ? d.j : -1;
+            h.off = d.take ? off_own : off_first;
+            h.starts = d.starts;
+            h.j = d.take ? d.j : -1;
             k_next = fetch_k(p + d.n);
 #pragma unroll
-            for (int b = 0; b < BATCH; ++b) xraw[b] = x[(size_t)b * K + k_own];
+            for (int b = 0; b < BATCH; ++b) h.xraw[b] = x[(size_t)b * K + k_own];
             return p + d.n;
         };
-        // The scales of the lane's 4 rows in each group of the pass; groups it does not reach repeat its last one.
-        auto load_scales = [&](u32x2(&sc)[GROUPS]) {
-            uint64_t left = starts;
-            int at = 0;
-#pragma unroll
-            for (int i = 0; i < GROUPS; ++i) {
-                at = left ? (int)__builtin_ctzll(left) : at;     // selects, no branch
-                left &= left - 1ull;
-                const uint32_t gi = (uint32_t)__builtin_amdgcn_readlane(g, at);
-                sc[i] = *reinterpret_cast<const u32x2 *>(row_base + (size_t)(gi * chunk_b) + (size_t)(out4 * 8u));
-            }
-        };
-
-        const uint8_t *columns = row_base + kScaleBytes;
-        u32x2 w[16], sc[GROUPS];
-        u32x4 x0, x1;
-        f32x4 d[4];
-        int turn = part;
         k_next = all_kept ? pos + lane : fetch_k(pos);
         SPQT_TL_WAIT(2);
-        pos = head(pos);
-        load_columns<0, 16>(columns, off, n8, w);
-        load_scales(sc);
-        SPQT_TL_WAIT(3);
-        while (pos < end) {
-            stage_x<BATCH, GROUPS>(staged[wave], lane, lane, j, j >= 0, negated(turn), xraw);
-            pos = head(pos);
-            keep_order();
-            start_products(staged[wave], lane, x0, x1, d);
-            half_pass<0>(w, x0, lane, d);
-            keep_order();
-            load_columns<0, 8>(columns, off, n8, w);
-            keep_order();
-            half_pass<1>(w, x1, lane, d);
-            keep_order();
-            load_columns<8, 16>(columns, off, n8, w);
-            keep_order();
-            add_scaled<BATCH, GROUPS>(d, sc, negated(turn), acc);
-            load_scales(sc);
-            ++turn;
-            keep_order();
-        }
-        stage_x<BATCH, GROUPS>(staged[wave], lane, lane, j, j >= 0, negated(turn), xraw);
-        start_products(staged[wave], lane, x0, x1, d);
-        half_pass<0>(w, x0, lane, d);
-        half_pass<1>(w, x1, lane, d);
-        add_scaled<BATCH, GROUPS>(d, sc, negated(turn), acc);
+        run_passes<BATCH, GROUPS>(staged[wave], row_base, chunk_b, lane, n8, out4, part, pos, h, head, [&](int p) { return p < end; },
+                                  [&]() {}, [&]() { SPQT_TL_WAIT(3); }, acc);
     }
 
     SPQT_TL(4);

@@ -157,19 +157,84 @@ __device__ __forceinline__ Deal deal_groups(int kk, int g, int lane) {
     return d;
 }
 
-// Stages the x of a pass: entry `slot` of lane `lane` carries x[b] for group j of the pass.
-template <int BATCH, int GROUPS>
-__device__ __forceinline__ void stage_x(StagedX &xs, int lane, int slot, int j, bool take, bool neg, const uint32_t (&xraw)[BATCH]) {
+// Stages the x of a pass: the entry of lane `lane`, in the slot of that number, carries x[b] for group j of the pass (j < 0: none).
+template <int BATCH>
+__device__ __forceinline__ void stage_x(StagedX &xs, int lane, int j, bool neg, const uint32_t (&xraw)[BATCH]) {
     constexpr int kRows = padded_rows(BATCH);
     {   // slots that no entry writes must read as zero
         reinterpret_cast<u32x2 *>(&xs.v[0][0])[lane] = u32x2{0u, 0u};
         __builtin_amdgcn_wave_barrier();
     }
-    // no branch on `take`: a divergent one inside the pipeline's loop makes the compiler join the loop's exits with its
+    // no branch on j >= 0: a divergent one inside the pipeline's loop makes the compiler join the loop's exits with its
     // entry and wait for all loads there
 #pragma unroll
-    for (int b = 0; b < BATCH; ++b) xs.v[take ? j * kRows + b : 4][slot] = (uint16_t)(xraw[b] ^ (neg ? 0x8000u : 0u));
+    for (int b = 0; b < BATCH; ++b) xs.v[j >= 0 ? j * kRows + b : 4][lane] = (uint16_t)(xraw[b] ^ (neg ? 0x8000u : 0u));
     __builtin_amdgcn_wave_barrier();
+}
+
+// What the HEAD of a pass leaves for its loads and its products.
+template <int BATCH>
+struct PassHead {
+    uint32_t off;          // byte offset of the column this lane owns in the pass whose weights are requested next
+    uint64_t starts;       // where the groups of that pass start
+    int g;                 // group of the lane's candidate of that pass
+    int j;                 // group of the lane's entry inside that pass, or -1: not part of it
+    uint32_t xraw[BATCH];  // its x
+};
+
+// The scales of the lane's 4 rows in each group of the pass; groups it does not reach repeat its last one.
+template <int BATCH, int GROUPS>
+__device__ __forceinline__ void load_scales(const uint8_t *row_base, uint32_t chunk_b, uint32_t out4, const PassHead<BATCH> &h, u32x2 (&sc)[GROUPS]) {
+    uint64_t left = h.starts;
+    int at = 0;
+#pragma unroll
+    for (int i = 0; i < GROUPS; ++i) {
+        at = left ? (int)__builtin_ctzll(left) : at;     // selects, no branch
+        left &= left - 1ull;
+        const uint32_t gi = (uint32_t)__builtin_amdgcn_readlane(h.g, at);
+        sc[i] = *reinterpret_cast<const u32x2 *>(row_base + (size_t)(gi * chunk_b) + (size_t)(out4 * 8u));
+    }
+}
+
+// The passes of a wavefront's slice, at least one.  head(p) is the HEAD of the pass that starts at entry p: it fills h, requests what
+// later passes need and returns where the next pass starts; more(p) tells whether there is one.  One buffer of weights, refilled
+// half by half as a pass is multiplied.  first_requested and first_here: where the timeline build stamps.
+template <int BATCH, int GROUPS, class Head, class More, class Stamp2, class Stamp3>
+__device__ __forceinline__ void run_passes(StagedX &staged, const uint8_t *row_base, uint32_t chunk_b, int lane, uint32_t n8, uint32_t out4,
+                                           int turn, int pos, PassHead<BATCH> &h, Head head, More more, Stamp2 first_requested,
+                                           Stamp3 first_here, float (&acc)[BATCH][4]) {
+    const uint8_t *columns = row_base + kScaleBytes;
+    u32x2 w[16], sc[GROUPS];
+    u32x4 x0, x1;
+    f32x4 d[4];
+    pos = head(pos);
+    first_requested();
+    load_columns<0, 16>(columns, h.off, n8, w);
+    load_scales<BATCH, GROUPS>(row_base, chunk_b, out4, h, sc);
+    first_here();
+    while (more(pos)) {
+        stage_x<BATCH>(staged, lane, h.j, negated(turn), h.xraw);
+        pos = head(pos);
+        keep_order();
+        start_products(staged, lane, x0, x1, d);
+        half_pass<0>(w, x0, lane, d);
+        keep_order();
+        load_columns<0, 8>(columns, h.off, n8, w);
+        keep_order();
+        half_pass<1>(w, x1, lane, d);
+        keep_order();
+        load_columns<8, 16>(columns, h.off, n8, w);
+        keep_order();
+        add_scaled<BATCH, GROUPS>(d, sc, negated(turn), acc);
+        load_scales<BATCH, GROUPS>(row_base, chunk_b, out4, h, sc);
+        ++turn;
+        keep_order();
+    }
+    stage_x<BATCH>(staged, lane, h.j, negated(turn), h.xraw);
+    start_products(staged, lane, x0, x1, d);
+    half_pass<0>(w, x0, lane, d);
+    half_pass<1>(w, x1, lane, d);
+    add_scaled<BATCH, GROUPS>(d, sc, negated(turn), acc);
 }
 
 }  // namespace spqt
