@@ -347,7 +347,7 @@ int run_cb(int mode, int batch, const void *packed_dev, int64_t M, int64_t K, co
         return SPQT_EALIGN;
     spqt_launch_cfg c;
     const Columns from = mode == 1 || mode == 4 ? Columns::dense : mode == 2 || mode == 5 ? Columns::units : Columns::list;
-    c.splits = colblock_splits(tiles(M), K, from, batch, 3);
+    c.splits = colblock_splits(tiles(M), K, from, batch, colblock4_depth(tiles(M), from, batch, mode >= 3));
     while (c.splits > K / kGroup) --c.splits;      // at least a quarter of a chunk per wavefront
     c.waves = 4;
     size_t need = 0;

@@ -120,6 +120,14 @@ inline int colblock_splits(int64_t T, int64_t K, Columns from, int batch, int ma
     return (int)(from == Columns::units ? fewest(S) : S);
 }
 
+// max_depth of the 4-bit layouts.  The K-quant kernel stages a minimum beside every scale: with 2 rows (172 VGPRs) a CU holds two of its
+// workgroups, not three, so the third that a list takes for a 3 % fuller round starts a round of its own (22016 x 1024 S = 5 / 8
+// 7.2 / 10.0 us, 13824 x 4096 S = 9 / 14 9.8 / 12.1; the least gain is a loss, 16896 x 4096 S = 7 / 11 12.1 / 11.7).  Above 128 block-rows the
+// split is so coarse that a finer one is worth that round (35072 x 2048 S = 3 / 5 11.9 / 11.6, 43932 x 8192 S = 2 / 4 35.6 / 32.2).
+inline int colblock4_depth(int64_t T, Columns from, int batch, bool kquant) {
+    return kquant && from == Columns::list && batch == 2 && T <= 128 ? 2 : 3;
+}
+
 // max_depth of the 8-bit layout.  Dense, one row, 129 to 256 block-rows, slices from 768 columns on: one workgroup per CU on two
 // thirds of the CUs already reads at the rate of the memory, so a third workgroup per CU only adds the exchange (22016 x 4096 S = 1 / 4
 // 18.2 / 19.1 us, 24576 x 8192 34.5 / 37.0; below two thirds two per CU pay, 16640 x 8192 S = 1 / 3 29.8 / 27.7, and short slices

@@ -359,16 +359,25 @@ def test_default_launch_shape_can_be_asked_for(M, K, batch, sparse, shape):
 
 def test_colblock_launch_shapes(tmp_path):
     """Workgroups per block-row that were measured to be the faster ones where a fuller last round may not pay for the exchange it
-    brings in (8-bit dense from two thirds of the CUs on, one launch over few units) or is none once the slices are whole units."""
+    brings in (8-bit dense from two thirds of the CUs on, one launch over few units) or is none: once the slices are whole units, and
+    where a CU cannot hold the workgroups (K-quant list with 2 rows: two per CU).  Layout "k" stands for that one."""
     import subprocess
     shapes = [("dense", 172, 4096, "8", 1), ("dense", 192, 8192, "8", 1), ("dense", 130, 8192, "8", 3), ("dense", 172, 1024, "8", 4),
               ("dense", 258, 4096, "8", 2), ("dense", 192, 8192, "4", 4),
               ("units", 172, 1024, "8", 1), ("units", 172, 1280, "4", 1), ("units", 258, 1280, "8", 1), ("units", 172, 1536, "8", 2),
               ("units", 320, 2304, "8", 1), ("units", 320, 2816, "8", 2), ("units", 320, 1536, "4", 2), ("units", 192, 1536, "4", 2), ("units", 172, 1792, "4", 4),
               ("units", 172, 2048, "8", 4), ("units", 130, 1536, "8", 3), ("units", 52, 6144, "8", 8), ("units", 58, 10240, "4", 8),
-              ("units", 86, 5120, "4", 5), ("units", 104, 4096, "8", 4), ("units", 130, 4096, "4", 3), ("units", 112, 8192, "4", 4)]
-    calls = "".join(f'    std::printf("%d ", colblock_splits({T}, {K}, Columns::{mode}, 1, '
-                    + (f"colblock8_depth({T}, {K}, Columns::{mode}, 1)" if bits == "8" else "3") + "));\n" for mode, T, K, bits, _ in shapes)
+              ("units", 86, 5120, "4", 5), ("units", 104, 4096, "8", 4), ("units", 130, 4096, "4", 3), ("units", 112, 8192, "4", 4),
+              ("list", 54, 4096, "k", 9), ("list", 86, 1024, "k", 5), ("list", 128, 1024, "k", 4),
+              ("list", 130, 2048, "k", 5), ("list", 172, 8192, "k", 4)]
+
+    def split(mode, T, K, bits):
+        rows = 2 if bits == "k" else 1
+        depth = {"8": f"colblock8_depth({T}, {K}, Columns::{mode}, 1)", "4": f"colblock4_depth({T}, Columns::{mode}, 1, false)",
+                 "k": f"colblock4_depth({T}, Columns::{mode}, 2, true)"}[bits]
+        return f'    std::printf("%d ", colblock_splits({T}, {K}, Columns::{mode}, {rows}, {depth}));\n'
+
+    calls = "".join(split(*s[:4]) for s in shapes)
     src = tmp_path / "splits.cpp"
     src.write_text('#include <cstdio>\n#include "spqt_internal.h"\nusing namespace spqt;\nint main() {\n' + calls + "}\n")
     subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2511_04477_amd", "csrc"),
