@@ -155,7 +155,7 @@ def test_launch_shapes_and_ragged_sizes(gpu, M, K, splits, waves):
 def test_threshold_zero_equals_dense_kernel_bitwise(gpu):
     """thr = 0 lists every column, so the list kernel with one-group passes must do exactly what the
     index-free dense kernel does in the same launch shape (same partition, same order) - identical
-    bits.  The default list kernel (row-aligned passes) sums in another order: equal within tolerance."""
+    bits.  The default list kernel (passes of up to 4 groups) sums in another order: equal within tolerance."""
     import paper_2511_04477_amd as spqt
     case = make_case(1, "w")
     for splits, waves in ((1, 4), (2, 4), (4, 2)):
@@ -163,7 +163,7 @@ def test_threshold_zero_equals_dense_kernel_bitwise(gpu):
         b = gpu_gemv(gpu, case, case["x"], 0.0, dense=True, splits=splits, waves=waves)
         assert np.array_equal(a, b), (splits, waves)
         c = gpu_gemv(gpu, case, case["x"], 0.0, splits=splits, waves=waves)
-        assert_close(c, b.astype(np.float64), "row-aligned passes at threshold 0")
+        assert_close(c, b.astype(np.float64), "passes of up to 4 groups at threshold 0")
 
 
 def test_exact_arithmetic_case_is_bit_exact(gpu):
@@ -587,7 +587,7 @@ def test_non_finite_activation_makes_every_output_nan(gpu):
 
 
 def test_matrix_cores_take_fp16_subnormals_unflushed(gpu):
-    """The multiply feeds the 4-bit codes to v_mfma_f32_4x4x4_16B_f16 as fp16 SUBNORMALS (code * 2^-24).  Were
+    """The multiply feeds the 4-bit codes to v_mfma_f32_16x16x32_f16 as fp16 SUBNORMALS (code * 2^-22 or 2^-18).  Were
     subnormal inputs flushed to zero, every product would vanish and y would be -8 * scale * sum(x) for every
     row.  Codes 1 (q = -7) and 15 (q = +7) with scale 1 and x = 1 on the kept columns: y = -7 n or +7 n exactly."""
     M, K = 512, 1024

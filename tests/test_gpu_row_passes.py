@@ -1,6 +1,5 @@
-"""GPU parity for the two ways the index-list GEMV for one activation row consumes its list - row-aligned
-passes (the default: only a row of 8 slots must be of one quantization group) and one-group passes
-(SPQT_CFG_GROUP_PASSES) - against the oracle: |y_gpu - y_ref| <= 1e-2 + 2e-3 * |y_ref| on the same
+"""GPU parity for the two ways the index-list GEMV for one activation row consumes its list - passes
+of up to 4 quantization groups (the default) and one-group passes (SPQT_CFG_GROUP_PASSES) - against the oracle: |y_gpu - y_ref| <= 1e-2 + 2e-3 * |y_ref| on the same
 seeded inputs.  Sparsities from 0 to 1 put from one to many groups into a pass; the hand-made lists
 cover what a threshold on iid activations never produces."""
 import numpy as np
