@@ -230,8 +230,9 @@ int spqt_gemv_static(const void *packed_dev, int64_t M, int64_t K, int group, co
  * columns of each 64-column stretch with a wavefront ballot, and multiplies - no index list
  * is written and n_ns is never materialised.  Same y as spqt_gather followed by spqt_gemv (the
  * summation order differs, so the last bits may).  Because the index list does not exist, the
- * work of a block-row is split into equal COLUMN ranges instead of equal shares of the list
- * (Section 4.2.3): balanced when the kept columns are spread evenly, as with iid activations;
+ * work of a block-row is split into equal numbers of COLUMNS instead of equal shares of the list
+ * (Section 4.2.3): balanced when the kept columns are spread evenly, as with iid activations (long
+ * slices are taken from two or four parts of K, which evens out kept columns that crowd together);
  * SPQT_CFG_EVEN_SHARES selects the kernel that splits the kept columns evenly instead.
  * This is the combination the paper's threshold sharing aims at (Section 5: fewer index collections
  * per layer), taken to one collection per GEMV at no extra launch.

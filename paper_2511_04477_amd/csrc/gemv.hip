@@ -27,8 +27,9 @@ using namespace spqt;
 // COMPACT == false is an ablation: same test, same static ranges, but NO compaction - a dropped column keeps its entry
 // with x = 0 (and re-reads a kept column's line), so skipping saves memory traffic but not one product.
 constexpr int kRefill = 4;                   // units compacted together: their x is requested one refill ahead
+// SPREAD: a slice is a static range of each of SPREAD equal parts of K, at the same place in each (spread_of below), not one range.
 constexpr int kRing = 512;                   // ring entries per wavefront; a refill adds at most 256 to at most 63 live ones
-template <int WAVES, int BATCH, bool COMPACT>
+template <int WAVES, int BATCH, bool COMPACT, int SPREAD>
 __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
     const uint8_t *__restrict__ packed, const uint16_t *__restrict__ x, float *__restrict__ y, void *partials,
     int32_t *ws_flags, int K, int NG, int S, int T, int M, float thr) {
@@ -49,12 +50,15 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
     int t, s;
     if (!block_of((int)blockIdx.x, S, T, t, s)) return;
 
-    const int units = K / kPassCols;
+    // Positions: a unit, or SPREAD units that lie `apart` from each other; a refill takes kStep positions, unit i of it is
+    // u + i % kStep + i / kStep * apart.
+    constexpr int kStep = kRefill / SPREAD;
+    const int positions = K / kPassCols / SPREAD, apart = positions;
     const int parts = S * WAVES;
     const int part = s * WAVES + wave;
-    // units <= 2^18 and part < 512: the products fit 32 bits
-    int u = (int)(((uint32_t)units * (uint32_t)part) / (uint32_t)parts);
-    const int end = (int)(((uint32_t)units * (uint32_t)(part + 1)) / (uint32_t)parts);
+    // positions <= 2^18 and part < 512: the products fit 32 bits
+    int u = (int)(((uint32_t)positions * (uint32_t)part) / (uint32_t)parts);
+    const int end = (int)(((uint32_t)positions * (uint32_t)(part + 1)) / (uint32_t)parts);
     SPQT_TL(1);
 
     // quantization groups of 128 or 64 columns: NG tells which (K % 128 == 0 either way)
@@ -70,16 +74,16 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
 
     if (u < end) {
         const bool own = BATCH > 1 && (M & kOwnSetsBit) != 0;
-        int filled = 0;                   // entries written to the ring so far; u = the next unit to compact
+        int filled = 0;                   // entries written to the ring so far; u = the next position to compact
 
-        // This lane's x of kRefill units from `unit` on (index clamped: values past the slice are unused).  Atomic loads (the
+        // This lane's x of kRefill units from position `at` on (index clamped: values past the slice are unused).  Atomic loads (the
         // same instructions) because the compiler moves plain ones down to the use of their values, behind the weights, and
         // then waits for those too.
         uint16_t xr[kRefill][BATCH];
-        auto fetch_x = [&](int unit) {
+        auto fetch_x = [&](int at) {
 #pragma unroll
             for (int i = 0; i < kRefill; ++i) {
-                const int c = (unit + i) * kPassCols + lane;
+                const int c = (at + i % kStep + i / kStep * apart) * kPassCols + lane;
 #pragma unroll
                 for (int b = 0; b < BATCH; ++b)
                     xr[i][b] = __hip_atomic_load(x + (size_t)b * K + (c < K ? c : K - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
@@ -95,7 +99,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
                 bool keep = false;
 #pragma unroll
                 for (int b = 0; b < BATCH; ++b) {
-                    kb[b] = u + i < end && !(__builtin_fabsf(half_bits_to_float(xr[i][b])) < thr);
+                    kb[b] = u + i % kStep < end && !(__builtin_fabsf(half_bits_to_float(xr[i][b])) < thr);
                     keep = keep || kb[b];
                 }
                 const uint64_t mask = __ballot(keep);
@@ -107,12 +111,12 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
                 const int first = mask ? (int)__builtin_ctzll(mask) : 0;
                 const bool enter = COMPACT ? keep : mask != 0ull;
                 const int at = enter ? ((filled + (COMPACT ? rank : lane)) & (kRing - 1)) : kRing + lane;
-                ring[wave][at] = u32x2{(uint32_t)((u + i) * kPassCols + (keep ? lane : first)), xb[0] | (xb[1] << 16)};
+                ring[wave][at] = u32x2{(uint32_t)((u + i % kStep + i / kStep * apart) * kPassCols + (keep ? lane : first)), xb[0] | (xb[1] << 16)};
                 if (BATCH > 2) ring23[wave][at] = xb[2] | (xb[3] << 16);
                 filled += COMPACT ? (int)__popcll(mask) : (mask ? kPassCols : 0);
             }
             filled = __builtin_amdgcn_readfirstlane(filled);
-            u += kRefill;
+            u += kStep;
             __builtin_amdgcn_wave_barrier();
         };
 
@@ -164,16 +168,31 @@ __global__ void spqt_fill_zero_kernel(uint32_t *p, size_t n_words) {
     if (i < n_words) p[i] = 0u;
 }
 
-template <int WAVES, int BATCH, bool COMPACT>
+template <int WAVES, int BATCH, bool COMPACT, int SPREAD = 1>
 void start_fused(int grid, hipStream_t stream, const uint8_t *packed, const uint16_t *x, float thr, float *y, void *partials,
                  int32_t *ws_flags, int K, int NG, int S, int T, int m_and_flags) {
-    hipLaunchKernelGGL((spqt_gemv_fused_kernel<WAVES, BATCH, COMPACT>), dim3(grid), dim3(WAVES * 64), 0, stream, packed, x, y,
+    hipLaunchKernelGGL((spqt_gemv_fused_kernel<WAVES, BATCH, COMPACT, SPREAD>), dim3(grid), dim3(WAVES * 64), 0, stream, packed, x, y,
                        partials, ws_flags, K, NG, S, T, m_and_flags, thr);
+}
+
+// In how many parts of K a slice of the one-row kernel lies, with `parts` slices.  With one range per slice, activations whose kept
+// columns crowd into one part of K leave the other wavefronts idle for as long as the crowded slices have passes.  28672 x 8192 at 50 %, 7 of 8
+// kept columns in the first half, one range / four 22.9 / 15.8 us; evenly kept columns 17.6 / 17.4; 14336 x 14336, two ranges, 21.0 / 15.3 and
+// 15.6 / 15.6.  Only where no slice gets longer by it (14336 x 14336 in four parts: 16 units instead of 14) and from 5 units per slice on: shorter
+// slices are a pass or two either way.
+inline int spread_of(int units, int parts) {
+    if (units < 5 * parts) return 1;
+    for (int f = 4; f > 1; f /= 2)
+        if (units % f == 0 && f * ((units / f + parts - 1) / parts) <= (units + parts - 1) / parts) return f;
+    return 1;
 }
 
 hipError_t launch_fused(int waves, bool compact, int grid, hipStream_t st, const uint8_t *pk, const uint16_t *x, float thr,
                         float *y, void *part, int32_t *fl, int K, int NG, int S, int T, int mf) {
-    switch (waves) {
+    const int spread = waves == 4 && compact ? spread_of(K / kPassCols, S * 4) : 1;
+    if (spread == 4) start_fused<4, 1, true, 4>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf);
+    else if (spread == 2) start_fused<4, 1, true, 2>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf);
+    else switch (waves) {
         case 1: compact ? start_fused<1, 1, true>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf) : start_fused<1, 1, false>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf); break;
         case 2: compact ? start_fused<2, 1, true>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf) : start_fused<2, 1, false>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf); break;
         default: compact ? start_fused<4, 1, true>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf) : start_fused<4, 1, false>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf); break;
