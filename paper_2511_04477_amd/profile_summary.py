@@ -132,7 +132,7 @@ def main(argv=None) -> int:
     if lay == "group-layout":
         L += ["", "spqt_gemv_list_kernel<wavefronts per workgroup, DENSE, BATCH, groups per pass>: <4, false, 1, 4> list-driven (spqt_gemv with an",
               "index list, one activation row), <4, true, 1, 1> dense, <4, false, 1, 1> list-driven with one-group passes (SPQT_CFG_GROUP_PASSES,",
-              "an ablation).  spqt_gemv_fused_kernel<4, 1, true>: one launch with static column ranges (spqt_gemv_fused).",
+              "an ablation).  spqt_gemv_fused_kernel<4, 1, true, 1, 2 or 4>: one launch with static column ranges (spqt_gemv_fused).",
               "spqt_gemv_bal_kernel<4>: one launch with even shares of the kept columns (SPQT_CFG_EVEN_SHARES)."]
 
     f, w, sq = (counters(os.path.join(D, x), kname) for x in ("fetch", "write", "sq"))

@@ -22,7 +22,7 @@ def test_summary_and_traffic_table_from_synthetic_csvs(tmp_path):
     LIST = "void (anonymous namespace)::spqt_gemv_list_kernel<4, false, 1, 4>(unsigned char const*, int)"
     GROUPS = "void (anonymous namespace)::spqt_gemv_list_kernel<4, false, 1, 1>(unsigned char const*, int)"
     DENSE = "void (anonymous namespace)::spqt_gemv_list_kernel<4, true, 1, 1>(unsigned char const*, int)"
-    ONE = "void (anonymous namespace)::spqt_gemv_fused_kernel<4, 1, true>(unsigned char const*, int)"
+    ONE = "void (anonymous namespace)::spqt_gemv_fused_kernel<4, 1, true, 4>(unsigned char const*, int)"
     COPY = "(anonymous namespace)::copy_kernel(unsigned int*, unsigned int const*, unsigned long)"
     GATHER = "void (anonymous namespace)::spqt_gather_kernel<1, false>(unsigned short const*)"
     kept, dense = 60_000_000, 120_000_000
