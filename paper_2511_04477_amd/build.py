@@ -36,6 +36,8 @@ HIPCC_FLAGS = [
     # matrix-core results stay in ordinary VGPRs: with a separate accumulator file the kernels that use
     # v_mfma would copy their sums to scale and add them
     "-mllvm", "-amdgpu-mfma-vgpr-form",
+    # the first 14 dwords of a kernel's arguments are in scalar registers when a wavefront starts (gemv_common.hpp)
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wno-unused-command-line-argument",
 ]
 JOBS = max(1, min(8, os.cpu_count() or 1))

@@ -32,10 +32,9 @@
 namespace spqt {
 
 template <class F, int WAVES, bool DENSE, bool FUSED, int BATCH = 1>
-__device__ __forceinline__ void colblock_width_gemv(const uint8_t *__restrict__ packed, const uint16_t *__restrict__ x,
-                                                    const int32_t *__restrict__ idx, const int32_t *__restrict__ count,
-                                                    float *__restrict__ y, void *partials, int32_t *ws_flags, int K, int NC,
-                                                    int S, int T, int M, float thr) {
+__device__ __forceinline__ void colblock_width_gemv(int S, int T, int K, int M, uint32_t inv, float thr, const int32_t *__restrict__ count,
+                                                    const int32_t *__restrict__ idx, const uint8_t *__restrict__ packed,
+                                                    const uint16_t *__restrict__ x, float *__restrict__ y, uint32_t *ws) {
     __shared__ uint32_t stage_off[WAVES][kPassCols];                                          // byte offset of each column
     static_assert(!FUSED || BATCH == 1, "the one-launch mode takes one activation row");
     __shared__ __attribute__((aligned(16))) float stage_xs[WAVES][BATCH][kPassCols][F::kBlocks];   // x * scale per block
@@ -48,18 +47,19 @@ __device__ __forceinline__ void colblock_width_gemv(const uint8_t *__restrict__ 
     const int seg = lane & 7;      // eighth of the block-row this lane reads
     const int cgr = ((cg & 1) << 2) | (cg & 2) | (cg >> 2);
     const uint32_t seg16 = (uint32_t)seg * 16u;
-    int t, s;
-    if (!block_of((int)blockIdx.x, S, T, t, s)) return;
-
     // what is split evenly: the kept-column list, all columns, or (one launch) the 64-column units
-    const int n_raw = FUSED ? K / kPassCols : (DENSE ? K : __builtin_amdgcn_readfirstlane(*count));
+    const int n_raw = FUSED ? K / kPassCols : (DENSE ? K : *count);     // requested first
+    int t, s;
+    if (!block_of<WAVES>(blockIdx.x, S, T, inv, t, s)) return;
+
     const int n_ns = n_raw < 0 ? 0 : (n_raw > K ? K : n_raw);
     const int parts = S * WAVES;
     const int part = s * WAVES + wave;
-    int pos = (int)(((int64_t)n_ns * part) / parts);
-    const int end = (int)(((int64_t)n_ns * (part + 1)) / parts);
+    const Share share = share_of<WAVES>(n_ns, part, parts, inv);
+    int pos = share.begin;
+    const int end = share.end;
 
-    const uint8_t *row_base = packed + (size_t)t * NC * F::kChunkBytes;
+    const uint8_t *row_base = packed + (size_t)t * (size_t)(K >> 7) * F::kChunkBytes;
 
     float acc[BATCH][F::kAcc];
     typename F::Sums bs[BATCH];
@@ -212,7 +212,7 @@ __device__ __forceinline__ void colblock_width_gemv(const uint8_t *__restrict__ 
 #pragma unroll
     for (int b = 0; b < BATCH; ++b) F::finish(acc[b], bs[b], seg, cgr, red[wave][b]);
     __syncthreads();
-    combine_block_row<WAVES, BATCH, F::kRows>(&red[0][0][0], tid, t, s, S, T, partials, ws_flags, y, M);
+    combine_block_row<WAVES, BATCH, F::kRows>(&red[0][0][0], tid, t, s, S, T, ws, y, M);
 }
 
 // Host side shared by the entry points: argument checks, launch shape, workspace, grid.  `launch` starts the
@@ -241,19 +241,17 @@ int colblock_width_run(int mode, int batch, int max_splits, int default_splits, 
     }
     if (S < 1 || S > max_splits) return SPQT_EINVAL;
     if (waves != 1 && waves != 2 && waves != 4) return SPQT_EINVAL;
-    void *partials = nullptr;
-    int32_t *ws_flags = nullptr;
+    uint32_t *ws = nullptr;
     if (S > 1) {
         if (!workspace_dev) return SPQT_EINVAL;
         if (workspace_bytes < need) return SPQT_ESIZE;
         if ((uintptr_t)workspace_dev % 256 != 0) return SPQT_EALIGN;
-        ws_flags = (int32_t *)workspace_dev;
-        partials = (void *)((uint8_t *)workspace_dev + counter_bytes(M));
+        ws = (uint32_t *)workspace_dev;
     }
-    const int T = (int)T64, NC = (int)(K / kGroup);
+    const int T = (int)T64;
     const int grid = grid_blocks(T, S);
     const int m_and_flags = (int)M | (y_half ? kHalfOutputBit : 0);
-    const hipError_t err = launch(waves, mode, grid, partials, ws_flags, NC, S, T, m_and_flags);
+    const hipError_t err = launch(waves, mode, grid, ws, S, T, m_and_flags);
     return err == hipSuccess ? SPQT_OK : SPQT_EHIP;
 }
 

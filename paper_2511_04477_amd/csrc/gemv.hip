@@ -31,8 +31,8 @@ constexpr int kRefill = 4;                   // units compacted together: their 
 constexpr int kRing = 512;                   // ring entries per wavefront; a refill adds at most 256 to at most 63 live ones
 template <int WAVES, int BATCH, bool COMPACT, int SPREAD>
 __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
-    const uint8_t *__restrict__ packed, const uint16_t *__restrict__ x, float *__restrict__ y, void *partials,
-    int32_t *ws_flags, int K, int NG, int S, int T, int M, float thr) {
+    int S, int T, int K, int M, uint32_t inv, float thr, const uint16_t *__restrict__ x, const uint8_t *__restrict__ packed,
+    float *__restrict__ y, uint32_t *ws) {
     constexpr int kGroups = groups_per_pass(BATCH);
     __shared__ __attribute__((aligned(16))) StagedX staged[WAVES];
     // the wavefront's kept columns: {column, x[0] | x[1] << 16}, x[2] | x[3] << 16 (+ 64 entries that nothing reads)
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
     const uint32_t n8 = (uint32_t)n * 8u;
     const uint32_t out4 = (uint32_t)(4 * n + (lane >> 4));    // the lane's 4 outputs: rows 4 out4 .. 4 out4 + 3
     int t, s;
-    if (!block_of((int)blockIdx.x, S, T, t, s)) return;
+    if (!block_of<WAVES>(blockIdx.x, S, T, inv, t, s)) return;
 
     // Positions: a unit, or SPREAD units that lie `apart` from each other; a refill takes kStep positions, unit i of it is
     // u + i % kStep + i / kStep * apart.
@@ -56,15 +56,15 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
     const int positions = K / kPassCols / SPREAD, apart = positions;
     const int parts = S * WAVES;
     const int part = s * WAVES + wave;
-    // positions <= 2^18 and part < 512: the products fit 32 bits
-    int u = (int)(((uint32_t)positions * (uint32_t)part) / (uint32_t)parts);
-    const int end = (int)(((uint32_t)positions * (uint32_t)(part + 1)) / (uint32_t)parts);
+    const Share share = share_of<WAVES>(positions, part, parts, inv);
+    int u = share.begin;
+    const int end = share.end;
     SPQT_TL(1);
 
-    // quantization groups of 128 or 64 columns: NG tells which (K % 128 == 0 either way)
-    const int log2g = (NG << 7) == K ? 7 : 6;
+    // quantization groups of 128 or 64 columns
+    const int log2g = M & kGroup64Bit ? 6 : 7;
     const uint32_t chunk_b = (uint32_t)(kScaleBytes + (kColBytes << log2g));
-    const uint8_t *row_base = packed + (size_t)t * NG * chunk_b;
+    const uint8_t *row_base = packed + (size_t)t * (size_t)(K >> log2g) * chunk_b;
 
     float acc[BATCH][4];   // rows 4 out4 + p of the block-row, scaled, in the products' units
 #pragma unroll
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
                                                              acc[b][2] * kEvenUnit, acc[b][3] * kOddUnit};
     __syncthreads();
     SPQT_TL(5);
-    combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, t, s, S, T, partials, ws_flags, y, M);
+    combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, t, s, S, T, ws, y, M);
     SPQT_TL_END(WAVES, wave, lane, S > 1 && s == S - 1);
 }
 
@@ -169,10 +169,10 @@ __global__ void spqt_fill_zero_kernel(uint32_t *p, size_t n_words) {
 }
 
 template <int WAVES, int BATCH, bool COMPACT, int SPREAD = 1>
-void start_fused(int grid, hipStream_t stream, const uint8_t *packed, const uint16_t *x, float thr, float *y, void *partials,
-                 int32_t *ws_flags, int K, int NG, int S, int T, int m_and_flags) {
-    hipLaunchKernelGGL((spqt_gemv_fused_kernel<WAVES, BATCH, COMPACT, SPREAD>), dim3(grid), dim3(WAVES * 64), 0, stream, packed, x, y,
-                       partials, ws_flags, K, NG, S, T, m_and_flags, thr);
+void start_fused(int grid, hipStream_t stream, const uint8_t *packed, const uint16_t *x, float thr, float *y, uint32_t *ws,
+                 int K, int S, int T, int m_and_flags) {
+    hipLaunchKernelGGL((spqt_gemv_fused_kernel<WAVES, BATCH, COMPACT, SPREAD>), dim3(grid), dim3(WAVES * 64), 0, stream, S, T, K,
+                       m_and_flags, inverse_of(S * WAVES), thr, x, packed, y, ws);
 }
 
 // In how many parts of K a slice of the one-row kernel lies, with `parts` slices.  With one range per slice, activations whose kept
@@ -188,25 +188,25 @@ inline int spread_of(int units, int parts) {
 }
 
 hipError_t launch_fused(int waves, bool compact, int grid, hipStream_t st, const uint8_t *pk, const uint16_t *x, float thr,
-                        float *y, void *part, int32_t *fl, int K, int NG, int S, int T, int mf) {
+                        float *y, uint32_t *ws, int K, int S, int T, int mf) {
     const int spread = waves == 4 && compact ? spread_of(K / kPassCols, S * 4) : 1;
-    if (spread == 4) start_fused<4, 1, true, 4>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf);
-    else if (spread == 2) start_fused<4, 1, true, 2>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf);
+    if (spread == 4) start_fused<4, 1, true, 4>(grid, st, pk, x, thr, y, ws, K, S, T, mf);
+    else if (spread == 2) start_fused<4, 1, true, 2>(grid, st, pk, x, thr, y, ws, K, S, T, mf);
     else switch (waves) {
-        case 1: compact ? start_fused<1, 1, true>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf) : start_fused<1, 1, false>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf); break;
-        case 2: compact ? start_fused<2, 1, true>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf) : start_fused<2, 1, false>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf); break;
-        default: compact ? start_fused<4, 1, true>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf) : start_fused<4, 1, false>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf); break;
+        case 1: compact ? start_fused<1, 1, true>(grid, st, pk, x, thr, y, ws, K, S, T, mf) : start_fused<1, 1, false>(grid, st, pk, x, thr, y, ws, K, S, T, mf); break;
+        case 2: compact ? start_fused<2, 1, true>(grid, st, pk, x, thr, y, ws, K, S, T, mf) : start_fused<2, 1, false>(grid, st, pk, x, thr, y, ws, K, S, T, mf); break;
+        default: compact ? start_fused<4, 1, true>(grid, st, pk, x, thr, y, ws, K, S, T, mf) : start_fused<4, 1, false>(grid, st, pk, x, thr, y, ws, K, S, T, mf); break;
     }
     return hipGetLastError();
 }
 
 // One launch for 2..4 activation rows (4 or 8 wavefronts per workgroup).
 hipError_t launch_fused_rows(int waves, int batch, int grid, hipStream_t st, const uint8_t *pk, const uint16_t *x, float thr,
-                             float *y, void *part, int32_t *fl, int K, int NG, int S, int T, int mf) {
+                             float *y, uint32_t *ws, int K, int S, int T, int mf) {
     switch (batch) {
-        case 2: start_fused<4, 2, true>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf); break;
-        case 3: waves == 8 ? start_fused<8, 3, true>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf) : start_fused<4, 3, true>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf); break;
-        default: waves == 8 ? start_fused<8, 4, true>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf) : start_fused<4, 4, true>(grid, st, pk, x, thr, y, part, fl, K, NG, S, T, mf); break;
+        case 2: start_fused<4, 2, true>(grid, st, pk, x, thr, y, ws, K, S, T, mf); break;
+        case 3: waves == 8 ? start_fused<8, 3, true>(grid, st, pk, x, thr, y, ws, K, S, T, mf) : start_fused<4, 3, true>(grid, st, pk, x, thr, y, ws, K, S, T, mf); break;
+        default: waves == 8 ? start_fused<8, 4, true>(grid, st, pk, x, thr, y, ws, K, S, T, mf) : start_fused<4, 4, true>(grid, st, pk, x, thr, y, ws, K, S, T, mf); break;
     }
     return hipGetLastError();
 }
@@ -217,12 +217,12 @@ extern "C" int spqt_workspace_bytes(int64_t M, int64_t K, int batch, size_t *out
     if (!out_bytes) return SPQT_EINVAL;
     if (int rc = check_shape(M, K, kGroup)) return rc;
     if (batch < 1 || batch > SPQT_MAX_BATCH) return SPQT_ESHAPE;
-    *out_bytes = counter_bytes(M) + (size_t)tiles(M) * kTileRows * SPQT_MAX_SPLITS * 2 * sizeof(float) * (size_t)batch;
+    *out_bytes = kWorkspaceHead + (size_t)tiles(M) * kTileRows * SPQT_MAX_SPLITS * 2 * sizeof(float) * (size_t)batch;
     return SPQT_OK;
 }
 
 extern "C" int spqt_workspace_init(void *workspace_dev, size_t workspace_bytes, void *stream) {
-    if (!workspace_dev || workspace_bytes < 256) return SPQT_EINVAL;
+    if (!workspace_dev || workspace_bytes < kWorkspaceHead) return SPQT_EINVAL;
     if ((uintptr_t)workspace_dev % 256 != 0) return SPQT_EALIGN;
     // The poison flag and every exchange word start at zero: clear all of it.
     size_t words = workspace_bytes / 4;
@@ -249,6 +249,9 @@ size_t needed_bytes(int64_t M, int64_t K, int batch, int S, bool tight) {
     spqt_workspace_bytes(M, K, batch, &need);
     return need;
 }
+
+// M and the flags of a call as the kernels take them.
+int kernel_rows(int64_t M, int group, int y_half) { return (int)M | (y_half ? kHalfOutputBit : 0) | (group == kGroup ? 0 : kGroup64Bit); }
 
 // spqt_gemv_ex, and the allocation-free variant: `tight` accepts a workspace that holds just the
 // exchange words this launch shape touches instead of the size spqt_workspace_bytes reports.
@@ -278,24 +281,21 @@ int gemv_run(const void *packed_dev, int64_t M, int64_t K, int group, const void
     if (c.waves != 1 && c.waves != 2 && c.waves != 4 && c.waves != 8) return SPQT_EINVAL;
 
     const size_t need = needed_bytes(M, K, batch, c.splits, tight);
-    void *partials = nullptr;
-    int32_t *ws_flags = nullptr;
+    uint32_t *ws = nullptr;
     if (c.splits > 1) {
         if (!workspace_dev) return SPQT_EINVAL;
         if (workspace_bytes < need) return SPQT_ESIZE;
         if ((uintptr_t)workspace_dev % 256 != 0) return SPQT_EALIGN;
-        ws_flags = (int32_t *)workspace_dev;
-        partials = (void *)((uint8_t *)workspace_dev + counter_bytes(M));
+        ws = (uint32_t *)workspace_dev;
     }
 
-    const int T = (int)tiles(M), NG = (int)(K / group);
+    const int T = (int)tiles(M);
     const int grid = grid_blocks(T, c.splits);
     hipStream_t st = (hipStream_t)stream;
     hipError_t err;
     const uint8_t *pk = (const uint8_t *)packed_dev;
     const uint16_t *xp = (const uint16_t *)x_dev;
-    const ListLaunch a = {pk, xp, idx_dev, count_dev, (float *)y_dev, partials, ws_flags, (int)K, NG, c.splits, T,
-                          (int)M | (y_half ? kHalfOutputBit : 0)};
+    const ListLaunch a = {pk, xp, idx_dev, count_dev, (float *)y_dev, ws, (int)K, c.splits, T, kernel_rows(M, group, y_half)};
     err = launch_gemv_list(c.waves, batch, one_group, grid, st, a);
     if (err != hipSuccess) return SPQT_EHIP;
     return SPQT_OK;
@@ -373,16 +373,14 @@ extern "C" int spqt_gemv_fused(const void *packed_dev, int64_t M, int64_t K, int
     if (c.splits < 1 || c.splits > SPQT_MAX_SPLITS) return SPQT_EINVAL;
     if (c.waves != 1 && c.waves != 2 && c.waves != 4) return SPQT_EINVAL;
     const size_t need = needed_bytes(M, K, 1, c.splits, false);
-    void *partials = nullptr;
-    int32_t *ws_flags = nullptr;
+    uint32_t *ws = nullptr;
     if (c.splits > 1) {
         if (!workspace_dev) return SPQT_EINVAL;
         if (workspace_bytes < need) return SPQT_ESIZE;
         if ((uintptr_t)workspace_dev % 256 != 0) return SPQT_EALIGN;
-        ws_flags = (int32_t *)workspace_dev;
-        partials = (void *)((uint8_t *)workspace_dev + counter_bytes(M));
+        ws = (uint32_t *)workspace_dev;
     }
-    const int T = (int)tiles(M), NG = (int)(K / group);
+    const int T = (int)tiles(M);
     const int grid = grid_blocks(T, c.splits);
     const bool compact = !(cfg && (cfg->flags & SPQT_CFG_NO_COMPACTION));
     hipStream_t st = (hipStream_t)stream;
@@ -390,12 +388,12 @@ extern "C" int spqt_gemv_fused(const void *packed_dev, int64_t M, int64_t K, int
     const uint16_t *xp = (const uint16_t *)x_dev;
     hipError_t err;
     if (!static_ranges) {
-        err = launch_gemv_bal(c.waves, grid, st, pk, xp, threshold, (float *)y_dev, partials, ws_flags, (int)K, NG,
-                              c.splits, T, (int)M | (y_half ? kHalfOutputBit : 0));
+        err = launch_gemv_bal(c.waves, grid, st, pk, xp, threshold, (float *)y_dev, ws, (int)K,
+                              c.splits, T, kernel_rows(M, group, y_half));
         return err == hipSuccess ? SPQT_OK : SPQT_EHIP;
     }
-    err = launch_fused(c.waves, compact, grid, st, pk, xp, threshold, (float *)y_dev, partials, ws_flags, (int)K, NG, c.splits, T,
-                       (int)M | (y_half ? kHalfOutputBit : 0));
+    err = launch_fused(c.waves, compact, grid, st, pk, xp, threshold, (float *)y_dev, ws, (int)K, c.splits, T,
+                       kernel_rows(M, group, y_half));
     return err == hipSuccess ? SPQT_OK : SPQT_EHIP;
 }
 
@@ -422,20 +420,18 @@ extern "C" int spqt_gemv_fused_rows(const void *packed_dev, int64_t M, int64_t K
     if (c.waves != 4 && !(c.waves == 8 && batch >= 3)) return SPQT_EINVAL;
     if (c.splits < 1 || c.splits > SPQT_MAX_SPLITS) return SPQT_EINVAL;
     const size_t need = needed_bytes(M, K, batch, c.splits, false);
-    void *partials = nullptr;
-    int32_t *ws_flags = nullptr;
+    uint32_t *ws = nullptr;
     if (c.splits > 1) {
         if (!workspace_dev) return SPQT_EINVAL;
         if (workspace_bytes < need) return SPQT_ESIZE;
         if ((uintptr_t)workspace_dev % 256 != 0) return SPQT_EALIGN;
-        ws_flags = (int32_t *)workspace_dev;
-        partials = (void *)((uint8_t *)workspace_dev + counter_bytes(M));
+        ws = (uint32_t *)workspace_dev;
     }
-    const int T = (int)tiles(M), NG = (int)(K / group);
+    const int T = (int)tiles(M);
     const int grid = grid_blocks(T, c.splits);
-    const int mf = (int)M | (y_half ? kHalfOutputBit : 0) | (own_sets ? kOwnSetsBit : 0);
+    const int mf = kernel_rows(M, group, y_half) | (own_sets ? kOwnSetsBit : 0);
     hipError_t err = launch_fused_rows(c.waves, batch, grid, (hipStream_t)stream, (const uint8_t *)packed_dev, (const uint16_t *)x_dev,
-                                       threshold, (float *)y_dev, partials, ws_flags, (int)K, NG, c.splits, T, mf);
+                                       threshold, (float *)y_dev, ws, (int)K, c.splits, T, mf);
     return err == hipSuccess ? SPQT_OK : SPQT_EHIP;
 }
 

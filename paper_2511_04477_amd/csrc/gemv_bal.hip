@@ -63,8 +63,8 @@ __device__ __forceinline__ int wave_inclusive_scan(int v, int lane, int &total) 
 }
 template <int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
-    const uint8_t *__restrict__ packed, const uint16_t *__restrict__ x, float thr, float *__restrict__ y,
-    void *partials, int32_t *ws_flags, int K, int NG, int S, int T, int M) {
+    int S, int T, int K, int M, uint32_t inv, float thr, const uint16_t *__restrict__ x, const uint8_t *__restrict__ packed,
+    float *__restrict__ y, uint32_t *ws) {
     __shared__ __attribute__((aligned(16))) StagedX staged[WAVES];
     __shared__ __attribute__((aligned(16))) float red[WAVES][1][kTileRows];
     // kept columns per step: word [w][q][row of 16 lanes] holds, 10 bits each, that row's counts of the steps
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
     const uint32_t n8 = (uint32_t)n * 8u;
     const uint32_t out4 = (uint32_t)(4 * n + (lane >> 4));    // the lane's 4 outputs: rows 4 out4 .. 4 out4 + 3
     int t, s;
-    if (!block_of((int)blockIdx.x, S, T, t, s)) return;
+    if (!block_of<WAVES>(blockIdx.x, S, T, inv, t, s)) return;
 
     // 1. COUNT: x into LDS, then the kept columns of every 512-column step (every workgroup does all of x).
     const int nsteps = (K + kStepCols - 1) / kStepCols;      // <= kXsSteps (checked on the host)
@@ -128,13 +128,12 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
     const int p0 = wave_inclusive_scan(c0, lane, n_ns);
     const int parts = S * WAVES;
     const int part = s * WAVES + wave;
-    // n_ns <= 32768 and part < parts <= 256: the products fit 32 bits
-    const int begin = (int)(((uint32_t)n_ns * (uint32_t)part) / (uint32_t)parts);     // ranks [begin, begin + total) of the kept columns
-    const int total = (int)(((uint32_t)n_ns * (uint32_t)(part + 1)) / (uint32_t)parts) - begin;
+    const Share share = share_of<WAVES>(n_ns, part, parts, inv);
+    const int begin = share.begin, total = share.end - begin;             // ranks [begin, begin + total) of the kept columns
 
-    const int log2g = (NG << 7) == K ? 7 : 6;
+    const int log2g = M & kGroup64Bit ? 6 : 7;
     const uint32_t chunk_b = (uint32_t)(kScaleBytes + (kColBytes << log2g));
-    const uint8_t *row_base = packed + (size_t)t * NG * chunk_b;
+    const uint8_t *row_base = packed + (size_t)t * (size_t)(K >> log2g) * chunk_b;
 
     float acc[1][4] = {{0.0f, 0.0f, 0.0f, 0.0f}};   // rows 4 out4 + p of the block-row, scaled, in the products' units
 
@@ -200,7 +199,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
                                                          acc[0][2] * kEvenUnit, acc[0][3] * kOddUnit};
     __syncthreads();
     SPQT_TL(5);
-    combine_block_row<WAVES, 1>(&red[0][0][0], tid, t, s, S, T, partials, ws_flags, y, M);
+    combine_block_row<WAVES, 1>(&red[0][0][0], tid, t, s, S, T, ws, y, M);
     SPQT_TL_END(WAVES, wave, lane, S > 1 && s == S - 1);
 }
 
@@ -211,11 +210,11 @@ namespace spqt {
 SPQT_TL_SETTER(spqt_timeline_set_bal)
 
 hipError_t launch_gemv_bal(int waves, int grid, hipStream_t stream, const uint8_t *packed, const uint16_t *x, float thr,
-                           float *y, void *partials, int32_t *ws_flags, int K, int NG, int S, int T, int m_and_flags) {
+                           float *y, uint32_t *ws, int K, int S, int T, int m_and_flags) {
     switch (waves) {
-        case 1: hipLaunchKernelGGL((spqt_gemv_bal_kernel<1>), dim3(grid), dim3(64), 0, stream, packed, x, thr, y, partials, ws_flags, K, NG, S, T, m_and_flags); break;
-        case 2: hipLaunchKernelGGL((spqt_gemv_bal_kernel<2>), dim3(grid), dim3(128), 0, stream, packed, x, thr, y, partials, ws_flags, K, NG, S, T, m_and_flags); break;
-        default: hipLaunchKernelGGL((spqt_gemv_bal_kernel<4>), dim3(grid), dim3(256), 0, stream, packed, x, thr, y, partials, ws_flags, K, NG, S, T, m_and_flags); break;
+        case 1: hipLaunchKernelGGL((spqt_gemv_bal_kernel<1>), dim3(grid), dim3(64), 0, stream, S, T, K, m_and_flags, inverse_of(S * 1), thr, x, packed, y, ws); break;
+        case 2: hipLaunchKernelGGL((spqt_gemv_bal_kernel<2>), dim3(grid), dim3(128), 0, stream, S, T, K, m_and_flags, inverse_of(S * 2), thr, x, packed, y, ws); break;
+        default: hipLaunchKernelGGL((spqt_gemv_bal_kernel<4>), dim3(grid), dim3(256), 0, stream, S, T, K, m_and_flags, inverse_of(S * 4), thr, x, packed, y, ws); break;
     }
     return hipGetLastError();
 }

@@ -49,9 +49,8 @@ static_assert(kCbChunkBytes == kCbScaleBytes + kGroup * kColBytes, "chunk size")
 // multiply is unchanged, and the minima take the place of the offset-binary bias.
 template <int WAVES, bool DENSE, bool FUSED, int BATCH, bool KQ = false>
 __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
-    const uint8_t *__restrict__ packed, const uint16_t *__restrict__ x,
-    const int32_t *__restrict__ idx, const int32_t *__restrict__ count, float *__restrict__ y,
-    void *partials, int32_t *ws_flags, int K, int NC, int S, int T, int M, float thr) {
+    int S, int T, int K, int M, uint32_t inv, float thr, const int32_t *__restrict__ count, const int32_t *__restrict__ idx,
+    const uint8_t *__restrict__ packed, const uint16_t *__restrict__ x, float *__restrict__ y, uint32_t *ws) {
     // One staging area per wavefront is enough: offsets are written and read back inside a FETCH
     // stage, products inside a MULTIPLY stage, and a wavefront runs its stages one after the other.
     __shared__ uint32_t stage_off[WAVES][kPassCols];                               // byte offset of each column
@@ -66,18 +65,19 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
     const int seg = lane & 7;
     const int cgr = ((cg & 1) << 2) | (cg & 2) | (cg >> 2);
     const uint32_t seg16 = (uint32_t)seg * 16u;
+    const int n_raw = FUSED ? K / kPassCols : (DENSE ? K : *count);     // requested first
     int t, s;
-    if (!block_of((int)blockIdx.x, S, T, t, s)) return;
+    if (!block_of<WAVES>(blockIdx.x, S, T, inv, t, s)) return;
 
     // (a count outside 0..K cannot come from spqt_gather; clamping keeps a corrupt one inside idx)
-    const int n_raw = FUSED ? K / kPassCols : (DENSE ? K : __builtin_amdgcn_readfirstlane(*count));
     const int n_ns = n_raw < 0 ? 0 : (n_raw > K ? K : n_raw);
     const int parts = S * WAVES;
     const int part = s * WAVES + wave;
-    int pos = (int)(((int64_t)n_ns * part) / parts);
-    const int end = (int)(((int64_t)n_ns * (part + 1)) / parts);
+    const Share share = share_of<WAVES>(n_ns, part, parts, inv);
+    int pos = share.begin;
+    const int end = share.end;
 
-    const uint8_t *row_base = packed + (size_t)t * NC * kCbChunkBytes;
+    const uint8_t *row_base = packed + (size_t)t * (size_t)(K >> 7) * kCbChunkBytes;
 
     float acc[BATCH][32];   // this lane's 32 rows, summed over its columns of the whole slice
     float bsum[BATCH];      // sum of the staged products this lane multiplied with (its block)
@@ -290,48 +290,48 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
             f32x4{r4[0] - bias, r4[1] - bias, r4[2] - bias, r4[3] - bias};
     }
     __syncthreads();
-    combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, t, s, S, T, partials, ws_flags, y, M);
+    combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, t, s, S, T, ws, y, M);
 }
 
 template <int WAVES, int BATCH>
 hipError_t launch_cb_batch(int mode, int grid, hipStream_t stream, const uint8_t *packed, const uint16_t *x,
-                           const int32_t *idx, const int32_t *count, float *y, void *partials, int32_t *ws_flags,
-                           int K, int NC, int S, int T, int M, int y_half) {
+                           const int32_t *idx, const int32_t *count, float *y, uint32_t *ws,
+                           int K, int S, int T, int M, int y_half) {
     const dim3 g(grid), b(WAVES * 64);
     if (mode == 3)        // K-quant flavour, index list
-        hipLaunchKernelGGL((spqt_cb_gemv_kernel<WAVES, false, false, BATCH, true>), g, b, 0, stream, packed, x, idx, count, y,
-                           partials, ws_flags, K, NC, S, T, M | (y_half ? kHalfOutputBit : 0), 0.0f);
+        hipLaunchKernelGGL((spqt_cb_gemv_kernel<WAVES, false, false, BATCH, true>), g, b, 0, stream, S, T, K,
+                           M | (y_half ? kHalfOutputBit : 0), inverse_of(S * WAVES), 0.0f, count, idx, packed, x, y, ws);
     else if (mode == 4)   // K-quant flavour, dense
-        hipLaunchKernelGGL((spqt_cb_gemv_kernel<WAVES, true, false, BATCH, true>), g, b, 0, stream, packed, x, idx, count, y,
-                           partials, ws_flags, K, NC, S, T, M | (y_half ? kHalfOutputBit : 0), 0.0f);
+        hipLaunchKernelGGL((spqt_cb_gemv_kernel<WAVES, true, false, BATCH, true>), g, b, 0, stream, S, T, K,
+                           M | (y_half ? kHalfOutputBit : 0), inverse_of(S * WAVES), 0.0f, count, idx, packed, x, y, ws);
     else if (mode == 0)   // index list
-        hipLaunchKernelGGL((spqt_cb_gemv_kernel<WAVES, false, false, BATCH>), g, b, 0, stream, packed, x, idx, count, y,
-                           partials, ws_flags, K, NC, S, T, M | (y_half ? kHalfOutputBit : 0), 0.0f);
+        hipLaunchKernelGGL((spqt_cb_gemv_kernel<WAVES, false, false, BATCH>), g, b, 0, stream, S, T, K,
+                           M | (y_half ? kHalfOutputBit : 0), inverse_of(S * WAVES), 0.0f, count, idx, packed, x, y, ws);
     else                  // dense
-        hipLaunchKernelGGL((spqt_cb_gemv_kernel<WAVES, true, false, BATCH>), g, b, 0, stream, packed, x, idx, count, y,
-                           partials, ws_flags, K, NC, S, T, M | (y_half ? kHalfOutputBit : 0), 0.0f);
+        hipLaunchKernelGGL((spqt_cb_gemv_kernel<WAVES, true, false, BATCH>), g, b, 0, stream, S, T, K,
+                           M | (y_half ? kHalfOutputBit : 0), inverse_of(S * WAVES), 0.0f, count, idx, packed, x, y, ws);
     return hipGetLastError();
 }
 
 template <int WAVES>
 hipError_t launch_cb(int mode, int batch, int grid, hipStream_t stream, const uint8_t *packed, const uint16_t *x,
-                     const int32_t *idx, const int32_t *count, float *y, void *partials, int32_t *ws_flags,
-                     int K, int NC, int S, int T, int M, float thr, int y_half) {
+                     const int32_t *idx, const int32_t *count, float *y, uint32_t *ws,
+                     int K, int S, int T, int M, float thr, int y_half) {
     if (mode == 5) {      // K-quant flavour, threshold inside the kernel (batch 1)
-        hipLaunchKernelGGL((spqt_cb_gemv_kernel<WAVES, false, true, 1, true>), dim3(grid), dim3(WAVES * 64), 0, stream, packed,
-                           x, idx, count, y, partials, ws_flags, K, NC, S, T, M | (y_half ? kHalfOutputBit : 0), thr);
+        hipLaunchKernelGGL((spqt_cb_gemv_kernel<WAVES, false, true, 1, true>), dim3(grid), dim3(WAVES * 64), 0, stream, S, T,
+                           K, M | (y_half ? kHalfOutputBit : 0), inverse_of(S * WAVES), thr, count, idx, packed, x, y, ws);
         return hipGetLastError();
     }
     if (mode == 2) {      // threshold inside the kernel (batch 1)
-        hipLaunchKernelGGL((spqt_cb_gemv_kernel<WAVES, false, true, 1>), dim3(grid), dim3(WAVES * 64), 0, stream, packed,
-                           x, idx, count, y, partials, ws_flags, K, NC, S, T, M | (y_half ? kHalfOutputBit : 0), thr);
+        hipLaunchKernelGGL((spqt_cb_gemv_kernel<WAVES, false, true, 1>), dim3(grid), dim3(WAVES * 64), 0, stream, S, T,
+                           K, M | (y_half ? kHalfOutputBit : 0), inverse_of(S * WAVES), thr, count, idx, packed, x, y, ws);
         return hipGetLastError();
     }
     switch (batch) {
-        case 1: return launch_cb_batch<WAVES, 1>(mode, grid, stream, packed, x, idx, count, y, partials, ws_flags, K, NC, S, T, M, y_half);
-        case 2: return launch_cb_batch<WAVES, 2>(mode, grid, stream, packed, x, idx, count, y, partials, ws_flags, K, NC, S, T, M, y_half);
-        case 3: return launch_cb_batch<WAVES, 3>(mode, grid, stream, packed, x, idx, count, y, partials, ws_flags, K, NC, S, T, M, y_half);
-        default: return launch_cb_batch<WAVES, 4>(mode, grid, stream, packed, x, idx, count, y, partials, ws_flags, K, NC, S, T, M, y_half);
+        case 1: return launch_cb_batch<WAVES, 1>(mode, grid, stream, packed, x, idx, count, y, ws, K, S, T, M, y_half);
+        case 2: return launch_cb_batch<WAVES, 2>(mode, grid, stream, packed, x, idx, count, y, ws, K, S, T, M, y_half);
+        case 3: return launch_cb_batch<WAVES, 3>(mode, grid, stream, packed, x, idx, count, y, ws, K, S, T, M, y_half);
+        default: return launch_cb_batch<WAVES, 4>(mode, grid, stream, packed, x, idx, count, y, ws, K, S, T, M, y_half);
     }
 }
 
@@ -361,25 +361,23 @@ int run_cb(int mode, int batch, const void *packed_dev, int64_t M, int64_t K, co
     }
     if (c.splits < 1 || c.splits > SPQT_MAX_SPLITS) return SPQT_EINVAL;
     if (c.waves != 1 && c.waves != 2 && c.waves != 4) return SPQT_EINVAL;
-    void *partials = nullptr;
-    int32_t *ws_flags = nullptr;
+    uint32_t *ws = nullptr;
     if (c.splits > 1) {
         if (!workspace_dev) return SPQT_EINVAL;
         if (workspace_bytes < need) return SPQT_ESIZE;
         if ((uintptr_t)workspace_dev % 256 != 0) return SPQT_EALIGN;
-        ws_flags = (int32_t *)workspace_dev;
-        partials = (void *)((uint8_t *)workspace_dev + counter_bytes(M));
+        ws = (uint32_t *)workspace_dev;
     }
-    const int T = (int)tiles(M), NC = (int)(K / kGroup);
+    const int T = (int)tiles(M);
     const int grid = grid_blocks(T, c.splits);
     hipStream_t st = (hipStream_t)stream;
     const uint8_t *pk = (const uint8_t *)packed_dev;
     const uint16_t *xp = (const uint16_t *)x_dev;
     hipError_t err;
     switch (c.waves) {
-        case 1: err = launch_cb<1>(mode, batch, grid, st, pk, xp, idx_dev, count_dev, (float *)y_dev, partials, ws_flags, (int)K, NC, c.splits, T, (int)M, threshold, y_half); break;
-        case 2: err = launch_cb<2>(mode, batch, grid, st, pk, xp, idx_dev, count_dev, (float *)y_dev, partials, ws_flags, (int)K, NC, c.splits, T, (int)M, threshold, y_half); break;
-        default: err = launch_cb<4>(mode, batch, grid, st, pk, xp, idx_dev, count_dev, (float *)y_dev, partials, ws_flags, (int)K, NC, c.splits, T, (int)M, threshold, y_half); break;
+        case 1: err = launch_cb<1>(mode, batch, grid, st, pk, xp, idx_dev, count_dev, (float *)y_dev, ws, (int)K, c.splits, T, (int)M, threshold, y_half); break;
+        case 2: err = launch_cb<2>(mode, batch, grid, st, pk, xp, idx_dev, count_dev, (float *)y_dev, ws, (int)K, c.splits, T, (int)M, threshold, y_half); break;
+        default: err = launch_cb<4>(mode, batch, grid, st, pk, xp, idx_dev, count_dev, (float *)y_dev, ws, (int)K, c.splits, T, (int)M, threshold, y_half); break;
     }
     return err == hipSuccess ? SPQT_OK : SPQT_EHIP;
 }

@@ -109,15 +109,14 @@ static_assert(W2::kChunkBytes == W2::kScaleBytes + kGroup * 128, "chunk size");
 
 template <int WAVES, bool DENSE, bool FUSED, int BATCH>
 __global__ __launch_bounds__(WAVES * 64) void spqt_cb2_gemv_kernel(
-    const uint8_t *__restrict__ packed, const uint16_t *__restrict__ x, const int32_t *__restrict__ idx,
-    const int32_t *__restrict__ count, float *__restrict__ y, void *partials, int32_t *ws_flags, int K, int NC, int S,
-    int T, int M, float thr) {
-    colblock_width_gemv<W2, WAVES, DENSE, FUSED, BATCH>(packed, x, idx, count, y, partials, ws_flags, K, NC, S, T, M, thr);
+    int S, int T, int K, int M, uint32_t inv, float thr, const int32_t *__restrict__ count, const int32_t *__restrict__ idx,
+    const uint8_t *__restrict__ packed, const uint16_t *__restrict__ x, float *__restrict__ y, uint32_t *ws) {
+    colblock_width_gemv<W2, WAVES, DENSE, FUSED, BATCH>(S, T, K, M, inv, thr, count, idx, packed, x, y, ws);
 }
 
 #define SPQT_CB2_LAUNCH(W, D, F, B)                                                                                \
-    hipLaunchKernelGGL((spqt_cb2_gemv_kernel<W, D, F, B>), dim3(grid), dim3(W * 64), 0, st, pk, xp, idx_dev, count_dev, \
-                       (float *)y_dev, partials, ws_flags, (int)K, NC, S, T, m_and_flags, thr)
+    hipLaunchKernelGGL((spqt_cb2_gemv_kernel<W, D, F, B>), dim3(grid), dim3(W * 64), 0, st, S, T, (int)K,         \
+                       m_and_flags, inverse_of(S * W), thr, count_dev, idx_dev, pk, xp, (float *)y_dev, ws)
 // mode 0 = index list, 1 = dense, 2 = one launch (one activation row)
 #define SPQT_CB2_MODES(W, B)                                   \
     do {                                                         \
@@ -152,7 +151,7 @@ int run2(int mode, int batch, const void *packed_dev, int64_t M, int64_t K, cons
     const uint16_t *xp = (const uint16_t *)x_dev;
     return colblock_width_run<W2>(
         mode, batch, kMaxSplits2, S0, false, packed_dev, M, K, x_dev, idx_dev, count_dev, y_dev, workspace_dev, workspace_bytes, cfg,
-        [&](int waves, int md, int grid, void *partials, int32_t *ws_flags, int NC, int S, int T, int m_and_flags) {
+        [&](int waves, int md, int grid, uint32_t *ws, int S, int T, int m_and_flags) {
             switch (waves) {
                 case 1: SPQT_CB2_ROWS(1); break;
                 case 2: SPQT_CB2_ROWS(2); break;

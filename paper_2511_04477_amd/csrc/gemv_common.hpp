@@ -22,6 +22,7 @@ constexpr int kPassCols = 64;                  // most columns one pass covers
 constexpr float kTwo24 = 16777216.0f;          // 2^24: undoes the fp16 subnormal exponent
 constexpr int kHalfOutputBit = 1 << 30;        // in the kernels' M argument: y is fp16, not fp32
 constexpr int kOwnSetsBit = 1 << 29;           // in the kernels' M argument: every activation row keeps its own set
+constexpr int kGroup64Bit = 1 << 28;           // in the kernels' M argument: quantization groups of 64 columns, not 128
 constexpr int kRowsMask = (1 << 25) - 1;       // the bits of that argument that hold M (M <= 2^24)
 #ifdef SPQT_TEST_GIVE_UP
 // Test build (libspqt_giveup.so): the producers publish nothing and the reducer's wait is a handful of polls, so
@@ -186,7 +187,7 @@ __device__ __forceinline__ float sum_over_columns(float v) {
 
 // The one-launch kernel for one activation row: list built in the kernel, even shares (gemv_bal.hip).
 hipError_t launch_gemv_bal(int waves, int grid, hipStream_t stream, const uint8_t *packed, const uint16_t *x, float thr,
-                           float *y, void *partials, int32_t *ws_flags, int K, int NG, int S, int T, int m_and_flags);
+                           float *y, uint32_t *ws, int K, int S, int T, int m_and_flags);
 
 // The index-list and dense kernels (gemv_list.hip); idx == nullptr: dense.  one_group: passes of one quantization group.
 struct ListLaunch {
@@ -194,9 +195,8 @@ struct ListLaunch {
     const uint16_t *x;
     const int32_t *idx, *count;
     float *y;
-    void *partials;
-    int32_t *ws_flags;
-    int K, NG, S, T, m_and_flags;
+    uint32_t *ws;
+    int K, S, T, m_and_flags;
 };
 hipError_t launch_gemv_list(int waves, int batch, bool one_group, int grid, hipStream_t stream, const ListLaunch &a);
 
@@ -207,22 +207,50 @@ hipError_t launch_gemv_list(int waves, int batch, bool one_group, int grid, hipS
 // spread block-row's reducer may run before producers on another XCD are dispatched, which combine_block_row allows for.
 // Returns false for the padding of the grid (grid_blocks).
 __device__ __forceinline__ bool is_spread(int t, int T) { return t >= (T & ~7); }
-__device__ __forceinline__ bool block_of(int index, int S, int T, int &t, int &s) {
-    const int xcd = index & 7;
-    const int slot = index >> 3;               // position among this XCD's workgroups
-    const int whole = (T >> 3) * S;            // workgroups of whole block-rows per XCD
-    if (slot < whole) {
-        t = xcd + 8 * (slot / S);
-        s = slot % S;
-        return true;
-    }
-    const int left = (T & 7) * S;
-    const int per_xcd = (left + 7) >> 3;
-    const int r = xcd * per_xcd + slot - whole;
-    t = (T & ~7) + r / S;
-    s = r % S;
-    return slot - whole < per_xcd && r < left;
+// inv: inverse_of(S * WAVES).
+template <int WAVES>
+__device__ __forceinline__ bool block_of(uint32_t index, int S, int T, uint32_t inv, int &t, int &s) {
+    const uint32_t xcd = index & 7u;
+    const uint32_t slot = index >> 3;                                          // position among this XCD's workgroups
+    const uint32_t whole = ((uint32_t)T >> 3) * (uint32_t)S;                   // workgroups of whole block-rows per XCD
+    const uint32_t left = ((uint32_t)T & 7u) * (uint32_t)S;
+    const uint32_t per_xcd = (left + 7u) >> 3;
+    const bool in_whole = slot < whole;
+    const uint32_t r = in_whole ? slot : xcd * per_xcd + slot - whole;         // one division serves both
+    // r / S; r < 2^19 (M <= 2^24, S <= 64), so the rounded-up inverse gives it exactly: r * WAVES * (S * WAVES) < 2^32
+    const uint32_t q = WAVES == 1 ? r / (uint32_t)S : __umulhi(r * (uint32_t)WAVES, inv);
+    t = (int)(in_whole ? xcd + 8u * q : ((uint32_t)T & ~7u) + q);
+    s = (int)(r - q * (uint32_t)S);
+    return in_whole || (slot - whole < per_xcd && r < left);
 }
+
+// Part `part` of `parts` equal parts of n things: [floor(n * part / parts), floor(n * (part + 1) / parts)).  In 32-bit
+// arithmetic for every n <= 2^24 and parts <= 512: with n = q * parts + r a part starts at q * part + floor(r * part / parts).
+// The divisions are products with inv = inverse_of(parts), rounded up: exact for r * part < 2^18, and for n the quotient may be
+// one too large, which shows as a negative remainder.
+struct Share {
+    int begin, end;
+};
+template <int WAVES>
+__device__ __forceinline__ Share share_of(int n, int part, int parts, uint32_t inv) {
+    int q, r;
+    if (WAVES == 1) {              // parts may be 1, which has no 32-bit inverse
+        q = (int)((uint32_t)n / (uint32_t)parts);
+        r = n - q * parts;
+        return {q * part + (int)((uint32_t)(r * part) / (uint32_t)parts), q * (part + 1) + (int)((uint32_t)(r * (part + 1)) / (uint32_t)parts)};
+    }
+    q = (int)__umulhi((uint32_t)n, inv);
+    r = n - q * parts;
+    q -= r < 0 ? 1 : 0;
+    r += r < 0 ? parts : 0;
+    return {q * part + (int)__umulhi((uint32_t)(r * part), inv), q * (part + 1) + (int)__umulhi((uint32_t)(r * (part + 1)), inv)};
+}
+
+// The order of the kernels' arguments: what a wavefront needs before it can request anything comes first.  The first 14 dwords of
+// the arguments are in scalar registers when a wavefront starts (-amdgpu-kernarg-preload-count in the build), the rest is a
+// load away; with that, and products with an inverse from the host in place of five divisions before the first request, a
+// launch takes 0.2 to 0.5 us less (gather + GEMV where there is a list, us: 4096 x 4096 at 50 % 7.78 / 7.46, column blocks 8.11 / 7.60;
+// dense 5120 x 5120 7.32 / 6.94; one launch, 11008 x 4096 at 40 % 8.00 / 7.70).
 
 // Combine the S workgroups of block-row t (paper Section 4.2.2: the partial sums of the
 // threadgroups that share a superblock row are reduced once at the end, without atomics on y).
@@ -255,8 +283,8 @@ __device__ __forceinline__ uint32_t exchange_word(float v) {
     return w ? w : 1u;
 }
 template <int WAVES, int BATCH, int ROWS = kTileRows>
-__device__ __forceinline__ void combine_block_row(const float *red, int tid, int t, int s, int S, int T, void *partials,
-                                                  int32_t *ws_flags, float *__restrict__ y, int m_and_flags) {
+__device__ __forceinline__ void combine_block_row(const float *red, int tid, int t, int s, int S, int T, uint32_t *ws,
+                                                  float *__restrict__ y, int m_and_flags) {
     // One kernel argument carries both (M <= 2^24).
     const int M = m_and_flags & kRowsMask;
     const bool y_half = (m_and_flags & kHalfOutputBit) != 0;
@@ -269,11 +297,11 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, int
     // A thread that owns several units handles 2 of them together, so that the reducer's loads for
     // all of them are in flight at once (one round trip instead of one per unit).
     constexpr int kTogether = kPerThread < 2 ? kPerThread : 2;
-    Word *slots = reinterpret_cast<Word *>(partials) + (size_t)t * S * kUnits;    // [S][kUnits]; S - 1: handed over
+    Word *slots = reinterpret_cast<Word *>(ws + kWorkspaceHead / 4) + (size_t)t * S * kUnits;    // [S][kUnits]; S - 1: handed over
     const bool reducer = S > 1 && s == S - 1;
     const bool spread = is_spread(t, T) && !kMuteProducers;   // the build with silent producers is for give-ups only
     uint32_t poisoned = 0u;
-    if (reducer) poisoned = __hip_atomic_load(reinterpret_cast<uint32_t *>(ws_flags), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (reducer) poisoned = __hip_atomic_load(ws, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (int i0 = tid; i0 < kUnits; i0 += kTogether * kThreads) {
         uint32_t at[kTogether];
         float sum[kTogether][kVals];
@@ -389,7 +417,7 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, int
             if (S <= 5) collect(std::integral_constant<int, 4>{});
             else collect(std::integral_constant<int, 16>{});
             if (!handed_over) {
-                if (gave_up) __hip_atomic_store(reinterpret_cast<uint32_t *>(ws_flags), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (gave_up) __hip_atomic_store(ws, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const bool bad = gave_up || poisoned;
 #pragma unroll
                 for (int i = 0; i < kTogether; ++i)
@@ -417,7 +445,7 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, int
                 if (!all_here) continue;         // whoever publishes the missing word comes by here too
                 const Word own = __hip_atomic_exchange(from + (size_t)(S - 1) * kUnits, (Word)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (own == 0) continue;          // another thread does it
-                const uint32_t bad = __hip_atomic_load(reinterpret_cast<uint32_t *>(ws_flags), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const uint32_t bad = __hip_atomic_load(ws, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 float total[kVals];
 #pragma unroll
                 for (int q = 0; q < kVals; ++q) total[q] = 0.0f;

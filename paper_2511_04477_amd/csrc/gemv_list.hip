@@ -23,9 +23,8 @@ using namespace spqt;
 
 template <int WAVES, bool DENSE, int BATCH, int GROUPS>
 __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
-    const uint8_t *__restrict__ packed, const uint16_t *__restrict__ x, const int32_t *__restrict__ idx,
-    const int32_t *__restrict__ count, float *__restrict__ y, void *partials, int32_t *ws_flags, int K, int NG,
-    int S, int T, int M) {
+    int S, int T, int K, int M, uint32_t inv, const int32_t *__restrict__ count, const int32_t *__restrict__ idx,
+    const uint8_t *__restrict__ packed, const uint16_t *__restrict__ x, float *__restrict__ y, uint32_t *ws) {
     __shared__ __attribute__((aligned(16))) StagedX staged[WAVES];
     __shared__ __attribute__((aligned(16))) float red[WAVES][BATCH][kTileRows];
 
@@ -36,32 +35,25 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
     const int n = lane & 15;       // 16-row segment of the block-row this lane reads
     const uint32_t n8 = (uint32_t)n * 8u;
     const uint32_t out4 = (uint32_t)(4 * n + (lane >> 4));    // the lane's 4 outputs: rows 4 out4 .. 4 out4 + 3
+    const int n_raw = DENSE ? K : *count;      // requested first
     int t, s;
-    if (!block_of((int)blockIdx.x, S, T, t, s)) return;
+    if (!block_of<WAVES>(blockIdx.x, S, T, inv, t, s)) return;
 
     // (a count outside 0..K cannot come from spqt_gather; clamping keeps a corrupt one inside idx)
-    const int n_raw = DENSE ? K : __builtin_amdgcn_readfirstlane(*count);
     const int n_ns = n_raw < 0 ? 0 : (n_raw > K ? K : n_raw);
     SPQT_TL(1);
     const int parts = S * WAVES;
     const int part = s * WAVES + wave;
-    // even shares [n_ns * part / parts, n_ns * (part + 1) / parts); 32-bit arithmetic when the products fit
-    int pos, end;
-    if (n_ns < (1 << 23)) {
-        pos = (int)(((uint32_t)n_ns * (uint32_t)part) / (uint32_t)parts);
-        end = (int)(((uint32_t)n_ns * (uint32_t)(part + 1)) / (uint32_t)parts);
-    } else {
-        pos = (int)(((int64_t)n_ns * part) / parts);
-        end = (int)(((int64_t)n_ns * (part + 1)) / parts);
-    }
+    const Share share = share_of<WAVES>(n_ns, part, parts, inv);
+    const int pos = share.begin, end = share.end;
     // One activation row: a list of K entries holds every column once, so every pass takes columns 0, 1, 2, ... in its place
     // whatever order the list has.  The FIRST pass then does not wait for its entries, which takes a dependent memory
     // access off the start.
     const bool all_kept = DENSE || (BATCH == 1 && n_ns == K);
 
-    const int log2g = (NG << 7) == K ? 7 : 6;
+    const int log2g = M & kGroup64Bit ? 6 : 7;
     const uint32_t chunk_b = (uint32_t)(kScaleBytes + (kColBytes << log2g));
-    const uint8_t *row_base = packed + (size_t)t * NG * chunk_b;
+    const uint8_t *row_base = packed + (size_t)t * (size_t)(K >> log2g) * chunk_b;
 
     float acc[BATCH][4];   // rows 4 out4 + p of the block-row, scaled, in the products' units
 #pragma unroll
@@ -114,14 +106,14 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
                                                              acc[b][2] * kEvenUnit, acc[b][3] * kOddUnit};
     __syncthreads();
     SPQT_TL(5);
-    combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, t, s, S, T, partials, ws_flags, y, M);
+    combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, t, s, S, T, ws, y, M);
     SPQT_TL_END(WAVES, wave, lane, S > 1 && s == S - 1);
 }
 
 template <int WAVES, bool DENSE, int BATCH, int GROUPS>
 void start(int grid, hipStream_t stream, const ListLaunch &a) {
-    hipLaunchKernelGGL((spqt_gemv_list_kernel<WAVES, DENSE, BATCH, GROUPS>), dim3(grid), dim3(WAVES * 64), 0, stream, a.packed,
-                       a.x, a.idx, a.count, a.y, a.partials, a.ws_flags, a.K, a.NG, a.S, a.T, a.m_and_flags);
+    hipLaunchKernelGGL((spqt_gemv_list_kernel<WAVES, DENSE, BATCH, GROUPS>), dim3(grid), dim3(WAVES * 64), 0, stream, a.S, a.T, a.K, a.m_and_flags,
+                       inverse_of(a.S * WAVES), a.count, a.idx, a.packed, a.x, a.y, a.ws);
 }
 
 // Which kernels have workgroups of 8 wavefronts: an index list with one row, and 3 and 4 rows (the callers refuse the others).

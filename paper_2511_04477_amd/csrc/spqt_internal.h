@@ -20,12 +20,12 @@ inline int64_t tiles(int64_t M) { return (M + kTileRows - 1) / kTileRows; }
 
 // Bytes reserved at the head of the workspace: word 0 is the poison flag the reducers raise when a
 // wait for partial sums is abandoned; the rest keeps the exchange words 256-byte aligned.
-inline size_t counter_bytes(int64_t) { return 256; }
+constexpr int kWorkspaceHead = 256;
 
 // Bytes asked for where a launch with S workgroups per block-row brings just its exchange words (8 bytes for each of the
 // `rows` outputs per block-row and activation row; the words are 32-bit, so half of it stays unused), head included.
 inline size_t exchange_bytes(int64_t n_tiles, int rows, int S, int batch) {
-    return 256 + (size_t)n_tiles * (size_t)rows * (size_t)S * (size_t)batch * 8;
+    return kWorkspaceHead + (size_t)n_tiles * (size_t)rows * (size_t)S * (size_t)batch * 8;
 }
 
 // Bytes of one chunk (block-row t, group g) of the group layout: 256 fp16 scales + `group` column runs.
@@ -37,6 +37,9 @@ inline int check_shape(int64_t M, int64_t K, int group) {
     if (M > (int64_t)1 << 24 || K > (int64_t)1 << 24) return SPQT_ESHAPE;
     return SPQT_OK;
 }
+
+// ceil(2^32 / n): what the kernels divide by n with (n >= 2; 0 for n = 1, which they do not use).
+inline uint32_t inverse_of(int n) { return (uint32_t)((((uint64_t)1 << 32) + (uint32_t)n - 1) / (uint32_t)n); }
 
 // Workgroups in the grid of a group-layout launch (block_of in gemv_common.hpp says which is which).
 inline int grid_blocks(int64_t T, int S) { return 8 * (int)((T / 8) * S + ((T % 8) * S + 7) / 8); }
