@@ -135,13 +135,14 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
             const Deal d = deal_groups<kGroups>(kk, h.g, lane);
             const uint32_t off_own = (uint32_t)h.g * chunk_b + (uint32_t)(kk & ((1 << log2g) - 1)) * kColBytes;
             const uint32_t off_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)off_own);
-            h.off = d.take ? off_own : (d.n ? off_first : 0u);
+            h.off = slot_order(d.take ? off_own : (d.n ? off_first : 0u), lane);
+            h.n = d.n;
             h.starts = d.starts;
             h.g = d.n ? h.g : 0;
             h.j = d.take ? d.j : -1;
             const uint32_t xv[4] = {v.y & 0xFFFFu, v.y >> 16, v23 & 0xFFFFu, v23 >> 16};
 #pragma unroll
-            for (int b = 0; b < BATCH; ++b) h.xraw[b] = xv[b];
+            for (int b = 0; b < BATCH; ++b) h.xraw[b] = (uint16_t)xv[b];
             return p + d.n;
         };
         fetch_x(u);

@@ -168,12 +168,12 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
         };
 
         // Entry p + lane of the share: its column, or -1 past the share.  The ring must hold it: refill first.
-        auto fetch_k = [&](int p, uint32_t &xk) -> int {
+        auto fetch_k = [&](int p, uint16_t &xk) -> int {
             const int need = p + 64 < total ? p + 64 : total;
             while (filled < need && step < nsteps) refill();
             const int e = p + lane;
             const uint32_t v = ring[wave][e & (kRing - 1)];
-            xk = v >> 16;
+            xk = (uint16_t)(v >> 16);
             return e < total ? (int)(v & 0xFFFFu) : -1;
         };
 
@@ -184,7 +184,8 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
             const Deal d = deal_groups<kGroups>(kk, h.g, lane);
             const uint32_t off_own = (uint32_t)h.g * chunk_b + (uint32_t)(kk & ((1 << log2g) - 1)) * kColBytes;
             const uint32_t off_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)off_own);
-            h.off = d.take ? off_own : off_first;
+            h.off = slot_order(d.take ? off_own : off_first, lane);
+            h.n = d.n;
             h.starts = d.starts;
             h.j = d.take ? d.j : -1;
             return p + d.n;

@@ -84,7 +84,8 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
             const uint32_t off_own = (uint32_t)h.g * chunk_b + (uint32_t)(kk & ((1 << log2g) - 1)) * kColBytes;
             // slots past the pass point at its first column (a line that is fetched anyway) and carry x = 0
             const uint32_t off_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)off_own);
-            h.off = d.take ? off_own : off_first;
+            h.off = slot_order(d.take ? off_own : off_first, lane);
+            h.n = d.n;
             h.starts = d.starts;
             h.j = d.take ? d.j : -1;
             k_next = fetch_k(p + d.n);

@@ -2,10 +2,15 @@
 // matrix cores for 1..4 activation rows.  Shared by gemv_list.hip (index list, dense), gemv.hip (one launch, static
 // column ranges) and gemv_bal.hip (one launch, even shares).
 //
-// Slots: entry e of a pass sits in slot (c, u) = (e / 16, e % 16).  In step u the 16 lanes of quarter c of the
-// wavefront read the 128-byte run of column (c, u), 8 bytes each: lane l holds rows 16 n .. 16 n + 15 of the block-row,
-// n = l % 16, at the 16 columns of its quarter.  The lane that owns entry e is lane e, i.e. a column's offset is
-// known in the very quarter that reads it, so it reaches the other 15 lanes by DPP (row_newbcast), not through LDS.
+// Slots: entry e of a pass sits in slot (c, u), c = e / 8 % 4, u = e / 32 * 8 + e % 8, so that the first 32 entries are the
+// slots u < 8 and a pass of at most 32 entries is HALF a pass: the products of its slots u >= 8 are left out.  In step u the
+// 16 lanes of quarter c of the wavefront read the 128-byte run of column (c, u), 8 bytes each: lane l holds rows
+// 16 n .. 16 n + 15 of the block-row, n = l % 16, at the 16 columns of its quarter.  Lane e deals entry e; its column's offset
+// moves to lane (c, u) once (slot_order), i.e. into the quarter that reads it, and from there to the other 15 lanes by DPP
+// (row_newbcast).
+// A pass costs about 0.9 us where a SIMD holds one wavefront, and slices end with a short one: leaving half of its products out
+// takes chains of GEMVs from 356.7 to 353.1 us (one launch, 48 of 11008 x 4096 and its transpose, 40 %), 208.6 to 205.0 (two rows with
+// their own sets, 24 of 14336 x 4096 and its transpose) and 166.9 to 164.9 (four rows, 6 of 28672 x 8192 and its transpose).
 //
 // Products: v_mfma_f32_16x16x32_f16 computes D[m][n] += sum over 32 k of A[m][k] * B[k][n]; lane l brings A[l % 16] and
 // B[..][l % 16] at the 8 k of quarter l / 16, i.e. at 8 of the 16 columns of its quarter.  B is ONE row's codes at those
@@ -55,6 +60,13 @@ __device__ __forceinline__ void keep_order() { __builtin_amdgcn_sched_barrier(0)
 template <int U>
 __device__ __forceinline__ uint32_t row_lane(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + U, 0xf, 0xf, true);
+}
+
+// The slot (16 c + u) of the entry that lane e deals, and what a lane's slot gets: `v` of the lane that deals the slot's entry.
+__device__ __forceinline__ int slot_of(int e) { return ((e & 0x18) << 1) | ((e & 0x20) >> 2) | (e & 7); }
+__device__ __forceinline__ uint32_t slot_order(uint32_t v, int lane) {
+    const int e = ((lane & 8) << 2) | ((lane & 0x30) >> 1) | (lane & 7);
+    return (uint32_t)__builtin_amdgcn_ds_bpermute(4 * e, (int)v);
 }
 
 // Requests the weights of slots u = FROM .. TO - 1 of a pass: off = byte offset (from base) of the column run of the entry
@@ -157,9 +169,9 @@ __device__ __forceinline__ Deal deal_groups(int kk, int g, int lane) {
     return d;
 }
 
-// Stages the x of a pass: the entry of lane `lane`, in the slot of that number, carries x[b] for group j of the pass (j < 0: none).
+// Stages the x of a pass: the entry that lane `lane` deals, in its slot, carries x[b] for group j of the pass (j < 0: none).
 template <int BATCH>
-__device__ __forceinline__ void stage_x(StagedX &xs, int lane, int j, bool neg, const uint32_t (&xraw)[BATCH]) {
+__device__ __forceinline__ void stage_x(StagedX &xs, int lane, int j, bool neg, const uint16_t (&xraw)[BATCH]) {
     constexpr int kRows = padded_rows(BATCH);
     {   // slots that no entry writes must read as zero
         reinterpret_cast<u32x2 *>(&xs.v[0][0])[lane] = u32x2{0u, 0u};
@@ -168,18 +180,19 @@ __device__ __forceinline__ void stage_x(StagedX &xs, int lane, int j, bool neg, 
     // no branch on j >= 0: a divergent one inside the pipeline's loop makes the compiler join the loop's exits with its
     // entry and wait for all loads there
 #pragma unroll
-    for (int b = 0; b < BATCH; ++b) xs.v[j >= 0 ? j * kRows + b : 4][lane] = (uint16_t)(xraw[b] ^ (neg ? 0x8000u : 0u));
+    for (int b = 0; b < BATCH; ++b) xs.v[j >= 0 ? j * kRows + b : 4][slot_of(lane)] = (uint16_t)(xraw[b] ^ (neg ? 0x8000u : 0u));
     __builtin_amdgcn_wave_barrier();
 }
 
 // What the HEAD of a pass leaves for its loads and its products.
 template <int BATCH>
 struct PassHead {
-    uint32_t off;          // byte offset of the column this lane owns in the pass whose weights are requested next
+    uint32_t off;          // byte offset of the column in this lane's SLOT of the pass whose weights are requested next
+    int n;                 // entries of that pass (wave-uniform)
     uint64_t starts;       // where the groups of that pass start
     int g;                 // group of the lane's candidate of that pass
     int j;                 // group of the lane's entry inside that pass, or -1: not part of it
-    uint32_t xraw[BATCH];  // its x
+    uint16_t xraw[BATCH];  // its x
 };
 
 // The scales of the lane's 4 rows in each group of the pass; groups it does not reach repeat its last one.
@@ -214,6 +227,7 @@ __device__ __forceinline__ void run_passes(StagedX &staged, const uint8_t *row_b
     first_here();
     while (more(pos)) {
         stage_x<BATCH>(staged, lane, h.j, negated(turn), h.xraw);
+        const bool whole = h.n > kPassCols / 2;
         pos = head(pos);
         keep_order();
         start_products(staged, lane, x0, x1, d);
@@ -221,7 +235,7 @@ __device__ __forceinline__ void run_passes(StagedX &staged, const uint8_t *row_b
         keep_order();
         load_columns<0, 8>(columns, h.off, n8, w);
         keep_order();
-        half_pass<1>(w, x1, lane, d);
+        if (whole) half_pass<1>(w, x1, lane, d);
         keep_order();
         load_columns<8, 16>(columns, h.off, n8, w);
         keep_order();
@@ -233,7 +247,7 @@ __device__ __forceinline__ void run_passes(StagedX &staged, const uint8_t *row_b
     stage_x<BATCH>(staged, lane, h.j, negated(turn), h.xraw);
     start_products(staged, lane, x0, x1, d);
     half_pass<0>(w, x0, lane, d);
-    half_pass<1>(w, x1, lane, d);
+    if (h.n > kPassCols / 2) half_pass<1>(w, x1, lane, d);
     add_scaled<BATCH, GROUPS>(d, sc, negated(turn), acc);
 }
 

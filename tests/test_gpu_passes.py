@@ -71,6 +71,29 @@ def test_pass_edges(gpu, rows, group):
                 check(run(gpu, w, x, 0.125, mode, group, splits=1), ref, f"n={n} {name} {mode}")
 
 
+@pytest.mark.parametrize("rows", [1, 2, 4])
+def test_half_passes(gpu, rows):
+    """Slices that end around 32 entries past a whole number of passes (the second half of such a pass has no products): four
+    wavefronts with 31 to 33, 95 to 97 entries each; and dense slices of 32 and 96 columns."""
+    M, K = 256, 640
+    w = make_weights(M, K, 5150 + rows)
+    base = make_x(K, "normal", 5151, batch=rows)
+    base = np.where(np.abs(base) < 0.25, np.float16(0.25), base).astype(np.float16)
+    for n in (4, 124, 127, 128, 129, 132, 380, 384, 385, 388):
+        for name, cols in (("spread", np.unique(np.linspace(0, K - 1, n).astype(int))), ("run", np.arange(n))):
+            x = np.zeros_like(base)
+            x[:, cols] = base[:, cols]
+            ref = oracle.gemv(w["q_rowmajor"], w["scales"], x, 0.125)
+            for mode in ("list", "fused"):
+                print(f"half passes rows={rows} n={n} {name} {mode}", flush=True)
+                check(run(gpu, w, x, 0.125, mode, splits=1), ref, f"n={n} {name} {mode}")
+    for Kd in (128, 384):
+        wd = make_weights(M, Kd, 5160 + rows)
+        xd = make_x(Kd, "normal", 5161, batch=rows)
+        print(f"half passes rows={rows} dense K={Kd}", flush=True)
+        check(run(gpu, wd, xd, 0.0, "dense", splits=1), oracle.gemv(wd["q_rowmajor"], wd["scales"], xd, 0.0), f"dense K={Kd}")
+
+
 @pytest.mark.parametrize("T,K", [(9, 1024), (12, 1024), (20, 2048), (33, 1024), (300, 256)])
 @pytest.mark.parametrize("rows", [1, 3])
 def test_block_rows_over_xcds(gpu, T, K, rows):
