@@ -3,9 +3,9 @@
 //
 // Paper Section 2: a column is sparse iff |x_i| < threshold; Section 4.2.2 (zigzag kernel): one block-row = 256 outputs is
 // shared by n1 threadgroups x n2 simdgroups that keep partial sums locally and combine them once.  Instead of reading an
-// index list, the kernel tests x itself: the slice of a wavefront is a static range of 64-column units (K/64 units split
-// evenly over the S*WAVES wavefronts of the block-row).  A wavefront compacts its range, kRefill units at a time and only
-// as its passes need them, into a ring of (column, x) entries in LDS - lane l tests column 64u + l, a ballot gives the kept
+// index list, the kernel tests x itself: the slice of a wavefront is a static range of columns (K split evenly over the S*WAVES
+// wavefronts of the block-row, to the column).  A wavefront compacts its range, kRefill units of 64 columns at a time and only
+// as its passes need them, into a ring of (column, x) entries in LDS - lane l tests the unit's column l, a ballot gives the kept
 // set, mbcnt the rank - and takes its passes (pass.hpp) from the ring exactly as gemv_list.hip takes them from idx.
 //
 // Why a ring: with one pass per 64-column unit a pass is as full as the unit (38 of 64 slots at 40 % sparsity), and
@@ -50,15 +50,17 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
     int t, s;
     if (!block_of<WAVES>(blockIdx.x, S, T, inv, t, s)) return;
 
-    // Positions: a unit, or SPREAD units that lie `apart` from each other; a refill takes kStep positions, unit i of it is
-    // u + i % kStep + i / kStep * apart.
+    // Positions are columns of one part of K; SPREAD columns that lie `apart` from each other share one.  A refill takes kStep
+    // units of each part, and unit_at(u, i) is the first column of unit i of the refill at position u.
     constexpr int kStep = kRefill / SPREAD;
-    const int positions = K / kPassCols / SPREAD, apart = positions;
+    const int apart = K / SPREAD;
+    auto unit_at = [&](int at, int i) { return at + i % kStep * kPassCols + i / kStep * apart; };
     const int parts = S * WAVES;
     const int part = s * WAVES + wave;
-    const Share share = share_of<WAVES>(positions, part, parts, inv);
-    int u = share.begin;
-    const int end = share.end;
+    constexpr int kQuantum = COMPACT ? 1 : kPassCols;    // the ablation's passes are whole units, so its slices are too
+    const Share share = share_of<WAVES>(apart / kQuantum, part, parts, inv);
+    int u = share.begin * kQuantum;
+    const int end = share.end * kQuantum;
     SPQT_TL(1);
 
     // quantization groups of 128 or 64 columns
@@ -83,7 +85,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
         auto fetch_x = [&](int at) {
 #pragma unroll
             for (int i = 0; i < kRefill; ++i) {
-                const int c = (at + i % kStep + i / kStep * apart) * kPassCols + lane;
+                const int c = unit_at(at, i) + lane;
 #pragma unroll
                 for (int b = 0; b < BATCH; ++b)
                     xr[i][b] = __hip_atomic_load(x + (size_t)b * K + (c < K ? c : K - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
@@ -99,7 +101,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
                 bool keep = false;
 #pragma unroll
                 for (int b = 0; b < BATCH; ++b) {
-                    kb[b] = u + i % kStep < end && !(__builtin_fabsf(half_bits_to_float(xr[i][b])) < thr);
+                    kb[b] = u + i % kStep * kPassCols + lane < end && !(__builtin_fabsf(half_bits_to_float(xr[i][b])) < thr);
                     keep = keep || kb[b];
                 }
                 const uint64_t mask = __ballot(keep);
@@ -111,12 +113,12 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
                 const int first = mask ? (int)__builtin_ctzll(mask) : 0;
                 const bool enter = COMPACT ? keep : mask != 0ull;
                 const int at = enter ? ((filled + (COMPACT ? rank : lane)) & (kRing - 1)) : kRing + lane;
-                ring[wave][at] = u32x2{(uint32_t)((u + i % kStep + i / kStep * apart) * kPassCols + (keep ? lane : first)), xb[0] | (xb[1] << 16)};
+                ring[wave][at] = u32x2{(uint32_t)(unit_at(u, i) + (keep ? lane : first)), xb[0] | (xb[1] << 16)};
                 if (BATCH > 2) ring23[wave][at] = xb[2] | (xb[3] << 16);
                 filled += COMPACT ? (int)__popcll(mask) : (mask ? kPassCols : 0);
             }
             filled = __builtin_amdgcn_readfirstlane(filled);
-            u += kStep;
+            u += kStep * kPassCols;
             __builtin_amdgcn_wave_barrier();
         };
 
@@ -179,7 +181,7 @@ void start_fused(int grid, hipStream_t stream, const uint8_t *packed, const uint
 // In how many parts of K a slice of the one-row kernel lies, with `parts` slices.  With one range per slice, activations whose kept
 // columns crowd into one part of K leave the other wavefronts idle for as long as the crowded slices have passes.  28672 x 8192 at 50 %, 7 of 8
 // kept columns in the first half, one range / four 22.9 / 15.8 us; evenly kept columns 17.6 / 17.4; 14336 x 14336, two ranges, 21.0 / 15.3 and
-// 15.6 / 15.6.  Only where no slice gets longer by it (14336 x 14336 in four parts: 16 units instead of 14) and from 5 units per slice on: shorter
+// 15.6 / 15.6.  Only where no slice gets more units to compact by it (14336 x 14336 in four parts: 16 instead of 14) and from 5 units per slice on: shorter
 // slices are a pass or two either way.
 inline int spread_of(int units, int parts) {
     if (units < 5 * parts) return 1;

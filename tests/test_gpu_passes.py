@@ -94,6 +94,18 @@ def test_half_passes(gpu, rows):
         check(run(gpu, wd, xd, 0.0, "dense", splits=1), oracle.gemv(wd["q_rowmajor"], wd["scales"], xd, 0.0), f"dense K={Kd}")
 
 
+@pytest.mark.parametrize("rows", [1, 2, 4])
+@pytest.mark.parametrize("K,splits", [(128, 1), (384, 2), (640, 3), (1152, 5), (2944, 1)])
+def test_one_launch_slices_of_any_column(gpu, rows, K, splits):
+    """One launch: the slices are columns, not whole units of 64, so they begin and end anywhere inside a unit and a group."""
+    w = make_weights(256, K, 5170 + K)
+    x = make_x(K, "laplace", 5171 + K, batch=rows)
+    for sparsity in (0.0, 0.5, 0.98):
+        thr = quantile_threshold(x, sparsity) if sparsity else 0.0
+        print(f"any column rows={rows} K={K} splits={splits} sparsity={sparsity}", flush=True)
+        check(run(gpu, w, x, thr, "fused", splits=splits), oracle.gemv(w["q_rowmajor"], w["scales"], x, thr), f"K={K} sparsity={sparsity}")
+
+
 @pytest.mark.parametrize("T,K", [(9, 1024), (12, 1024), (20, 2048), (33, 1024), (300, 256)])
 @pytest.mark.parametrize("rows", [1, 3])
 def test_block_rows_over_xcds(gpu, T, K, rows):
