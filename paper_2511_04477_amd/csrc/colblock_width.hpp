@@ -7,11 +7,11 @@
 // list entries per pass; the height of a block-row follows from the width (128 bytes of codes).
 // Everything else follows spqt_cb_gemv_kernel: even split of the index list over the S x WAVES
 // wavefronts of a block-row (Section 4.2.3), the scales folded into x by the lane that owns the list
-// entry, two-stage software pipeline with unpredicated clamped loads, one fold of the 8 column-lanes at
+// entry, one buffer of weights refilled half by half with unpredicated clamped loads, one fold of the 8 column-lanes at
 // the end, reduction through LDS and the workspace.  Three modes: list-driven, dense (every
 // column, no list), and ONE-LAUNCH (FUSED, one activation row): the kernel applies the sparsity test of
-// Section 2 itself on static 64-column units - lane l tests column 64 u + l, a ballot gives the kept set,
-// mbcnt the rank, and the kept columns are staged in rank order - so no index list exists.
+// Section 2 itself on static column ranges and takes its entries from a ring of kept columns in LDS (kept_ring.hpp), so
+// no index list exists.
 // BATCH activation rows (Section 3.3: small beams) share the union index list and ONE pass over the
 // weights; every row has its own staged products, accumulators and offset sums.
 //
@@ -27,7 +27,7 @@
 #ifndef SPQT_COLBLOCK_WIDTH_HPP
 #define SPQT_COLBLOCK_WIDTH_HPP
 
-#include "gemv_common.hpp"
+#include "kept_ring.hpp"
 
 namespace spqt {
 
@@ -39,6 +39,7 @@ __device__ __forceinline__ void colblock_width_gemv(int S, int T, int K, int M, 
     static_assert(!FUSED || BATCH == 1, "the one-launch mode takes one activation row");
     __shared__ __attribute__((aligned(16))) float stage_xs[WAVES][BATCH][kPassCols][F::kBlocks];   // x * scale per block
     __shared__ __attribute__((aligned(16))) float red[WAVES][BATCH][F::kRows];
+    __shared__ u32x2 ring_slots[FUSED ? WAVES : 1][FUSED ? kRingSlots : 1];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -47,8 +48,8 @@ __device__ __forceinline__ void colblock_width_gemv(int S, int T, int K, int M, 
     const int seg = lane & 7;      // eighth of the block-row this lane reads
     const int cgr = ((cg & 1) << 2) | (cg & 2) | (cg >> 2);
     const uint32_t seg16 = (uint32_t)seg * 16u;
-    // what is split evenly: the kept-column list, all columns, or (one launch) the 64-column units
-    const int n_raw = FUSED ? K / kPassCols : (DENSE ? K : *count);     // requested first
+    // what is split evenly: the kept-column list, or (dense, one launch) all columns
+    const int n_raw = FUSED || DENSE ? K : *count;     // requested first
     int t, s;
     if (!block_of<WAVES>(blockIdx.x, S, T, inv, t, s)) return;
 
@@ -71,142 +72,100 @@ __device__ __forceinline__ void colblock_width_gemv(int S, int T, int K, int M, 
     }
 
     if (pos < end) {
-        // The weights of the 64 staged columns: 8 loads of 8 columns each.
-        auto load_weights = [&](u32x4(&w)[8]) {
-            uint32_t off[8];
+        KeptRing ring(ring_slots[FUSED ? wave : 0], x, K, pos, end, thr, lane);
+        // atomic loads (the same instructions): plain ones the compiler moves behind the weights, to their use
+        auto fetch_k = [&](int p) -> int {
+            const int e = p + lane;
+            if (DENSE) return e < end ? e : 0;
+            return __hip_atomic_load(idx + (e < end ? e : end - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        };
+        // One buffer of weights, refilled half by half as a pass is multiplied: when the products of steps u < 4 are done, their
+        // registers receive the same steps of the next pass, whose HEAD has run before the products.  Only the last pass of a
+        // list has fewer than 64 entries, so only behind the loop are steps left out.  (Two buffers with steps left out in every
+        // pass: 30 registers more, and as the compiler cannot know which loads such steps left in flight it waited for all loads
+        // at every other pass.  Before, list at 50 % / dense: 8-bit 4096 x 14336 10.2 / 14.1 us, now 9.5 / 13.3; 28672 x 8192 24.2 / 40.3, now
+        // 23.5 / 39.8; 2-bit 4096 x 14336 9.8 / 12.9, now 8.7 / 11.4; 28672 x 8192 15.9 / 22.8, now 14.4 / 21.3.)
+        u32x4 w[8];
+        typename F::Scales sv;                  // raw scales and x of the entry this lane owns, of the pass whose products come next
+        uint32_t xr[BATCH], off[8];        // off: byte offsets of the columns this lane reads
+        int n, k_next = 0;                 // entries of that pass (wave-uniform); the lane's entry of the one after it
+
+        // HEAD of the pass at list position p: request the entries of the pass after it, this pass's x and scales, and deal the
+        // offsets of its columns.  Lanes past the pass point at its first column and carry x = 0.  Returns where the next pass starts.
+        auto head = [&](int p) -> int {
+            int kk = k_next;
+            uint32_t kept_x = 0u;
+            if constexpr (FUSED) {
+                const u32x2 kept = ring.take(p, n);
+                kk = (int)kept.x;
+                kept_x = kept.y;
+            } else {
+                n = end - p < kPassCols ? end - p : kPassCols;
+                k_next = fetch_k(p + kPassCols);
+            }
+            const int k_first = n ? __builtin_amdgcn_readfirstlane(kk) : 0;
+            const int kc = lane < n ? kk : k_first;
+            const uint32_t chunk_off = (uint32_t)(kc >> 7) * (uint32_t)F::kChunkBytes;
+            const uint32_t col = (uint32_t)(kc & (kGroup - 1));
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b) xr[b] = FUSED ? kept_x : (uint32_t)x[(size_t)b * K + kc];
+            sv = F::load_scales(row_base + (size_t)(chunk_off + col * (uint32_t)(2 * F::kBlocks)));
+            stage_off[wave][lane] = chunk_off + (uint32_t)F::kScaleBytes + col * (uint32_t)kColBytes;
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int u = 0; u < 8; ++u) off[u] = stage_off[wave][u * 8 + cg] + seg16;
+            __builtin_amdgcn_wave_barrier();
+            return p + n;
+        };
+        auto load_half = [&](int half) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
+            for (int u = 4 * half; u < 4 * half + 4; ++u)
                 w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(row_base + (size_t)off[u]));
         };
-        // MULTIPLY stage: the lane that owns entry `ent` stages the products x * s_b of its column
-        // (xf = 0 for a filler entry); every lane then reads the products of its own block(s).
-        auto multiply = [&](int n, const float(&xf)[BATCH], int ent, typename F::Scales sv, const u32x4(&w)[8]) {
+        // The lane that owns an entry stages the products x * s_b of its column; a step (8 columns) takes those of the lane's block(s).
+        auto stage = [&]() {
+            if (FUSED && lane >= n) sv = typename F::Scales{};     // an empty pass points at column 0, which may be dropped
 #pragma unroll
-            for (int b = 0; b < BATCH; ++b) F::stage(xf[b], sv, stage_xs[wave][b][ent]);
-            __builtin_amdgcn_wave_barrier();
-            if (BATCH == 1) {
-                typename F::Mine xl[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) xl[u] = F::read_mine(stage_xs[wave][0][u * 8 + cg], seg);
-                F::step(w[0], xl[0], acc[0], bs[0]);
-#pragma unroll
-                for (int u = 1; u < 8; ++u)
-                    if (u * 8 < n) F::step(w[u], xl[u], acc[0], bs[0]);
-            } else {
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (u == 0 || u * 8 < n) {
-#pragma unroll
-                        for (int b = 0; b < BATCH; ++b)
-                            F::step(w[u], F::read_mine(stage_xs[wave][b][u * 8 + cg], seg), acc[b], bs[b]);
-                    }
-            }
+            for (int b = 0; b < BATCH; ++b) F::stage(lane < n ? half_bits_to_float(xr[b]) : 0.0f, sv, stage_xs[wave][b][lane]);
             __builtin_amdgcn_wave_barrier();
         };
-
-        u32x4 wA[8], wB[8];
-        typename F::Scales svA, svB;
-        int nA, nB;
+        auto step = [&](int u) {
+            if (BATCH * F::kAcc > 64) keep_order();     // x of several steps at once would not fit the registers
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b) F::step(w[u], F::read_mine(stage_xs[wave][b][u * 8 + cg], seg), acc[b], bs[b]);
+        };
         if (FUSED) {
-            // FETCH stage of unit u (xr = this lane's x[64 u + lane], requested one stage earlier):
-            // threshold, rank, stage the offsets, request the next unit's x, this unit's scales (every
-            // lane its own column's) and weights.  Kept columns go to entries 0..n-1 in ascending order;
-            // the other lanes fill entries n..63 with the unit's first kept column and x = 0.
-            auto fetch_unit = [&](uint32_t xr, int u, u32x4(&w)[8], int &n_out, float(&xf_out)[BATCH], int &ent_out,
-                                  typename F::Scales &sv_out, uint32_t &xr_next) {
-                const bool any = u < end;
-                const float xv = half_bits_to_float(xr);
-                const bool keep = any && !(__builtin_fabsf(xv) < thr);
-                const uint64_t mask = __ballot(keep);
-                const int n = __builtin_amdgcn_readfirstlane((int)__popcll(mask));
-                const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                {
-                    const int c = (u + 1) * kPassCols + lane;
-                    xr_next = __hip_atomic_load(x + (c < K ? c : K - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-                }
-                const int uu = any ? u : 0;
-                const uint32_t chunk_off = (uint32_t)(uu >> 1) * (uint32_t)F::kChunkBytes;
-                const uint32_t col_own = (uint32_t)((uu & 1) * kPassCols + lane);
-                const uint32_t col_first = (uint32_t)((uu & 1) * kPassCols + (n ? (int)__builtin_ctzll(mask) : 0));
-                sv_out = F::load_scales(row_base + (size_t)(chunk_off + col_own * (uint32_t)(2 * F::kBlocks)));
-                const int entry = keep ? rank : n + lane - rank;
-                stage_off[wave][entry] = chunk_off + (uint32_t)F::kScaleBytes + (keep ? col_own : col_first) * 128u;
-                __builtin_amdgcn_wave_barrier();
-                load_weights(w);
-                n_out = n;
-                xf_out[0] = keep ? xv : 0.0f;
-                ent_out = entry;
-            };
-            float xfA[BATCH], xfB[BATCH];
-            int entA, entB;
-            uint32_t xa = x[pos * kPassCols + lane], xb;
-            fetch_unit(xa, pos, wA, nA, xfA, entA, svA, xb);
-            for (;;) {
-                const int uB = pos + 1;
-                fetch_unit(xb, uB, wB, nB, xfB, entB, svB, xa);
-                if (nA > 0) multiply(nA, xfA, entA, svA, wA);
-                if (uB >= end) break;
-                const int uA = uB + 1;
-                fetch_unit(xa, uA, wA, nA, xfA, entA, svA, xb);
-                if (nB > 0) multiply(nB, xfB, entB, svB, wB);
-                if (uA >= end) break;
-                pos = uA;
-            }
+            ring.fetch();
+            pos = 0;                 // from here on a position among the kept columns of the slice
         } else {
-            // atomic loads (the same instructions): plain ones the compiler moves behind the weights, to their use
-            auto fetch_k = [&](int p) -> int {
-                const int e = p + lane;
-                if (DENSE) return e < end ? e : 0;
-                return __hip_atomic_load(idx + (e < end ? e : end - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-            };
-            // FETCH stage of the pass at list position p: the next pass's entries, this pass's x, scales
-            // and weights.  Lanes past the pass point at its first column and later carry x = 0.
-            auto fetch = [&](int kk, int p, u32x4(&w)[8], int &n_out, uint32_t(&xraw_out)[BATCH], typename F::Scales &sv_out,
-                             int &k_after) {
-                const int left = end - p;
-                const int n = left < 0 ? 0 : (left < kPassCols ? left : kPassCols);
-                k_after = fetch_k(p + kPassCols);
-                const int k_first = n ? __builtin_amdgcn_readfirstlane(kk) : 0;
-                const int kc = lane < n ? kk : k_first;
-                const uint32_t chunk_off = (uint32_t)(kc >> 7) * (uint32_t)F::kChunkBytes;
-                const uint32_t col = (uint32_t)(kc & (kGroup - 1));
-#pragma unroll
-                for (int b = 0; b < BATCH; ++b) xraw_out[b] = x[(size_t)b * K + kc];
-                sv_out = F::load_scales(row_base + (size_t)(chunk_off + col * (uint32_t)(2 * F::kBlocks)));
-                stage_off[wave][lane] = chunk_off + (uint32_t)F::kScaleBytes + col * 128u;
-                __builtin_amdgcn_wave_barrier();
-                load_weights(w);
-                n_out = n;
-            };
-            auto multiply_list = [&](int n, const uint32_t(&xraw)[BATCH], typename F::Scales sv, const u32x4(&w)[8]) {
-                float xf[BATCH];
-#pragma unroll
-                for (int b = 0; b < BATCH; ++b) xf[b] = lane < n ? half_bits_to_float(xraw[b]) : 0.0f;
-                multiply(n, xf, lane, sv, w);
-            };
-            uint32_t xrA[BATCH], xrB[BATCH];
-            int kA, kB;
-            kA = fetch_k(pos);
-            fetch(kA, pos, wA, nA, xrA, svA, kB);
-            if (pos + nA >= end) {
-                multiply_list(nA, xrA, svA, wA);      // the whole slice is one pass
-            } else {
-                for (;;) {
-                    const int posB = pos + nA;
-                    fetch(kB, posB, wB, nB, xrB, svB, kA);
-                    multiply_list(nA, xrA, svA, wA);
-                    if (posB >= end) break;
-                    const int posA = posB + nB;
-                    fetch(kA, posA, wA, nA, xrA, svA, kB);
-                    multiply_list(nB, xrB, svB, wB);
-                    if (posA >= end) break;
-                    pos = posA;
-                }
-            }
+            k_next = fetch_k(pos);
         }
+        auto more = [&](int p) { return FUSED ? ring.more(p) : p < end; };
+        pos = head(pos);
+        load_half(0);
+        load_half(1);
+        while (more(pos)) {
+            stage();
+            const bool whole = !FUSED || n > kPassCols / 2;
+            pos = head(pos);
+            keep_order();
+#pragma unroll
+            for (int u = 0; u < 4; ++u) step(u);
+            keep_order();
+            load_half(0);
+            keep_order();
+            if (whole) {
+#pragma unroll
+                for (int u = 4; u < 8; ++u) step(u);
+            }
+            keep_order();
+            load_half(1);
+            keep_order();
+        }
+        stage();
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (u * 8 < n) step(u);
     }
 
 #pragma unroll

@@ -19,12 +19,12 @@
 //   - the 32 accumulators run through the whole slice; the 8 column-lanes are folded once at
 //     the end, and the offset-binary bias (stored = q + 8) is removed there as -8 * (sum of
 //     x * s of the lane's block over the slice).
-//   - two-stage software pipeline, unpredicated clamped loads, reduction through LDS and the
+//   - one buffer of weights refilled half by half, unpredicated clamped loads, reduction through LDS and the
 //     workspace exactly as in gemv_list.hip.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "gemv_common.hpp"
+#include "kept_ring.hpp"
 #include "spqt_colblock.h"
 
 namespace {
@@ -36,9 +36,8 @@ constexpr int kCbChunkBytes = SPQT_CB_CHUNK_BYTES;
 static_assert(kCbChunkBytes == kCbScaleBytes + kGroup * kColBytes, "chunk size");
 
 // FUSED: the kernel applies the sparsity test itself instead of reading an index list (as
-// spqt_gemv_fused does for the group layout): a wavefront's slice is a static range of
-// 64-column units; lane l tests column 64u + l, a ballot gives the kept set, mbcnt the rank,
-// and the kept columns are staged in rank order.
+// spqt_gemv_fused does for the group layout): a wavefront's slice is a static range of columns, and its
+// entries come from a ring of kept columns in LDS (kept_ring.hpp).
 // BATCH activation rows share the (union) index list and ONE pass over the weights; every row has
 // its own staged products, accumulators and bias sum.
 //
@@ -51,12 +50,13 @@ template <int WAVES, bool DENSE, bool FUSED, int BATCH, bool KQ = false>
 __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
     int S, int T, int K, int M, uint32_t inv, float thr, const int32_t *__restrict__ count, const int32_t *__restrict__ idx,
     const uint8_t *__restrict__ packed, const uint16_t *__restrict__ x, float *__restrict__ y, uint32_t *ws) {
-    // One staging area per wavefront is enough: offsets are written and read back inside a FETCH
-    // stage, products inside a MULTIPLY stage, and a wavefront runs its stages one after the other.
+    // One staging area per wavefront is enough: offsets are written and read back inside a HEAD, and the products of a pass are read
+    // before those of the next one are staged.
     __shared__ uint32_t stage_off[WAVES][kPassCols];                               // byte offset of each column
     __shared__ __attribute__((aligned(16))) float stage_xs[WAVES][BATCH][kPassCols][8];  // x * scale * 2^24 per block
     __shared__ __attribute__((aligned(16))) float stage_xm[KQ ? WAVES : 1][BATCH][KQ ? kPassCols : 1][8];  // x * minimum * 2^24
     __shared__ __attribute__((aligned(16))) float red[WAVES][BATCH][kTileRows];
+    __shared__ u32x2 ring_slots[FUSED ? WAVES : 1][FUSED ? kRingSlots : 1];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
     const int seg = lane & 7;
     const int cgr = ((cg & 1) << 2) | (cg & 2) | (cg >> 2);
     const uint32_t seg16 = (uint32_t)seg * 16u;
-    const int n_raw = FUSED ? K / kPassCols : (DENSE ? K : *count);     // requested first
+    const int n_raw = FUSED || DENSE ? K : *count;     // requested first
     int t, s;
     if (!block_of<WAVES>(blockIdx.x, S, T, inv, t, s)) return;
 
@@ -89,6 +89,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
     }
 
     if (pos < end) {
+        KeptRing ring(ring_slots[FUSED ? wave : 0], x, K, pos, end, thr, lane);
         // Atomic loads (the same instructions): the compiler moves plain ones down to the use of their values, behind the
         // weights, and then waits for those too (10240 x 18944, list, 4 rows: 42.4 us with plain loads, 39.0 with these).
         auto fetch_k = [&](int p) -> int {
@@ -97,37 +98,53 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
             return __hip_atomic_load(idx + (e < end ? e : end - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         };
 
-        // FETCH stage of the pass at list position p (kk = its entries): request the next pass's
-        // entries, this pass's x, scales and weights.  Lanes past the pass point at its first
-        // column and later carry x = 0; past the end of the slice the stage degenerates to n = 0
-        // with harmless re-reads.
-        auto fetch = [&](int kk, int p, int slot, u32x4(&w)[8], int &n_out, uint32_t(&xraw_out)[BATCH],
-                         u32x4 &sv_out, int &k_after) {
-            const int left = end - p;
-            const int n = left < 0 ? 0 : (left < kPassCols ? left : kPassCols);
-            k_after = fetch_k(p + kPassCols);
+        // One buffer of weights, refilled half by half as a pass is multiplied: when the products of steps u < 4 are done, their
+        // registers receive the same steps of the next pass, whose HEAD has run before the products.  Only the last pass of a
+        // list has fewer than 64 entries, so only behind the loop are steps left out.  (Two buffers with steps left out in every
+        // pass: 30 registers more, and as the compiler cannot know which loads such steps left in flight it waited for all loads
+        // at every other pass.  Before: list at 50 % / dense 28672 x 8192 17.8 / 26.8 us, now 16.5 / 25.0; 4096 x 14336
+        // 8.8 / 11.0, now 7.8 / 10.0; 4096 x 4096 5.5 / 6.1, now 5.2 / 5.9.)
+        u32x4 w[8];
+        u32x4 sv;                  // raw scales and x of the entry this lane owns, of the pass whose products come next
+        uint32_t xr[BATCH], off[8];        // off: byte offsets of the columns this lane reads
+        int n, k_next = 0;                 // entries of that pass (wave-uniform); the lane's entry of the one after it
+
+        // HEAD of the pass at list position p: request the entries of the pass after it, this pass's x and scales, and deal the
+        // offsets of its columns.  Lanes past the pass point at its first column and carry x = 0.  Returns where the next pass starts.
+        auto head = [&](int p) -> int {
+            int kk = k_next;
+            uint32_t kept_x = 0u;
+            if constexpr (FUSED) {
+                const u32x2 kept = ring.take(p, n);
+                kk = (int)kept.x;
+                kept_x = kept.y;
+            } else {
+                n = end - p < kPassCols ? end - p : kPassCols;
+                k_next = fetch_k(p + kPassCols);
+            }
             const int k_first = n ? __builtin_amdgcn_readfirstlane(kk) : 0;
             const int kc = lane < n ? kk : k_first;
             const uint32_t chunk_off = (uint32_t)(kc >> 7) * (uint32_t)kCbChunkBytes;
             const uint32_t col = (uint32_t)(kc & (kGroup - 1));
 #pragma unroll
-            for (int b = 0; b < BATCH; ++b) xraw_out[b] = x[(size_t)b * K + kc];
-            sv_out = *reinterpret_cast<const u32x4 *>(row_base + (size_t)(chunk_off + col * 16u));
+            for (int b = 0; b < BATCH; ++b) xr[b] = FUSED ? kept_x : (uint32_t)x[(size_t)b * K + kc];
+            sv = *reinterpret_cast<const u32x4 *>(row_base + (size_t)(chunk_off + col * 16u));
             stage_off[wave][lane] = chunk_off + (uint32_t)kCbScaleBytes + col * (uint32_t)kColBytes;
             __builtin_amdgcn_wave_barrier();
-            uint32_t off[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) off[u] = stage_off[wave][u * 8 + cg] + seg16;
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(row_base + (size_t)off[u]));
-            n_out = n;
+            __builtin_amdgcn_wave_barrier();
+            return p + n;
         };
-
-        // MULTIPLY stage of a fetched pass: the lane that owns list entry `ent` stages the 8
-        // products x * s_b * 2^24 of its column (xf = x * 2^24, or 0 for a filler entry), per row.
-        auto multiply = [&](int n, const float(&xf)[BATCH], int ent, u32x4 sv, int slot, const u32x4(&w)[8]) {
+        auto load_half = [&](int half) {
+#pragma unroll
+            for (int u = 4 * half; u < 4 * half + 4; ++u)
+                w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(row_base + (size_t)off[u]));
+        };
+        // The lane that owns an entry stages the 8 products x * s_b * 2^24 of its column, per row.
+        auto stage = [&]() {
             float sc[8], mn[8];
+            if (FUSED && lane >= n) sv = u32x4{0u, 0u, 0u, 0u};      // an empty pass points at column 0, which may be dropped
             if (KQ) {
                 const float d = half_bits_to_float(sv.x & 0xFFFFu), dm = half_bits_to_float(sv.x >> 16);
                 const uint64_t lo = (uint64_t)sv.y | ((uint64_t)sv.z << 32);
@@ -155,128 +172,60 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
             }
 #pragma unroll
             for (int b = 0; b < BATCH; ++b) {
-                f32x4 *dst = reinterpret_cast<f32x4 *>(stage_xs[wave][b][ent]);
-                dst[0] = f32x4{xf[b] * sc[0], xf[b] * sc[1], xf[b] * sc[2], xf[b] * sc[3]};
-                dst[1] = f32x4{xf[b] * sc[4], xf[b] * sc[5], xf[b] * sc[6], xf[b] * sc[7]};
+                const float xf = lane < n ? half_bits_to_float(xr[b]) * kTwo24 : 0.0f;
+                f32x4 *dst = reinterpret_cast<f32x4 *>(stage_xs[wave][b][lane]);
+                dst[0] = f32x4{xf * sc[0], xf * sc[1], xf * sc[2], xf * sc[3]};
+                dst[1] = f32x4{xf * sc[4], xf * sc[5], xf * sc[6], xf * sc[7]};
                 if (KQ) {
-                    f32x4 *dm4 = reinterpret_cast<f32x4 *>(stage_xm[wave][b][ent]);
-                    dm4[0] = f32x4{xf[b] * mn[0], xf[b] * mn[1], xf[b] * mn[2], xf[b] * mn[3]};
-                    dm4[1] = f32x4{xf[b] * mn[4], xf[b] * mn[5], xf[b] * mn[6], xf[b] * mn[7]};
+                    f32x4 *dm4 = reinterpret_cast<f32x4 *>(stage_xm[wave][b][lane]);
+                    dm4[0] = f32x4{xf * mn[0], xf * mn[1], xf * mn[2], xf * mn[3]};
+                    dm4[1] = f32x4{xf * mn[4], xf * mn[5], xf * mn[6], xf * mn[7]};
                 }
             }
             __builtin_amdgcn_wave_barrier();
-            if (BATCH == 1) {
-                float xl[8];
+        };
+        // Step u: 8 columns.  The bias sum takes the product itself, or x * minimum.
+        auto step = [&](int u) {
+            if (BATCH > 2) keep_order();     // x of several steps at once would not fit the registers
 #pragma unroll
-                for (int u = 0; u < 8; ++u) xl[u] = stage_xs[wave][0][u * 8 + cg][seg];
-                float xb[8];     // what step u adds to the bias sum: the product itself, or x * minimum
-#pragma unroll
-                for (int u = 0; u < 8; ++u) xb[u] = KQ ? stage_xm[wave][0][u * 8 + cg][seg] : xl[u];
-                fma_step(w[0], xl[0], acc[0]);
-                bsum[0] += xb[0];
-#pragma unroll
-                for (int u = 1; u < 8; ++u)
-                    if (u * 8 < n) {
-                        fma_step(w[u], xl[u], acc[0]);
-                        bsum[0] += xb[u];
-                    }
-            } else {
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (u == 0 || u * 8 < n) {
-#pragma unroll
-                        for (int b = 0; b < BATCH; ++b) {
-                            const float xl = stage_xs[wave][b][u * 8 + cg][seg];
-                            fma_step(w[u], xl, acc[b]);
-                            bsum[b] += KQ ? stage_xm[wave][b][u * 8 + cg][seg] : xl;
-                        }
-                    }
+            for (int b = 0; b < BATCH; ++b) {
+                const float xl = stage_xs[wave][b][u * 8 + cg][seg];
+                fma_step(w[u], xl, acc[b]);
+                bsum[b] += KQ ? stage_xm[wave][b][u * 8 + cg][seg] : xl;
             }
-            __builtin_amdgcn_wave_barrier();
         };
-        auto multiply_list = [&](int n, const uint32_t(&xraw)[BATCH], u32x4 sv, int slot, const u32x4(&w)[8]) {
-            float xf[BATCH];
-#pragma unroll
-            for (int b = 0; b < BATCH; ++b) xf[b] = lane < n ? half_bits_to_float(xraw[b]) * kTwo24 : 0.0f;
-            multiply(n, xf, lane, sv, slot, w);
-        };
-
-        u32x4 wA[8], wB[8], svA, svB;
-        int nA, nB;
         if (FUSED) {
-            // FETCH stage of unit u (xr = this lane's x[64u + lane], requested one stage earlier):
-            // threshold, rank, stage the offsets, request the next unit's x, this unit's scales
-            // (every lane its own column's) and weights.
-            auto fetch_unit = [&](uint32_t xr, int u, int slot, u32x4(&w)[8], int &n_out, float(&xf_out)[BATCH],
-                                  int &ent_out, u32x4 &sv_out, uint32_t &xr_next) {
-                const bool any = u < end;
-                const float xv = half_bits_to_float(xr);
-                const bool keep = any && !(__builtin_fabsf(xv) < thr);
-                const uint64_t mask = __ballot(keep);
-                const int n = __builtin_amdgcn_readfirstlane((int)__popcll(mask));
-                const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                {
-                    const int c = (u + 1) * kPassCols + lane;
-                    xr_next = __hip_atomic_load(x + (c < K ? c : K - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-                }
-                const int uu = any ? u : 0;
-                const uint32_t chunk_off = (uint32_t)(uu >> 1) * (uint32_t)kCbChunkBytes;
-                const uint32_t col_own = (uint32_t)((uu & 1) * kPassCols + lane);
-                const uint32_t col_first = (uint32_t)((uu & 1) * kPassCols + (n ? (int)__builtin_ctzll(mask) : 0));
-                sv_out = *reinterpret_cast<const u32x4 *>(row_base + (size_t)(chunk_off + col_own * 16u));
-                // kept columns go to entries 0..n-1 in ascending order; the other lanes fill entries
-                // n..63 with the unit's first kept column and x = 0
-                const int entry = keep ? rank : n + lane - rank;
-                stage_off[wave][entry] =
-                    chunk_off + (uint32_t)kCbScaleBytes + (keep ? col_own : col_first) * (uint32_t)kColBytes;
-                __builtin_amdgcn_wave_barrier();
-                uint32_t off[8];
-#pragma unroll
-                for (int v = 0; v < 8; ++v) off[v] = stage_off[wave][v * 8 + cg] + seg16;
-#pragma unroll
-                for (int v = 0; v < 8; ++v)
-                    w[v] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(row_base + (size_t)off[v]));
-                n_out = n;
-                xf_out[0] = keep ? xv * kTwo24 : 0.0f;
-                ent_out = entry;
-            };
-            float xfA[BATCH], xfB[BATCH];
-            int entA, entB;
-            uint32_t xa = x[pos * kPassCols + lane], xb;
-            fetch_unit(xa, pos, 0, wA, nA, xfA, entA, svA, xb);
-            for (;;) {
-                const int uB = pos + 1;
-                fetch_unit(xb, uB, 1, wB, nB, xfB, entB, svB, xa);
-                if (nA > 0) multiply(nA, xfA, entA, svA, 0, wA);
-                if (uB >= end) break;
-                const int uA = uB + 1;
-                fetch_unit(xa, uA, 0, wA, nA, xfA, entA, svA, xb);
-                if (nB > 0) multiply(nB, xfB, entB, svB, 1, wB);
-                if (uA >= end) break;
-                pos = uA;
-            }
+            ring.fetch();
+            pos = 0;                 // from here on a position among the kept columns of the slice
         } else {
-            uint32_t xrA[BATCH], xrB[BATCH];
-            int kA, kB;
-            kA = fetch_k(pos);
-            fetch(kA, pos, 0, wA, nA, xrA, svA, kB);
-            if (pos + nA >= end) {
-                multiply_list(nA, xrA, svA, 0, wA);      // the whole slice is one pass
-            } else {
-                for (;;) {
-                    const int posB = pos + nA;
-                    fetch(kB, posB, 1, wB, nB, xrB, svB, kA);
-                    multiply_list(nA, xrA, svA, 0, wA);
-                    if (posB >= end) break;
-                    const int posA = posB + nB;
-                    fetch(kA, posA, 0, wA, nA, xrA, svA, kB);
-                    multiply_list(nB, xrB, svB, 1, wB);
-                    if (posA >= end) break;
-                    pos = posA;
-                }
-            }
+            k_next = fetch_k(pos);
         }
+        auto more = [&](int p) { return FUSED ? ring.more(p) : p < end; };
+        pos = head(pos);
+        load_half(0);
+        load_half(1);
+        while (more(pos)) {
+            stage();
+            const bool whole = !FUSED || n > kPassCols / 2;
+            pos = head(pos);
+            keep_order();
+#pragma unroll
+            for (int u = 0; u < 4; ++u) step(u);
+            keep_order();
+            load_half(0);
+            keep_order();
+            if (whole) {
+#pragma unroll
+                for (int u = 4; u < 8; ++u) step(u);
+            }
+            keep_order();
+            load_half(1);
+            keep_order();
+        }
+        stage();
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (u * 8 < n) step(u);
     }
 
     // fold the 8 column-lanes once and remove the bias.  The products are already in true units

@@ -110,6 +110,9 @@ __device__ __forceinline__ void fma_step(u32x4 w, float xl, float *acc) {
     fma_codes(w.w, xl, xh, acc + 24);
 }
 
+// Keeps the compiler from moving instructions across: it would gather requests behind products, or products before requests.
+__device__ __forceinline__ void keep_order() { __builtin_amdgcn_sched_barrier(0); }
+
 // The three levels of the column fold are written as asm blocks: the lane swaps work in place
 // on both of their registers (no copies), and the wait states a swap or DPP read needs after a
 // VALU write of its operand are paid once per block instead of once per instruction.

@@ -53,9 +53,6 @@ struct StagedX {
     uint16_t pad[8];   // a multiple of 16 bytes per wavefront
 };
 
-// Keeps the compiler from moving instructions across: it would gather the refills behind the products.
-__device__ __forceinline__ void keep_order() { __builtin_amdgcn_sched_barrier(0); }
-
 // v of lane U of the caller's row of 16 lanes, in every lane of the row.
 template <int U>
 __device__ __forceinline__ uint32_t row_lane(uint32_t v) {

@@ -80,7 +80,9 @@ inline void choose_cfg(int64_t M, int64_t K, int batch, spqt_launch_cfg *out) {
 //     but 4-bit 9000 x 2944 with 105 columns S = 7 / 14 6.0 / 6.2);
 //   - dense slices of at most one pass, if 3 workgroups per CU reach that without a less full round (4-bit 11008 x 4096 S = 5 / 16
 //     9.7 / 8.9, 9000 x 2944 S = 7 / 14 7.5 / 6.9);
-//   - one launch: passes are half full, so slices of more than 5 units want a second workgroup per CU (4-bit 28672 x 8192
+//   - one launch (swept with kernels whose passes were one unit each; now that kept_ring.hpp fills them the split matters less: 4-bit
+//     28672 x 8192 S = 2 / 4 / 6 17.7 / 17.2 / 17.6, K-quant 13824 x 5120 at 40 % S = 4 / 9 / 14 9.5 / 9.6 / 9.4): slices differ in their
+//     kept columns, so those of more than 5 units want a second workgroup per CU (4-bit 28672 x 8192
 //     S = 2 / 4 23.0 / 19.4, 8-bit 4096 x 11008 S = 8 / 16 9.4 / 9.1, but 4-bit 13824 x 5120 with 5 units S = 4 / 7 9.8 / 10.0), and
 //     S is the smallest with the same number of units in the longest slice (4-bit 5120 x 5120 S = 12 / 10 6.6 / 6.4).  A third
 //     workgroup per CU has to leave a fuller round after that, too (14848 x 10240, 4-bit S = 8 / 10 14.7 / 16.8, K-quant 15.2 / 17.4, 8-bit with
