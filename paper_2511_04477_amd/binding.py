@@ -166,41 +166,79 @@ def spqt_unpack(packed: np.ndarray, M: int, K: int, group: int = GROUP):
 
 # --------------------------------------------------------------------------- device calls
 
-def _stream_ptr(stream) -> int:
+_torch = None          # the torch module, once a device call has needed it
+_raw_stream = None     # () -> handle of torch's current stream
+
+
+def _load_torch():
+    global _torch, _raw_stream
     import torch
+    device, stream = getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if device and stream:      # the handle alone: a torch.cuda.Stream object around it takes a microsecond
+        _raw_stream = lambda: stream(device())
+    else:
+        _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
+    _torch = torch
+    return torch
+
+
+def _stream_ptr(stream) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return _raw_stream()
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _dev(t, dtype, what):
-    import torch
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous() and t.dtype == dtype):
+    if not (isinstance(t, _torch.Tensor) and t.is_cuda and t.is_contiguous() and t.dtype == dtype):
         raise SpqtError(f"{what}: need a contiguous CUDA tensor of dtype {dtype}")
     return t.data_ptr()
 
 
 def _y_out(y):
     """(device pointer, flag bits) of an output tensor: fp32, or fp16 with SPQT_CFG_Y_FP16."""
-    import torch
-    if isinstance(y, torch.Tensor) and y.dtype == torch.float16:
-        return _dev(y, torch.float16, "y"), CFG_Y_FP16
-    return _dev(y, torch.float32, "y"), 0
+    if isinstance(y, _torch.Tensor) and y.dtype == _torch.float16:
+        return _dev(y, _torch.float16, "y"), CFG_Y_FP16
+    return _dev(y, _torch.float32, "y"), 0
+
+
+def _bytes_of(M, K, columns: int, rows: int, chunk: int, query) -> int:
+    """Bytes of a packed matrix with chunks of `chunk` bytes for `rows` x `columns` weights; `query`, the library's own
+    function, says what is wrong with a shape that it does not take."""
+    M, K = int(M), int(K)
+    if 0 < M <= 1 << 24 and 0 < K <= 1 << 24 and K % GROUP == 0 and columns in (64, GROUP):
+        return -(-M // rows) * (K // columns) * chunk
+    return query()
 
 
 def _cfg(splits, waves, flags) -> LaunchCfg:
     return LaunchCfg(int(splits), int(waves), int(flags))
 
 
+def _group_bytes(M, K, group):
+    return _bytes_of(M, K, group, TILE_ROWS, 2 * TILE_ROWS + 128 * group, lambda: spqt_packed_bytes(M, K, group))
+
+
+def _cb_bytes(M, K):
+    return _bytes_of(M, K, GROUP, 256, CB_CHUNK_BYTES, lambda: spqt_cb_packed_bytes(M, K))
+
+
+def _cb8_bytes(M, K):
+    return _bytes_of(M, K, GROUP, 128, CB8_CHUNK_BYTES, lambda: spqt_cb8_packed_bytes(M, K))
+
+
+def _cb2_bytes(M, K):
+    return _bytes_of(M, K, GROUP, 512, CB2_CHUNK_BYTES, lambda: spqt_cb2_packed_bytes(M, K))
+
+
 def spqt_workspace_init(workspace, stream=None) -> None:
-    import torch
+    torch = _torch or _load_torch()
     p = _dev(workspace, torch.uint8, "workspace")
     _check(lib().spqt_workspace_init(p, workspace.numel(), _stream_ptr(stream)))
 
 
 def new_workspace(M: int, K: int, batch: int = 1, device="cuda"):
     """Allocate and prepare a workspace tensor for spqt_gemv on this shape."""
-    import torch
+    torch = _torch or _load_torch()
     ws = torch.empty(spqt_workspace_bytes(M, K, batch), dtype=torch.uint8, device=device)
     spqt_workspace_init(ws)
     return ws
@@ -208,7 +246,7 @@ def new_workspace(M: int, K: int, batch: int = 1, device="cuda"):
 
 def spqt_gather(x, threshold: float, idx_out, count_out, stream=None) -> None:
     """x fp16[K] or [batch, K]; idx_out int32[>=K]; count_out int32[1] (all on the GPU)."""
-    import torch
+    torch = _torch or _load_torch()
     xp = _dev(x, torch.float16, "x")
     batch, K = (1, x.shape[0]) if x.dim() == 1 else (x.shape[0], x.shape[1])
     ip = _dev(idx_out, torch.int32, "idx_out")
@@ -221,7 +259,7 @@ def spqt_gather(x, threshold: float, idx_out, count_out, stream=None) -> None:
 def spqt_gather_rows(x, threshold: float, idx_out, count_out, x_masked_out, stream=None) -> None:
     """spqt_gather plus x_masked_out (fp16, same shape as x): every row with its own dropped
     entries zeroed; feed it to a GEMV with idx_out / count_out for per-row kept sets."""
-    import torch
+    torch = _torch or _load_torch()
     xp = _dev(x, torch.float16, "x")
     batch, K = (1, x.shape[0]) if x.dim() == 1 else (x.shape[0], x.shape[1])
     ip = _dev(idx_out, torch.int32, "idx_out")
@@ -236,12 +274,12 @@ def spqt_gemv(packed, M: int, K: int, x, idx, count, y, workspace, stream=None, 
               splits: int = 0, waves: int = 0, flags: int = 0) -> None:
     """packed uint8 (device); x fp16[K] or [batch,K]; idx/count from spqt_gather or None/None
     for the dense kernel; y fp32 (or fp16) [M] or [batch,M]; workspace from new_workspace()."""
-    import torch
+    torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
     yp, yflags = _y_out(y)
     batch = 1 if x.dim() == 1 else x.shape[0]
-    if x.shape[-1] != K or y.numel() != batch * M or packed.numel() < spqt_packed_bytes(M, K, group):
+    if x.shape[-1] != K or y.numel() != batch * M or packed.numel() < _group_bytes(M, K, group):
         raise SpqtError("spqt_gemv: x / y / packed sizes do not match M, K, batch")
     ip = cp = None
     if idx is not None:
@@ -261,12 +299,12 @@ def spqt_gemv(packed, M: int, K: int, x, idx, count, y, workspace, stream=None, 
 
 def spqt_gemv_static(packed, M: int, K: int, x, idx, count, y, stream=None, group: int = GROUP) -> None:
     """spqt_gemv without a workspace argument: the exchange words live in the library's own device array."""
-    import torch
+    torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
     yp = _dev(y, torch.float32, "y")
     batch = 1 if x.dim() == 1 else x.shape[0]
-    if x.shape[-1] != K or y.numel() != batch * M or packed.numel() < spqt_packed_bytes(M, K, group):
+    if x.shape[-1] != K or y.numel() != batch * M or packed.numel() < _group_bytes(M, K, group):
         raise SpqtError("spqt_gemv_static: x / y / packed sizes do not match M, K, batch")
     ip = cp = None
     if idx is not None:
@@ -278,11 +316,11 @@ def spqt_gemv_static(packed, M: int, K: int, x, idx, count, y, stream=None, grou
 def spqt_gemv_fused(packed, M: int, K: int, x, threshold: float, y, workspace, stream=None,
                     group: int = GROUP, splits: int = 0, waves: int = 0, flags: int = 0) -> None:
     """Threshold + compaction + GEMV in one launch (batch 1): x fp16[K], y fp32 (or fp16) [M]."""
-    import torch
+    torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
     yp, yflags = _y_out(y)
-    if x.numel() != K or y.numel() != M or packed.numel() < spqt_packed_bytes(M, K, group):
+    if x.numel() != K or y.numel() != M or packed.numel() < _group_bytes(M, K, group):
         raise SpqtError("spqt_gemv_fused: x / y / packed sizes do not match M, K (batch 1 only)")
     wp, wbytes = None, 0
     if workspace is not None:
@@ -296,12 +334,12 @@ def spqt_gemv_fused_rows(packed, M: int, K: int, x, threshold: float, y, workspa
                          group: int = GROUP, splits: int = 0, waves: int = 0) -> None:
     """Threshold + compaction + GEMV in one launch for x fp16[batch, K], batch 1..4; y fp32 (or fp16) [batch, M].
     own_sets: every row sums over its own kept columns instead of the union."""
-    import torch
+    torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
     yp, yflags = _y_out(y)
     batch = 1 if x.dim() == 1 else x.shape[0]
-    if x.shape[-1] != K or y.numel() != batch * M or packed.numel() < spqt_packed_bytes(M, K, group):
+    if x.shape[-1] != K or y.numel() != batch * M or packed.numel() < _group_bytes(M, K, group):
         raise SpqtError("spqt_gemv_fused_rows: x / y / packed sizes do not match M, K, batch")
     wp, wbytes = None, 0
     if workspace is not None:
@@ -344,12 +382,12 @@ def spqt_cb_gemv(packed, M: int, K: int, x, idx, count, y, workspace, stream=Non
     """Column-block GEMV: packed uint8 (device), x fp16[K] or [batch, K], idx/count from spqt_gather
     or None/None for the dense kernel, y fp32 (or fp16) [M] or [batch, M], workspace from
     new_workspace()."""
-    import torch
+    torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
     yp, yflags = _y_out(y)
     batch = 1 if x.dim() == 1 else x.shape[0]
-    if x.shape[-1] != K or y.numel() != batch * M or packed.numel() < spqt_cb_packed_bytes(M, K):
+    if x.shape[-1] != K or y.numel() != batch * M or packed.numel() < _cb_bytes(M, K):
         raise SpqtError("spqt_cb_gemv: x / y / packed sizes do not match M, K, batch")
     ip = cp = None
     if idx is not None:
@@ -365,11 +403,11 @@ def spqt_cb_gemv(packed, M: int, K: int, x, idx, count, y, workspace, stream=Non
 def spqt_cb_gemv_fused(packed, M: int, K: int, x, threshold: float, y, workspace, stream=None,
                        splits: int = 0, waves: int = 0) -> None:
     """Threshold + compaction + column-block GEMV in one launch (batch 1)."""
-    import torch
+    torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
     yp, yflags = _y_out(y)
-    if x.numel() != K or y.numel() != M or packed.numel() < spqt_cb_packed_bytes(M, K):
+    if x.numel() != K or y.numel() != M or packed.numel() < _cb_bytes(M, K):
         raise SpqtError("spqt_cb_gemv_fused: x / y / packed sizes do not match M, K (batch 1 only)")
     wp, wbytes = None, 0
     if workspace is not None:
@@ -404,12 +442,12 @@ def spqt_cbk_dequantize(packed: np.ndarray, M: int, K: int) -> np.ndarray:
 def spqt_cbk_gemv(packed, M: int, K: int, x, idx, count, y, workspace, stream=None, splits: int = 0,
                   waves: int = 0) -> None:
     """K-quant column-block GEMV: x fp16[K] or [batch, K] (idx/count None/None for the dense kernel)."""
-    import torch
+    torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
     yp, yflags = _y_out(y)
     batch = 1 if x.dim() == 1 else x.shape[0]
-    if x.shape[-1] != K or y.numel() != batch * M or packed.numel() < spqt_cb_packed_bytes(M, K):
+    if x.shape[-1] != K or y.numel() != batch * M or packed.numel() < _cb_bytes(M, K):
         raise SpqtError("spqt_cbk_gemv: x / y / packed sizes do not match M, K, batch")
     ip = cp = None
     if idx is not None:
@@ -425,11 +463,11 @@ def spqt_cbk_gemv(packed, M: int, K: int, x, idx, count, y, workspace, stream=No
 def spqt_cbk_gemv_fused(packed, M: int, K: int, x, threshold: float, y, workspace, stream=None,
                         splits: int = 0, waves: int = 0) -> None:
     """Threshold + compaction + K-quant column-block GEMV in one launch (batch 1)."""
-    import torch
+    torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
     yp, yflags = _y_out(y)
-    if x.numel() != K or y.numel() != M or packed.numel() < spqt_cb_packed_bytes(M, K):
+    if x.numel() != K or y.numel() != M or packed.numel() < _cb_bytes(M, K):
         raise SpqtError("spqt_cbk_gemv_fused: x / y / packed sizes do not match M, K (batch 1 only)")
     wp, wbytes = None, 0
     if workspace is not None:
@@ -470,11 +508,11 @@ def spqt_cb8_dequantize(packed: np.ndarray, M: int, K: int) -> np.ndarray:
 def spqt_cb8_gemv(packed, M: int, K: int, x, idx, count, y, workspace, stream=None, splits: int = 0,
                   waves: int = 0) -> None:
     """8-bit column-block GEMV, batch 1 (idx/count None/None for the dense kernel)."""
-    import torch
+    torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
     yp, yflags = _y_out(y)
-    if x.numel() != K or y.numel() != M or packed.numel() < spqt_cb8_packed_bytes(M, K):
+    if x.numel() != K or y.numel() != M or packed.numel() < _cb8_bytes(M, K):
         raise SpqtError("spqt_cb8_gemv: x / y / packed sizes do not match M, K (batch 1 only)")
     ip = cp = None
     if idx is not None:
@@ -518,11 +556,11 @@ def spqt_cb2_dequantize(packed: np.ndarray, M: int, K: int) -> np.ndarray:
 def spqt_cb2_gemv(packed, M: int, K: int, x, idx, count, y, workspace, stream=None, splits: int = 0,
                   waves: int = 0) -> None:
     """2-bit column-block GEMV, batch 1 (idx/count None/None for the dense kernel)."""
-    import torch
+    torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
     yp, yflags = _y_out(y)
-    if x.numel() != K or y.numel() != M or packed.numel() < spqt_cb2_packed_bytes(M, K):
+    if x.numel() != K or y.numel() != M or packed.numel() < _cb2_bytes(M, K):
         raise SpqtError("spqt_cb2_gemv: x / y / packed sizes do not match M, K (batch 1 only)")
     ip = cp = None
     if idx is not None:
@@ -536,7 +574,7 @@ def spqt_cb2_gemv(packed, M: int, K: int, x, idx, count, y, workspace, stream=No
 
 
 def _width_fused(fn_name, bytes_fn, packed, M, K, x, threshold, y, workspace, stream, splits, waves):
-    import torch
+    torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
     yp, yflags = _y_out(y)
@@ -552,17 +590,17 @@ def _width_fused(fn_name, bytes_fn, packed, M, K, x, threshold, y, workspace, st
 def spqt_cb8_gemv_fused(packed, M: int, K: int, x, threshold: float, y, workspace, stream=None, splits: int = 0,
                         waves: int = 0) -> None:
     """8-bit column-block gather + GEMV in one launch, batch 1."""
-    _width_fused("spqt_cb8_gemv_fused", spqt_cb8_packed_bytes, packed, M, K, x, threshold, y, workspace, stream, splits, waves)
+    _width_fused("spqt_cb8_gemv_fused", _cb8_bytes, packed, M, K, x, threshold, y, workspace, stream, splits, waves)
 
 
 def spqt_cb2_gemv_fused(packed, M: int, K: int, x, threshold: float, y, workspace, stream=None, splits: int = 0,
                         waves: int = 0) -> None:
     """2-bit column-block gather + GEMV in one launch, batch 1."""
-    _width_fused("spqt_cb2_gemv_fused", spqt_cb2_packed_bytes, packed, M, K, x, threshold, y, workspace, stream, splits, waves)
+    _width_fused("spqt_cb2_gemv_fused", _cb2_bytes, packed, M, K, x, threshold, y, workspace, stream, splits, waves)
 
 
 def _width_rows(fn_name, bytes_fn, packed, M, K, x, idx, count, y, workspace, stream, splits, waves):
-    import torch
+    torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
     yp, yflags = _y_out(y)
@@ -583,10 +621,10 @@ def _width_rows(fn_name, bytes_fn, packed, M, K, x, idx, count, y, workspace, st
 def spqt_cb8_gemv_rows(packed, M: int, K: int, x, idx, count, y, workspace, stream=None, splits: int = 0,
                        waves: int = 0) -> None:
     """8-bit column-block GEMV for x fp16[batch][K], batch 1..4, on the union list (or dense)."""
-    _width_rows("spqt_cb8_gemv_rows", spqt_cb8_packed_bytes, packed, M, K, x, idx, count, y, workspace, stream, splits, waves)
+    _width_rows("spqt_cb8_gemv_rows", _cb8_bytes, packed, M, K, x, idx, count, y, workspace, stream, splits, waves)
 
 
 def spqt_cb2_gemv_rows(packed, M: int, K: int, x, idx, count, y, workspace, stream=None, splits: int = 0,
                        waves: int = 0) -> None:
     """2-bit column-block GEMV for x fp16[batch][K], batch 1..3, on the union list (or dense)."""
-    _width_rows("spqt_cb2_gemv_rows", spqt_cb2_packed_bytes, packed, M, K, x, idx, count, y, workspace, stream, splits, waves)
+    _width_rows("spqt_cb2_gemv_rows", _cb2_bytes, packed, M, K, x, idx, count, y, workspace, stream, splits, waves)
