@@ -84,12 +84,15 @@ inline void choose_cfg(int64_t M, int64_t K, int batch, spqt_launch_cfg *out) {
 //     28672 x 8192 S = 2 / 4 / 6 17.7 / 17.2 / 17.6, K-quant 13824 x 5120 at 40 % S = 4 / 9 / 14 9.5 / 9.6 / 9.4): slices differ in their
 //     kept columns, so those of more than 5 units want a second workgroup per CU (4-bit 28672 x 8192
 //     S = 2 / 4 23.0 / 19.4, 8-bit 4096 x 11008 S = 8 / 16 9.4 / 9.1, but 4-bit 13824 x 5120 with 5 units S = 4 / 7 9.8 / 10.0), and
-//     S is the smallest with the same number of units in the longest slice (4-bit 5120 x 5120 S = 12 / 10 6.6 / 6.4).  A third
+//     with more than one per CU S is the smallest with the same number of units in the longest slice.  With one per CU it is not: slices
+//     are split to the column, so every workgroup less makes the longest slice longer (smallest such S / one per CU: 4-bit 6400 x 16896 at
+//     40 % 13.1 / 11.7, 8704 x 7424 at 20 % 10.8 / 10.1, K-quant 5888 x 3200 6.3 / 5.9, 5120 x 13824 10.1 / 9.9); it only leaves no slice shorter than a unit.  A third
 //     workgroup per CU has to leave a fuller round after that, too (14848 x 10240, 4-bit S = 8 / 10 14.7 / 16.8, K-quant 15.2 / 17.4, 8-bit with
 //     58 block-rows 12.7 / 14.3).  More than 128 block-rows with slices of at most 5 units exchange nothing (S = 1): a fuller round is worth
 //     less than the exchange (22016 x 1024 8-bit S = 1 / 4 6.5 / 7.0, 44032 x 1280 4-bit S = 1 / 3 8.6 / 9.8, K-quant 9.2 / 10.0);
 //   - several rows with slices from 1024 columns on: two workgroups per CU (4-bit, 4 rows, 28672 x 8192 S = 2 / 4 36.7 / 34.0).
-// max_depth 1: one workgroup fills a CU's registers (2-bit: 28672 x 8192 S = 4 / 8 16.1 / 17.3).
+// max_depth 1 (2-bit): a second workgroup per CU does not pay (list 28672 x 8192 S = 4 / 8 / 9 14.1 / 15.2 / 14.5, 24576 x 2048 S = 5 / 10 6.8 / 7.5;
+// dense alone gains where the last round is fuller, 28672 x 8192 S = 4 / 9 21.1 / 19.5).
 enum class Columns { list, dense, units };    // units: one launch, static ranges of 64-column units
 inline int colblock_splits(int64_t T, int64_t K, Columns from, int batch, int max_depth) {
     auto deepest = [&](int64_t depth) {
@@ -122,7 +125,10 @@ inline int colblock_splits(int64_t T, int64_t K, Columns from, int batch, int ma
     if (from == Columns::dense && slice(S) > 64)
         for (int64_t d = 2; d <= max_depth; ++d)
             if (K <= 4 * 64 * deepest(d) && fill(deepest(d)) >= fill(S)) { S = deepest(d); break; }
-    return (int)(from == Columns::units ? fewest(S) : S);
+    if (from != Columns::units) return (int)S;
+    if (T * S > 256) return (int)fewest(S);
+    while (S > 1 && 4 * 64 * (S - 1) >= K) --S;
+    return (int)S;
 }
 
 // max_depth of the 4-bit layouts.  The K-quant kernel stages a minimum beside every scale: with 2 rows (172 VGPRs) a CU holds two of its
