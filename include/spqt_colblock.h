@@ -73,7 +73,7 @@ int spqt_cb_gemv(const void *packed_dev, int64_t M, int64_t K, const void *x_dev
 
 /* DEVICE, async.  Gather and GEMV in ONE launch (the column-block counterpart of
  * spqt_gemv_fused): the kernel applies the sparsity test of Section 2 to x itself on static
- * 64-column ranges, compacts the kept columns with a wavefront ballot and multiplies; no index
+ * column ranges, compacts the kept columns with a wavefront ballot and multiplies; no index
  * list exists.  Same y as spqt_gather followed by spqt_cb_gemv up to summation order. */
 int spqt_cb_gemv_fused(const void *packed_dev, int64_t M, int64_t K, const void *x_dev, float threshold,
                        void *y_dev, void *workspace_dev, size_t workspace_bytes, void *stream,
@@ -137,7 +137,7 @@ int spqt_cb8_gemv_rows(const void *packed_dev, int64_t M, int64_t K, const void 
                        const int32_t *idx_dev, const int32_t *count_dev, void *y_dev, void *workspace_dev,
                        size_t workspace_bytes, void *stream, const spqt_launch_cfg *cfg);
 /* DEVICE, async.  As spqt_cb_gemv_fused (gather and GEMV in one launch, batch 1: the sparsity test of
- * Section 2 runs inside the kernel on static 64-column ranges), on spqt_cb8_quantize's output. */
+ * Section 2 runs inside the kernel on static column ranges), on spqt_cb8_quantize's output. */
 int spqt_cb8_gemv_fused(const void *packed_dev, int64_t M, int64_t K, const void *x_dev, float threshold,
                         void *y_dev, void *workspace_dev, size_t workspace_bytes, void *stream,
                         const spqt_launch_cfg *cfg);

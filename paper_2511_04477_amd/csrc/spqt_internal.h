@@ -131,7 +131,7 @@ inline int colblock_splits(int64_t T, int64_t K, Columns from, int batch, int ma
     return (int)S;
 }
 
-// max_depth of the 4-bit layouts.  The K-quant kernel stages a minimum beside every scale: with 2 rows (172 VGPRs) a CU holds two of its
+// max_depth of the 4-bit layouts.  The K-quant kernel stages a minimum beside every scale: with 2 rows (172 VGPRs with the two weight buffers it had when this was swept, 158 now) a CU held two of its
 // workgroups, not three, so the third that a list takes for a 3 % fuller round starts a round of its own (22016 x 1024 S = 5 / 8
 // 7.2 / 10.0 us, 13824 x 4096 S = 9 / 14 9.8 / 12.1; the least gain is a loss, 16896 x 4096 S = 7 / 11 12.1 / 11.7).  Above 128 block-rows the
 // split is so coarse that a finer one is worth that round (35072 x 2048 S = 3 / 5 11.9 / 11.6, 43932 x 8192 S = 2 / 4 35.6 / 32.2).
