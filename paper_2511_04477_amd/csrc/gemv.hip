@@ -4,7 +4,7 @@
 // Paper Section 2: a column is sparse iff |x_i| < threshold; Section 4.2.2 (zigzag kernel): one block-row = 256 outputs is
 // shared by n1 threadgroups x n2 simdgroups that keep partial sums locally and combine them once.  Instead of reading an
 // index list, the kernel tests x itself: the slice of a wavefront is a static range of columns (K split evenly over the S*WAVES
-// wavefronts of the block-row, to the column).  A wavefront compacts its range, kRefill units of 64 columns at a time and only
+// wavefronts of the block-row, to the column or to the unit: slice_quantum).  A wavefront compacts its range, kRefill units of 64 columns at a time and only
 // as its passes need them, into a ring of (column, x) entries in LDS - lane l tests the unit's column l, a ballot gives the kept
 // set, mbcnt the rank - and takes its passes (pass.hpp) from the ring exactly as gemv_list.hip takes them from idx.
 //
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
     auto unit_at = [&](int at, int i) { return at + i % kStep * kPassCols + i / kStep * apart; };
     const int parts = S * WAVES;
     const int part = s * WAVES + wave;
-    constexpr int kQuantum = COMPACT ? 1 : kPassCols;    // the ablation's passes are whole units, so its slices are too
+    constexpr int kQuantum = slice_quantum(BATCH, COMPACT);
     const Share share = share_of<WAVES>(apart / kQuantum, part, parts, inv);
     int u = share.begin * kQuantum;
     const int end = share.end * kQuantum;

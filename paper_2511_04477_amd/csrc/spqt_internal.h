@@ -41,6 +41,15 @@ inline int check_shape(int64_t M, int64_t K, int group) {
 // ceil(2^32 / n): what the kernels divide by n with (n >= 2; 0 for n = 1, which they do not use).
 inline uint32_t inverse_of(int n) { return (uint32_t)((((uint64_t)1 << 32) + (uint32_t)n - 1) / (uint32_t)n); }
 
+// Columns that the slices of the one-launch kernel of the group layout (gemv.hip) are whole multiples of; 31 heights and widths, both group
+// sizes, to the column / units.  One or two rows: 1, so that slices are as even as can be (681 x 8960 at 20 % 6.2 / 7.1 us, 11008 x 4096
+// at 20 % 8.0 / 8.7, two rows at 40 % 8.5 / 9.2; up to 70 % sparsity 2 % faster on average; few kept columns want units, as a pass ends with its
+// last group: two rows at 95 % 4 % slower on average, 11008 x 4096 6.2 / 5.7).  Three or four rows: a unit.  Their passes hold ONE quantization group, so a slice
+// that begins and ends inside a unit takes a pass more than its units do (4 rows at 40 %: groups of 64, 5120 x 5120 10.6 / 8.8, 5321 x 1920 8.6 / 7.4;
+// groups of 128, 13678 x 2816 11.0 / 9.5, 11001 x 4224 11.4 / 10.0; 5 % faster on average, and 1 % slower where units make the longest slice half a pass
+// longer, 13824 x 5120 12.9 / 13.0, 4096 x 14336 12.1 / 12.2).  Without compaction a pass IS a unit.
+constexpr int slice_quantum(int batch, bool compact) { return compact && batch <= 2 ? 1 : 64; }
+
 // Workgroups in the grid of a group-layout launch (block_of in gemv_common.hpp says which is which).
 inline int grid_blocks(int64_t T, int S) { return 8 * (int)((T / 8) * S + ((T % 8) * S + 7) / 8); }
 
