@@ -148,7 +148,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
             return p + d.n;
         };
         fetch_x(u);
-        run_passes<BATCH, kGroups>(staged[wave], row_base, chunk_b, lane, n8, out4, part, 0, h, head,
+        run_passes<BATCH, kGroups, true>(staged[wave], row_base, chunk_b, lane, n8, out4, part, 0, h, head,
                                    [&](int p) { return p < filled || u < end; }, [&]() {}, [&]() {}, acc);
     }
 

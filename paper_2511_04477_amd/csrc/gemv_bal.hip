@@ -191,7 +191,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
             return p + d.n;
         };
         // 4. GEMV
-        run_passes<1, kGroups>(staged[wave], row_base, chunk_b, lane, n8, out4, part, 0, h, head, [&](int p) { return p < total; },
+        run_passes<1, kGroups, false>(staged[wave], row_base, chunk_b, lane, n8, out4, part, 0, h, head, [&](int p) { return p < total; },
                                [&]() { SPQT_TL(2); }, [&]() { SPQT_TL_WAIT(3); }, acc);
     }
     SPQT_TL(4);

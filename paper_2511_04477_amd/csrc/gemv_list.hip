@@ -95,7 +95,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
         };
         k_next = all_kept ? pos + lane : fetch_k(pos);
         SPQT_TL_WAIT(2);
-        run_passes<BATCH, GROUPS>(staged[wave], row_base, chunk_b, lane, n8, out4, part, pos, h, head, [&](int p) { return p < end; },
+        run_passes<BATCH, GROUPS, false>(staged[wave], row_base, chunk_b, lane, n8, out4, part, pos, h, head, [&](int p) { return p < end; },
                                   [&]() {}, [&]() { SPQT_TL_WAIT(3); }, acc);
     }
 

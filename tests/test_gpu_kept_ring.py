@@ -36,7 +36,7 @@ def test_kept_columns_of_any_slice(layout, K, splits):
             assert np.all(err <= 1e-2 + 2e-3 * np.abs(ref)), f"n={n} {name}: max err {np.nanmax(err):.3e}"
 
 
-@pytest.mark.parametrize("layout", ["cb", "cb8", "cb2"])
+@pytest.mark.parametrize("layout", ["cb", "cbk", "cb8", "cb2"])
 def test_dropped_columns_stay_out_of_empty_passes(layout):
     """Column 0 is dropped and its scales are infinite: a pass without entries points at it and must not multiply it."""
     import torch
@@ -44,8 +44,8 @@ def test_dropped_columns_stay_out_of_empty_passes(layout):
     M, K = 512, 1024
     packed_np = getattr(spqt, f"spqt_{layout}_quantize")(make_fp_weights(M, K, 6400))
     deq = getattr(spqt, f"spqt_{layout}_dequantize")(packed_np, M, K).astype(np.float64)
-    per_column = {"cb": 16, "cb8": 8, "cb2": 32}[layout]
-    chunk = {"cb": 18432, "cb8": 17408, "cb2": 20480}[layout]
+    per_column = {"cb": 16, "cbk": 4, "cb8": 8, "cb2": 32}[layout]      # cbk: d and dmin, then the 6-bit fields
+    chunk = {"cb": 18432, "cbk": 18432, "cb8": 17408, "cb2": 20480}[layout]
     for t in range(packed_np.size // (K // 128 * chunk)):
         at = t * (K // 128) * chunk
         packed_np[at:at + per_column] = np.full(per_column // 2, np.inf, dtype=np.float16).view(np.uint8)

@@ -106,6 +106,23 @@ def test_one_launch_slices_of_any_column(gpu, rows, K, splits):
         check(run(gpu, w, x, thr, "fused", splits=splits), oracle.gemv(w["q_rowmajor"], w["scales"], x, thr), f"K={K} sparsity={sparsity}")
 
 
+@pytest.mark.parametrize("group", [128, 64])
+@pytest.mark.parametrize("rows", [1, 2, 3, 4])
+def test_dropped_groups_stay_out(gpu, rows, group):
+    """All columns of the first groups are dropped and the scales of group 0 are infinite: slices and refills that keep nothing take
+    passes without entries, which must not multiply those scales."""
+    M, K = 512, 1024
+    w = make_weights(M, K, 5180, group=group)
+    x = np.zeros((rows, K), dtype=np.float16)
+    x[:, 700:] = make_x(K, "normal", 5181, batch=rows)[:, 700:]
+    ref = oracle.gemv(w["q_rowmajor"], w["scales"], x, 0.125, group=group)
+    w["scales"][:, 0] = np.float16(np.inf)
+    for mode in ("list", "fused"):
+        for splits in (1, 0):
+            print(f"dropped groups rows={rows} group={group} {mode} splits={splits}", flush=True)
+            check(run(gpu, w, x, 0.125, mode, group, splits), ref, f"{mode} splits={splits}")
+
+
 @pytest.mark.parametrize("T,K", [(9, 1024), (12, 1024), (20, 2048), (33, 1024), (300, 256)])
 @pytest.mark.parametrize("rows", [1, 3])
 def test_block_rows_over_xcds(gpu, T, K, rows):
