@@ -167,19 +167,35 @@ def spqt_unpack(packed: np.ndarray, M: int, K: int, group: int = GROUP):
 # --------------------------------------------------------------------------- device calls
 
 _torch = None          # the torch module, once a device call has needed it
-_raw_stream = None     # () -> handle of torch's current stream
 
 
 def _load_torch():
-    global _torch, _raw_stream
+    global _torch
     import torch
-    device, stream = getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    if device and stream:      # the handle alone: a torch.cuda.Stream object around it takes a microsecond
-        _raw_stream = lambda: stream(device())
-    else:
-        _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
     _torch = torch
     return torch
+
+
+def _public_stream() -> int:
+    return _torch.cuda.current_stream().cuda_stream
+
+
+def _first_stream() -> int:
+    """Handle of torch's current stream, and how later calls get it: by two private functions of torch where they are there and
+    agree with the public way (a torch.cuda.Stream object around the handle takes a microsecond)."""
+    global _raw_stream
+    handle = _public_stream()
+    _raw_stream = _public_stream
+    try:
+        device, stream = _torch._C._cuda_getDevice, _torch._C._cuda_getCurrentRawStream
+        if stream(device()) == handle:
+            _raw_stream = lambda: stream(device())
+    except Exception:      # another signature, or gone: the public way
+        pass
+    return handle
+
+
+_raw_stream = _first_stream
 
 
 def _stream_ptr(stream) -> int:

@@ -4,6 +4,7 @@ errors come back as status codes.  No kernel is launched here."""
 import ctypes
 import os
 import re
+import sys
 
 import numpy as np
 import pytest
@@ -331,6 +332,23 @@ def test_null_and_small_buffers_are_rejected_on_the_host():
     assert fr(128, 256, 128, 128, 16, 2, ctypes.c_float(0.0), 0, 16, None, 0, None, ctypes.byref(two_waves)) == -1
     no_ws = spqt.binding.LaunchCfg(4, 0, 0)
     assert fr(128, 1024, 1024, 128, 16, 2, ctypes.c_float(0.0), 0, 16, None, 0, None, ctypes.byref(no_ws)) == -1
+
+
+@pytest.mark.parametrize("private", [{}, {"_cuda_getDevice": lambda: 0, "_cuda_getCurrentRawStream": lambda device: 4096 + device},
+                                     {"_cuda_getDevice": lambda: 0, "_cuda_getCurrentRawStream": lambda: 4096},
+                                     {"_cuda_getDevice": lambda: 0, "_cuda_getCurrentRawStream": lambda device: 8192}])
+def test_current_stream_without_the_private_functions(monkeypatch, private):
+    """The handle of torch's current stream is what the public call gives whether torch's private functions are gone, are as they
+    were, take other arguments or return something else."""
+    import types
+    from paper_2511_04477_amd import binding
+    fake = types.SimpleNamespace(_C=types.SimpleNamespace(**private),
+                                 cuda=types.SimpleNamespace(current_stream=lambda: types.SimpleNamespace(cuda_stream=4096)))
+    monkeypatch.setitem(sys.modules, "torch", fake)
+    monkeypatch.setattr(binding, "_torch", None)
+    monkeypatch.setattr(binding, "_raw_stream", getattr(binding, "_first_stream", None))
+    binding._load_torch()
+    assert [binding._stream_ptr(None) for _ in range(3)] == [4096] * 3
 
 
 @pytest.mark.parametrize("M,K", [(512, 1024), (4096, 4096), (1024, 4096), (11008, 4096), (4096, 11008),
