@@ -1,4 +1,4 @@
-"""Thin ctypes binding over libspqt.so: argument marshalling only.
+"""Thin ctypes binding over libspqt.so: argument marshalling, and the sizes and types of the tensors that a device call is given.
 
 Same names as the C ABI (include/spqt.h).  Host calls take NumPy arrays; device calls take
 torch CUDA tensors (PyTorch supplies device memory and the stream, nothing else) and launch

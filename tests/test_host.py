@@ -334,6 +334,26 @@ def test_null_and_small_buffers_are_rejected_on_the_host():
     assert fr(128, 1024, 1024, 128, 16, 2, ctypes.c_float(0.0), 0, 16, None, 0, None, ctypes.byref(no_ws)) == -1
 
 
+@pytest.mark.parametrize("ours,library", [
+    (lambda M, K: spqt.binding._group_bytes(M, K, 128), lambda M, K: spqt.spqt_packed_bytes(M, K, 128)),
+    (lambda M, K: spqt.binding._group_bytes(M, K, 64), lambda M, K: spqt.spqt_packed_bytes(M, K, 64)),
+    (lambda M, K: spqt.binding._group_bytes(M, K, 32), lambda M, K: spqt.spqt_packed_bytes(M, K, 32)),
+    (spqt.binding._cb_bytes, spqt.spqt_cb_packed_bytes), (spqt.binding._cb8_bytes, spqt.spqt_cb8_packed_bytes),
+    (spqt.binding._cb2_bytes, spqt.spqt_cb2_packed_bytes)], ids=["g128", "g64", "g32", "cb", "cb8", "cb2"])
+def test_sizes_the_device_calls_check_are_the_librarys(ours, library):
+    """The size that a device call asks of `packed`, which keeps a kernel inside it, is the library's, and so are the refusals."""
+    def result(fn, M, K):
+        try:
+            return fn(M, K)
+        except spqt.SpqtError as e:
+            return str(e)
+    heights = [-1, 0, 1, 2, 127, 128, 129, 255, 256, 257, 511, 512, 513, 28672, (1 << 24) - 1, 1 << 24, (1 << 24) + 1]
+    widths = [-128, 0, 64, 100, 128, 129, 256, 1152, 28672, 1 << 24, (1 << 24) + 128]
+    for M in heights:
+        for K in widths:
+            assert result(ours, M, K) == result(library, M, K), (M, K)
+
+
 @pytest.mark.parametrize("private", [{}, {"_cuda_getDevice": lambda: 0, "_cuda_getCurrentRawStream": lambda device: 4096 + device},
                                      {"_cuda_getDevice": lambda: 0, "_cuda_getCurrentRawStream": lambda: 4096},
                                      {"_cuda_getDevice": lambda: 0, "_cuda_getCurrentRawStream": lambda device: 8192}])
