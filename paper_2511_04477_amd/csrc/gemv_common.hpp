@@ -9,7 +9,7 @@
 
 #include <type_traits>
 
-#include "spqt_internal.h"
+#include "split.hpp"
 
 namespace spqt {
 
@@ -202,52 +202,6 @@ struct ListLaunch {
     int K, S, T, m_and_flags;
 };
 hipError_t launch_gemv_list(int waves, int batch, bool one_group, int grid, hipStream_t stream, const ListLaunch &a);
-
-// Which workgroup of which block-row a launch index is.  Workgroups go to the 8 XCDs round-robin by index; the S workgroups
-// of a block-row are kept on ONE XCD as far as that leaves the XCDs equally loaded: block-rows in multiples of 8 go to the
-// XCDs whole, and the workgroups of the T % 8 that are left are spread over the XCDs evenly (with 20 block-rows, whole
-// ones would give four XCDs 3 and four 2: 5120 x 13824 dense, 12 workgroups per block-row, 13.1 us, evenly 10.4).  A
-// spread block-row's reducer may run before producers on another XCD are dispatched, which combine_block_row allows for.
-// Returns false for the padding of the grid (grid_blocks).
-__device__ __forceinline__ bool is_spread(int t, int T) { return t >= (T & ~7); }
-// inv: inverse_of(S * WAVES).
-template <int WAVES>
-__device__ __forceinline__ bool block_of(uint32_t index, int S, int T, uint32_t inv, int &t, int &s) {
-    const uint32_t xcd = index & 7u;
-    const uint32_t slot = index >> 3;                                          // position among this XCD's workgroups
-    const uint32_t whole = ((uint32_t)T >> 3) * (uint32_t)S;                   // workgroups of whole block-rows per XCD
-    const uint32_t left = ((uint32_t)T & 7u) * (uint32_t)S;
-    const uint32_t per_xcd = (left + 7u) >> 3;
-    const bool in_whole = slot < whole;
-    const uint32_t r = in_whole ? slot : xcd * per_xcd + slot - whole;         // one division serves both
-    // r / S; r < 2^19 (M <= 2^24, S <= 64), so the rounded-up inverse gives it exactly: r * WAVES * (S * WAVES) < 2^32
-    const uint32_t q = WAVES == 1 ? r / (uint32_t)S : __umulhi(r * (uint32_t)WAVES, inv);
-    t = (int)(in_whole ? xcd + 8u * q : ((uint32_t)T & ~7u) + q);
-    s = (int)(r - q * (uint32_t)S);
-    return in_whole || (slot - whole < per_xcd && r < left);
-}
-
-// Part `part` of `parts` equal parts of n things: [floor(n * part / parts), floor(n * (part + 1) / parts)).  In 32-bit
-// arithmetic for every n <= 2^24 and parts <= 512: with n = q * parts + r a part starts at q * part + floor(r * part / parts).
-// The divisions are products with inv = inverse_of(parts), rounded up: exact for r * part < 2^18, and for n the quotient may be
-// one too large, which shows as a negative remainder.
-struct Share {
-    int begin, end;
-};
-template <int WAVES>
-__device__ __forceinline__ Share share_of(int n, int part, int parts, uint32_t inv) {
-    int q, r;
-    if (WAVES == 1) {              // parts may be 1, which has no 32-bit inverse
-        q = (int)((uint32_t)n / (uint32_t)parts);
-        r = n - q * parts;
-        return {q * part + (int)((uint32_t)(r * part) / (uint32_t)parts), q * (part + 1) + (int)((uint32_t)(r * (part + 1)) / (uint32_t)parts)};
-    }
-    q = (int)__umulhi((uint32_t)n, inv);
-    r = n - q * parts;
-    q -= r < 0 ? 1 : 0;
-    r += r < 0 ? parts : 0;
-    return {q * part + (int)__umulhi((uint32_t)(r * part), inv), q * (part + 1) + (int)__umulhi((uint32_t)(r * (part + 1)), inv)};
-}
 
 // The order of the kernels' arguments: what a wavefront needs before it can request anything comes first.  The first 14 dwords of
 // the arguments are in scalar registers when a wavefront starts (-amdgpu-kernarg-preload-count in the build), the rest is a
