@@ -300,6 +300,29 @@ def test_cb2_several_rows_on_the_union_list(gpu, M, K, batch, splits, waves, spa
     assert_close(run_rows(gpu, spqt.spqt_cb2_quantize(W), M, K, x, thr, splits=splits, waves=waves), ref, "cb2 rows")
 
 
+@pytest.mark.parametrize("batch", [2, 3])
+def test_cb2_rows_with_slices_of_one_pass_and_more(gpu, batch):
+    """One slice with as many entries as end a step, a pass or the second one: a slice of one pass runs code of its own."""
+    import paper_2511_04477_amd as spqt
+    M, K = 512, 256
+    W = make_fp_weights(M, K, 9802)
+    base = make_x(K, "normal", 9803, batch=batch)
+    base = np.where(np.abs(base) < 0.25, np.float16(0.25), base).astype(np.float16)
+    q, s = c2.quantize(W)
+    packed = spqt.spqt_cb2_quantize(W)
+    for n in (1, 8, 9, 63, 64, 65, 72, 73, 127, 128, 129):
+        x = np.zeros_like(base)
+        cols = np.linspace(0, K - 1, n).astype(int)
+        x[:, cols] = base[:, cols]
+        say(f"cb2 rows batch={batch} n={n}")
+        assert_close(run_rows(gpu, packed, M, K, x, 0.125, splits=1, waves=1), c2.gemv(q, s, x, 0.125), f"n={n}")
+    for Kd in (128, 384):     # dense, four slices of 32 and 96 columns
+        Wd, xd = make_fp_weights(M, Kd, 9804), make_x(Kd, "normal", 9805, batch=batch)
+        say(f"cb2 rows dense batch={batch} K={Kd}")
+        qd, sd = c2.quantize(Wd)
+        assert_close(run_rows(gpu, spqt.spqt_cb2_quantize(Wd), M, Kd, xd, 0.0, dense=True, splits=1), c2.gemv(qd, sd, xd, 0.0), f"dense {Kd}")
+
+
 def test_cb2_rows_dense_fp16_and_limits(gpu):
     """Dense mode with several rows, fp16 output, one row through the rows entry point equals the batch-1 entry
     point bit for bit, and a row count past the limit is refused."""
