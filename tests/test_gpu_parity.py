@@ -62,7 +62,7 @@ def gpu_gemv(gpu, w, x_np, thr, dense=False, splits=0, waves=0, packed=None, fla
 def assert_close(got, ref, what=""):
     err = np.abs(got.astype(np.float64) - ref)
     bound = ATOL + RTOL * np.abs(ref)
-    bad = np.argwhere(err > bound)
+    bad = np.argwhere(~(err <= bound))      # NaN is off, too
     assert bad.size == 0, f"{what}: {bad.shape[0]} outputs out of tolerance, first {bad[0]}, max err {err.max():.4g}"
     return float(err.max())
 

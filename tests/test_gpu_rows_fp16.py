@@ -34,7 +34,7 @@ def say(*a):
 
 def assert_close(got, ref, what):
     err = np.abs(got.astype(np.float64) - ref)
-    bad = err > ATOL + RTOL * np.abs(ref)
+    bad = ~(err <= ATOL + RTOL * np.abs(ref))      # NaN is off, too
     assert not bad.any(), f"{what}: {int(bad.sum())} outputs off, max err {err.max():.3e}"
 
 
