@@ -136,10 +136,9 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb2_gemv_kernel(
 int run2(int mode, int batch, const void *packed_dev, int64_t M, int64_t K, const void *x_dev, const int32_t *idx_dev,
          const int32_t *count_dev, float thr, void *y_dev, void *workspace_dev, size_t workspace_bytes, void *stream,
          const spqt_launch_cfg *cfg) {
-    // a fourth activation row's 64 accumulators no longer fit the register file next to two stages of weights
+    // three rows have 192 accumulators, 70 of which are already in the file that the VALU cannot read (colblock_width.hpp); a fourth row's 64 would be, too
     if (batch > kMaxRows2) return SPQT_ESHAPE;
-    // one workgroup of 4 wavefronts per CU: the 64 accumulators per activation row and two stages of weights leave
-    // room for one wavefront per SIMD
+    // one workgroup of 4 wavefronts per CU: a second one fits (138 VGPRs with one row), but does not pay (colblock_splits)
     const int64_t T64 = (M + W2::kRows - 1) / W2::kRows;
     int S0 = 1;
     if (check_shape(M, K, kGroup) == SPQT_OK) {    // colblock_width_run refuses the others

@@ -80,29 +80,28 @@ inline void choose_cfg(int64_t M, int64_t K, int batch, spqt_launch_cfg *out) {
 
 // Workgroups (of 4 wavefronts) per block-row of the column-block kernels, any integer up to 16; T block-rows.  What counts is
 // how full the last round over the 256 CUs is: `depth` workgroups per CU leave T * S <= 256 * depth.  Power-of-two S
-// left it at 62 to 87 % of the CUs for most heights.  Swept per layout, mode and shape (us, at 50 % sparsity or dense):
-//   - one workgroup per CU is where every kernel starts: 4-bit, T = 20, list 5120 x 13824 S = 16 / 12 10.6 / 9.3, dense 14.3 / 11.5;
-//   - lists of 1 or 2 rows go deeper for a 3 % fuller last round (4-bit, T = 54, 13824 x 5120 S = 4 / 8 / 14 9.4 / 9.8 / 8.6; 8-bit,
-//     T = 86, 11008 x 4096 S = 2 / 5 / 8 9.7 / 9.2 / 8.5), the others only for a 20 % fuller one, since two workgroups on a CU cost them
-//     more than that (4-bit dense 13824 x 5120 S = 4 / 8 12.0 / 12.6, 4 rows 15.8 / 16.3);
-//   - a list slice of 112 to 256 columns (1 or 2 rows) is a pass and a bit: two workgroups per CU (8-bit 4096 x 4096 S = 8 / 16 6.6 / 6.0,
-//     but 4-bit 9000 x 2944 with 105 columns S = 7 / 14 6.0 / 6.2);
-//   - dense slices of at most one pass, if 3 workgroups per CU reach that without a less full round (4-bit 11008 x 4096 S = 5 / 16
-//     9.7 / 8.9, 9000 x 2944 S = 7 / 14 7.5 / 6.9);
-//   - one launch (swept with kernels whose passes were one unit each; now that kept_ring.hpp fills them the split matters less: 4-bit
-//     28672 x 8192 S = 2 / 4 / 6 17.7 / 17.2 / 17.6, K-quant 13824 x 5120 at 40 % S = 4 / 9 / 14 9.5 / 9.6 / 9.4): slices differ in their
-//     kept columns, so those of more than 5 units want a second workgroup per CU (4-bit 28672 x 8192
-//     S = 2 / 4 23.0 / 19.4, 8-bit 4096 x 11008 S = 8 / 16 9.4 / 9.1, but 4-bit 13824 x 5120 with 5 units S = 4 / 7 9.8 / 10.0), and
-//     with more than one per CU S is the smallest with the same number of units in the longest slice.  With one per CU it is not: slices
-//     are split to the column, so every workgroup less makes the longest slice longer (smallest such S / one per CU: 4-bit 6400 x 16896 at
-//     40 % 13.1 / 11.7, 8704 x 7424 at 20 % 10.8 / 10.1, K-quant 5888 x 3200 6.3 / 5.9, 5120 x 13824 10.1 / 9.9); it only leaves no slice shorter than a unit.  A third
-//     workgroup per CU has to leave a fuller round after that, too (14848 x 10240, 4-bit S = 8 / 10 14.7 / 16.8, K-quant 15.2 / 17.4, 8-bit with
-//     58 block-rows 12.7 / 14.3).  More than 128 block-rows with slices of at most 5 units exchange nothing (S = 1): a fuller round is worth
-//     less than the exchange (22016 x 1024 8-bit S = 1 / 4 6.5 / 7.0, 44032 x 1280 4-bit S = 1 / 3 8.6 / 9.8, K-quant 9.2 / 10.0);
-//   - several rows with slices from 1024 columns on: two workgroups per CU (4-bit, 4 rows, 28672 x 8192 S = 2 / 4 36.7 / 34.0).
-// max_depth 1 (2-bit): a second workgroup per CU does not pay (list 28672 x 8192 S = 4 / 8 / 9 14.1 / 15.2 / 14.5, 24576 x 2048 S = 5 / 10 6.8 / 7.5;
-// dense alone gains where the last round is fuller, 28672 x 8192 S = 4 / 9 21.1 / 19.5).
-enum class Columns { list, dense, units };    // units: one launch, static ranges of 64-column units
+// left it at 62 to 87 % of the CUs for most heights.  The lines were drawn by sweeps of the kernels with two buffers of weights (4-bit 132
+// VGPRs, 8-bit 110); the figures are of the present ones (100 and 77), us at 50 % sparsity or dense, and where a line no longer pays that is said:
+//   - one workgroup per CU is where every kernel starts: 4-bit, T = 20, 5120 x 13824 S = 16 / 12 list 9.2 / 8.1, dense 12.3 / 10.3;
+//   - lists of 1 or 2 rows go deeper for a 3 % fuller last round (8-bit, T = 86, 11008 x 4096 S = 2 / 5 / 8 8.7 / 8.1 / 8.5; the third workgroup no
+//     longer pays there, and 4-bit, T = 54, 13824 x 5120 S = 4 / 8 / 14 is 8.1 / 8.6 / 8.2), the others only for a 20 % fuller one, since two
+//     workgroups on a CU cost them more than that (4-bit dense 13824 x 5120 S = 4 / 8 10.0 / 10.7, 4 rows 19.9 / 21.5);
+//   - a list slice of 112 to 256 columns (1 or 2 rows) is a pass and a bit: two workgroups per CU (no longer a gain: 8-bit 4096 x 4096
+//     S = 8 / 16 5.5 / 5.7; 4-bit 9000 x 2944 with 105 columns S = 7 / 14 5.9 / 6.0);
+//   - dense slices of at most one pass, if 3 workgroups per CU reach that without a less full round (no longer a gain: 4-bit 11008 x 4096
+//     S = 5 / 16 8.1 / 8.7, 9000 x 2944 S = 7 / 14 6.8 / 6.8);
+//   - one launch: slices of more than 5 units take a second workgroup per CU, S being the smallest with the same number of units in the longest
+//     slice.  That evened out passes of one unit each; with full passes (kept_ring.hpp) and slices that are split to the column one per CU is as fast
+//     or faster (S = one per CU / this rule: 4-bit 28672 x 8192 16.2 / 17.0, 14848 x 10240 12.3 / 13.0, 6400 x 16896 at 40 % 11.2 / 12.7, 8-bit 4096 x 11008
+//     8.2 / 8.4).  With one per CU S is not lowered like that: every workgroup less makes the longest slice longer (4-bit 8704 x 7424 at 20 %
+//     S = 6 / 7 10.1 / 9.7, K-quant 5120 x 13824 at 40 % S = 11 / 12 9.7 / 9.4); a workgroup goes only where no slice has more than 64 columns without it.
+//     A third workgroup per CU has to leave a fuller round after the second one's lowering, too (14848 x 10240, 4-bit S = 8 / 10 13.0 / 14.3, 8-bit with
+//     58 block-rows 11.2 / 12.2).  More than 128 block-rows with slices of at most 5 units exchange nothing (S = 1): a fuller round is worth
+//     less than the exchange (22016 x 1024 8-bit S = 1 / 4 5.7 / 6.0, 44032 x 1280 4-bit S = 1 / 3 7.0 / 8.1, K-quant 7.4 / 8.1);
+//   - several rows with slices from 1024 columns on: two workgroups per CU (4-bit, 4 rows, 28672 x 8192 S = 2 / 4 51 / 46.5).
+// max_depth 1 (2-bit): a second workgroup per CU does not pay (list 28672 x 8192 S = 4 / 8 / 9 14.2 / 15.4 / 14.8, 14336 x 4096 S = 9 / 16 7.7 / 8.2;
+// dense 24576 x 2048 S = 5 / 10 8.1 / 8.9, 14336 x 4096 S = 9 / 16 9.1 / 9.6, and where the last round is fuller 28672 x 8192 S = 4 / 9 20.3 / 19.7).
+enum class Columns { list, dense, units };    // units: one launch, static ranges of columns
 inline int colblock_splits(int64_t T, int64_t K, Columns from, int batch, int max_depth) {
     auto deepest = [&](int64_t depth) {
         const int64_t S = 256 * depth / T;
@@ -140,19 +139,20 @@ inline int colblock_splits(int64_t T, int64_t K, Columns from, int batch, int ma
     return (int)S;
 }
 
-// max_depth of the 4-bit layouts.  The K-quant kernel stages a minimum beside every scale: with 2 rows (172 VGPRs with the two weight buffers it had when this was swept, 158 now) a CU held two of its
-// workgroups, not three, so the third that a list takes for a 3 % fuller round starts a round of its own (22016 x 1024 S = 5 / 8
-// 7.2 / 10.0 us, 13824 x 4096 S = 9 / 14 9.8 / 12.1; the least gain is a loss, 16896 x 4096 S = 7 / 11 12.1 / 11.7).  Above 128 block-rows the
-// split is so coarse that a finer one is worth that round (35072 x 2048 S = 3 / 5 11.9 / 11.6, 43932 x 8192 S = 2 / 4 35.6 / 32.2).
+// max_depth of the 4-bit layouts.  The K-quant kernel stages a minimum beside every scale: with 2 rows a CU held two of its workgroups while
+// it had two buffers of weights (172 VGPRs), and the third that a list takes for a 3 % fuller round started a round of its own.  With one
+// buffer (158 VGPRs, 42 KB of LDS) three fit, and the third loses or gains: 22016 x 1024 S = 5 / 8 7.4 / 8.4 us, 16896 x 4096 S = 7 / 11
+// 12.3 / 12.6, but 13824 x 4096 S = 9 / 14 11.3 / 10.7, 14336 x 4096 S = 9 / 13 11.3 / 11.1.  Above 128 block-rows the split is so coarse that a finer one is worth
+// it (35072 x 2048 S = 3 / 5 12.5 / 12.5, 43932 x 8192 S = 2 / 4 45 / 37).
 inline int colblock4_depth(int64_t T, Columns from, int batch, bool kquant) {
     return kquant && from == Columns::list && batch == 2 && T <= 128 ? 2 : 3;
 }
 
-// max_depth of the 8-bit layout.  Dense, one row, 129 to 256 block-rows, slices from 768 columns on: one workgroup per CU on two
-// thirds of the CUs already reads at the rate of the memory, so a third workgroup per CU only adds the exchange (22016 x 4096 S = 1 / 4
-// 18.2 / 19.1 us, 24576 x 8192 34.5 / 37.0; below two thirds two per CU pay, 16640 x 8192 S = 1 / 3 29.8 / 27.7, and short slices
-// gain from parallelism, 22016 x 1024 S = 1 / 4 7.6 / 7.5).  One launch, more than 256 block-rows, fewer than 40 units: S = 1 / 2
-// 33024 x 1536 10.4 / 10.8, 40960 x 1536 11.6 / 11.9, 36864 x 2304 13.3 / 13.6 (2816 columns 16.6 / 16.7 and 14.1 / 13.9; K-quant 66048 x 1536 14.0 / 13.4).
+// max_depth of the 8-bit layout (figures of the present kernels; the lines were drawn with those of two buffers).  Dense, one row, 129 to 256
+// block-rows, slices from 768 columns on: one workgroup per CU on two thirds of the CUs already reads at the rate of the memory, so a third
+// workgroup per CU only adds the exchange (24576 x 8192 S = 1 / 4 35.9 / 37.2 us, 22016 x 4096 19.7 / 19.1, which was 18.2 / 19.1; below two thirds two per CU pay,
+// 16640 x 8192 S = 1 / 3 35.0 / 28.3; short slices 22016 x 1024 S = 1 / 4 7.2 / 7.4).  One launch, more than 256 block-rows, fewer than 40 units: S = 1 / 2
+// 33024 x 1536 9.3 / 9.3, 40960 x 1536 10.4 / 10.3, 36864 x 2304 13.4 / 13.0 (2816 columns 14.8 / 13.9 and 16.2 / 15.7; K-quant 66048 x 1536 11.9 / 11.3).
 inline int colblock8_depth(int64_t T, int64_t K, Columns from, int batch) {
     if (from == Columns::units) return T > 256 && K < 2560 ? 2 : 3;
     return from == Columns::dense && batch == 1 && T > 128 && T <= 256 && K >= 4 * 768 ? 2 : 3;
@@ -165,7 +165,7 @@ inline bool usable_workspace(const void *ws, size_t bytes, size_t need) {
 // Whether a column-block call that asks for no launch shape and brings no usable workspace runs with ONE workgroup per
 // block-row, which exchanges nothing.  Above these heights the block-rows alone keep the chip busy enough for that to be a
 // sensible shape (half the CUs for a matrix of 64 MB and more and one row, all of them otherwise, twice that for a
-// dense one, whose slices are shortest): 4-bit list at 50 % 33024 x 4096 without / with a workspace 13.8 / 13.0 us.
+// dense one, whose slices are shortest): 4-bit list at 50 % 33024 x 4096 without / with a workspace 14.5 / 12.0 us.
 inline bool runs_without_workspace(int64_t T, size_t code_bytes, Columns from, int batch) {
     const bool large = batch == 1 && code_bytes >= (size_t)64 << 20;
     return T > (large ? 128 : (from == Columns::dense && batch == 1 ? 512 : 256));

@@ -396,9 +396,8 @@ def test_default_launch_shape_can_be_asked_for(M, K, batch, sparse, shape):
 
 
 def test_colblock_launch_shapes(tmp_path):
-    """Workgroups per block-row that were measured to be the faster ones where a fuller last round may not pay for the exchange it
-    brings in (8-bit dense from two thirds of the CUs on, one launch over few units) or is none: once the slices are whole units, and
-    where a CU cannot hold the workgroups (K-quant list with 2 rows: two per CU).  Layout "k" stands for that one."""
+    """Workgroups per block-row of the column-block layouts on both sides of each line of the rules: 8-bit dense from two thirds of the CUs
+    on, one launch over few units, K-quant lists with 2 rows ("k": two per CU).  What the lines are worth stands beside the rules."""
     import subprocess
     shapes = [("dense", 172, 4096, "8", 1), ("dense", 192, 8192, "8", 1), ("dense", 130, 8192, "8", 3), ("dense", 172, 1024, "8", 4),
               ("dense", 258, 4096, "8", 2), ("dense", 192, 8192, "4", 4),
