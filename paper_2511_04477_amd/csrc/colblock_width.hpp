@@ -52,6 +52,7 @@ __device__ __forceinline__ void colblock_width_gemv(int S, int T, int K, int M, 
     const int n_raw = FUSED || DENSE ? K : *count;     // requested first
     int t, s;
     if (!block_of<WAVES>(blockIdx.x, S, T, inv, t, s)) return;
+    Outputs<BATCH * F::kRows> outputs(t, s, S, T, ws, y, M);
 
     const int n_ns = n_raw < 0 ? 0 : (n_raw > K ? K : n_raw);
     const int parts = S * WAVES;
@@ -144,6 +145,7 @@ __device__ __forceinline__ void colblock_width_gemv(int S, int T, int K, int M, 
         pos = head(pos);
         load_half(0);
         load_half(1);
+        outputs.read_now();
         auto pass = [&]() {          // every pass but the last one
             stage();
             const bool whole = !FUSED || n > kPassCols / 2;
@@ -183,12 +185,14 @@ __device__ __forceinline__ void colblock_width_gemv(int S, int T, int K, int M, 
             for (int u = 0; u < 8; ++u)
                 if (u * 8 < n) step(u);
         }
+    } else {
+        outputs.read_now();
     }
 
 #pragma unroll
     for (int b = 0; b < BATCH; ++b) F::finish(acc[b], bs[b], seg, cgr, red[wave][b]);
     __syncthreads();
-    combine_block_row<WAVES, BATCH, F::kRows>(&red[0][0][0], tid, t, s, S, T, ws, y, M);
+    combine_block_row<WAVES, BATCH, F::kRows>(&red[0][0][0], tid, outputs);
 }
 
 // Host side shared by the entry points: argument checks, launch shape, workspace, grid.  `launch` starts the

@@ -49,6 +49,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
     const uint32_t out4 = (uint32_t)(4 * n + (lane >> 4));    // the lane's 4 outputs: rows 4 out4 .. 4 out4 + 3
     int t, s;
     if (!block_of<WAVES>(blockIdx.x, S, T, inv, t, s)) return;
+    Outputs<BATCH * kTileRows> outputs(t, s, S, T, ws, y, M);
 
     // Positions are columns of one part of K; SPREAD columns that lie `apart` from each other share one.  A refill takes kStep
     // units of each part, and unit_at(u, i) is the first column of unit i of the refill at position u.
@@ -149,7 +150,9 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
         };
         fetch_x(u);
         run_passes<BATCH, kGroups, true>(staged[wave], row_base, chunk_b, lane, n8, out4, part, 0, h, head,
-                                   [&](int p) { return p < filled || u < end; }, [&]() {}, [&]() {}, acc);
+                                   [&](int p) { return p < filled || u < end; }, [&]() { outputs.read_now(); }, [&]() {}, acc);
+    } else {
+        outputs.read_now();
     }
 
     SPQT_TL(4);
@@ -160,7 +163,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
                                                              acc[b][2] * kEvenUnit, acc[b][3] * kOddUnit};
     __syncthreads();
     SPQT_TL(5);
-    combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, t, s, S, T, ws, y, M);
+    combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, outputs);
     SPQT_TL_END(WAVES, wave, lane, S > 1 && s == S - 1);
 }
 

@@ -82,6 +82,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
     const uint32_t out4 = (uint32_t)(4 * n + (lane >> 4));    // the lane's 4 outputs: rows 4 out4 .. 4 out4 + 3
     int t, s;
     if (!block_of<WAVES>(blockIdx.x, S, T, inv, t, s)) return;
+    Outputs<kTileRows> outputs(t, s, S, T, ws, y, M);
 
     // 1. COUNT: x into LDS, then the kept columns of every 512-column step (every workgroup does all of x).
     const int nsteps = (K + kStepCols - 1) / kStepCols;      // <= kXsSteps (checked on the host)
@@ -192,7 +193,9 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
         };
         // 4. GEMV
         run_passes<1, kGroups, false>(staged[wave], row_base, chunk_b, lane, n8, out4, part, 0, h, head, [&](int p) { return p < total; },
-                               [&]() { SPQT_TL(2); }, [&]() { SPQT_TL_WAIT(3); }, acc);
+                               [&]() { outputs.read_now(); SPQT_TL(2); }, [&]() { SPQT_TL_WAIT(3); }, acc);
+    } else {
+        outputs.read_now();
     }
     SPQT_TL(4);
 
@@ -200,7 +203,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
                                                          acc[0][2] * kEvenUnit, acc[0][3] * kOddUnit};
     __syncthreads();
     SPQT_TL(5);
-    combine_block_row<WAVES, 1>(&red[0][0][0], tid, t, s, S, T, ws, y, M);
+    combine_block_row<WAVES, 1>(&red[0][0][0], tid, outputs);
     SPQT_TL_END(WAVES, wave, lane, S > 1 && s == S - 1);
 }
 

@@ -68,6 +68,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
     const int n_raw = FUSED || DENSE ? K : *count;     // requested first
     int t, s;
     if (!block_of<WAVES>(blockIdx.x, S, T, inv, t, s)) return;
+    Outputs<BATCH * kTileRows> outputs(t, s, S, T, ws, y, M);
 
     // (a count outside 0..K cannot come from spqt_gather; clamping keeps a corrupt one inside idx)
     const int n_ns = n_raw < 0 ? 0 : (n_raw > K ? K : n_raw);
@@ -204,6 +205,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
         pos = head(pos);
         load_half(0);
         load_half(1);
+        outputs.read_now();
         while (more(pos)) {
             stage();
             const bool whole = !FUSED || n > kPassCols / 2;
@@ -226,6 +228,8 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
 #pragma unroll
         for (int u = 0; u < 8; ++u)
             if (u * 8 < n) step(u);
+    } else {
+        outputs.read_now();
     }
 
     // fold the 8 column-lanes once and remove the bias.  The products are already in true units
@@ -239,7 +243,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
             f32x4{r4[0] - bias, r4[1] - bias, r4[2] - bias, r4[3] - bias};
     }
     __syncthreads();
-    combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, t, s, S, T, ws, y, M);
+    combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, outputs);
 }
 
 template <int WAVES, int BATCH>

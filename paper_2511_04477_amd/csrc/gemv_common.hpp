@@ -214,13 +214,19 @@ hipError_t launch_gemv_list(int waves, int batch, bool one_group, int grid, hipS
 // `red` holds this workgroup's [WAVES][BATCH][ROWS] partial sums in LDS (already synchronised);
 // ROWS is the height of a block-row (256 for the 4-bit layouts).
 // Every workgroup but the last (s == S-1) publishes its ROWS partial sums as 32-bit words with device-scope stores
-// (two adjacent rows per store where a thread owns more than one).  A word is the COMPLEMENT of the sum's bits (never 0: the
-// one pattern that would give 0 is a NaN and is replaced by another NaN), and 0 means "not there yet".  The last
-// workgroup adds the others' words in index order, polling until none is 0, then its own sums, writes y, and stores zero
-// back into every word it consumed - so between calls the exchange area is all zeros whatever M, launch shape or kernel
+// (two adjacent rows per store where a thread owns more than one).  A word is the sum's bits, +0 written as -0, and 0 means "not
+// there yet".  The last workgroup adds the others' words in index order, polling until none is 0, then its own sums, writes y, and stores
+// zero back into every word it consumed - so between calls the exchange area is all zeros whatever M, launch shape or kernel
 // the calls had, and a word that is not 0 is always one of THIS call.  (A tag beside every value would double the bytes:
 // four activation rows, 1024 x 4096, 16 workgroups per block-row: 9.8 us with tagged 64-bit words, 7.4 without;
 // one row, 4096 x 4096: 5.6 and 5.2.)
+// What bounds it: a store's way to where the other XCDs see it and a load's way back (0.4 to 0.5 us), and the instructions of the one
+// wavefront per SIMD before and after, 2 ns each.  So the words to load are counted in fours (6 workgroups loaded 16 where 5 are real), a
+// word is added as it is, the poison flag comes with the first words and not before them, and the words are cleared 16 bytes per lane with
+// plain stores, which are acknowledged sooner than device-scope ones (nobody looks at them before the launch ends).  Before / now (us):
+// list at 50 % 4096 x 4096 4.95 / 4.72, 14336 x 4096 6.95 / 6.75, 4096 x 14336 7.20 / 6.99, one launch at 40 % 4096 x 11008 7.22 / 6.94, dense
+// 5120 x 5120 6.78 / 6.58, 4 rows 8192 x 28672 at 70 % 25.6 / 25.1, 2-bit 4096 x 4096 6.05 / 5.93; block-rows that are spread gain less (1024 x 4096
+// 4.56 / 4.47).
 //
 // Why the wait ends.  A whole block-row has all its workgroups on one XCD, where they are dispatched in index order: the
 // reducer has the highest index, so everything it waits for is running or finished.  The workgroups of a SPREAD block-row
@@ -236,15 +242,44 @@ hipError_t launch_gemv_list(int waves, int batch, bool one_group, int grid, hipS
 // (word 0 of its head): a late word of the abandoned call could otherwise be taken for a later call's, so from
 // then on every call on that workspace yields NaN until spqt_workspace_init clears it.
 __device__ __forceinline__ uint32_t exchange_word(float v) {
-    const uint32_t w = ~as_u32(v);
-    return w ? w : 1u;
+    const uint32_t w = as_u32(v);
+    return w ? w : 0x80000000u;
 }
+// Keeps the computation of a value where it stands: the compiler would move it down to its use, behind a wait.  (No instruction.)
+template <class V>
+__device__ __forceinline__ void compute_here(V &v) { asm volatile("" : "+v"(v)); }
+// The same for a pointer to global memory in scalar registers.
+template <class V>
+__device__ __forceinline__ void read_here(V *&p) {
+    uint64_t bits = (uint64_t)p;
+    asm volatile("" : "+s"(bits));
+    p = (V *)(__attribute__((address_space(1))) V *)bits;
+}
+
+// Where a workgroup's outputs go.  read_now() comes once the first weights are requested: the kernel's last arguments are not in registers when
+// it starts, and reading them where they are used puts a memory access on the way to the exchange.
+template <int OUT>
+struct Outputs {               // OUT: values of a workgroup
+    float *y;
+    uint32_t *ws, *slots, *mine;    // the workspace, the exchange words of the block-row, and those of this workgroup
+    int M, s, S, t;
+    bool y_half, spread, reducer;
+    // one kernel argument carries M (<= 2^24) and the flags; the build with silent producers is for give-ups only
+    __device__ __forceinline__ Outputs(int t_, int s_, int S_, int T, uint32_t *ws_, float *y_, int m_and_flags)
+        : y(y_), ws(ws_), slots(nullptr), mine(nullptr), M(m_and_flags & kRowsMask), s(s_), S(S_), t(t_),
+          y_half((m_and_flags & kHalfOutputBit) != 0), spread(is_spread(t_, T) && !kMuteProducers), reducer(S_ > 1 && s_ == S_ - 1) {}
+    __device__ __forceinline__ void read_now() {
+        read_here(y);
+        read_here(ws);
+        slots = ws + kWorkspaceHead / 4 + (size_t)((uint32_t)t * (uint32_t)S) * OUT;
+        mine = slots + (size_t)(uint32_t)s * OUT;
+        read_here(slots);
+        read_here(mine);
+    }
+};
+
 template <int WAVES, int BATCH, int ROWS = kTileRows>
-__device__ __forceinline__ void combine_block_row(const float *red, int tid, int t, int s, int S, int T, uint32_t *ws,
-                                                  float *__restrict__ y, int m_and_flags) {
-    // One kernel argument carries both (M <= 2^24).
-    const int M = m_and_flags & kRowsMask;
-    const bool y_half = (m_and_flags & kHalfOutputBit) != 0;
+__device__ __forceinline__ void combine_block_row(const float *red, int tid, const Outputs<BATCH * ROWS> &o) {
     constexpr int kOut = BATCH * ROWS;           // values one workgroup contributes: [BATCH][ROWS]
     constexpr int kThreads = WAVES * 64;
     constexpr int kVals = kOut > kThreads ? 2 : 1;     // adjacent values a thread moves at once: 64-bit or 32-bit accesses
@@ -254,12 +289,9 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, int
     // A thread that owns several units handles 2 of them together, so that the reducer's loads for
     // all of them are in flight at once (one round trip instead of one per unit).
     constexpr int kTogether = kPerThread < 2 ? kPerThread : 2;
-    Word *slots = reinterpret_cast<Word *>(ws + kWorkspaceHead / 4) + (size_t)t * S * kUnits;    // [S][kUnits]; S - 1: handed over
-    const bool reducer = S > 1 && s == S - 1;
-    const bool spread = is_spread(t, T) && !kMuteProducers;   // the build with silent producers is for give-ups only
-    uint32_t poisoned = 0u;
-    if (reducer) poisoned = __hip_atomic_load(ws, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (int i0 = tid; i0 < kUnits; i0 += kTogether * kThreads) {
+    const int S = o.S;
+    Word *slots = reinterpret_cast<Word *>(o.slots);    // [S][kUnits]; S - 1: handed over
+        for (int i0 = tid; kUnits == kThreads || i0 < kUnits; i0 += kTogether * kThreads) {
         uint32_t at[kTogether];
         float sum[kTogether][kVals];
 #pragma unroll
@@ -267,20 +299,25 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, int
             at[i] = (uint32_t)(i0 + i * kThreads < kUnits ? i0 + i * kThreads : i0);
 #pragma unroll
             for (int q = 0; q < kVals; ++q) {
-                sum[i][q] = 0.0f;
+                sum[i][q] = red[kVals * at[i] + q];
 #pragma unroll
-                for (int w2 = 0; w2 < WAVES; ++w2) sum[i][q] += red[w2 * kOut + kVals * at[i] + q];
+                for (int w2 = 1; w2 < WAVES; ++w2) sum[i][q] += red[w2 * kOut + kVals * at[i] + q];
             }
         }
         // fp32 output, or the same value rounded to fp16 (nearest even) when the caller asked for it;
         // rows past M are the last block-row's zero padding
+        uint32_t y_at[kTogether];                // element number, less than 2^26
+        int rows_left[kTogether];
+#pragma unroll
+        for (int i = 0; i < kTogether; ++i) {
+            const int r = (int)(kVals * at[i]), row = o.t * ROWS + r % ROWS;
+            y_at[i] = (uint32_t)((r / ROWS) * o.M + row);
+            rows_left[i] = o.M - row;
+        }
         auto store_y = [&](int i, int q, float v) {
-            const int r = (int)(kVals * at[i]) + q;
-            const int row = t * ROWS + r % ROWS;
-            const size_t y_at = (size_t)(r / ROWS) * M + row;
-            if (row < M) {
-                if (y_half) reinterpret_cast<_Float16 *>(y)[y_at] = (_Float16)v;
-                else y[y_at] = v;
+            if (q < rows_left[i]) {
+                if (o.y_half) reinterpret_cast<_Float16 *>(o.y)[y_at[i] + (uint32_t)q] = (_Float16)v;
+                else o.y[y_at[i] + (uint32_t)q] = v;
             }
         };
         auto word_of = [&](const float (&values)[kVals]) -> Word {
@@ -288,12 +325,13 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, int
             if (kVals == 2) word |= (Word)((unsigned long long)exchange_word(values[kVals - 1]) << 32);
             return word;
         };
+        auto value_of = [&](Word word, int q) { return as_float((uint32_t)((unsigned long long)word >> (32 * q))); };
         auto publish = [&]() {
 #pragma unroll
             for (int i = 0; i < kTogether; ++i) {
                 if (i > 0 && at[i] == at[0]) continue;   // a clamped duplicate: already published
                 if (kMuteProducers) continue;
-                __hip_atomic_store(slots + (size_t)s * kUnits + at[i], word_of(sum[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(reinterpret_cast<Word *>(o.mine) + at[i], word_of(sum[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         };
         bool handed_over = false;                // (wave-uniform) the reducer of a spread block-row has not waited for all
@@ -302,90 +340,96 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, int
             for (int i = 0; i < kTogether; ++i)
 #pragma unroll
                 for (int q = 0; q < kVals; ++q) store_y(i, q, sum[i][q]);
-        } else if (!reducer) {
+        } else if (!o.reducer) {
             publish();
-            if (spread) {
+            if (o.spread) {
                 // A device-scope store has reached every XCD when it is acknowledged: of two threads that publish and then look
                 // for each other's words one at least finds them.
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 Word there = 0;
 #pragma unroll
                 for (int i = 0; i < kTogether; ++i)
-                    there |= __hip_atomic_load(slots + (size_t)(S - 1) * kUnits + at[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    there |= __hip_atomic_load(slots + (size_t)((S - 1) * kUnits) + at[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 handed_over = __ballot(there != 0) != 0ull;
             }
         } else {
+            const uint32_t poisoned = __hip_atomic_load(o.ws, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // comes with the first words
             float total[kTogether][kVals];
 #pragma unroll
-            for (int i = 0; i < kTogether; ++i)
+            for (int i = 0; i < kTogether; ++i) {
+                compute_here(y_at[i]);
+                compute_here(rows_left[i]);
 #pragma unroll
-                for (int q = 0; q < kVals; ++q) total[i][q] = 0.0f;
-            bool gave_up = false;
-            int p0 = 0;                          // partial sums consumed so far
-            // N partial sums per round; with few workgroups per block-row the larger N would read some of them many times
-            auto collect = [&](auto count) {
-                constexpr int N = decltype(count)::value;
-                for (; p0 < S - 1; p0 += N) {
-                    Word v[kTogether][N];
-                    const bool at_once = kAlwaysHandOver && spread && p0 + N >= S - 1;
-                    int polls = 0;
-                    bool all_here;
-                    do {
-                        // unconditional loads back to back (clamped index), then one check
+                for (int q = 0; q < kVals; ++q) {
+                    total[i][q] = 0.0f;
+                    compute_here(sum[i][q]);
+                }
+            }
+            bool all_here = true;                // wave-uniform
+            // N partial sums, of which those from number SURE on may lie behind the block-row's: their words are loaded (they are inside
+            // the workspace, which holds two words for each of these) and not looked at.
+            auto collect = [&](auto count, auto sure, int p0) {
+                constexpr int N = decltype(count)::value, SURE = decltype(sure)::value;
+                Word v[kTogether][N];
+                const bool at_once = kAlwaysHandOver && o.spread && p0 + N >= S - 1;
+                const Word *from = slots + (size_t)(p0 * kUnits);
+                int polls = 0;
+                do {
+                    // unconditional loads back to back, then one check
 #pragma unroll
-                        for (int j = 0; j < N; ++j) {
-                            const Word *from = slots + (size_t)(p0 + j < S - 1 ? p0 + j : S - 2) * kUnits;   // wave-uniform
+                    for (int j = 0; j < N; ++j)
 #pragma unroll
-                            for (int i = 0; i < kTogether; ++i)
-                                v[i][j] = __hip_atomic_load(from + at[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        }
-                        uint32_t least = ~0u;   // one running minimum: a comparison per word costs 0.5 us here
+                        for (int i = 0; i < kTogether; ++i)
+                            v[i][j] = __hip_atomic_load(from + j * kUnits + at[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    uint32_t least = ~0u;   // one running minimum: a comparison per word costs 0.5 us here
+#pragma unroll
+                    for (int j = 0; j < N; ++j)
 #pragma unroll
                         for (int i = 0; i < kTogether; ++i)
 #pragma unroll
-                            for (int j = 0; j < N; ++j)
-#pragma unroll
-                                for (int q = 0; q < kVals; ++q) {
-                                    const uint32_t word = (uint32_t)((unsigned long long)v[i][j] >> (32 * q));
-                                    least = word < least ? word : least;
-                                }
-                        all_here = least != 0u;
-                    } while (!all_here && !at_once && ++polls < (spread ? kHandOverPolls : kMaxPolls));
-                    if (spread && (at_once || __ballot(!all_here) != 0ull)) {     // wave-uniform, like p0: the addresses stay scalar
-                        handed_over = true;
-                        return;
-                    }
-                    gave_up = gave_up || !all_here;
-#pragma unroll
-                    for (int j = 0; j < N; ++j)
-                        if (p0 + j < S - 1) {
-                            Word *from = slots + (size_t)(p0 + j) * kUnits;
-#pragma unroll
-                            for (int i = 0; i < kTogether; ++i) {
-#pragma unroll
-                                for (int q = 0; q < kVals; ++q)
-                                    total[i][q] += as_float(~(uint32_t)((unsigned long long)v[i][j] >> (32 * q)));
-                                // consumed: the words go back to zero for whatever call comes next
-                                __hip_atomic_store(from + at[i], (Word)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            for (int q = 0; q < kVals; ++q) {
+                                uint32_t word = (uint32_t)((unsigned long long)v[i][j] >> (32 * q));
+                                if (j >= SURE) word = p0 + j < S - 1 ? word : ~0u;
+                                least = word < least ? word : least;
                             }
+                    all_here = __builtin_amdgcn_ballot_w64(least == 0u) == 0ull;
+                } while (!all_here && !at_once && ++polls < (o.spread ? kHandOverPolls : kMaxPolls));
+                if (at_once) all_here = false;
+#pragma unroll
+                for (int j = 0; j < N; ++j)
+#pragma unroll
+                    for (int i = 0; i < kTogether; ++i)
+#pragma unroll
+                        for (int q = 0; q < kVals; ++q) {
+                            const float f = value_of(v[i][j], q);
+                            total[i][q] += j < SURE || p0 + j < S - 1 ? f : 0.0f;
                         }
-                }
             };
-            if (S <= 5) collect(std::integral_constant<int, 4>{});
-            else collect(std::integral_constant<int, 16>{});
-            if (!handed_over) {
-                if (gave_up) __hip_atomic_store(ws, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const bool bad = gave_up || poisoned;
+            typedef std::integral_constant<int, 1> One;
+            if (S <= 5) collect(std::integral_constant<int, 4>{}, One{}, 0);
+            else if (S <= 9) collect(std::integral_constant<int, 8>{}, std::integral_constant<int, 5>{}, 0);
+            else if (S <= 13) collect(std::integral_constant<int, 12>{}, std::integral_constant<int, 9>{}, 0);
+            else if (S <= 17) collect(std::integral_constant<int, 16>{}, std::integral_constant<int, 13>{}, 0);
+            else
+                for (int p0 = 0; p0 < S - 1 && all_here; p0 += 16) collect(std::integral_constant<int, 16>{}, One{}, p0);
+            if (all_here || !o.spread) {
+                if (!all_here) __hip_atomic_store(o.ws, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const bool bad = !all_here || poisoned;
 #pragma unroll
                 for (int i = 0; i < kTogether; ++i)
 #pragma unroll
                     for (int q = 0; q < kVals; ++q) store_y(i, q, bad ? __builtin_nanf("") : total[i][q] + sum[i][q]);
-            } else {
-                // what was consumed in earlier rounds (no default launch shape has several) is handed over as the first word
-                for (int p = 0; p < p0; ++p)
+                // Consumed: the words go back to zero for whatever call comes next.  A wavefront clears what its own lanes have seen, 16 bytes
+                // per lane, i.e. several partial sums at a time.
+                constexpr int kLanes = 64 * (int)sizeof(Word) / 16;      // lanes that cover the wavefront's words of one partial sum
 #pragma unroll
-                    for (int i = 0; i < kTogether; ++i)
-                        __hip_atomic_store(slots + (size_t)p * kUnits + at[i], p ? (Word)~0ull : word_of(total[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                for (int i = 0; i < kTogether; ++i) {
+                    if (i > 0 && at[i] == at[0]) continue;
+                    u32x4 *to = reinterpret_cast<u32x4 *>(slots + (at[i] & ~63u)) + (tid & (kLanes - 1));
+                    for (int p = (tid & 63) / kLanes; p < S - 1; p += 64 / kLanes) to[p * (kUnits * (int)sizeof(Word) / 16)] = u32x4{0u, 0u, 0u, 0u};
+                }
+            } else {
+                handed_over = true;
                 publish();
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
@@ -398,25 +442,26 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, int
                 Word *from = slots + at[i];
                 bool all_here = true;
                 for (int p = S - 1; p >= 0 && all_here; --p)
-                    all_here = __hip_atomic_load(from + (size_t)p * kUnits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+                    all_here = __hip_atomic_load(from + (size_t)(p * kUnits), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
                 if (!all_here) continue;         // whoever publishes the missing word comes by here too
-                const Word own = __hip_atomic_exchange(from + (size_t)(S - 1) * kUnits, (Word)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const Word own = __hip_atomic_exchange(from + (size_t)((S - 1) * kUnits), (Word)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (own == 0) continue;          // another thread does it
-                const uint32_t bad = __hip_atomic_load(ws, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const uint32_t bad = __hip_atomic_load(o.ws, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 float total[kVals];
 #pragma unroll
                 for (int q = 0; q < kVals; ++q) total[q] = 0.0f;
 #pragma unroll 1
                 for (int p = 0; p < S; ++p) {
-                    const Word v = p == S - 1 ? own : __hip_atomic_load(from + (size_t)p * kUnits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const Word v = p == S - 1 ? own : __hip_atomic_load(from + (size_t)(p * kUnits), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-                    for (int q = 0; q < kVals; ++q) total[q] += as_float(~(uint32_t)((unsigned long long)v >> (32 * q)));
-                    if (p < S - 1) __hip_atomic_store(from + (size_t)p * kUnits, (Word)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    for (int q = 0; q < kVals; ++q) total[q] += value_of(v, q);
+                    if (p < S - 1) __hip_atomic_store(from + (size_t)(p * kUnits), (Word)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
 #pragma unroll
                 for (int q = 0; q < kVals; ++q) store_y(i, q, bad ? __builtin_nanf("") : total[q]);
             }
         }
+        if (kUnits == kThreads) break;
     }
 }
 

@@ -38,6 +38,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
     const int n_raw = DENSE ? K : *count;      // requested first
     int t, s;
     if (!block_of<WAVES>(blockIdx.x, S, T, inv, t, s)) return;
+    Outputs<BATCH * kTileRows> outputs(t, s, S, T, ws, y, M);
 
     // (a count outside 0..K cannot come from spqt_gather; clamping keeps a corrupt one inside idx)
     const int n_ns = n_raw < 0 ? 0 : (n_raw > K ? K : n_raw);
@@ -96,7 +97,9 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
         k_next = all_kept ? pos + lane : fetch_k(pos);
         SPQT_TL_WAIT(2);
         run_passes<BATCH, GROUPS, false>(staged[wave], row_base, chunk_b, lane, n8, out4, part, pos, h, head, [&](int p) { return p < end; },
-                                  [&]() {}, [&]() { SPQT_TL_WAIT(3); }, acc);
+                                  [&]() { outputs.read_now(); }, [&]() { SPQT_TL_WAIT(3); }, acc);
+    } else {
+        outputs.read_now();
     }
 
     SPQT_TL(4);
@@ -107,7 +110,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
                                                              acc[b][2] * kEvenUnit, acc[b][3] * kOddUnit};
     __syncthreads();
     SPQT_TL(5);
-    combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, t, s, S, T, ws, y, M);
+    combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, outputs);
     SPQT_TL_END(WAVES, wave, lane, S > 1 && s == S - 1);
 }
 

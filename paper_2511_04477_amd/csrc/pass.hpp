@@ -221,9 +221,9 @@ __device__ __forceinline__ void run_passes(StagedX &staged, const uint8_t *row_b
     u32x4 x0, x1;
     f32x4 d[4];
     pos = head(pos);
-    first_requested();
     load_columns<0, 16>(columns, h.off, n8, w);
     load_scales<BATCH, GROUPS>(row_base, chunk_b, out4, h, sc);
+    first_requested();
     first_here();
     while (more(pos)) {
         stage_x<BATCH>(staged, lane, h.j, negated(turn), h.xraw);
