@@ -89,7 +89,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
                 const int c = unit_at(at, i) + lane;
 #pragma unroll
                 for (int b = 0; b < BATCH; ++b)
-                    xr[i][b] = __hip_atomic_load(x + (size_t)b * K + (c < K ? c : K - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                    xr[i][b] = __hip_atomic_load(element(x, (uint32_t)(b * K + (c < K ? c : K - 1))), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
             }
         };
 
@@ -134,22 +134,14 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
             const u32x2 v = ring[wave][e & (kRing - 1)];
             const uint32_t v23 = BATCH > 2 ? ring23[wave][e & (kRing - 1)] : 0u;
             const int kk = e < filled ? (int)v.x : -1;
-            h.g = kk >> log2g;
-            const Deal d = deal_groups<kGroups>(kk, h.g, lane);
-            const uint32_t off_own = (uint32_t)h.g * chunk_b + (uint32_t)(kk & ((1 << log2g) - 1)) * kColBytes;
-            const uint32_t off_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)off_own);
-            h.off = slot_order(d.take ? off_own : (d.n ? off_first : 0u), lane);
-            h.n = d.n;
-            h.starts = d.starts;
-            h.g = d.n ? h.g : 0;
-            h.j = d.take ? d.j : -1;
+            const Deal d = deal_columns<kGroups>(h, kk, log2g, chunk_b, lane);
             const uint32_t xv[4] = {v.y & 0xFFFFu, v.y >> 16, v23 & 0xFFFFu, v23 >> 16};
 #pragma unroll
             for (int b = 0; b < BATCH; ++b) h.xraw[b] = (uint16_t)xv[b];
             return p + d.n;
         };
         fetch_x(u);
-        run_passes<BATCH, kGroups, true>(staged[wave], row_base, chunk_b, lane, n8, out4, part, 0, h, head,
+        run_passes<BATCH, kGroups, true>(staged[wave], row_base, lane, n8, out4, part, 0, h, head,
                                    [&](int p) { return p < filled || u < end; }, [&]() { outputs.read_now(); }, [&]() {}, acc);
     } else {
         outputs.read_now();

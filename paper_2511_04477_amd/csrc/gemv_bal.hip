@@ -181,18 +181,11 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
         PassHead<1> h;
         auto head = [&](int p) -> int {
             const int kk = fetch_k(p, h.xraw[0]);
-            h.g = kk >> log2g;
-            const Deal d = deal_groups<kGroups>(kk, h.g, lane);
-            const uint32_t off_own = (uint32_t)h.g * chunk_b + (uint32_t)(kk & ((1 << log2g) - 1)) * kColBytes;
-            const uint32_t off_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)off_own);
-            h.off = slot_order(d.take ? off_own : off_first, lane);
-            h.n = d.n;
-            h.starts = d.starts;
-            h.j = d.take ? d.j : -1;
+            const Deal d = deal_columns<kGroups>(h, kk, log2g, chunk_b, lane);
             return p + d.n;
         };
         // 4. GEMV
-        run_passes<1, kGroups, false>(staged[wave], row_base, chunk_b, lane, n8, out4, part, 0, h, head, [&](int p) { return p < total; },
+        run_passes<1, kGroups, false>(staged[wave], row_base, lane, n8, out4, part, 0, h, head, [&](int p) { return p < total; },
                                [&]() { outputs.read_now(); SPQT_TL(2); }, [&]() { SPQT_TL_WAIT(3); }, acc);
     } else {
         outputs.read_now();

@@ -69,7 +69,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
         auto fetch_k = [&](int p) -> int {
             const int e = p + lane;
             if (DENSE) return e;
-            return __hip_atomic_load(idx + (e < n_ns ? e : n_ns - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            return __hip_atomic_load(element(idx, (uint32_t)(e < n_ns ? e : n_ns - 1)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         };
 
         int k_next;                // the lane's list entry for the pass whose HEAD comes next
@@ -79,24 +79,16 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
         // entries of the pass after it and its x.  Returns where the pass after it starts.
         auto head = [&](int p) -> int {
             const int kk = p + lane < end ? (BATCH == 1 && all_kept ? p + lane : k_next) : -1;
-            h.g = kk >> log2g;
-            const Deal d = deal_groups<GROUPS>(kk, h.g, lane);
-            const int k_own = d.take ? kk : 0;
-            const uint32_t off_own = (uint32_t)h.g * chunk_b + (uint32_t)(kk & ((1 << log2g) - 1)) * kColBytes;
-            // slots past the pass point at its first column (a line that is fetched anyway) and carry x = 0
-            const uint32_t off_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)off_own);
-            h.off = slot_order(d.take ? off_own : off_first, lane);
-            h.n = d.n;
-            h.starts = d.starts;
-            h.j = d.take ? d.j : -1;
+            const Deal d = deal_columns<GROUPS>(h, kk, log2g, chunk_b, lane);
+            const uint32_t k_own = d.take ? (uint32_t)kk : 0u;
             k_next = fetch_k(p + d.n);
 #pragma unroll
-            for (int b = 0; b < BATCH; ++b) h.xraw[b] = x[(size_t)b * K + k_own];
+            for (int b = 0; b < BATCH; ++b) h.xraw[b] = *element(x, (uint32_t)(b * K) + k_own);
             return p + d.n;
         };
         k_next = all_kept ? pos + lane : fetch_k(pos);
         SPQT_TL_WAIT(2);
-        run_passes<BATCH, GROUPS, false>(staged[wave], row_base, chunk_b, lane, n8, out4, part, pos, h, head, [&](int p) { return p < end; },
+        run_passes<BATCH, GROUPS, false>(staged[wave], row_base, lane, n8, out4, part, pos, h, head, [&](int p) { return p < end; },
                                   [&]() { outputs.read_now(); }, [&]() { SPQT_TL_WAIT(3); }, acc);
     } else {
         outputs.read_now();

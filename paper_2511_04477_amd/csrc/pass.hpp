@@ -8,7 +8,11 @@
 // 16 n .. 16 n + 15 of the block-row, n = l % 16, at the 16 columns of its quarter.  Lane e deals entry e; its column's offset
 // moves to lane (c, u) once (slot_order), i.e. into the quarter that reads it, and from there to the other 15 lanes by DPP
 // (row_newbcast).
-// A pass costs about 0.9 us where a SIMD holds one wavefront, and slices end with a short one: leaving half of its products out
+// What bounds a pass: its instructions, where a SIMD holds one wavefront (2 ns each).  About 500 of them became 420 when the masked A came to be read
+// from LDS, the sign of x to be undone by the addend of the next pass, and scales to be found with one v_readlane each; before / now (us): list
+// at 50 % 28672 x 8192 16.4 / 15.8, one launch at 40 % 11008 x 4096 7.28 / 7.07, 2 rows with their own sets at 65 % 14336 x 4096 8.25 / 7.99, dense
+// 13824 x 5120 10.16 / 9.99.
+// Slices end with a short one: leaving half of its products out
 // takes chains of GEMVs from 356.7 to 353.1 us (one launch, 48 of 11008 x 4096 and its transpose, 40 %), 208.6 to 205.0 (two rows with
 // their own sets, 24 of 14336 x 4096 and its transpose) and 166.9 to 164.9 (four rows, 6 of 28672 x 8192 and its transpose).
 //
@@ -50,7 +54,18 @@ constexpr int groups_per_pass(int batch) { return 4 / padded_rows(batch); }
 // x of the 64 slots of a pass as fp16, [j][slot] with j as above; row 4 takes what no product reads.
 struct StagedX {
     uint16_t v[5][kPassCols];
-    uint16_t pad[8];   // a multiple of 16 bytes per wavefront
+    uint16_t zeros[16];
+};
+// Where in StagedX a lane reads its part of A: the x of row j = lane % 4 at the 16 slots of its quarter, in the variant of A that is the
+// lane's; zeros in the three others.  (Reading the zeros costs one instruction per 16 bytes; masking what is read, four.)
+struct ReadsX {
+    const u32x4 *mine, *of_variant[4];
+    __device__ __forceinline__ ReadsX(StagedX &xs, int lane) {
+        if (lane < 8) reinterpret_cast<uint32_t *>(xs.zeros)[lane] = 0u;
+        mine = reinterpret_cast<const u32x4 *>(&xs.v[lane & 3][lane & 48]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) of_variant[v] = ((lane >> 2) & 3) == v ? mine : reinterpret_cast<const u32x4 *>(xs.zeros);
+    }
 };
 
 // v of lane U of the caller's row of 16 lanes, in every lane of the row.
@@ -75,18 +90,18 @@ __device__ __forceinline__ void load_columns(const uint8_t *base, uint32_t off, 
 }
 
 // Products of the 32 slots (c, u), u = 8 SET .. 8 SET + 7: d[p][j] += sum of code(row 16 n + 4 v + p, slot) * x(j, slot)
-// in units of kEvenUnit (even p) or kOddUnit (odd p).  xa = the lane's x of those slots: row j = lane % 4 of the staged x,
-// quarter lane / 16.
+// in units of kEvenUnit (even p) or kOddUnit (odd p).
 // A code sits at bits 2..5 or 6..9 of its half, not at 0..3 or 4..7 (which would save one shift in six instructions): the
 // matrix cores align products by the exponent FIELDS, so bits that a subnormal has above its code are bits of
 // precision lost in every product.
 template <int SET>
-__device__ __forceinline__ void half_pass(const u32x2 (&w)[16], u32x4 xa, int lane, f32x4 (&d)[4]) {
-    const int variant = (lane >> 2) & 3;
+__device__ __forceinline__ void half_pass(const u32x2 (&w)[16], const ReadsX &rx, f32x4 (&d)[4]) {
+    u32x4 x[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[v] = rx.of_variant[v][SET];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-        const bool mine = variant == v;
-        const f16x8 a = as_f16x8(u32x4{mine ? xa.x : 0u, mine ? xa.y : 0u, mine ? xa.z : 0u, mine ? xa.w : 0u});
+        const f16x8 a = as_f16x8(x[v]);
         const uint32_t sel = (v & 1) ? 0x07060302u : 0x05040100u;   // which 16 bits of the dword: rows 0..3 or 4..7 of it
         uint32_t t[4];
 #pragma unroll
@@ -104,11 +119,9 @@ __device__ __forceinline__ void half_pass(const u32x2 (&w)[16], u32x4 xa, int la
 }
 
 // The bias of the offset-binary codes (stored = q + 8) enters as the accumulators' initial value: the product of x with
-// the constant -8 in the codes' own units.  x0, x1 = the lane's x of slots u < 8 and u >= 8.
-__device__ __forceinline__ void start_products(const StagedX &xs, int lane, u32x4 &x0, u32x4 &x1, f32x4 (&d)[4]) {
-    const u32x4 *src = reinterpret_cast<const u32x4 *>(&xs.v[lane & 3][lane & 48]);
-    x0 = src[0];
-    x1 = src[1];
+// the constant -8 in the codes' own units.
+__device__ __forceinline__ void start_products(const ReadsX &rx, f32x4 (&d)[4]) {
+    const u32x4 x0 = rx.mine[0], x1 = rx.mine[1];
     const f16x8 even = as_f16x8(u32x4{0x80208020u, 0x80208020u, 0x80208020u, 0x80208020u});
     const f16x8 odd = as_f16x8(u32x4{0x82008200u, 0x82008200u, 0x82008200u, 0x82008200u});
     const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -118,28 +131,34 @@ __device__ __forceinline__ void start_products(const StagedX &xs, int lane, u32x
     d[3] = d[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(x1), odd, d[1], 0, 0, 0);
 }
 
-// Whether a pass is computed with -x (and its sums subtracted).  The matrix cores round the terms of a product DOWN, so a
+// Every other pass is computed with -x.  The matrix cores round the terms of a product DOWN, so a
 // sum over many passes carries a negative bias, relative to the result in proportion to sqrt(K).  With x negated the bias
 // changes sign, so every other pass is negated and it cancels: against 64-bit arithmetic (relative 2-norm, 1024 x 28672
 // dense, one row) 4.4e-6 -> 4.6e-7 for Laplace x and 1.3e-5 -> 7.8e-7 for SiLU products.  (The 4-wide products of
-// v_mfma_f32_4x4x4 have a bias of the same sign, 1.1e-5 and 2.7e-5.)  `turn` counts passes, from another start in every
-// wavefront of a block-row, so slices of one pass cancel too.
-__device__ __forceinline__ bool negated(int turn) { return (turn & 1) != 0; }
+// v_mfma_f32_4x4x4 have a bias of the same sign, 1.1e-5 and 2.7e-5.)  The wavefronts of a block-row start with different signs,
+// so slices of one pass cancel too.
+constexpr uint32_t kSignOfX = 0x8000u;
+
+// Element i of an array in global memory, with a 32-bit byte offset (the arrays that are read so are far smaller than 4 GB).
+template <class V>
+__device__ __forceinline__ const V *element(const V *base, uint32_t i) {
+    return reinterpret_cast<const V *>(reinterpret_cast<const char *>(base) + (size_t)(i * (uint32_t)sizeof(V)));
+}
 
 // Applies the scales of a pass's groups (sc[g] = the fp16 scales of the lane's 4 rows in group g of the pass) and adds to
-// the lane's running sums, which stay in the products' units.
+// the lane's running sums, which stay in the products' units.  The sums carry the sign of the pass's x: each pass subtracts the sums
+// of those before it.
 template <int BATCH, int GROUPS>
-__device__ __forceinline__ void add_scaled(const f32x4 (&d)[4], const u32x2 (&sc)[GROUPS], bool neg, float (&acc)[BATCH][4]) {
+__device__ __forceinline__ void add_scaled(const f32x4 (&d)[4], const u32x2 (&sc)[GROUPS], float (&acc)[BATCH][4]) {
     constexpr int kRows = padded_rows(BATCH);
-    const uint32_t sign = neg ? 0x80008000u : 0u;
 #pragma unroll
     for (int g = 0; g < GROUPS; ++g) {
-        const f16x2 h01 = as_f16x2(sc[g].x ^ sign), h23 = as_f16x2(sc[g].y ^ sign);
+        const f16x2 h01 = as_f16x2(sc[g].x), h23 = as_f16x2(sc[g].y);
         const float s[4] = {(float)h01.x, (float)h01.y, (float)h23.x, (float)h23.y};
 #pragma unroll
         for (int b = 0; b < BATCH; ++b)
 #pragma unroll
-            for (int p = 0; p < 4; ++p) acc[b][p] = __builtin_fmaf(s[p], d[p][g * kRows + b], acc[b][p]);
+            for (int p = 0; p < 4; ++p) acc[b][p] = __builtin_fmaf(s[p], d[p][g * kRows + b], g == 0 ? -acc[b][p] : acc[b][p]);
     }
 }
 
@@ -157,18 +176,18 @@ __device__ __forceinline__ Deal deal_groups(int kk, int g, int lane) {
     Deal d;
     const bool cand = kk >= 0;
     const int gprev = __builtin_amdgcn_update_dpp(-1, g, 0x138, 0xf, 0xf, false);   // wave_shr:1; lane 0 keeps -1
-    const uint64_t starts = __ballot(cand && (lane == 0 || g != gprev));
-    const int before = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(starts >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)starts, 0u));
-    d.j = before - 1 + (int)((starts >> lane) & 1ull);
-    d.take = cand && d.j < GROUPS;
-    d.n = __builtin_amdgcn_readfirstlane((int)__popcll(__ballot(d.take)));
-    d.starts = starts;
+    const uint64_t cands = __builtin_amdgcn_ballot_w64(cand);
+    d.starts = __builtin_amdgcn_ballot_w64(g != gprev) & cands;
+    const uint64_t further = d.starts >> 1;      // counted below lane l: the starts at lanes 1 .. l
+    d.j = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(further >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)further, 0u));
+    d.n = (int)__popcll(__builtin_amdgcn_ballot_w64(d.j < GROUPS) & cands);
+    d.take = lane < d.n;                         // candidates and groups come in the order of the lanes
     return d;
 }
 
 // Stages the x of a pass: the entry that lane `lane` deals, in its slot, carries x[b] for group j of the pass (j < 0: none).
 template <int BATCH>
-__device__ __forceinline__ void stage_x(StagedX &xs, int lane, int j, bool neg, const uint16_t (&xraw)[BATCH]) {
+__device__ __forceinline__ void stage_x(StagedX &xs, int lane, int j, uint32_t sign, const uint16_t (&xraw)[BATCH]) {
     constexpr int kRows = padded_rows(BATCH);
     {   // slots that no entry writes must read as zero
         reinterpret_cast<u32x2 *>(&xs.v[0][0])[lane] = u32x2{0u, 0u};
@@ -177,7 +196,7 @@ __device__ __forceinline__ void stage_x(StagedX &xs, int lane, int j, bool neg, 
     // no branch on j >= 0: a divergent one inside the pipeline's loop makes the compiler join the loop's exits with its
     // entry and wait for all loads there
 #pragma unroll
-    for (int b = 0; b < BATCH; ++b) xs.v[j >= 0 ? j * kRows + b : 4][slot_of(lane)] = (uint16_t)(xraw[b] ^ (neg ? 0x8000u : 0u));
+    for (int b = 0; b < BATCH; ++b) xs.v[j >= 0 ? j * kRows + b : 4][slot_of(lane)] = (uint16_t)(xraw[b] ^ sign);
     __builtin_amdgcn_wave_barrier();
 }
 
@@ -187,22 +206,37 @@ struct PassHead {
     uint32_t off;          // byte offset of the column in this lane's SLOT of the pass whose weights are requested next
     int n;                 // entries of that pass (wave-uniform)
     uint64_t starts;       // where the groups of that pass start
-    int g;                 // group of the lane's candidate of that pass
+    uint32_t chunk;        // byte offset of the chunk of the lane's candidate of that pass, of some chunk of the pass where it takes none
     int j;                 // group of the lane's entry inside that pass, or -1: not part of it
     uint16_t xraw[BATCH];  // its x
 };
 
-// The scales of the lane's 4 rows in each group of the pass; groups it does not reach repeat its last one.
+// Deals the candidates kk (-1 past the slice) and notes in h what the pass's loads and products need, but its x.  Lanes that take none point at the
+// pass's first column (a line that is fetched anyway; the first column of all in a pass without entries) and carry x = 0.
+template <int GROUPS, int BATCH>
+__device__ __forceinline__ Deal deal_columns(PassHead<BATCH> &h, int kk, int log2g, uint32_t chunk_b, int lane) {
+    const int g = kk >> log2g;
+    const Deal d = deal_groups<GROUPS>(kk, g, lane);
+    const int k_first = __builtin_amdgcn_readfirstlane(kk);
+    const uint32_t k = (uint32_t)(d.take ? kk : (k_first < 0 ? 0 : k_first));
+    h.chunk = (k >> log2g) * chunk_b;
+    h.off = slot_order(h.chunk + (k & ((1u << log2g) - 1u)) * kColBytes, lane);
+    h.n = d.n;
+    h.starts = d.starts;
+    h.j = d.take ? d.j : -1;
+    return d;
+}
+
+// The scales of the lane's 4 rows in each group of the pass; behind its last one, those of some group of it.
 template <int BATCH, int GROUPS>
-__device__ __forceinline__ void load_scales(const uint8_t *row_base, uint32_t chunk_b, uint32_t out4, const PassHead<BATCH> &h, u32x2 (&sc)[GROUPS]) {
+__device__ __forceinline__ void load_scales(const uint8_t *row_base, uint32_t out4, const PassHead<BATCH> &h, u32x2 (&sc)[GROUPS]) {
     uint64_t left = h.starts;
-    int at = 0;
 #pragma unroll
     for (int i = 0; i < GROUPS; ++i) {
-        at = left ? (int)__builtin_ctzll(left) : at;     // selects, no branch
-        left &= left - 1ull;
-        const uint32_t gi = (uint32_t)__builtin_amdgcn_readlane(h.g, at);
-        sc[i] = *reinterpret_cast<const u32x2 *>(row_base + (size_t)(gi * chunk_b) + (size_t)(out4 * 8u));
+        int at;      // the first start that is left, or -1, which v_readlane takes as lane 63
+        asm("s_ff1_i32_b64 %0, %1\n\ts_bitset0_b64 %1, %0" : "=&s"(at), "+s"(left));
+        const uint32_t chunk = (uint32_t)__builtin_amdgcn_readlane((int)h.chunk, at);
+        sc[i] = *reinterpret_cast<const u32x2 *>(row_base + (size_t)(chunk + out4 * 8u));
     }
 }
 
@@ -211,44 +245,52 @@ __device__ __forceinline__ void load_scales(const uint8_t *row_base, uint32_t ch
 // half by half as a pass is multiplied.  EMPTY: a pass may have no entries; its scales, which may be those of a group whose columns
 // are all dropped, are then not applied (infinite ones times its sums, which are zero, would be NaN).  A branch around the adds: one launch, one
 // and two rows, 0.2 % slower on average than without the test, 3 and 4 rows as fast; zeroes in place of the scales cost 0.5 and 0.2 %.
-// first_requested and first_here: where the timeline build stamps.
+// first_requested and first_here: what is done, and where the timeline build stamps, when the first pass is requested.
 template <int BATCH, int GROUPS, bool EMPTY, class Head, class More, class Stamp2, class Stamp3>
-__device__ __forceinline__ void run_passes(StagedX &staged, const uint8_t *row_base, uint32_t chunk_b, int lane, uint32_t n8, uint32_t out4,
-                                           int turn, int pos, PassHead<BATCH> &h, Head head, More more, Stamp2 first_requested,
+__device__ __forceinline__ void run_passes(StagedX &staged, const uint8_t *row_base, int lane, uint32_t n8, uint32_t out4,
+                                           int part, int pos, PassHead<BATCH> &h, Head head, More more, Stamp2 first_requested,
                                            Stamp3 first_here, float (&acc)[BATCH][4]) {
     const uint8_t *columns = row_base + kScaleBytes;
     u32x2 w[16], sc[GROUPS];
-    u32x4 x0, x1;
     f32x4 d[4];
+    uint32_t sign = part & 1 ? kSignOfX : 0u;
     pos = head(pos);
     load_columns<0, 16>(columns, h.off, n8, w);
-    load_scales<BATCH, GROUPS>(row_base, chunk_b, out4, h, sc);
+    load_scales<BATCH, GROUPS>(row_base, out4, h, sc);
+    const ReadsX rx(staged, lane);
     first_requested();
     first_here();
     while (more(pos)) {
-        stage_x<BATCH>(staged, lane, h.j, negated(turn), h.xraw);
+        stage_x<BATCH>(staged, lane, h.j, sign, h.xraw);
         const bool whole = h.n > kPassCols / 2, any = !EMPTY || h.n > 0;
         pos = head(pos);
         keep_order();
-        start_products(staged, lane, x0, x1, d);
-        half_pass<0>(w, x0, lane, d);
+        start_products(rx, d);
+        half_pass<0>(w, rx, d);
         keep_order();
         load_columns<0, 8>(columns, h.off, n8, w);
         keep_order();
-        if (whole) half_pass<1>(w, x1, lane, d);
+        if (whole) half_pass<1>(w, rx, d);
         keep_order();
         load_columns<8, 16>(columns, h.off, n8, w);
         keep_order();
-        if (any) add_scaled<BATCH, GROUPS>(d, sc, negated(turn), acc);
-        load_scales<BATCH, GROUPS>(row_base, chunk_b, out4, h, sc);
-        ++turn;
+        if (any) {
+            add_scaled<BATCH, GROUPS>(d, sc, acc);
+            sign ^= kSignOfX;
+        }
+        load_scales<BATCH, GROUPS>(row_base, out4, h, sc);
         keep_order();
     }
-    stage_x<BATCH>(staged, lane, h.j, negated(turn), h.xraw);
-    start_products(staged, lane, x0, x1, d);
-    half_pass<0>(w, x0, lane, d);
-    if (h.n > kPassCols / 2) half_pass<1>(w, x1, lane, d);
-    if (!EMPTY || h.n > 0) add_scaled<BATCH, GROUPS>(d, sc, negated(turn), acc);
+    stage_x<BATCH>(staged, lane, h.j, sign, h.xraw);
+    start_products(rx, d);
+    half_pass<0>(w, rx, d);
+    if (h.n > kPassCols / 2) half_pass<1>(w, rx, d);
+    if (!EMPTY || h.n > 0) add_scaled<BATCH, GROUPS>(d, sc, acc);
+    else sign ^= kSignOfX;       // the sums still have the sign of the pass before
+#pragma unroll
+    for (int b = 0; b < BATCH; ++b)
+#pragma unroll
+        for (int p = 0; p < 4; ++p) acc[b][p] = as_float(as_u32(acc[b][p]) ^ (sign << 16));
 }
 
 }  // namespace spqt
