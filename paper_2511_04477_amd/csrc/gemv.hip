@@ -151,8 +151,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
     // back to true units, then the WAVES wavefronts are combined through LDS
 #pragma unroll
     for (int b = 0; b < BATCH; ++b)
-        reinterpret_cast<f32x4 *>(red[wave][b])[out4] = f32x4{acc[b][0] * kEvenUnit, acc[b][1] * kOddUnit,
-                                                             acc[b][2] * kEvenUnit, acc[b][3] * kOddUnit};
+        reinterpret_cast<f32x4 *>(red[wave][b])[out4] = f32x4{acc[b][0] * kUnit[0], acc[b][1] * kUnit[1], acc[b][2] * kUnit[2], acc[b][3] * kUnit[3]};
     __syncthreads();
     SPQT_TL(5);
     combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, outputs);

@@ -192,8 +192,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
     }
     SPQT_TL(4);
 
-    reinterpret_cast<f32x4 *>(red[wave][0])[out4] = f32x4{acc[0][0] * kEvenUnit, acc[0][1] * kOddUnit,
-                                                         acc[0][2] * kEvenUnit, acc[0][3] * kOddUnit};
+    reinterpret_cast<f32x4 *>(red[wave][0])[out4] = f32x4{acc[0][0] * kUnit[0], acc[0][1] * kUnit[1], acc[0][2] * kUnit[2], acc[0][3] * kUnit[3]};
     __syncthreads();
     SPQT_TL(5);
     combine_block_row<WAVES, 1>(&red[0][0][0], tid, outputs);

@@ -110,6 +110,12 @@ __device__ __forceinline__ void fma_step(u32x4 w, float xl, float *acc) {
     fma_codes(w.w, xl, xh, acc + 24);
 }
 
+// Element i of an array in global memory, with a 32-bit byte offset (the arrays that are read so are far smaller than 4 GB).
+template <class V>
+__device__ __forceinline__ const V *element(const V *base, uint32_t i) {
+    return reinterpret_cast<const V *>(reinterpret_cast<const char *>(base) + (size_t)(i * (uint32_t)sizeof(V)));
+}
+
 // Keeps the compiler from moving instructions across: it would gather requests behind products, or products before requests.
 __device__ __forceinline__ void keep_order() { __builtin_amdgcn_sched_barrier(0); }
 

@@ -9,19 +9,23 @@
 // moves to lane (c, u) once (slot_order), i.e. into the quarter that reads it, and from there to the other 15 lanes by DPP
 // (row_newbcast).
 // What bounds a pass: its instructions, where a SIMD holds one wavefront (2 ns each).  About 500 of them became 420 when the masked A came to be read
-// from LDS, the sign of x to be undone by the addend of the next pass, and scales to be found with one v_readlane each; before / now (us): list
-// at 50 % 28672 x 8192 16.4 / 15.8, one launch at 40 % 11008 x 4096 7.28 / 7.07, 2 rows with their own sets at 65 % 14336 x 4096 8.25 / 7.99, dense
-// 13824 x 5120 10.16 / 9.99.
+// from LDS, the sign of x to be undone by the addend of the next pass, and scales to be found with one v_readlane each (index list at 50 %
+// 28672 x 8192 16.4 / 15.8 us, one launch at 40 % 11008 x 4096 7.28 / 7.07), and 400 when the two rows that share a dword came to be told apart by A, not by
+// pairing the halves of two columns (before / now, us: dense 5120 x 5120 6.37 / 6.16, 13824 x 5120 8.97 / 8.67, 5120 x 13824 9.30 / 8.98; with a list or in one
+// launch, whose slices also wait for entries, 0 to 1 %: 4096 x 14336 at 50 % with the gather 9.48 / 9.40; 4 rows 28672 x 8192 at 70 % 26.8 / 26.65).
+// Two passes' weights requested ahead of the products (a second buffer) were 3 to 6 % slower: the memory, not the order of the requests, sets
+// when the second pass arrives.
 // Slices end with a short one: leaving half of its products out
 // takes chains of GEMVs from 356.7 to 353.1 us (one launch, 48 of 11008 x 4096 and its transpose, 40 %), 208.6 to 205.0 (two rows with
 // their own sets, 24 of 14336 x 4096 and its transpose) and 166.9 to 164.9 (four rows, 6 of 28672 x 8192 and its transpose).
 //
 // Products: v_mfma_f32_16x16x32_f16 computes D[m][n] += sum over 32 k of A[m][k] * B[k][n]; lane l brings A[l % 16] and
-// B[..][l % 16] at the 8 k of quarter l / 16, i.e. at 8 of the 16 columns of its quarter.  B is ONE row's codes at those
-// columns (fp16 subnormals, code * 2^-22 or 2^-18, shifted and masked after one v_perm_b32), A the raw fp16 x.
+// B[..][l % 16] at the 8 k of quarter l / 16, i.e. at 4 of the 16 columns of its quarter with two k each, h = 0 and 1.  B is one dword of each
+// column, shifted and masked: the halves are ONE code each (fp16 subnormals), of two rows of W.  A is the raw fp16 x, in row m at the k of the half
+// that row m is about and zero at the other: the two rows that share a dword need not be brought apart.
 // The sum over k is the sum over all columns of the pass, so nothing is left to fold across lanes.
-// The 16 rows of A are 4 v + j: v (four variants of A, zero in the other rows) says which four of the lane's 16 rows of
-// W the product belongs to, so that all 16 rows end up in FOUR accumulator tuples D[p], and j = 0..3 separates
+// The 16 rows of A are 4 v + j: v = 2 d + h (d: which dword of the column, two variants of A with zeros in the other rows; h: which half) says which
+// four of the lane's 16 rows of W the product belongs to, so that all 16 rows end up in FOUR accumulator tuples D[p], and j = 0..3 separates
 // activation rows and quantization groups (j = group of the pass * rows + activation row): one activation row takes
 // columns of up to 4 groups per pass, two rows 2 groups, three or four rows one.  Lane (v, n) = (l / 16, l % 16) ends
 // up with rows 16 n + 4 v + p, p = 0..3, in D[p][j]; the group's scale is applied there and the lane's 4 outputs per
@@ -44,27 +48,30 @@ namespace spqt {
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ f16x8 as_f16x8(u32x4 bits) { return __builtin_bit_cast(f16x8, bits); }
 
-// What undoes the units of the products: a code at bits 2..5 of an fp16 half is code * 2^-22, at bits 6..9 code * 2^-18.
-constexpr float kEvenUnit = 4194304.0f, kOddUnit = 262144.0f;
+// Where the four codes of 16 bits of a column run are multiplied, and what undoes the units: a code at bits 6..9 of an fp16 half is code * 2^-18,
+// at bits 4..7 code * 2^-20, at bits 2..5 code * 2^-22.  Code 0 is shifted left by 6, code 1 stays, codes 2 and 3 are shifted right by 6.
+constexpr float kUnit[4] = {262144.0f, 1048576.0f, 4194304.0f, 262144.0f};
 
 // activation rows as the passes count them (3 is treated as 4 with a zero row), and quantization groups per pass
 constexpr int padded_rows(int batch) { return batch == 3 ? 4 : batch; }
 constexpr int groups_per_pass(int batch) { return 4 / padded_rows(batch); }
 
-// x of the 64 slots of a pass as fp16, [j][slot] with j as above; row 4 takes what no product reads.
+// x of the 64 slots of a pass as fp16, a dword per slot: rows 2 j + h, j as above, x in the lower (h = 0) or the upper half (h = 1) of the
+// dword and zero in the other; rows 8 and 9 take what no product reads.  A row is 16 bytes longer than its slots, so that the 8 rows that are
+// read together lie in different banks.
 struct StagedX {
-    uint16_t v[5][kPassCols];
-    uint16_t zeros[16];
+    uint32_t v[10][kPassCols + 4];
+    uint32_t zeros[16];
 };
-// Where in StagedX a lane reads its part of A: the x of row j = lane % 4 at the 16 slots of its quarter, in the variant of A that is the
-// lane's; zeros in the three others.  (Reading the zeros costs one instruction per 16 bytes; masking what is read, four.)
+// Where in StagedX a lane reads its part of A: the x of its row m = 8 d + 4 h + j at the 16 slots of its quarter, in the variant of A that is the
+// lane's; zeros in the other.  (Reading the zeros costs one instruction per 16 bytes; masking what is read, four.)
 struct ReadsX {
-    const u32x4 *mine, *of_variant[4];
+    const u32x4 *mine, *of_variant[2];
     __device__ __forceinline__ ReadsX(StagedX &xs, int lane) {
-        if (lane < 8) reinterpret_cast<uint32_t *>(xs.zeros)[lane] = 0u;
-        mine = reinterpret_cast<const u32x4 *>(&xs.v[lane & 3][lane & 48]);
+        if (lane < 16) xs.zeros[lane] = 0u;
+        mine = reinterpret_cast<const u32x4 *>(&xs.v[2 * (lane & 3) + ((lane >> 2) & 1)][lane & 48]);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) of_variant[v] = ((lane >> 2) & 3) == v ? mine : reinterpret_cast<const u32x4 *>(xs.zeros);
+        for (int d = 0; d < 2; ++d) of_variant[d] = ((lane >> 3) & 1) == d ? mine : reinterpret_cast<const u32x4 *>(xs.zeros);
     }
 };
 
@@ -90,45 +97,45 @@ __device__ __forceinline__ void load_columns(const uint8_t *base, uint32_t off, 
 }
 
 // Products of the 32 slots (c, u), u = 8 SET .. 8 SET + 7: d[p][j] += sum of code(row 16 n + 4 v + p, slot) * x(j, slot)
-// in units of kEvenUnit (even p) or kOddUnit (odd p).
-// A code sits at bits 2..5 or 6..9 of its half, not at 0..3 or 4..7 (which would save one shift in six instructions): the
-// matrix cores align products by the exponent FIELDS, so bits that a subnormal has above its code are bits of
-// precision lost in every product.
+// in units of kUnit[p].
+// The matrix cores align products by the exponent FIELDS, so bits that a subnormal has above its code are bits of
+// precision lost in every product: codes sit as high as one shift per two codes brings them.
 template <int SET>
 __device__ __forceinline__ void half_pass(const u32x2 (&w)[16], const ReadsX &rx, f32x4 (&d)[4]) {
     u32x4 x[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) x[v] = rx.of_variant[v][SET];
+    for (int i = 0; i < 4; ++i) x[i] = rx.of_variant[i & 1][2 * SET + (i >> 1)];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const f16x8 a = as_f16x8(x[v]);
-        const uint32_t sel = (v & 1) ? 0x07060302u : 0x05040100u;   // which 16 bits of the dword: rows 0..3 or 4..7 of it
-        uint32_t t[4];
+    for (int i = 0; i < 4; ++i) {
+        const f16x8 a = as_f16x8(x[i]);
+        const int first = 8 * SET + 4 * (i >> 1), dw = i & 1;
+        u32x4 b[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            t[k] = __builtin_amdgcn_perm(w[8 * SET + 2 * k + 1][v >> 1], w[8 * SET + 2 * k][v >> 1], sel);
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const uint32_t m = (p & 1) ? 0x03C003C0u : 0x003C003Cu;
-            u32x4 b;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) b[k] = (p < 2 ? t[k] << 2 : t[k] >> 6) & m;
-            d[p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, as_f16x8(b), d[p], 0, 0, 0);
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t c = w[first + k][dw], right = c >> 6;
+            b[0][k] = (c << 6) & 0x03C003C0u;
+            b[1][k] = c & 0x00F000F0u;
+            b[2][k] = right & 0x003C003Cu;
+            b[3][k] = right & 0x03C003C0u;
         }
+#pragma unroll
+        for (int p = 0; p < 4; ++p) d[p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, as_f16x8(b[p]), d[p], 0, 0, 0);
     }
 }
 
 // The bias of the offset-binary codes (stored = q + 8) enters as the accumulators' initial value: the product of x with
 // the constant -8 in the codes' own units.
 __device__ __forceinline__ void start_products(const ReadsX &rx, f32x4 (&d)[4]) {
-    const u32x4 x0 = rx.mine[0], x1 = rx.mine[1];
-    const f16x8 even = as_f16x8(u32x4{0x80208020u, 0x80208020u, 0x80208020u, 0x80208020u});
-    const f16x8 odd = as_f16x8(u32x4{0x82008200u, 0x82008200u, 0x82008200u, 0x82008200u});
-    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-    d[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(x0), even, zero, 0, 0, 0);
-    d[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(x0), odd, zero, 0, 0, 0);
-    d[2] = d[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(x1), even, d[0], 0, 0, 0);
-    d[3] = d[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(x1), odd, d[1], 0, 0, 0);
+    const f16x8 eight = as_f16x8(u32x4{0x80208020u, 0x80208020u, 0x80208020u, 0x80208020u});    // -8 * 2^-22
+    f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(rx.mine[i]), eight, sum, 0, 0, 0);
+    d[2] = sum;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        d[0][j] = d[3][j] = sum[j] * (kUnit[2] / kUnit[0]);
+        d[1][j] = sum[j] * (kUnit[2] / kUnit[1]);
+    }
 }
 
 // Every other pass is computed with -x.  The matrix cores round the terms of a product DOWN, so a
@@ -138,12 +145,6 @@ __device__ __forceinline__ void start_products(const ReadsX &rx, f32x4 (&d)[4]) 
 // v_mfma_f32_4x4x4 have a bias of the same sign, 1.1e-5 and 2.7e-5.)  The wavefronts of a block-row start with different signs,
 // so slices of one pass cancel too.
 constexpr uint32_t kSignOfX = 0x8000u;
-
-// Element i of an array in global memory, with a 32-bit byte offset (the arrays that are read so are far smaller than 4 GB).
-template <class V>
-__device__ __forceinline__ const V *element(const V *base, uint32_t i) {
-    return reinterpret_cast<const V *>(reinterpret_cast<const char *>(base) + (size_t)(i * (uint32_t)sizeof(V)));
-}
 
 // Applies the scales of a pass's groups (sc[g] = the fp16 scales of the lane's 4 rows in group g of the pass) and adds to
 // the lane's running sums, which stay in the products' units.  The sums carry the sign of the pass's x: each pass subtracts the sums
@@ -186,17 +187,25 @@ __device__ __forceinline__ Deal deal_groups(int kk, int g, int lane) {
 }
 
 // Stages the x of a pass: the entry that lane `lane` deals, in its slot, carries x[b] for group j of the pass (j < 0: none).
-template <int BATCH>
+// Slots that no entry writes must read as zero: with one group per pass every lane writes its slot, and the rest is cleared once.
+__device__ __forceinline__ void clear_x(StagedX &xs, int lane) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) reinterpret_cast<u32x4 *>(xs.v[4 * i + (lane >> 4)])[lane & 15] = u32x4{0u, 0u, 0u, 0u};
+    __builtin_amdgcn_wave_barrier();
+}
+template <int BATCH, int GROUPS>
 __device__ __forceinline__ void stage_x(StagedX &xs, int lane, int j, uint32_t sign, const uint16_t (&xraw)[BATCH]) {
     constexpr int kRows = padded_rows(BATCH);
-    {   // slots that no entry writes must read as zero
-        reinterpret_cast<u32x2 *>(&xs.v[0][0])[lane] = u32x2{0u, 0u};
-        __builtin_amdgcn_wave_barrier();
-    }
+    if (GROUPS > 1) clear_x(xs, lane);
     // no branch on j >= 0: a divergent one inside the pipeline's loop makes the compiler join the loop's exits with its
     // entry and wait for all loads there
 #pragma unroll
-    for (int b = 0; b < BATCH; ++b) xs.v[j >= 0 ? j * kRows + b : 4][slot_of(lane)] = (uint16_t)(xraw[b] ^ sign);
+    for (int b = 0; b < BATCH; ++b) {
+        const uint16_t v = (uint16_t)(GROUPS > 1 || j >= 0 ? xraw[b] ^ sign : 0u);
+        uint16_t *at = reinterpret_cast<uint16_t *>(&xs.v[2 * (GROUPS > 1 ? (j >= 0 ? j * kRows + b : 4) : b)][slot_of(lane)]);
+        at[0] = v;
+        at[2 * (kPassCols + 4) + 1] = v;
+    }
     __builtin_amdgcn_wave_barrier();
 }
 
@@ -258,10 +267,11 @@ __device__ __forceinline__ void run_passes(StagedX &staged, const uint8_t *row_b
     load_columns<0, 16>(columns, h.off, n8, w);
     load_scales<BATCH, GROUPS>(row_base, out4, h, sc);
     const ReadsX rx(staged, lane);
+    if (GROUPS == 1) clear_x(staged, lane);
     first_requested();
     first_here();
     while (more(pos)) {
-        stage_x<BATCH>(staged, lane, h.j, sign, h.xraw);
+        stage_x<BATCH, GROUPS>(staged, lane, h.j, sign, h.xraw);
         const bool whole = h.n > kPassCols / 2, any = !EMPTY || h.n > 0;
         pos = head(pos);
         keep_order();
@@ -281,7 +291,7 @@ __device__ __forceinline__ void run_passes(StagedX &staged, const uint8_t *row_b
         load_scales<BATCH, GROUPS>(row_base, out4, h, sc);
         keep_order();
     }
-    stage_x<BATCH>(staged, lane, h.j, sign, h.xraw);
+    stage_x<BATCH, GROUPS>(staged, lane, h.j, sign, h.xraw);
     start_products(rx, d);
     half_pass<0>(w, rx, d);
     if (h.n > kPassCols / 2) half_pass<1>(w, rx, d);

@@ -71,6 +71,20 @@ def test_pass_edges(gpu, rows, group):
                 check(run(gpu, w, x, 0.125, mode, group, splits=1), ref, f"n={n} {name} {mode}")
 
 
+@pytest.mark.parametrize("rows", [1, 2, 3, 4])
+@pytest.mark.parametrize("mode", ["dense", "list", "fused"])
+def test_short_pass_behind_a_full_one_is_exact(gpu, rows, mode):
+    """Slices of 96 columns: a pass of 64 entries, then one of 32, whose other slots must not keep the x of the first.  Small
+    integers and scales that are powers of two: every product and sum is exact, so the outputs are the oracle's bit for bit."""
+    M, K = 300, 384
+    w = make_weights(M, K, 5300)
+    w["scales"] = (2.0 ** np.random.default_rng(5301).integers(-3, 1, w["scales"].shape)).astype(np.float16)
+    x = np.random.default_rng(5302 + rows).integers(1, 9, (rows, K)).astype(np.float16)
+    ref = oracle.gemv(w["q_rowmajor"], w["scales"], x, 0.0)
+    print(f"short pass rows={rows} {mode}", flush=True)
+    assert np.array_equal(run(gpu, w, x, 0.0, mode, splits=1).astype(np.float64), ref)
+
+
 @pytest.mark.parametrize("rows", [1, 2, 4])
 def test_half_passes(gpu, rows):
     """Slices that end around 32 entries past a whole number of passes (the second half of such a pass has no products): four
