@@ -11,7 +11,7 @@
 //   - lane (cg, seg) = (lane/8, lane%8) of a step reads bytes [16 seg, 16 seg + 16) of column cg
 //     of the step: the 32 rows of ONE quantization block.  The block's scale is therefore a
 //     per-lane scalar, and it is folded into the activation before the multiply:
-//     acc[row] += n * (x * s * 2^24) with the stored code n taken as an fp16 subnormal.
+//     acc[row] += n * (x * s) with the stored code n taken as an fp16 subnormal.
 //   - a pass is simply the next (up to) 64 entries of the wavefront's slice of the index list:
 //     there is no group structure to respect, no per-group fold, no flush.  The lane that owns
 //     entry l loads x and the 8 scales of its column (one 16-byte load) and stages the 8
@@ -19,6 +19,8 @@
 //   - the 32 accumulators run through the whole slice; the 8 column-lanes are folded once at
 //     the end, and the offset-binary bias (stored = q + 8) is removed there as -8 * (sum of
 //     x * s of the lane's block over the slice).
+//   - (Scaling x by 2^24 and by 1/16 for the odd nibbles where it is staged and read, and 64-bit addresses, took 20 of 520 instructions a pass more: list at
+//     50 % with the gather 4096 x 4096 7.78 / 7.68 us, 5120 x 13824 10.5 / 10.4, K-quant in one launch at 40 % 5120 x 13824 8.96 / 8.86.)
 //   - one buffer of weights refilled half by half, unpredicated clamped loads, reduction through LDS and the
 //     workspace exactly as in gemv_list.hip.
 #include <hip/hip_runtime.h>
@@ -53,8 +55,8 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
     // One staging area per wavefront is enough: offsets are written and read back inside a HEAD, and the products of a pass are read
     // before those of the next one are staged.
     __shared__ uint32_t stage_off[WAVES][kPassCols];                               // byte offset of each column
-    __shared__ __attribute__((aligned(16))) float stage_xs[WAVES][BATCH][kPassCols][8];  // x * scale * 2^24 per block
-    __shared__ __attribute__((aligned(16))) float stage_xm[KQ ? WAVES : 1][BATCH][KQ ? kPassCols : 1][8];  // x * minimum * 2^24
+    __shared__ __attribute__((aligned(16))) float stage_xs[WAVES][BATCH][kPassCols][8];  // x * scale per block
+    __shared__ __attribute__((aligned(16))) float stage_xm[KQ ? WAVES : 1][BATCH][KQ ? kPassCols : 1][8];  // x * minimum
     __shared__ __attribute__((aligned(16))) float red[WAVES][BATCH][kTileRows];
     __shared__ u32x2 ring_slots[FUSED ? WAVES : 1][FUSED ? kRingSlots : 1];
 
@@ -96,7 +98,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
         auto fetch_k = [&](int p) -> int {
             const int e = p + lane;
             if (DENSE) return e < end ? e : 0;
-            return __hip_atomic_load(idx + (e < end ? e : end - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            return __hip_atomic_load(element(idx, (uint32_t)(e < end ? e : end - 1)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         };
 
         // One buffer of weights, refilled half by half as a pass is multiplied: when the products of steps u < 4 are done, their
@@ -128,7 +130,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
             const uint32_t chunk_off = (uint32_t)(kc >> 7) * (uint32_t)kCbChunkBytes;
             const uint32_t col = (uint32_t)(kc & (kGroup - 1));
 #pragma unroll
-            for (int b = 0; b < BATCH; ++b) xr[b] = FUSED ? kept_x : (uint32_t)x[(size_t)b * K + kc];
+            for (int b = 0; b < BATCH; ++b) xr[b] = FUSED ? kept_x : (uint32_t)*element(x, (uint32_t)(b * K + kc));
             sv = *reinterpret_cast<const u32x4 *>(row_base + (size_t)(chunk_off + col * 16u));
             stage_off[wave][lane] = chunk_off + (uint32_t)kCbScaleBytes + col * (uint32_t)kColBytes;
             __builtin_amdgcn_wave_barrier();
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
             for (int u = 4 * half; u < 4 * half + 4; ++u)
                 w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(row_base + (size_t)off[u]));
         };
-        // The lane that owns an entry stages the 8 products x * s_b * 2^24 of its column, per row.
+        // The lane that owns an entry stages the 8 products x * s_b of its column, per row.
         auto stage = [&]() {
             float sc[8], mn[8];
             if (FUSED && lane >= n) sv = u32x4{0u, 0u, 0u, 0u};      // an empty pass points at column 0, which may be dropped
@@ -161,26 +163,25 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
                     sc[b] = d * (float)fs;
                     mn[b] = dm * (float)fm;
                 }
-            } else {
-                sc[0] = half_bits_to_float(sv.x & 0xFFFFu);
-                sc[1] = half_bits_to_float(sv.x >> 16);
-                sc[2] = half_bits_to_float(sv.y & 0xFFFFu);
-                sc[3] = half_bits_to_float(sv.y >> 16);
-                sc[4] = half_bits_to_float(sv.z & 0xFFFFu);
-                sc[5] = half_bits_to_float(sv.z >> 16);
-                sc[6] = half_bits_to_float(sv.w & 0xFFFFu);
-                sc[7] = half_bits_to_float(sv.w >> 16);
             }
 #pragma unroll
             for (int b = 0; b < BATCH; ++b) {
-                const float xf = lane < n ? half_bits_to_float(xr[b]) * kTwo24 : 0.0f;
+                const float xf = lane < n ? half_bits_to_float(xr[b]) : 0.0f;
                 f32x4 *dst = reinterpret_cast<f32x4 *>(stage_xs[wave][b][lane]);
-                dst[0] = f32x4{xf * sc[0], xf * sc[1], xf * sc[2], xf * sc[3]};
-                dst[1] = f32x4{xf * sc[4], xf * sc[5], xf * sc[6], xf * sc[7]};
                 if (KQ) {
+                    dst[0] = f32x4{xf * sc[0], xf * sc[1], xf * sc[2], xf * sc[3]};
+                    dst[1] = f32x4{xf * sc[4], xf * sc[5], xf * sc[6], xf * sc[7]};
                     f32x4 *dm4 = reinterpret_cast<f32x4 *>(stage_xm[wave][b][lane]);
                     dm4[0] = f32x4{xf * mn[0], xf * mn[1], xf * mn[2], xf * mn[3]};
                     dm4[1] = f32x4{xf * mn[4], xf * mn[5], xf * mn[6], xf * mn[7]};
+                } else {
+                    // (as sums with 0: the half then needs no instruction of its own to become a float)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const f16x2 h01 = as_f16x2(i ? sv.z : sv.x), h23 = as_f16x2(i ? sv.w : sv.y);
+                        dst[i] = f32x4{__builtin_fmaf((float)h01.x, xf, 0.0f), __builtin_fmaf((float)h01.y, xf, 0.0f),
+                                       __builtin_fmaf((float)h23.x, xf, 0.0f), __builtin_fmaf((float)h23.y, xf, 0.0f)};
+                    }
                 }
             }
             __builtin_amdgcn_wave_barrier();
@@ -232,15 +233,13 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
         outputs.read_now();
     }
 
-    // fold the 8 column-lanes once and remove the bias.  The products are already in true units
-    // (code * 2^-24 times x * s * 2^24); the staged values the bias sums are still scaled by 2^24.
+    // fold the 8 column-lanes once, bring the sums to true units and remove the bias
 #pragma unroll
     for (int b = 0; b < BATCH; ++b) {
         float r4[4];
         fold_columns(acc[b], r4);
-        const float bias = sum_over_columns(bsum[b]) * ((KQ ? 1.0f : 8.0f) / kTwo24);
-        reinterpret_cast<f32x4 *>(red[wave][b])[8 * seg + cgr] =
-            f32x4{r4[0] - bias, r4[1] - bias, r4[2] - bias, r4[3] - bias};
+        const float bias = sum_over_columns(bsum[b]) * (KQ ? 1.0f : 8.0f);
+        reinterpret_cast<f32x4 *>(red[wave][b])[8 * seg + cgr] = true_rows(r4, bias);
     }
     __syncthreads();
     combine_block_row<WAVES, BATCH>(&red[0][0][0], tid, outputs);

@@ -83,31 +83,36 @@ __device__ __forceinline__ float as_float(uint32_t bits) { return __builtin_bit_
 __device__ __forceinline__ uint32_t as_u32(float f) { return __builtin_bit_cast(uint32_t, f); }
 __device__ __forceinline__ f16x2 as_f16x2(uint32_t bits) { return __builtin_bit_cast(f16x2, bits); }
 
-// Eight codes of one dword: acc[i] += n_i * x for nibble i (row 8d+i of the lane's 32 rows).
-// xlo = x * 2^24 pairs with nibbles sitting at bits 0..3 of a half, xhi = x * 2^20 with
-// nibbles at bits 4..7 (value 16 n * 2^-24).
-__device__ __forceinline__ void fma_codes(uint32_t w, float xlo, float xhi, float *acc) {
+// Eight codes of one dword, nibble i = row 8d + i of the lane's 32 rows, times x: a nibble at bits 0..3 of a half is the subnormal
+// n * 2^-24, one at bits 4..7 n * 2^-20 (the smallest product of a code with x * scale is 2^-72); true_rows() undoes that once per output.
+__device__ __forceinline__ void fma_codes(uint32_t w, float x, float *acc) {
     const uint32_t w8 = w >> 8;
     const f16x2 a = as_f16x2(w & 0x000F000Fu);    // nibbles 0, 4
     const f16x2 b = as_f16x2(w & 0x00F000F0u);    // nibbles 1, 5
     const f16x2 c = as_f16x2(w8 & 0x000F000Fu);   // nibbles 2, 6
     const f16x2 d = as_f16x2(w8 & 0x00F000F0u);   // nibbles 3, 7
-    acc[0] = __builtin_fmaf((float)a.x, xlo, acc[0]);
-    acc[4] = __builtin_fmaf((float)a.y, xlo, acc[4]);
-    acc[1] = __builtin_fmaf((float)b.x, xhi, acc[1]);
-    acc[5] = __builtin_fmaf((float)b.y, xhi, acc[5]);
-    acc[2] = __builtin_fmaf((float)c.x, xlo, acc[2]);
-    acc[6] = __builtin_fmaf((float)c.y, xlo, acc[6]);
-    acc[3] = __builtin_fmaf((float)d.x, xhi, acc[3]);
-    acc[7] = __builtin_fmaf((float)d.y, xhi, acc[7]);
+    acc[0] = __builtin_fmaf((float)a.x, x, acc[0]);
+    acc[4] = __builtin_fmaf((float)a.y, x, acc[4]);
+    acc[1] = __builtin_fmaf((float)b.x, x, acc[1]);
+    acc[5] = __builtin_fmaf((float)b.y, x, acc[5]);
+    acc[2] = __builtin_fmaf((float)c.x, x, acc[2]);
+    acc[6] = __builtin_fmaf((float)c.y, x, acc[6]);
+    acc[3] = __builtin_fmaf((float)d.x, x, acc[3]);
+    acc[7] = __builtin_fmaf((float)d.y, x, acc[7]);
 }
 
-__device__ __forceinline__ void fma_step(u32x4 w, float xl, float *acc) {
-    const float xh = xl * 0.0625f;
-    fma_codes(w.x, xl, xh, acc + 0);
-    fma_codes(w.y, xl, xh, acc + 8);
-    fma_codes(w.z, xl, xh, acc + 16);
-    fma_codes(w.w, xl, xh, acc + 24);
+__device__ __forceinline__ void fma_step(u32x4 w, float x, float *acc) {
+    fma_codes(w.x, x, acc + 0);
+    fma_codes(w.y, x, acc + 8);
+    fma_codes(w.z, x, acc + 16);
+    fma_codes(w.w, x, acc + 24);
+}
+
+// Four adjacent rows of fma_codes (after the fold over the lanes), less the bias.
+__device__ __forceinline__ f32x4 true_rows(const float (&r)[4], float bias) {
+    constexpr float kTwo20 = kTwo24 / 16.0f;
+    return f32x4{__builtin_fmaf(r[0], kTwo24, -bias), __builtin_fmaf(r[1], kTwo20, -bias), __builtin_fmaf(r[2], kTwo24, -bias),
+                 __builtin_fmaf(r[3], kTwo20, -bias)};
 }
 
 // Element i of an array in global memory, with a 32-bit byte offset (the arrays that are read so are far smaller than 4 GB).
