@@ -5,10 +5,12 @@
 // decide.  One column's 128-byte run is 128 rows, so a block-row is 128 rows high, a lane owns 16 rows
 // (half a 32-row block) and keeps 16 accumulators.
 //
-// Codes become floats without a conversion instruction: v_perm_b32 puts byte b under the fp16
-// exponent 0x64 (value 1024 + b, exact), two codes per permute, and v_fma_mix_f32 multiplies a
-// half of that pair by the staged x * s in fp32.  The stored byte is q + 128, so every product
-// carries (q + 1152) * xs; the lane sums the xs it used and 1152 times that sum comes off at the end.
+// Codes become floats without a conversion instruction: v_perm_b32 puts byte b under a zero byte, which
+// makes it the fp16 subnormal b * 2^-24, two codes per permute, and v_fma_mix_f32 multiplies a
+// half of that pair by the staged x * s in fp32 (the smallest product is 2^-72).  The stored byte is q + 128, so every product
+// carries (q + 128) * 2^-24 * xs; the lane sums the xs it used, and 2^24 and 128 times that sum are made good at the end.
+// (Under the exponent of 1024, where a byte is 1024 + b, the sums carried 1152 * xs: error against 64-bit arithmetic, list at 50 %
+// 11008 x 4096 1.4e-6, now 2.1e-7.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -32,7 +34,7 @@ struct W8 {
     static constexpr int kScaleBytes = kGroup * 2 * kBlocks;   // 1024
     static constexpr int kChunkBytes = SPQT_CB8_CHUNK_BYTES;
     static constexpr int kAcc = 16;
-    static constexpr float kCodeBias = 1024.0f + 128.0f;
+    static constexpr float kCodeBias = 128.0f;
     typedef u32x2 Scales;
     typedef float Mine;      // a lane's 16 rows lie in one block
     typedef float Sums;
@@ -46,10 +48,10 @@ struct W8 {
     }
     static __device__ __forceinline__ Mine read_mine(const float *col, int seg) { return col[seg >> 1]; }
 
-    // Four codes of one dword (rows 4d .. 4d+3 of the lane's 16): acc[i] += (1024 + byte_i) * xs.
+    // Four codes of one dword (rows 4d .. 4d+3 of the lane's 16): acc[i] += byte_i * 2^-24 * xs.
     static __device__ __forceinline__ void fma_bytes(uint32_t w, float xs, float *acc) {
-        const f16x2 p01 = as_f16x2(__builtin_amdgcn_perm(0x64646464u, w, 0x04010400u));   // {b0, 0x64, b1, 0x64}
-        const f16x2 p23 = as_f16x2(__builtin_amdgcn_perm(0x64646464u, w, 0x04030402u));   // {b2, 0x64, b3, 0x64}
+        const f16x2 p01 = as_f16x2(__builtin_amdgcn_perm(w, w, 0x0C010C00u));   // {b0, 0, b1, 0}
+        const f16x2 p23 = as_f16x2(__builtin_amdgcn_perm(w, w, 0x0C030C02u));   // {b2, 0, b3, 0}
         acc[0] = __builtin_fmaf((float)p01.x, xs, acc[0]);
         acc[1] = __builtin_fmaf((float)p01.y, xs, acc[1]);
         acc[2] = __builtin_fmaf((float)p23.x, xs, acc[2]);
@@ -74,8 +76,8 @@ struct W8 {
 #pragma unroll
         for (int i = 0; i < 2; ++i) r2[i] = fold32(u[i], u[i + 2]);
         const float bias = sum_over_columns(bs) * kCodeBias;
-        red[16 * seg + 2 * cgr + 0] = r2[0] - bias;
-        red[16 * seg + 2 * cgr + 1] = r2[1] - bias;
+        red[16 * seg + 2 * cgr + 0] = __builtin_fmaf(r2[0], kTwo24, -bias);
+        red[16 * seg + 2 * cgr + 1] = __builtin_fmaf(r2[1], kTwo24, -bias);
     }
 };
 static_assert(W8::kChunkBytes == W8::kScaleBytes + kGroup * 128, "chunk size");
@@ -116,6 +118,10 @@ int run8(int mode, int batch, const void *packed_dev, int64_t M, int64_t K, cons
     if (check_shape(M, K, kGroup) == SPQT_OK) {    // colblock_width_run refuses the others
         const Columns from = mode == 1 ? Columns::dense : mode == 2 ? Columns::units : Columns::list;
         S0 = colblock_splits(T64, K, from, batch, colblock8_depth(T64, K, from, batch));
+        // (a call without a usable workspace stays with the rule that tells whether it is refused)
+        size_t need = 0;
+        spqt_workspace_bytes(M, K, batch, &need);
+        if (mode == 0 && batch == 1 && usable_workspace(workspace_dev, workspace_bytes, need)) S0 = colblock8_list_splits(T64, K, S0);
         without_workspace = runs_without_workspace(T64, (size_t)M * (size_t)K, from, batch);
         while (mode == 2 && S0 > 1 && (int64_t)S0 * 4 * kPassCols > K) --S0;   // one launch: at least one unit per wavefront
     }

@@ -158,6 +158,22 @@ inline int colblock8_depth(int64_t T, int64_t K, Columns from, int batch) {
     return from == Columns::dense && batch == 1 && T > 128 && T <= 256 && K >= 4 * 768 ? 2 : 3;
 }
 
+// Workgroups per block-row of the 8-bit list kernel with one activation row, at most as many as `S`, what colblock_splits gives.  That rule was drawn with two
+// buffers of weights; with one, a second and third workgroup per CU for a slightly fuller last round cost more in start and exchange than they
+// bring.  Up to 128 block-rows: one per CU, two where they fill the last round a fifth better (S = this rule / before, us with the gather at 50 %:
+// 9472 x 4096 S = 3 / 10 9.71 / 10.03, 9472 x 14336 18.8 / 19.6, 13440 x 8192 S = 2 / 7 16.3 / 16.9, 11008 x 4096 S = 5 / 8 10.2 / 10.6, 4096 x 8192 S = 8 / 16
+// 9.48 / 9.74; slower by at most 1 %, 3072 x 4096 S = 10 / 16 7.72 / 7.66).  From 129 to 256 a block-row has one workgroup unless the idle CUs have much to
+// read, K * (256 - T) above 400 thousand columns (S = 1 / 4: 23552 x 1152 7.6 / 8.2, 22016 x 4096, 344 thousand, 13.9 / 14.7, but 23552 x 8192, 590 thousand,
+// 25.3 / 24.7; 17707 x 4096, 479 thousand, S = 1 / 5 13.2 / 12.9).  From 96 MB on the rule stays as it was: calls on one or two matrices of that size find
+// kept columns in the 256 MB cache, where more requests in flight pay (13440 x 9728 at 70 %, S = 2 / 7, two matrices in turn 16.9 / 16.5, five 14.5 / 14.9).
+inline int colblock8_list_splits(int64_t T, int64_t K, int S) {
+    if (T > 256 || T * K >= (int64_t)96 * 8192) return S;         // (128 rows per block-row)
+    if (T > 128) return K * (256 - T) <= 400000 ? 1 : S;
+    const int64_t one = 256 / T, two = 512 / T;                   // one and two workgroups per CU
+    const int64_t least = one * 6 * 2 <= two * 5 ? two : one;     // two * T of 512 slots against one * T of 256: fuller by a fifth
+    return least < S ? (int)least : S;
+}
+
 // A workspace the exchange can use: calls with several workgroups per block-row refuse any other.
 inline bool usable_workspace(const void *ws, size_t bytes, size_t need) {
     return ws && bytes >= need && (uintptr_t)ws % 256 == 0;

@@ -254,3 +254,32 @@ def test_cb8_rows_dense_fp16_and_limits(gpu):
     yb = torch.zeros((5) * M, dtype=torch.float32, device=dev)
     with pytest.raises(spqt.SpqtError):
         spqt.spqt_cb8_gemv_rows(torch.from_numpy(packed).to(dev), M, K, xb, None, None, yb, spqt.new_workspace(M, K, 4))
+
+
+@pytest.mark.parametrize("M, K", [(128, 1152), (9400, 1152), (11008, 2688), (16385, 1152), (23552, 1152), (17707, 4096), (33024, 1152)])
+def test_list_error_and_shapes(gpu, M, K):
+    """The list kernel's default shapes on either side of its lines (128 and 256 block-rows, one or two workgroups per CU), and how far its
+    sums are from 64-bit arithmetic: fp32 sums of at most K / 4 products in a row, codes centred on 128, stay below 1e-6 (with codes
+    centred on 1152 they were at 1.2e-6 to 2.3e-6)."""
+    torch, spqt, dev = gpu
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(8100 + M)
+    T, n = -(-M // 128), K // 128
+    buf = torch.randint(0, 256, (T, n, 1024 + 128 * 128), dtype=torch.uint8, device=dev, generator=gen)
+    scales = (torch.rand((T, n, 512), device=dev, generator=gen) * 0.0015 + 0.0005).half()
+    buf[:, :, :1024] = scales.view(torch.uint8)
+    x = torch.randn(K, device=dev, generator=gen).half()
+    idx = torch.zeros(K, dtype=torch.int32, device=dev)
+    cnt = torch.zeros(1, dtype=torch.int32, device=dev)
+    y = torch.full((M,), float("nan"), dtype=torch.float32, device=dev)
+    spqt.spqt_gather(x, 0.6, idx, cnt)
+    spqt.spqt_cb8_gemv(buf.view(-1), M, K, x, idx, cnt, y, spqt.new_workspace(M, K))
+    kept = x.double() * (x.float().abs() >= 0.6)
+    ref = torch.empty(T * 128, dtype=torch.float64, device=dev)
+    for t in range(T):
+        q = buf[t, :, 1024:].reshape(K, 128).double() - 128.0
+        s = scales[t].reshape(K, 4).double()
+        ref[128 * t:128 * (t + 1)] = ((q.view(K, 4, 32) * s[:, :, None]).view(K, 128) * kept[:, None]).sum(0)
+    err = float((y.double() - ref[:M]).norm() / ref[:M].norm())
+    print(f"8-bit list {M} x {K}: {err:.2e}", flush=True)
+    assert err < 1e-6
