@@ -377,13 +377,16 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, con
                 }
             }
             bool all_here = true;                // wave-uniform
-            // N partial sums, of which those from number SURE on may lie behind the block-row's: their words are loaded (they are inside
-            // the workspace, which holds two words for each of these) and not looked at.
+            // N partial sums; those from number SURE on may lie behind the block-row's, and then the first one's words are loaded once more: the words
+            // behind are another block-row's, or nobody's, and a load of them goes past this XCD's L2 (8-bit list 3200 x 4864 7.78 / 7.64 us).
             auto collect = [&](auto count, auto sure, int p0) {
                 constexpr int N = decltype(count)::value, SURE = decltype(sure)::value;
                 Word v[kTogether][N];
                 const bool at_once = kAlwaysHandOver && o.spread && p0 + N >= S - 1;
                 const Word *from = slots + (size_t)(p0 * kUnits);
+                uint32_t step[N];        // to partial sum p0 + j, or to p0 where that lies behind the block-row's
+#pragma unroll
+                for (int j = 0; j < N; ++j) step[j] = j < SURE || p0 + j < S - 1 ? (uint32_t)(j * kUnits) : 0u;
                 int polls = 0;
                 do {
                     // unconditional loads back to back, then one check
@@ -391,7 +394,7 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, con
                     for (int j = 0; j < N; ++j)
 #pragma unroll
                         for (int i = 0; i < kTogether; ++i)
-                            v[i][j] = __hip_atomic_load(from + j * kUnits + at[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            v[i][j] = __hip_atomic_load(element(from, step[j] + at[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     uint32_t least = ~0u;   // one running minimum: a comparison per word costs 0.5 us here
 #pragma unroll
                     for (int j = 0; j < N; ++j)
@@ -399,8 +402,7 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, con
                         for (int i = 0; i < kTogether; ++i)
 #pragma unroll
                             for (int q = 0; q < kVals; ++q) {
-                                uint32_t word = (uint32_t)((unsigned long long)v[i][j] >> (32 * q));
-                                if (j >= SURE) word = p0 + j < S - 1 ? word : ~0u;
+                                const uint32_t word = (uint32_t)((unsigned long long)v[i][j] >> (32 * q));
                                 least = word < least ? word : least;
                             }
                     all_here = __builtin_amdgcn_ballot_w64(least == 0u) == 0ull;
