@@ -1,4 +1,5 @@
-"""Thin ctypes binding over libspqt.so: argument marshalling, and the sizes and types of the tensors that a device call is given.
+"""Thin ctypes binding over libspqt.so: argument marshalling, and the sizes and types of the tensors that a device call is given
+(in the extension module _fastcall where they are the plainest).
 
 Same names as the C ABI (include/spqt.h).  Host calls take NumPy arrays; device calls take
 torch CUDA tensors (PyTorch supplies device memory and the stream, nothing else) and launch
@@ -9,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import types
 
 import numpy as np
 
@@ -101,6 +103,8 @@ def lib() -> ctypes.CDLL:
         L.spqt_cb2_gemv_fused.argtypes = [vp, i64, i64, vp, c.c_float, vp, vp, sz, vp, c.POINTER(LaunchCfg)]
         for name in EXPORTS[1:] + CB_EXPORTS:
             getattr(L, name).restype = i32
+        # the device functions' addresses, for _fastcall
+        L.at = {name: c.cast(getattr(L, name), vp).value for name in EXPORTS + CB_EXPORTS if "gemv" in name or "gather" in name}
         _lib = L
     return _lib
 
@@ -165,13 +169,19 @@ def spqt_unpack(packed: np.ndarray, M: int, K: int, group: int = GROUP):
 
 
 # --------------------------------------------------------------------------- device calls
+#
+# A device call goes to _fastcall first, which checks its arguments and calls the library in half a microsecond where the code here takes 2
+# to 3; it returns None, having done nothing, for all but the plainest arguments, and the code here goes on.
 
 _torch = None          # the torch module, once a device call has needed it
+_fast = None           # the extension module _fastcall (csrc/fastcall.cpp) from then on
 
 
 def _load_torch():
-    global _torch
+    global _torch, _fast
     import torch
+    if _fast is None and isinstance(torch, types.ModuleType):
+        from . import _fastcall as _fast      # built in-tree beside libspqt.so
     _torch = torch
     return torch
 
@@ -262,6 +272,10 @@ def new_workspace(M: int, K: int, batch: int = 1, device="cuda"):
 
 def spqt_gather(x, threshold: float, idx_out, count_out, stream=None) -> None:
     """x fp16[K] or [batch, K]; idx_out int32[>=K]; count_out int32[1] (all on the GPU)."""
+    if _fast is not None:
+        rc = _fast.gather((_lib or lib()).at["spqt_gather"], x, threshold, idx_out, count_out, stream)
+        if rc is not None:
+            return _check(rc)
     torch = _torch or _load_torch()
     xp = _dev(x, torch.float16, "x")
     batch, K = (1, x.shape[0]) if x.dim() == 1 else (x.shape[0], x.shape[1])
@@ -275,6 +289,10 @@ def spqt_gather(x, threshold: float, idx_out, count_out, stream=None) -> None:
 def spqt_gather_rows(x, threshold: float, idx_out, count_out, x_masked_out, stream=None) -> None:
     """spqt_gather plus x_masked_out (fp16, same shape as x): every row with its own dropped
     entries zeroed; feed it to a GEMV with idx_out / count_out for per-row kept sets."""
+    if _fast is not None:
+        rc = _fast.gather_rows((_lib or lib()).at["spqt_gather_rows"], x, threshold, idx_out, count_out, x_masked_out, stream)
+        if rc is not None:
+            return _check(rc)
     torch = _torch or _load_torch()
     xp = _dev(x, torch.float16, "x")
     batch, K = (1, x.shape[0]) if x.dim() == 1 else (x.shape[0], x.shape[1])
@@ -290,6 +308,10 @@ def spqt_gemv(packed, M: int, K: int, x, idx, count, y, workspace, stream=None, 
               splits: int = 0, waves: int = 0, flags: int = 0) -> None:
     """packed uint8 (device); x fp16[K] or [batch,K]; idx/count from spqt_gather or None/None
     for the dense kernel; y fp32 (or fp16) [M] or [batch,M]; workspace from new_workspace()."""
+    if _fast is not None:
+        rc = _fast.gemv((_lib or lib()).at["spqt_gemv_ex"], packed, M, K, x, idx, count, y, workspace, stream, group, splits, waves, flags)
+        if rc is not None:
+            return _check(rc)
     torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
@@ -332,6 +354,10 @@ def spqt_gemv_static(packed, M: int, K: int, x, idx, count, y, stream=None, grou
 def spqt_gemv_fused(packed, M: int, K: int, x, threshold: float, y, workspace, stream=None,
                     group: int = GROUP, splits: int = 0, waves: int = 0, flags: int = 0) -> None:
     """Threshold + compaction + GEMV in one launch (batch 1): x fp16[K], y fp32 (or fp16) [M]."""
+    if _fast is not None:
+        rc = _fast.gemv_fused((_lib or lib()).at["spqt_gemv_fused"], packed, M, K, x, threshold, y, workspace, stream, group, splits, waves, flags)
+        if rc is not None:
+            return _check(rc)
     torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
@@ -350,6 +376,10 @@ def spqt_gemv_fused_rows(packed, M: int, K: int, x, threshold: float, y, workspa
                          group: int = GROUP, splits: int = 0, waves: int = 0) -> None:
     """Threshold + compaction + GEMV in one launch for x fp16[batch, K], batch 1..4; y fp32 (or fp16) [batch, M].
     own_sets: every row sums over its own kept columns instead of the union."""
+    if _fast is not None:
+        rc = _fast.gemv_fused_rows((_lib or lib()).at["spqt_gemv_fused_rows"], packed, M, K, x, threshold, own_sets, y, workspace, stream, group, splits, waves)
+        if rc is not None:
+            return _check(rc)
     torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
@@ -398,6 +428,10 @@ def spqt_cb_gemv(packed, M: int, K: int, x, idx, count, y, workspace, stream=Non
     """Column-block GEMV: packed uint8 (device), x fp16[K] or [batch, K], idx/count from spqt_gather
     or None/None for the dense kernel, y fp32 (or fp16) [M] or [batch, M], workspace from
     new_workspace()."""
+    if _fast is not None:
+        rc = _fast.cb_gemv((_lib or lib()).at["spqt_cb_gemv"], packed, M, K, x, idx, count, y, workspace, stream, splits, waves, 256, CB_CHUNK_BYTES)
+        if rc is not None:
+            return _check(rc)
     torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
@@ -419,6 +453,10 @@ def spqt_cb_gemv(packed, M: int, K: int, x, idx, count, y, workspace, stream=Non
 def spqt_cb_gemv_fused(packed, M: int, K: int, x, threshold: float, y, workspace, stream=None,
                        splits: int = 0, waves: int = 0) -> None:
     """Threshold + compaction + column-block GEMV in one launch (batch 1)."""
+    if _fast is not None:
+        rc = _fast.cb_gemv_fused((_lib or lib()).at["spqt_cb_gemv_fused"], packed, M, K, x, threshold, y, workspace, stream, splits, waves, 256, CB_CHUNK_BYTES)
+        if rc is not None:
+            return _check(rc)
     torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
@@ -458,6 +496,10 @@ def spqt_cbk_dequantize(packed: np.ndarray, M: int, K: int) -> np.ndarray:
 def spqt_cbk_gemv(packed, M: int, K: int, x, idx, count, y, workspace, stream=None, splits: int = 0,
                   waves: int = 0) -> None:
     """K-quant column-block GEMV: x fp16[K] or [batch, K] (idx/count None/None for the dense kernel)."""
+    if _fast is not None:
+        rc = _fast.cb_gemv((_lib or lib()).at["spqt_cbk_gemv"], packed, M, K, x, idx, count, y, workspace, stream, splits, waves, 256, CB_CHUNK_BYTES)
+        if rc is not None:
+            return _check(rc)
     torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
@@ -479,6 +521,10 @@ def spqt_cbk_gemv(packed, M: int, K: int, x, idx, count, y, workspace, stream=No
 def spqt_cbk_gemv_fused(packed, M: int, K: int, x, threshold: float, y, workspace, stream=None,
                         splits: int = 0, waves: int = 0) -> None:
     """Threshold + compaction + K-quant column-block GEMV in one launch (batch 1)."""
+    if _fast is not None:
+        rc = _fast.cb_gemv_fused((_lib or lib()).at["spqt_cbk_gemv_fused"], packed, M, K, x, threshold, y, workspace, stream, splits, waves, 256, CB_CHUNK_BYTES)
+        if rc is not None:
+            return _check(rc)
     torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
@@ -524,6 +570,10 @@ def spqt_cb8_dequantize(packed: np.ndarray, M: int, K: int) -> np.ndarray:
 def spqt_cb8_gemv(packed, M: int, K: int, x, idx, count, y, workspace, stream=None, splits: int = 0,
                   waves: int = 0) -> None:
     """8-bit column-block GEMV, batch 1 (idx/count None/None for the dense kernel)."""
+    if _fast is not None:
+        rc = _fast.cb_gemv_one((_lib or lib()).at["spqt_cb8_gemv"], packed, M, K, x, idx, count, y, workspace, stream, splits, waves, 128, CB8_CHUNK_BYTES)
+        if rc is not None:
+            return _check(rc)
     torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
@@ -572,6 +622,10 @@ def spqt_cb2_dequantize(packed: np.ndarray, M: int, K: int) -> np.ndarray:
 def spqt_cb2_gemv(packed, M: int, K: int, x, idx, count, y, workspace, stream=None, splits: int = 0,
                   waves: int = 0) -> None:
     """2-bit column-block GEMV, batch 1 (idx/count None/None for the dense kernel)."""
+    if _fast is not None:
+        rc = _fast.cb_gemv_one((_lib or lib()).at["spqt_cb2_gemv"], packed, M, K, x, idx, count, y, workspace, stream, splits, waves, 512, CB2_CHUNK_BYTES)
+        if rc is not None:
+            return _check(rc)
     torch = _torch or _load_torch()
     pp = _dev(packed, torch.uint8, "packed")
     xp = _dev(x, torch.float16, "x")
@@ -606,12 +660,20 @@ def _width_fused(fn_name, bytes_fn, packed, M, K, x, threshold, y, workspace, st
 def spqt_cb8_gemv_fused(packed, M: int, K: int, x, threshold: float, y, workspace, stream=None, splits: int = 0,
                         waves: int = 0) -> None:
     """8-bit column-block gather + GEMV in one launch, batch 1."""
+    if _fast is not None:
+        rc = _fast.cb_gemv_fused((_lib or lib()).at["spqt_cb8_gemv_fused"], packed, M, K, x, threshold, y, workspace, stream, splits, waves, 128, CB8_CHUNK_BYTES)
+        if rc is not None:
+            return _check(rc)
     _width_fused("spqt_cb8_gemv_fused", _cb8_bytes, packed, M, K, x, threshold, y, workspace, stream, splits, waves)
 
 
 def spqt_cb2_gemv_fused(packed, M: int, K: int, x, threshold: float, y, workspace, stream=None, splits: int = 0,
                         waves: int = 0) -> None:
     """2-bit column-block gather + GEMV in one launch, batch 1."""
+    if _fast is not None:
+        rc = _fast.cb_gemv_fused((_lib or lib()).at["spqt_cb2_gemv_fused"], packed, M, K, x, threshold, y, workspace, stream, splits, waves, 512, CB2_CHUNK_BYTES)
+        if rc is not None:
+            return _check(rc)
     _width_fused("spqt_cb2_gemv_fused", _cb2_bytes, packed, M, K, x, threshold, y, workspace, stream, splits, waves)
 
 
@@ -637,10 +699,18 @@ def _width_rows(fn_name, bytes_fn, packed, M, K, x, idx, count, y, workspace, st
 def spqt_cb8_gemv_rows(packed, M: int, K: int, x, idx, count, y, workspace, stream=None, splits: int = 0,
                        waves: int = 0) -> None:
     """8-bit column-block GEMV for x fp16[batch][K], batch 1..4, on the union list (or dense)."""
+    if _fast is not None:
+        rc = _fast.cb_gemv((_lib or lib()).at["spqt_cb8_gemv_rows"], packed, M, K, x, idx, count, y, workspace, stream, splits, waves, 128, CB8_CHUNK_BYTES)
+        if rc is not None:
+            return _check(rc)
     _width_rows("spqt_cb8_gemv_rows", _cb8_bytes, packed, M, K, x, idx, count, y, workspace, stream, splits, waves)
 
 
 def spqt_cb2_gemv_rows(packed, M: int, K: int, x, idx, count, y, workspace, stream=None, splits: int = 0,
                        waves: int = 0) -> None:
     """2-bit column-block GEMV for x fp16[batch][K], batch 1..3, on the union list (or dense)."""
+    if _fast is not None:
+        rc = _fast.cb_gemv((_lib or lib()).at["spqt_cb2_gemv_rows"], packed, M, K, x, idx, count, y, workspace, stream, splits, waves, 512, CB2_CHUNK_BYTES)
+        if rc is not None:
+            return _check(rc)
     _width_rows("spqt_cb2_gemv_rows", _cb2_bytes, packed, M, K, x, idx, count, y, workspace, stream, splits, waves)

@@ -29,6 +29,10 @@ GIVEUP_SOURCES = ["pack.cpp", "gemv.hip", "gemv_list.hip", "gemv_bal.hip"]
 # The library with reducers that never wait in a block-row spread over several XCDs: they hand the sum over at once.
 HANDOVER_LIB = os.path.join(PKG, "libspqt_handover.so")
 
+# Device calls of binding.py as a Python extension module: host code against torch's headers and libraries.
+FASTCALL_LIB = os.path.join(PKG, "_fastcall.so")
+FASTCALL_SOURCE = "fastcall.cpp"
+
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # keep the compiler from forming packed-fp32 VALU ops
@@ -60,6 +64,16 @@ def _run(cmd, verbose: bool) -> None:
         print(out)
 
 
+def _fastcall_command(lib: str):
+    import sysconfig
+    import torch
+    base = os.path.dirname(torch.__file__)
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+            "-isystem", os.path.join(base, "include"), "-isystem", os.path.join(base, "include/torch/csrc/api/include"), "-isystem", "/opt/rocm/include",
+            "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), "-o", lib, os.path.join(CSRC, FASTCALL_SOURCE),
+            "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+
+
 def _jobs(lib: str, sources, defines=(), tag: str = ""):
     """(compile command, ...) per source and the link command of one library."""
     objs = [os.path.join(OBJ, f"{tag}{os.path.splitext(s)[0]}.o") for s in sources]
@@ -77,8 +91,11 @@ def build(verbose: bool = False) -> str:
             _jobs(LIB, SOURCES)]
     # every object of every library in one pool (longest first), then the links
     compiles = sorted((c for cs, _ in plan for c in cs), key=lambda c: -os.path.getsize(c[-1]))
+    fastcall = FASTCALL_LIB + f".tmp{os.getpid()}"
+    compiles.insert(0, _fastcall_command(fastcall))
     with ThreadPoolExecutor(JOBS) as pool:
         list(pool.map(lambda c: _run(c, verbose), compiles))
+    os.replace(fastcall, FASTCALL_LIB)
     for _, (lib, objs) in plan:
         tmp = lib + f".tmp{os.getpid()}"
         _run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
