@@ -141,7 +141,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_fused_kernel(
             return p + d.n;
         };
         fetch_x(u);
-        run_passes<BATCH, kGroups, true>(staged[wave], row_base, lane, n8, out4, part, 0, h, head,
+        run_passes<BATCH, kGroups, true, false>(staged[wave], row_base, lane, n8, out4, part, 0, h, head,
                                    [&](int p) { return p < filled || u < end; }, [&]() { outputs.read_now(); }, [&]() {}, acc);
     } else {
         outputs.read_now();

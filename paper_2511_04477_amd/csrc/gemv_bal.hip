@@ -185,7 +185,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_bal_kernel(
             return p + d.n;
         };
         // 4. GEMV
-        run_passes<1, kGroups, false>(staged[wave], row_base, lane, n8, out4, part, 0, h, head, [&](int p) { return p < total; },
+        run_passes<1, kGroups, false, false>(staged[wave], row_base, lane, n8, out4, part, 0, h, head, [&](int p) { return p < total; },
                                [&]() { outputs.read_now(); SPQT_TL(2); }, [&]() { SPQT_TL_WAIT(3); }, acc);
     } else {
         outputs.read_now();

@@ -88,7 +88,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
         };
         k_next = all_kept ? pos + lane : fetch_k(pos);
         SPQT_TL_WAIT(2);
-        run_passes<BATCH, GROUPS, false>(staged[wave], row_base, lane, n8, out4, part, pos, h, head, [&](int p) { return p < end; },
+        run_passes<BATCH, GROUPS, false, DENSE>(staged[wave], row_base, lane, n8, out4, part, pos, h, head, [&](int p) { return p < end; },
                                   [&]() { outputs.read_now(); }, [&]() { SPQT_TL_WAIT(3); }, acc);
     } else {
         outputs.read_now();

@@ -2,8 +2,8 @@
 // matrix cores for 1..4 activation rows.  Shared by gemv_list.hip (index list, dense), gemv.hip (one launch, static
 // column ranges) and gemv_bal.hip (one launch, even shares).
 //
-// Slots: entry e of a pass sits in slot (c, u), c = e / 8 % 4, u = e / 32 * 8 + e % 8, so that the first 32 entries are the
-// slots u < 8 and a pass of at most 32 entries is HALF a pass: the products of its slots u >= 8 are left out.  In step u the
+// Slots: entry e of a pass sits in slot (c, u), c = e / 4 % 4, u = e / 16 * 4 + e % 4, so that 16 entries are four slots of every quarter and
+// a pass of few entries leaves out the products of the sixteens it does not reach.  In step u the
 // 16 lanes of quarter c of the wavefront read the 128-byte run of column (c, u), 8 bytes each: lane l holds rows
 // 16 n .. 16 n + 15 of the block-row, n = l % 16, at the 16 columns of its quarter.  Lane e deals entry e; its column's offset
 // moves to lane (c, u) once (slot_order), i.e. into the quarter that reads it, and from there to the other 15 lanes by DPP
@@ -15,9 +15,10 @@
 // launch, whose slices also wait for entries, 0 to 1 %: 4096 x 14336 at 50 % with the gather 9.48 / 9.40; 4 rows 28672 x 8192 at 70 % 26.8 / 26.65).
 // Two passes' weights requested ahead of the products (a second buffer) were 3 to 6 % slower: the memory, not the order of the requests, sets
 // when the second pass arrives.
-// Slices end with a short one: leaving half of its products out
-// takes chains of GEMVs from 356.7 to 353.1 us (one launch, 48 of 11008 x 4096 and its transpose, 40 %), 208.6 to 205.0 (two rows with
-// their own sets, 24 of 14336 x 4096 and its transpose) and 166.9 to 164.9 (four rows, 6 of 28672 x 8192 and its transpose).
+// Slices end with a short pass: leaving half of its products out took chains of GEMVs from 356.7 to 353.1 us (one launch, 48 of 11008 x 4096 and its
+// transpose, 40 %), 208.6 to 205.0 (two rows with their own sets, 24 of 14336 x 4096 and its transpose) and 166.9 to 164.9 (four rows, 6 of
+// 28672 x 8192 and its transpose).  By sixteens instead of halves, before / now: list with the gather 4096 x 4096 at 50 % (32 or 33 entries per
+// wavefront) 7.13 / 7.04, at 40 % 7.53 / 7.40, 4 rows at 70 % 8192 x 28672 27.0 / 26.8, one launch at 40 % 11008 x 4096 6.88 / 6.81.
 //
 // Products: v_mfma_f32_16x16x32_f16 computes D[m][n] += sum over 32 k of A[m][k] * B[k][n]; lane l brings A[l % 16] and
 // B[..][l % 16] at the 8 k of quarter l / 16, i.e. at 4 of the 16 columns of its quarter with two k each, h = 0 and 1.  B is one dword of each
@@ -81,12 +82,10 @@ __device__ __forceinline__ uint32_t row_lane(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + U, 0xf, 0xf, true);
 }
 
-// The slot (16 c + u) of the entry that lane e deals, and what a lane's slot gets: `v` of the lane that deals the slot's entry.
-__device__ __forceinline__ int slot_of(int e) { return ((e & 0x18) << 1) | ((e & 0x20) >> 2) | (e & 7); }
-__device__ __forceinline__ uint32_t slot_order(uint32_t v, int lane) {
-    const int e = ((lane & 8) << 2) | ((lane & 0x30) >> 1) | (lane & 7);
-    return (uint32_t)__builtin_amdgcn_ds_bpermute(4 * e, (int)v);
-}
+// The slot (16 c + u) of the entry that lane e deals, and what a lane's slot gets: `v` of the lane that deals the slot's entry (the same
+// permutation, which is its own inverse).
+__device__ __forceinline__ int slot_of(int e) { return ((e & 0x0C) << 2) | ((e & 0x30) >> 2) | (e & 3); }
+__device__ __forceinline__ uint32_t slot_order(uint32_t v, int lane) { return (uint32_t)__builtin_amdgcn_ds_bpermute(4 * slot_of(lane), (int)v); }
 
 // Requests the weights of slots u = FROM .. TO - 1 of a pass: off = byte offset (from base) of the column run of the entry
 // this lane owns, n8 = 8 * (lane % 16).
@@ -96,30 +95,26 @@ __device__ __forceinline__ void load_columns(const uint8_t *base, uint32_t off, 
     if constexpr (FROM + 1 < TO) load_columns<FROM + 1, TO>(base, off, n8, w);
 }
 
-// Products of the 32 slots (c, u), u = 8 SET .. 8 SET + 7: d[p][j] += sum of code(row 16 n + 4 v + p, slot) * x(j, slot)
+// Products of the 16 slots (c, u), u = 4 Q .. 4 Q + 3: d[p][j] += sum of code(row 16 n + 4 v + p, slot) * x(j, slot)
 // in units of kUnit[p].
 // The matrix cores align products by the exponent FIELDS, so bits that a subnormal has above its code are bits of
 // precision lost in every product: codes sit as high as one shift per two codes brings them.
-template <int SET>
-__device__ __forceinline__ void half_pass(const u32x2 (&w)[16], const ReadsX &rx, f32x4 (&d)[4]) {
-    u32x4 x[4];
+template <int Q>
+__device__ __forceinline__ void quarter_pass(const u32x2 (&w)[16], const ReadsX &rx, f32x4 (&d)[4]) {
+    const u32x4 x[2] = {rx.of_variant[0][Q], rx.of_variant[1][Q]};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) x[i] = rx.of_variant[i & 1][2 * SET + (i >> 1)];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const f16x8 a = as_f16x8(x[i]);
-        const int first = 8 * SET + 4 * (i >> 1), dw = i & 1;
+    for (int i = 0; i < 2; ++i) {
         u32x4 b[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const uint32_t c = w[first + k][dw], right = c >> 6;
+            const uint32_t c = w[4 * Q + k][i], right = c >> 6;
             b[0][k] = (c << 6) & 0x03C003C0u;
             b[1][k] = c & 0x00F000F0u;
             b[2][k] = right & 0x003C003Cu;
             b[3][k] = right & 0x03C003C0u;
         }
 #pragma unroll
-        for (int p = 0; p < 4; ++p) d[p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, as_f16x8(b[p]), d[p], 0, 0, 0);
+        for (int p = 0; p < 4; ++p) d[p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(x[i]), as_f16x8(b[p]), d[p], 0, 0, 0);
     }
 }
 
@@ -239,6 +234,10 @@ __device__ __forceinline__ Deal deal_columns(PassHead<BATCH> &h, int kk, int log
 // The scales of the lane's 4 rows in each group of the pass; behind its last one, those of some group of it.
 template <int BATCH, int GROUPS>
 __device__ __forceinline__ void load_scales(const uint8_t *row_base, uint32_t out4, const PassHead<BATCH> &h, u32x2 (&sc)[GROUPS]) {
+    if (GROUPS == 1) {           // the group of the pass's first entry
+        sc[0] = *reinterpret_cast<const u32x2 *>(row_base + (size_t)((uint32_t)__builtin_amdgcn_readfirstlane((int)h.chunk) + out4 * 8u));
+        return;
+    }
     uint64_t left = h.starts;
 #pragma unroll
     for (int i = 0; i < GROUPS; ++i) {
@@ -254,8 +253,9 @@ __device__ __forceinline__ void load_scales(const uint8_t *row_base, uint32_t ou
 // half by half as a pass is multiplied.  EMPTY: a pass may have no entries; its scales, which may be those of a group whose columns
 // are all dropped, are then not applied (infinite ones times its sums, which are zero, would be NaN).  A branch around the adds: one launch, one
 // and two rows, 0.2 % slower on average than without the test, 3 and 4 rows as fast; zeroes in place of the scales cost 0.5 and 0.2 %.
+// FULL: nearly all passes are full, and their products are not worth a branch per sixteen entries (dense 5120 x 5120 6.18 us without, 6.26 with).
 // first_requested and first_here: what is done, and where the timeline build stamps, when the first pass is requested.
-template <int BATCH, int GROUPS, bool EMPTY, class Head, class More, class Stamp2, class Stamp3>
+template <int BATCH, int GROUPS, bool EMPTY, bool FULL, class Head, class More, class Stamp2, class Stamp3>
 __device__ __forceinline__ void run_passes(StagedX &staged, const uint8_t *row_base, int lane, uint32_t n8, uint32_t out4,
                                            int part, int pos, PassHead<BATCH> &h, Head head, More more, Stamp2 first_requested,
                                            Stamp3 first_here, float (&acc)[BATCH][4]) {
@@ -268,23 +268,33 @@ __device__ __forceinline__ void run_passes(StagedX &staged, const uint8_t *row_b
     load_scales<BATCH, GROUPS>(row_base, out4, h, sc);
     const ReadsX rx(staged, lane);
     if (GROUPS == 1) clear_x(staged, lane);
+    auto first_half = [&](int n) {
+        quarter_pass<0>(w, rx, d);
+        if (FULL || n > 16) quarter_pass<1>(w, rx, d);
+    };
+    auto second_half = [&](int n) {
+        if (n > 32) {
+            quarter_pass<2>(w, rx, d);
+            if (FULL || n > 48) quarter_pass<3>(w, rx, d);
+        }
+    };
     first_requested();
     first_here();
     while (more(pos)) {
         stage_x<BATCH, GROUPS>(staged, lane, h.j, sign, h.xraw);
-        const bool whole = h.n > kPassCols / 2, any = !EMPTY || h.n > 0;
+        const int n = h.n;
         pos = head(pos);
         keep_order();
         start_products(rx, d);
-        half_pass<0>(w, rx, d);
+        first_half(n);
         keep_order();
         load_columns<0, 8>(columns, h.off, n8, w);
         keep_order();
-        if (whole) half_pass<1>(w, rx, d);
+        second_half(n);
         keep_order();
         load_columns<8, 16>(columns, h.off, n8, w);
         keep_order();
-        if (any) {
+        if (!EMPTY || n > 0) {
             add_scaled<BATCH, GROUPS>(d, sc, acc);
             sign ^= kSignOfX;
         }
@@ -293,8 +303,8 @@ __device__ __forceinline__ void run_passes(StagedX &staged, const uint8_t *row_b
     }
     stage_x<BATCH, GROUPS>(staged, lane, h.j, sign, h.xraw);
     start_products(rx, d);
-    half_pass<0>(w, rx, d);
-    if (h.n > kPassCols / 2) half_pass<1>(w, rx, d);
+    first_half(h.n);
+    second_half(h.n);
     if (!EMPTY || h.n > 0) add_scaled<BATCH, GROUPS>(d, sc, acc);
     else sign ^= kSignOfX;       // the sums still have the sign of the pass before
 #pragma unroll

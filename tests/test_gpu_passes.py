@@ -108,6 +108,23 @@ def test_half_passes(gpu, rows):
         check(run(gpu, wd, xd, 0.0, "dense", splits=1), oracle.gemv(wd["q_rowmajor"], wd["scales"], xd, 0.0), f"dense K={Kd}")
 
 
+@pytest.mark.parametrize("rows", [1, 2, 3, 4])
+def test_passes_end_at_any_sixteen(gpu, rows):
+    """Slices of 15 to 17, 31 to 33 and 47 to 49 entries, and of as many behind a full pass (the products of the sixteens that a pass does not
+    reach are left out): four wavefronts take a quarter of the list each.  Exact numbers, so the outputs are the oracle's bit for bit."""
+    M, K = 256, 640
+    w = make_weights(M, K, 5180)
+    w["scales"] = (2.0 ** np.random.default_rng(5181).integers(-3, 1, w["scales"].shape)).astype(np.float16)
+    base = np.random.default_rng(5182 + rows).integers(1, 9, (rows, K)).astype(np.float16)
+    for each in (1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 80, 81, 112, 113):
+        x = np.zeros_like(base)
+        x[:, : 4 * each] = base[:, : 4 * each]
+        ref = oracle.gemv(w["q_rowmajor"], w["scales"], x, 0.5)
+        for mode in ("list", "fused"):
+            print(f"sixteens rows={rows} each={each} {mode}", flush=True)
+            assert np.array_equal(run(gpu, w, x, 0.5, mode, splits=1).astype(np.float64), ref), (each, mode)
+
+
 @pytest.mark.parametrize("rows", [1, 2, 4])
 @pytest.mark.parametrize("K,splits", [(128, 1), (384, 2), (640, 3), (1152, 5), (2944, 1)])
 def test_one_launch_slices_of_any_column(gpu, rows, K, splits):
