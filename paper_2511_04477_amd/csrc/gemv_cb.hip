@@ -91,6 +91,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
         for (int i = 0; i < 32; ++i) acc[b][i] = 0.0f;
     }
 
+    constexpr float kBias = KQ ? 1.0f : 8.0f;      // what a product carries of the staged value that bsum sums
     if (pos < end) {
         KeptRing ring(ring_slots[FUSED ? wave : 0], x, K, pos, end, thr, lane);
         // Atomic loads (the same instructions): the compiler moves plain ones down to the use of their values, behind the
@@ -207,8 +208,26 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
         load_half(0);
         load_half(1);
         outputs.read_now();
-        while (more(pos)) {
+        // With a list, and dense, the sums start at the bias of the first pass, so that this pass's products carry none: products of codes that are not centred
+        // make sums that are further off (error against 64-bit arithmetic, list at 50 % 14336 x 4096 with 9 workgroups per block-row 1.81e-7 / 1.29e-7, with
+        // 4 of them 2.09e-7 / 1.63e-7), and staging a pass's x behind the products of the one before makes lists 0.5 to 1.5 % faster (dense: 0.3 to 1.7 % slower,
+        // K-quant 0.5 to 1 % faster; 4 rows, with four times the sums to set, 1 to 2.5 % slower).  In one launch it is slower (K-quant 13824 x 5120 9.03 / 9.12 us).
+        constexpr bool kCentred = !FUSED;
+        if constexpr (kCentred) {
             stage();
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b) {
+                float first = 0.0f;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) first += KQ ? stage_xm[wave][b][u * 8 + cg][seg] : stage_xs[wave][b][u * 8 + cg][seg];
+                bsum[b] = -first;
+                const float even = first * (-kBias / kTwo24), odd = first * (-kBias * 16.0f / kTwo24);
+#pragma unroll
+                for (int i = 0; i < 32; ++i) acc[b][i] = i & 1 ? odd : even;
+            }
+        }
+        while (more(pos)) {
+            if (!kCentred) stage();
             const bool whole = !FUSED || n > kPassCols / 2;
             pos = head(pos);
             keep_order();
@@ -224,8 +243,9 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
             keep_order();
             load_half(1);
             keep_order();
+            if (kCentred) stage();
         }
-        stage();
+        if (!kCentred) stage();
 #pragma unroll
         for (int u = 0; u < 8; ++u)
             if (u * 8 < n) step(u);
@@ -238,7 +258,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
     for (int b = 0; b < BATCH; ++b) {
         float r4[4];
         fold_columns(acc[b], r4);
-        const float bias = sum_over_columns(bsum[b]) * (KQ ? 1.0f : 8.0f);
+        const float bias = sum_over_columns(bsum[b]) * kBias;
         reinterpret_cast<f32x4 *>(red[wave][b])[8 * seg + cgr] = true_rows(r4, bias);
     }
     __syncthreads();
@@ -300,6 +320,7 @@ int run_cb(int mode, int batch, const void *packed_dev, int64_t M, int64_t K, co
     spqt_launch_cfg c;
     const Columns from = mode == 1 || mode == 4 ? Columns::dense : mode == 2 || mode == 5 ? Columns::units : Columns::list;
     c.splits = colblock_splits(tiles(M), K, from, batch, colblock4_depth(tiles(M), from, batch, mode >= 3));
+    if (mode == 0 && batch == 1) c.splits = colblock4_list_splits(tiles(M), K, c.splits);
     while (c.splits > K / kGroup) --c.splits;      // at least a quarter of a chunk per wavefront
     c.waves = 4;
     size_t need = 0;
