@@ -88,7 +88,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_gemv_list_kernel(
                 const int e = slot_of(lane);
                 h.chunk = chunk;
                 h.off = chunk + (uint32_t)in_group * kColBytes + (e < h.n ? (uint32_t)e * kColBytes : 0u);
-                h.j = lane < h.n ? 0 : -1;
+                h.j = lane < h.n ? 0 : 4;
 #pragma unroll
                 for (int b = 0; b < BATCH; ++b) h.xraw[b] = *element(x, (uint32_t)(b * K + p + (lane < h.n ? lane : 0)));
                 return p + h.n;
