@@ -86,6 +86,7 @@ inline void choose_cfg(int64_t M, int64_t K, int batch, spqt_launch_cfg *out) {
 //   - lists of 1 or 2 rows go deeper for a 3 % fuller last round (8-bit, T = 86, 11008 x 4096 S = 2 / 5 / 8 8.7 / 8.1 / 8.5; the third workgroup no
 //     longer pays there, and 4-bit, T = 54, 13824 x 5120 S = 4 / 8 / 14 is 8.1 / 8.6 / 8.2), the others only for a 20 % fuller one, since two
 //     workgroups on a CU cost them more than that (4-bit dense 13824 x 5120 S = 4 / 8 10.0 / 10.7, 4 rows 19.9 / 21.5);
+//     (with one row colblock4_list_splits and colblock8_list_splits below take back what no longer pays);
 //   - a list slice of 112 to 256 columns (1 or 2 rows) is a pass and a bit: two workgroups per CU (no longer a gain: 8-bit 4096 x 4096
 //     S = 8 / 16 5.5 / 5.7; 4-bit 9000 x 2944 with 105 columns S = 7 / 14 5.9 / 6.0);
 //   - dense slices of at most one pass, if 3 workgroups per CU reach that without a less full round (no longer a gain: 4-bit 11008 x 4096
