@@ -22,7 +22,7 @@
 //
 // Products: v_mfma_f32_16x16x32_f16 computes D[m][n] += sum over 32 k of A[m][k] * B[k][n]; lane l brings A[l % 16] and
 // B[..][l % 16] at the 8 k of quarter l / 16, i.e. at 4 of the 16 columns of its quarter with two k each, h = 0 and 1.  B is one dword of each
-// column, shifted and masked: the halves are ONE code each (fp16 subnormals), of two rows of W.  A is the raw fp16 x, in row m at the k of the half
+// column, shifted and masked: the halves are ONE code each, of two rows of W.  A is the raw fp16 x, in row m at the k of the half
 // that row m is about and zero at the other: the two rows that share a dword need not be brought apart.
 // The sum over k is the sum over all columns of the pass, so nothing is left to fold across lanes.
 // The 16 rows of A are 4 v + j: v = 2 d + h (d: which dword of the column, two variants of A with zeros in the other rows; h: which half) says which
@@ -49,9 +49,10 @@ namespace spqt {
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ f16x8 as_f16x8(u32x4 bits) { return __builtin_bit_cast(f16x8, bits); }
 
-// Where the four codes of 16 bits of a column run are multiplied, and what undoes the units: a code at bits 6..9 of an fp16 half is code * 2^-18,
-// at bits 4..7 code * 2^-20, at bits 2..5 code * 2^-22.  Code 0 is shifted left by 6, code 1 stays, codes 2 and 3 are shifted right by 6.
-constexpr float kUnit[4] = {262144.0f, 1048576.0f, 4194304.0f, 262144.0f};
+// Where the four codes of 16 bits of a column run are multiplied, and what undoes the units: codes 1 and 3 at bits 7..10 of an fp16 half (code * 2^-17;
+// from code 8 on the half has exponent field 1, whose step is the subnormals' 2^-24 too), codes 0 and 2 at bits 3..6 (code * 2^-21).  Codes 0 and 1 are
+// shifted left by 3, codes 2 and 3 right by 5.
+constexpr float kUnit[4] = {2097152.0f, 131072.0f, 2097152.0f, 131072.0f};
 
 // activation rows as the passes count them (3 is treated as 4 with a zero row), and quantization groups per pass
 constexpr int padded_rows(int batch) { return batch == 3 ? 4 : batch; }
@@ -97,8 +98,11 @@ __device__ __forceinline__ void load_columns(const uint8_t *base, uint32_t off, 
 
 // Products of the 16 slots (c, u), u = 4 Q .. 4 Q + 3: d[p][j] += sum of code(row 16 n + 4 v + p, slot) * x(j, slot)
 // in units of kUnit[p].
-// The matrix cores align products by the exponent FIELDS, so bits that a subnormal has above its code are bits of
-// precision lost in every product: codes sit as high as one shift per two codes brings them.
+// The matrix cores align products by the exponent FIELDS, so bits that a half has above its code are bits of precision lost in every product: codes sit as
+// high as one shift per two codes brings them.  That is by row, not only on the whole: error against 64-bit arithmetic of rows 0, 1, 2, 3 modulo 4,
+// dense 5120 x 5120, 1.7e-7 9.4e-8 1.7e-7 9.2e-8 with Laplace x, 5.5e-7 1.0e-7 5.4e-7 1.0e-7 with SiLU products.  (Other places for six instructions: at bits 6, 4, 2,
+// 6 with the bias at 2 2.6e-7 2.8e-7 5.4e-7 2.6e-7, at 7, 4, 3, 7 with SiLU products 1.1e-7 2.0e-7 5.4e-7 1.0e-7.  For seven, 7, 7, 3, 7, 1.1e-7 1.0e-7
+// 5.4e-7 1.0e-7 and 0.5 to 1 % longer calls; for eight, all at bit 7, 1.0e-7 in every row and 1 to 3 %.)
 template <int Q>
 __device__ __forceinline__ void quarter_pass(const u32x2 (&w)[16], const ReadsX &rx, f32x4 (&d)[4]) {
     const u32x4 x[2] = {rx.of_variant[0][Q], rx.of_variant[1][Q]};
@@ -107,11 +111,11 @@ __device__ __forceinline__ void quarter_pass(const u32x2 (&w)[16], const ReadsX 
         u32x4 b[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const uint32_t c = w[4 * Q + k][i], right = c >> 6;
-            b[0][k] = (c << 6) & 0x03C003C0u;
-            b[1][k] = c & 0x00F000F0u;
-            b[2][k] = right & 0x003C003Cu;
-            b[3][k] = right & 0x03C003C0u;
+            const uint32_t c = w[4 * Q + k][i], left = c << 3, right = c >> 5;
+            b[0][k] = left & 0x00780078u;
+            b[1][k] = left & 0x07800780u;
+            b[2][k] = right & 0x00780078u;
+            b[3][k] = right & 0x07800780u;
         }
 #pragma unroll
         for (int p = 0; p < 4; ++p) d[p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(x[i]), as_f16x8(b[p]), d[p], 0, 0, 0);
@@ -119,18 +123,15 @@ __device__ __forceinline__ void quarter_pass(const u32x2 (&w)[16], const ReadsX 
 }
 
 // The bias of the offset-binary codes (stored = q + 8) enters as the accumulators' initial value: the product of x with
-// the constant -8 in the codes' own units.
+// the constant -8 in the units of codes 1 and 3, where no bit of it is lost.
 __device__ __forceinline__ void start_products(const ReadsX &rx, f32x4 (&d)[4]) {
-    const f16x8 eight = as_f16x8(u32x4{0x80208020u, 0x80208020u, 0x80208020u, 0x80208020u});    // -8 * 2^-22
+    const f16x8 eight = as_f16x8(u32x4{0x84008400u, 0x84008400u, 0x84008400u, 0x84008400u});    // -8 * 2^-17
     f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int i = 0; i < 4; ++i) sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(rx.mine[i]), eight, sum, 0, 0, 0);
-    d[2] = sum;
+    d[1] = d[3] = sum;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        d[0][j] = d[3][j] = sum[j] * (kUnit[2] / kUnit[0]);
-        d[1][j] = sum[j] * (kUnit[2] / kUnit[1]);
-    }
+    for (int j = 0; j < 4; ++j) d[0][j] = d[2][j] = sum[j] * (kUnit[1] / kUnit[0]);
 }
 
 // Every other pass is computed with -x.  The matrix cores round the terms of a product DOWN, so a

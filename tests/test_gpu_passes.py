@@ -242,3 +242,28 @@ def test_no_bias_is_left_in_the_sums(gpu, rows, dist):
         rel = np.linalg.norm(got - ref) / np.linalg.norm(ref)
         print(f"bias rows={rows} {dist} {mode}: {rel:.2e}", flush=True)
         assert rel < 2e-6
+
+
+@pytest.mark.parametrize("rows,dist,high,low", [(1, "laplace", 1.2e-7, 3e-7), (2, "laplace", 1.2e-7, 3e-7), (4, "laplace", 1.2e-7, 3e-7),
+                                                (1, "silu_product", 1.6e-7, 8e-7)])
+def test_error_of_every_row_class(gpu, rows, dist, high, low):
+    """The four codes of 16 bits are multiplied at different bits of their halves, so rows differ by their number modulo 4.  The matrix cores keep 24 bits below
+    the largest exponent field of a product: codes 1 and 3 fill the bits below theirs, which leaves what 32-bit sums leave (1.0e-7), codes 0 and 2 sit
+    four bits lower and lose up to four bits of the small x (2.1e-7; SiLU products, with more small x, 5.0e-7).  The bounds lie below what rows 1, 2 and 3 were off
+    by with codes at bits 6, 4, 2 and 6 and the bias at 2 (1.2e-7 to 1.7e-7 and 3.6e-7 to 6.9e-7; SiLU products 8.3e-7 and 2.8e-6)."""
+    M, K = 1024, 5120
+    w = make_weights(M, K, 5600)
+    r = np.random.default_rng(5601)
+    if dist == "laplace":
+        x = r.laplace(size=(rows, K)).astype(np.float16)
+    else:
+        g, u = r.standard_normal((2, rows, K))
+        x = (g / (1 + np.exp(-g)) * u).astype(np.float16)
+    q = w["q_rowmajor"]
+    codes = np.stack([q & 15, q >> 4], -1).reshape(M, K).astype(np.int64)
+    W = np.where(codes > 7, codes - 16, codes) * np.repeat(w["scales"].view(np.float16).astype(np.float64), 128, axis=1)
+    ref = x.astype(np.float64) @ W.T
+    off = run(gpu, w, x, 0.0, "dense").astype(np.float64) - ref
+    rel = [float(np.linalg.norm(off[:, i::4]) / np.linalg.norm(ref[:, i::4])) for i in range(4)]
+    print(f"error by row rows={rows} {dist}: " + " ".join(f"{v:.2e}" for v in rel), flush=True)
+    assert max(rel[1], rel[3]) < high and max(rel[0], rel[2]) < low, rel
