@@ -18,7 +18,8 @@
 //     products in LDS; a lane picks up the product of its own (column, block) per step.
 //   - the 32 accumulators run through the whole slice; the 8 column-lanes are folded once at
 //     the end, and the offset-binary bias (stored = q + 8) is removed there as -8 * (sum of
-//     x * s of the lane's block over the slice).
+//     x * s of the lane's block) over the passes whose products carry it.  With a list, and dense,
+//     those of a slice's first pass, and of the second one in long slices, do not (`centre`).
 //   - (Scaling x by 2^24 and by 1/16 for the odd nibbles where it is staged and read, and 64-bit addresses, took 20 of 520 instructions a pass more: list at
 //     50 % with the gather 4096 x 4096 7.78 / 7.68 us, 5120 x 13824 10.5 / 10.4, K-quant in one launch at 40 % 5120 x 13824 8.96 / 8.86.)
 //   - one buffer of weights refilled half by half, unpredicated clamped loads, reduction through LDS and the
@@ -36,6 +37,8 @@ using namespace spqt;
 constexpr int kCbScaleBytes = kGroup * 16;                 // 128 columns x 8 fp16 scales
 constexpr int kCbChunkBytes = SPQT_CB_CHUNK_BYTES;
 static_assert(kCbChunkBytes == kCbScaleBytes + kGroup * kColBytes, "chunk size");
+
+constexpr int kLongSlicesBit = 1 << 26;        // in the kernel's M argument, above M: see `centre`
 
 // FUSED: the kernel applies the sparsity test itself instead of reading an index list (as
 // spqt_gemv_fused does for the group layout): a wavefront's slice is a static range of columns, and its
@@ -204,27 +207,40 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
             k_next = fetch_k(pos);
         }
         auto more = [&](int p) { return FUSED ? ring.more(p) : p < end; };
+        const int second_end = pos + 2 * kPassCols;      // of the second pass, where it is full
         pos = head(pos);
         load_half(0);
         load_half(1);
         outputs.read_now();
         // With a list, and dense, the sums start at the bias of the first pass, so that this pass's products carry none: products of codes that are not centred
-        // make sums that are further off (error against 64-bit arithmetic, list at 50 % 14336 x 4096 with 9 workgroups per block-row 1.81e-7 / 1.29e-7, with
-        // 4 of them 2.09e-7 / 1.63e-7), and staging a pass's x behind the products of the one before makes lists 0.5 to 1.5 % faster (dense: 0.3 to 1.7 % slower,
-        // K-quant 0.5 to 1 % faster; 4 rows, with four times the sums to set, 1 to 2.5 % slower).  In one launch it is slower (K-quant 13824 x 5120 9.03 / 9.12 us).
+        // make sums that are further off.  Error against 64-bit arithmetic, without / with, and time (us):
+        //   list, one row    14336 x 4096 at 50 %, S = 4   2.09e-7 / 1.63e-7   9.48 / 9.40
+        //   dense, one row   14336 x 4096                  2.84e-7 / 2.36e-7   8.62 / 8.62     4096 x 14336   2.73e-7 / 2.28e-7   9.18 / 9.25
+        //   list, 4 rows     14336 x 4096 at 60 %          2.64e-7 / 2.20e-7   18.75 / 18.76
+        //   dense, 4 rows    4096 x 4096                   1.95e-7 / 1.48e-7   9.37 / 9.36
+        //   K-quant          14336 x 4096 at 50 %          1.24e-7 / 1.15e-7   9.95 / 9.88     4 rows at 60 %   1.36e-7 / 1.33e-7   19.8 / 20.0
+        // In one launch it is slower (K-quant 13824 x 5120 9.03 / 9.12), and the sums stay as they were.
+        // Where colblock4_list_splits chose the launch shape (kLongSlicesBit), a slice well over two passes long takes the second pass so, too: where most columns are
+        // kept, its four passes would be further off than the two of the slices that they replace (14336 x 4096 with S = 9, no pass centred / S = 4, one pass / S = 4,
+        // two passes: all kept 2.18e-7 / 2.36e-7 / 2.00e-7, 80 % kept 2.00e-7 / 2.10e-7 / 1.75e-7; 12.8 / 11.65 / 11.71 us and 11.4 / 10.6 / 10.65).
         constexpr bool kCentred = !FUSED;
-        if constexpr (kCentred) {
-            stage();
+        constexpr bool kTwice = BATCH == 1 && !DENSE && !FUSED && !KQ;
+        // The products of the staged pass carry no bias: the sums are ahead of it by what its x adds up to.
+        auto centre = [&](bool first_pass) {
 #pragma unroll
             for (int b = 0; b < BATCH; ++b) {
-                float first = 0.0f;
+                float total = 0.0f;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) first += KQ ? stage_xm[wave][b][u * 8 + cg][seg] : stage_xs[wave][b][u * 8 + cg][seg];
-                bsum[b] = -first;
-                const float even = first * (-kBias / kTwo24), odd = first * (-kBias * 16.0f / kTwo24);
+                for (int u = 0; u < 8; ++u) total += KQ ? stage_xm[wave][b][u * 8 + cg][seg] : stage_xs[wave][b][u * 8 + cg][seg];
+                const float even = total * (-kBias / kTwo24), odd = total * (-kBias * 16.0f / kTwo24);
+                bsum[b] = first_pass ? -total : bsum[b] - total;
 #pragma unroll
-                for (int i = 0; i < 32; ++i) acc[b][i] = i & 1 ? odd : even;
+                for (int i = 0; i < 32; ++i) acc[b][i] = first_pass ? (i & 1 ? odd : even) : acc[b][i] + (i & 1 ? odd : even);
             }
+        };
+        if constexpr (kCentred) {
+            stage();
+            centre(true);
         }
         while (more(pos)) {
             if (!kCentred) stage();
@@ -244,6 +260,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
             load_half(1);
             keep_order();
             if (kCentred) stage();
+            if (kTwice && pos == second_end && end - pos > kPassCols / 2 && (M & kLongSlicesBit)) centre(false);
         }
         if (!kCentred) stage();
 #pragma unroll
@@ -320,7 +337,12 @@ int run_cb(int mode, int batch, const void *packed_dev, int64_t M, int64_t K, co
     spqt_launch_cfg c;
     const Columns from = mode == 1 || mode == 4 ? Columns::dense : mode == 2 || mode == 5 ? Columns::units : Columns::list;
     c.splits = colblock_splits(tiles(M), K, from, batch, colblock4_depth(tiles(M), from, batch, mode >= 3));
-    if (mode == 0 && batch == 1) c.splits = colblock4_list_splits(tiles(M), K, c.splits);
+    int long_slices = 0;
+    if (mode == 0 && batch == 1) {
+        const int few = colblock4_list_splits(tiles(M), K, c.splits);
+        if (few < c.splits && !(cfg && (cfg->splits || cfg->waves))) long_slices = kLongSlicesBit;
+        c.splits = few;
+    }
     while (c.splits > K / kGroup) --c.splits;      // at least a quarter of a chunk per wavefront
     c.waves = 4;
     size_t need = 0;
@@ -350,7 +372,7 @@ int run_cb(int mode, int batch, const void *packed_dev, int64_t M, int64_t K, co
     switch (c.waves) {
         case 1: err = launch_cb<1>(mode, batch, grid, st, pk, xp, idx_dev, count_dev, (float *)y_dev, ws, (int)K, c.splits, T, (int)M, threshold, y_half); break;
         case 2: err = launch_cb<2>(mode, batch, grid, st, pk, xp, idx_dev, count_dev, (float *)y_dev, ws, (int)K, c.splits, T, (int)M, threshold, y_half); break;
-        default: err = launch_cb<4>(mode, batch, grid, st, pk, xp, idx_dev, count_dev, (float *)y_dev, ws, (int)K, c.splits, T, (int)M, threshold, y_half); break;
+        default: err = launch_cb<4>(mode, batch, grid, st, pk, xp, idx_dev, count_dev, (float *)y_dev, ws, (int)K, c.splits, T, (int)M | long_slices, threshold, y_half); break;
     }
     return err == hipSuccess ? SPQT_OK : SPQT_EHIP;
 }

@@ -176,11 +176,13 @@ inline int colblock8_list_splits(int64_t T, int64_t K, int S) {
 }
 
 // The same for the 4-bit list kernel with one activation row (not its K-quant flavour): up to 128 block-rows one workgroup per CU where that leaves slices of
-// at most 256 columns, so that sums stay as short as before: they start at the first pass's bias (gemv_cb.hip), which a slice of one or two passes gains
-// most from (S = this rule / before, us with the gather and error against 64-bit arithmetic at 50 %: 14336 x 4096 S = 4 / 9 9.43 / 9.80, 1.63e-7 / 1.81e-7;
-// 11008 x 4096 S = 5 / 11 8.95 / 9.26, 1.61e-7 / 1.80e-7 at 40 %; 8192 x 8192 S = 8 / 16 10.1 / 10.55, 1.83e-7 / 2.01e-7; 9472 x 1152 S = 6 / 9 6.66 / 7.00; no height
-// slower by more than 0.5 %).  Longer slices would be 2 to 4 % faster and their sums further off (14336 x 8192 12.4 / 12.8, 2.29e-7 / 2.10e-7; K-quant 14336 x 4096
-// 9.58 / 9.87, 1.27e-7 / 1.24e-7).
+// at most 256 columns.  Their sums are no further off than those of the shorter slices whatever is kept, since the first pass of a slice is centred and of four
+// passes the second one too (gemv_cb.hip).  S = this rule / before, us with the gather and error against 64-bit arithmetic:
+//   14336 x 4096   S = 4 / 9    at 50 %  9.44 / 9.96   1.63e-7 / 1.81e-7     all kept  11.7 / 12.8   2.00e-7 / 2.18e-7
+//   11008 x 4096   S = 5 / 11   at 40 %  9.27 / 9.82   1.61e-7 / 1.80e-7     all kept  11.1 / 11.5   1.80e-7 / 2.08e-7
+//   8192 x 8192    S = 8 / 16   at 50 %  10.1 / 10.9   1.71e-7 / 1.92e-7     all kept  12.8 / 13.3   2.07e-7 / 2.29e-7
+// (no height slower by more than 0.5 %).  Longer slices would be 2 to 4 % faster and their sums further off (one pass centred, at 50 %: 14336 x 8192 12.4 / 12.8,
+// 2.29e-7 / 2.10e-7; K-quant 14336 x 4096 9.58 / 9.87, 1.27e-7 / 1.24e-7).
 inline int colblock4_list_splits(int64_t T, int64_t K, int S) {
     if (T > 128) return S;
     const int64_t one = 256 / T;
