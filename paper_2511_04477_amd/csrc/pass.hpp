@@ -220,19 +220,19 @@ struct PassHead {
     uint32_t off;          // byte offset of the column in this lane's SLOT of the pass whose weights are requested next
     int n;                 // entries of that pass (wave-uniform)
     uint64_t starts;       // where the groups of that pass start
-    uint32_t chunk;        // byte offset of the chunk of the lane's candidate of that pass, of some chunk of the pass where it takes none
+    uint32_t chunk;        // byte offset of the chunk of the lane's candidate of that pass, of the pass's last entry where it takes none
     int j;                 // group of the lane's entry inside that pass, or 4: not part of it
     uint16_t xraw[BATCH];  // its x
 };
 
 // Deals the candidates kk (-1 past the slice) and notes in h what the pass's loads and products need, but its x.  Lanes that take none point at the
-// pass's first column (a line that is fetched anyway; the first column of all in a pass without entries) and carry x = 0.
+// pass's last column (a line that is fetched anyway; the first column of all in a pass without entries) and carry x = 0.
 template <int GROUPS, int BATCH>
 __device__ __forceinline__ Deal deal_columns(PassHead<BATCH> &h, int kk, int log2g, uint32_t chunk_b, int lane) {
     const int g = kk >> log2g;
     const Deal d = deal_groups<GROUPS>(kk, g, lane);
-    const int k_first = __builtin_amdgcn_readfirstlane(kk);
-    const uint32_t k = (uint32_t)(d.take ? kk : (k_first < 0 ? 0 : k_first));
+    const int k_last = __builtin_amdgcn_readlane(kk, d.n - 1);       // (no entries: lane 63)
+    const uint32_t k = (uint32_t)(d.take ? kk : (k_last < 0 ? 0 : k_last));
     h.chunk = (k >> log2g) * chunk_b;
     h.off = slot_order(h.chunk + (k & ((1u << log2g) - 1u)) * kColBytes, lane);
     h.n = d.n;
@@ -241,7 +241,8 @@ __device__ __forceinline__ Deal deal_columns(PassHead<BATCH> &h, int kk, int log
     return d;
 }
 
-// The scales of the lane's 4 rows in each group of the pass; behind its last one, those of some group of it.
+// The scales of the lane's 4 rows in each group of the pass; behind its last one, that one's.  (They meet sums of zero, which an infinite scale makes NaN: so
+// no other group's, where a row whose scale is infinite would have been infinite.)
 template <int BATCH, int GROUPS>
 __device__ __forceinline__ void load_scales(const uint8_t *row_base, uint32_t out4, const PassHead<BATCH> &h, u32x2 (&sc)[GROUPS]) {
     if (GROUPS == 1) {           // the group of the pass's first entry
@@ -251,7 +252,7 @@ __device__ __forceinline__ void load_scales(const uint8_t *row_base, uint32_t ou
     uint64_t left = h.starts;
 #pragma unroll
     for (int i = 0; i < GROUPS; ++i) {
-        int at;      // the first start that is left, or -1, which v_readlane takes as lane 63
+        int at;      // the first start that is left, or -1, which v_readlane takes as lane 63: the last group's, whether it takes an entry or not
         asm("s_ff1_i32_b64 %0, %1\n\ts_bitset0_b64 %1, %0" : "=&s"(at), "+s"(left));
         const uint32_t chunk = (uint32_t)__builtin_amdgcn_readlane((int)h.chunk, at);
         sc[i] = *reinterpret_cast<const u32x2 *>(row_base + (size_t)(chunk + out4 * 8u));

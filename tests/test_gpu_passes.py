@@ -267,3 +267,38 @@ def test_error_of_every_row_class(gpu, rows, dist, high, low):
     rel = [float(np.linalg.norm(off[:, i::4]) / np.linalg.norm(ref[:, i::4])) for i in range(4)]
     print(f"error by row rows={rows} {dist}: " + " ".join(f"{v:.2e}" for v in rel), flush=True)
     assert max(rel[1], rel[3]) < high and max(rel[0], rel[2]) < low, rel
+
+
+@pytest.mark.parametrize("mode", ["list", "fused", "even"])
+def test_infinite_scale_in_a_pass_of_few_groups(gpu, mode):
+    """A pass with fewer groups than it could take applies the scales of its last one in their place, to sums that are zero: where an earlier group's scale
+    is infinite, the row's output is infinite and not NaN.  One wavefront, so that the groups share a pass; rows of every class modulo 4."""
+    torch, spqt, dev = gpu
+    M, K = 256, 512
+    w = make_weights(M, K, 5650)
+    w["q_rowmajor"][:] = 0x33
+    rows = np.array([0, 1, 2, 3, 129, 255])
+    for kept in ([5, 9, 130], [5, 130, 131, 200, 201], [0, 100, 127, 255]):
+        x = np.zeros(K, dtype=np.float16)
+        x[kept] = 1.5
+        ref = oracle.gemv(w["q_rowmajor"], w["scales"], x[None], 0.5)[0]
+        scales = w["scales"].copy()
+        scales[rows, 0] = np.float16(np.inf)
+        packed = torch.from_numpy(spqt.spqt_pack(w["q_rowmajor"], scales)).to(dev)
+        xd = torch.from_numpy(x).to(dev)
+        y = torch.full((M,), float("nan"), dtype=torch.float32, device=dev)
+        ws = spqt.new_workspace(M, K)
+        print(f"infinite scale {mode} kept={kept}", flush=True)
+        if mode == "list":
+            idx = torch.zeros(K, dtype=torch.int32, device=dev)
+            cnt = torch.zeros(1, dtype=torch.int32, device=dev)
+            spqt.spqt_gather(xd, 0.5, idx, cnt)
+            spqt.spqt_gemv(packed, M, K, xd, idx, cnt, y, ws, splits=1, waves=1)
+        else:
+            spqt.spqt_gemv_fused(packed, M, K, xd, 0.5, y, ws, splits=1, waves=1, flags=spqt.binding.CFG_EVEN_SHARES if mode == "even" else 0)
+        torch.cuda.synchronize()
+        got = y.cpu().numpy()
+        ref[rows] = np.inf
+        assert np.all(np.isinf(got[rows]) & (got[rows] > 0)), got[rows]
+        others = np.setdiff1d(np.arange(M), rows)
+        check(got[others], ref[others], f"{mode} {kept}")
