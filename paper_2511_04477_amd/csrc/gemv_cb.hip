@@ -225,7 +225,8 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
         // two passes: all kept 2.18e-7 / 2.36e-7 / 2.00e-7, 80 % kept 2.00e-7 / 2.10e-7 / 1.75e-7; 12.8 / 11.65 / 11.71 us and 11.4 / 10.6 / 10.65).
         constexpr bool kCentred = !FUSED;
         constexpr bool kTwice = BATCH == 1 && !DENSE && !FUSED && !KQ;
-        // The products of the staged pass carry no bias: the sums are ahead of it by what its x adds up to.
+        // The products of the staged pass carry no bias: the sums are ahead of it by what its x adds up to.  (K-quant: what the steps of that pass count is
+        // dropped instead; a minimum may be infinite where the products are not, and taken off and added again it would be NaN.)
         auto centre = [&](bool first_pass) {
 #pragma unroll
             for (int b = 0; b < BATCH; ++b) {
@@ -233,16 +234,23 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
 #pragma unroll
                 for (int u = 0; u < 8; ++u) total += KQ ? stage_xm[wave][b][u * 8 + cg][seg] : stage_xs[wave][b][u * 8 + cg][seg];
                 const float even = total * (-kBias / kTwo24), odd = total * (-kBias * 16.0f / kTwo24);
-                bsum[b] = first_pass ? -total : bsum[b] - total;
+                if (!KQ) bsum[b] = first_pass ? -total : bsum[b] - total;
 #pragma unroll
                 for (int i = 0; i < 32; ++i) acc[b][i] = first_pass ? (i & 1 ? odd : even) : acc[b][i] + (i & 1 ? odd : even);
             }
         };
         if constexpr (kCentred) {
+            if (KQ && lane >= n) sv = u32x4{0u, 0u, 0u, 0u};      // all 64 entries are counted: none of a column that is not the lane's
             stage();
             centre(true);
         }
+        const int first_end = pos;
+        auto drop_counted = [&]() {
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b) bsum[b] = 0.0f;
+        };
         while (more(pos)) {
+            const bool first = KQ && kCentred && pos == first_end;
             if (!kCentred) stage();
             const bool whole = !FUSED || n > kPassCols / 2;
             pos = head(pos);
@@ -259,6 +267,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
             keep_order();
             load_half(1);
             keep_order();
+            if (first) drop_counted();
             if (kCentred) stage();
             if (kTwice && pos == second_end && end - pos > kPassCols / 2 && (M & kLongSlicesBit)) centre(false);
         }
@@ -266,6 +275,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
 #pragma unroll
         for (int u = 0; u < 8; ++u)
             if (u * 8 < n) step(u);
+        if (KQ && kCentred && pos == first_end) drop_counted();
     } else {
         outputs.read_now();
     }

@@ -466,3 +466,36 @@ def test_list_error_at_any_sparsity(gpu, sparsity, bound):
     err = (off / whole) ** 0.5
     print(f"4-bit list, {sparsity:.0%} dropped: {err:.3e}", flush=True)
     assert err < bound
+
+
+@pytest.mark.parametrize("batch", [1, 3])
+@pytest.mark.parametrize("columns", [40, 128, 384])
+def test_cbk_infinite_minimum(gpu, batch, columns):
+    """The sums start at the minima of a slice's first pass; an infinite one (first column, its x of either sign) makes every output infinite, not NaN.
+    One wavefront; one pass, two and six."""
+    torch, spqt, dev = gpu
+    M, K = 512, 384
+    r = np.random.default_rng(9800)
+    chunks = r.integers(0, 256, (M // 256, K // 128, 2048 + 128 * 128), dtype=np.uint8)
+    head = chunks[:, :, :2048].reshape(M // 256, K // 128, 128, 16)
+    head[..., :4] = r.uniform(0.001, 0.01, head.shape[:3] + (2,)).astype(np.float16).view(np.uint8)
+    head[..., 4:] |= 0x41                       # no field is 0
+    head[:, 0, 0, 2:4] = np.frombuffer(np.float16(np.inf).tobytes(), np.uint8)
+    chunks[:, :, :2048] = head.reshape(M // 256, K // 128, 2048)
+    packed = torch.from_numpy(chunks.reshape(-1)).to(dev)
+    ws = spqt.new_workspace(M, K, batch)
+    for sign in (1.0, -1.0):
+        x = torch.from_numpy((sign * r.uniform(0.5, 2.0, (batch, K))).astype(np.float16)).to(dev)
+        x = x if batch > 1 else x[0].contiguous()
+        idx = torch.arange(K, dtype=torch.int32, device=dev)
+        cnt = torch.full((1,), columns, dtype=torch.int32, device=dev)
+        say(f"K-quant infinite minimum batch={batch} columns={columns} sign={sign}")
+        y = torch.full((batch, M) if batch > 1 else (M,), float("nan"), dtype=torch.float32, device=dev)
+        spqt.spqt_cbk_gemv(packed, M, K, x, idx, cnt, y, ws, splits=1, waves=1)
+        torch.cuda.synchronize()
+        assert bool(torch.all(y == -sign * float("inf"))), (columns, sign, y)
+        if columns == K:
+            y.fill_(float("nan"))
+            spqt.spqt_cbk_gemv(packed, M, K, x, None, None, y, ws, splits=1, waves=1)
+            torch.cuda.synchronize()
+            assert bool(torch.all(y == -sign * float("inf"))), (sign, y)
