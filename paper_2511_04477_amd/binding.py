@@ -3,14 +3,16 @@
 
 Same names as the C ABI (include/spqt.h).  Host calls take NumPy arrays; device calls take
 torch CUDA tensors (PyTorch supplies device memory and the stream, nothing else) and launch
-on torch's current stream unless one is given.  There is no fallback of any kind: if the
-shared library is missing, importing a symbol from it raises.
+on torch's current stream unless one is given.  There is no fallback of any kind for the
+shared library: if it is missing, importing a symbol from it raises.  Without _fastcall the code
+here makes the same calls.
 """
 from __future__ import annotations
 
 import ctypes
 import os
 import types
+import warnings
 
 import numpy as np
 
@@ -174,14 +176,28 @@ def spqt_unpack(packed: np.ndarray, M: int, K: int, group: int = GROUP):
 # to 3; it returns None, having done nothing, for all but the plainest arguments, and the code here goes on.
 
 _torch = None          # the torch module, once a device call has needed it
-_fast = None           # the extension module _fastcall (csrc/fastcall.cpp) from then on
+_fast = None           # the extension module _fastcall (csrc/fastcall.cpp) from then on, or None where there is none for this torch
+
+
+def _load_fast(torch):
+    """The extension module, built in-tree beside libspqt.so, or None and a warning where it is missing or was built against another torch: what it does
+    inline depends on torch's version."""
+    try:
+        from . import _fastcall
+        if _fastcall.torch_version == torch.__version__:
+            return _fastcall
+        why = f"was built for torch {_fastcall.torch_version}, this is {torch.__version__}"
+    except (ImportError, AttributeError) as e:
+        why = f"does not load ({e})"
+    warnings.warn(f"_fastcall {why}: device calls take 2 to 3 us longer each; run `python -m paper_2511_04477_amd.build`", RuntimeWarning, stacklevel=4)
+    return None
 
 
 def _load_torch():
     global _torch, _fast
     import torch
     if _fast is None and isinstance(torch, types.ModuleType):
-        from . import _fastcall as _fast      # built in-tree beside libspqt.so
+        _fast = _load_fast(torch)
     _torch = torch
     return torch
 

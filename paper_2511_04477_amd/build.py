@@ -9,6 +9,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -29,8 +30,9 @@ GIVEUP_SOURCES = ["pack.cpp", "gemv.hip", "gemv_list.hip", "gemv_bal.hip"]
 # The library with reducers that never wait in a block-row spread over several XCDs: they hand the sum over at once.
 HANDOVER_LIB = os.path.join(PKG, "libspqt_handover.so")
 
-# Device calls of binding.py as a Python extension module: host code against torch's headers and libraries.
-FASTCALL_LIB = os.path.join(PKG, "_fastcall.so")
+# Device calls of binding.py as a Python extension module: host code against the headers of one Python and one torch.  The only part that needs
+# torch; the libraries are built, and the binding works, without it.
+FASTCALL_LIB = os.path.join(PKG, "_fastcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 FASTCALL_SOURCE = "fastcall.cpp"
 
 HIPCC_FLAGS = [
@@ -59,16 +61,20 @@ def _run(cmd, verbose: bool) -> None:
     noise = "is not a recognized feature for this target"
     out = "\n".join(ln for ln in res.stdout.splitlines() if noise not in ln)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError(os.path.basename(cmd[0]) + " failed:\n" + out)
     if verbose and out.strip():
         print(out)
 
 
 def _fastcall_command(lib: str):
-    import sysconfig
-    import torch
+    """The compile command of the extension module, or None without torch."""
+    try:
+        import torch
+    except ImportError:
+        return None
     base = os.path.dirname(torch.__file__)
     return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+            f'-DSPQT_TORCH_VERSION="{torch.__version__}"',
             "-isystem", os.path.join(base, "include"), "-isystem", os.path.join(base, "include/torch/csrc/api/include"), "-isystem", "/opt/rocm/include",
             "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), "-o", lib, os.path.join(CSRC, FASTCALL_SOURCE),
             "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
@@ -92,14 +98,19 @@ def build(verbose: bool = False) -> str:
     # every object of every library in one pool (longest first), then the links
     compiles = sorted((c for cs, _ in plan for c in cs), key=lambda c: -os.path.getsize(c[-1]))
     fastcall = FASTCALL_LIB + f".tmp{os.getpid()}"
-    compiles.insert(0, _fastcall_command(fastcall))
+    command = _fastcall_command(fastcall)
     with ThreadPoolExecutor(JOBS) as pool:
+        module = pool.submit(_run, command, verbose) if command else None
         list(pool.map(lambda c: _run(c, verbose), compiles))
-    os.replace(fastcall, FASTCALL_LIB)
-    for _, (lib, objs) in plan:
-        tmp = lib + f".tmp{os.getpid()}"
-        _run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
-        os.replace(tmp, lib)
+        for _, (lib, objs) in plan:
+            tmp = lib + f".tmp{os.getpid()}"
+            _run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
+            os.replace(tmp, lib)
+        if module:
+            module.result()
+            os.replace(fastcall, FASTCALL_LIB)
+        else:
+            print("torch is not installed: _fastcall, the quicker way of device calls, is not built", flush=True)
     return LIB
 
 

@@ -255,4 +255,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", "Device calls of bindi
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fastcall() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__fastcall() {
+    PyObject *m = PyModule_Create(&module);
+    // binding.py uses the module only with the torch whose headers it was compiled against
+    if (m && PyModule_AddStringConstant(m, "torch_version", SPQT_TORCH_VERSION) < 0) Py_CLEAR(m);
+    return m;
+}

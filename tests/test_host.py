@@ -491,3 +491,69 @@ def test_packers_agree_on_random_shapes_and_bytes():
         assert np.array_equal(spqt.spqt_cb_quantize(W), cb.pack(q, s))
 
     check()
+
+
+def test_build_needs_torch_only_for_the_extension_module(tmp_path, monkeypatch):
+    """Without torch, or where the module does not compile, the libraries are built all the same, and the error names the compiler that failed."""
+    from paper_2511_04477_amd import build
+    for name in ("LIB", "CALIB_LIB", "TIMELINE_LIB", "GIVEUP_LIB", "HANDOVER_LIB", "FASTCALL_LIB"):
+        monkeypatch.setattr(build, name, str(tmp_path / os.path.basename(getattr(build, name))))
+    monkeypatch.setattr(build, "OBJ", str(tmp_path / "obj"))
+    libraries = {os.path.basename(getattr(build, n)) for n in ("LIB", "CALIB_LIB", "TIMELINE_LIB", "GIVEUP_LIB", "HANDOVER_LIB")}
+    failing = []
+
+    def compiled(cmd, verbose):
+        if cmd[0] in failing:
+            raise RuntimeError("g++ failed")
+        open(cmd[cmd.index("-o") + 1], "w").close()
+
+    real_run = build._run
+    monkeypatch.setattr(build, "_run", compiled)
+    with monkeypatch.context() as m:
+        m.setitem(sys.modules, "torch", None)
+        build.build()
+    assert {f.name for f in tmp_path.iterdir() if f.is_file()} == libraries
+    for f in libraries:
+        (tmp_path / f).unlink()
+    failing.append("g++")
+    with pytest.raises(RuntimeError, match="g\\+\\+ failed"):
+        build.build()
+    assert {f.name for f in tmp_path.iterdir() if f.is_file()} == libraries
+    failing.clear()
+    build.build()
+    assert os.path.exists(build.FASTCALL_LIB)
+    with pytest.raises(RuntimeError, match="^g\\+\\+ failed"):
+        real_run(["g++", str(tmp_path / "no_such_file.cpp")], False)
+
+
+@pytest.mark.parametrize("module", ["missing", "without a version", "another torch's", "right"])
+def test_device_calls_do_without_the_extension_module(monkeypatch, module):
+    """A _fastcall that is missing or was built for another torch is left alone with a warning: the Python code of the binding serves the calls."""
+    import types
+    import warnings
+    import torch
+    import paper_2511_04477_amd as package
+    from paper_2511_04477_amd import binding
+    name = "paper_2511_04477_amd._fastcall"
+    there = None if module == "missing" else types.ModuleType(name)
+    if module in ("another torch's", "right"):
+        there.torch_version = torch.__version__ if module == "right" else "0.1"
+    monkeypatch.setitem(sys.modules, name, there)
+    monkeypatch.setattr(package, "_fastcall", there, raising=False)
+    if there is None:
+        monkeypatch.delattr(package, "_fastcall")
+    monkeypatch.setattr(binding, "_fast", None)
+    monkeypatch.setattr(binding, "_torch", None)
+    with warnings.catch_warnings(record=True) as told:
+        warnings.simplefilter("always")
+        with pytest.raises(spqt.SpqtError, match="CUDA tensor"):      # what the Python code says of host tensors
+            spqt.spqt_workspace_init(torch.zeros(4, dtype=torch.uint8))
+    assert binding._fast is (there if module == "right" else None)
+    said = [str(w.message) for w in told if "paper_2511_04477_amd.build" in str(w.message)]
+    assert len(said) == (0 if module == "right" else 1), said
+
+
+def test_the_built_extension_module_is_for_this_torch():
+    import torch
+    from paper_2511_04477_amd import _fastcall
+    assert _fastcall.torch_version == torch.__version__
