@@ -6,8 +6,8 @@
 // 512 x 1024: 11.0 us in Python, 6.8 here; 4 of each on 11001 x 4224, with the GPU's share, 45.7 / 34.3).
 //
 // Every function returns the library's status, or None where anything is other than what it knows for certain - a tensor that is not plainly a
-// dense one of the type asked for, another size, an int or a threshold of another type, a stream given, a mode or a tracer looking on - and then has done
-// nothing.  The caller goes on with the Python code, which accepts or refuses as it always did.
+// dense one of the type asked for, another size, an int or a threshold of another type, a stream given, a torch-function mode, which the Python code's reads of
+// the tensors would reach - and then has done nothing.  The caller goes on with the Python code, which accepts or refuses as it always did.
 #include <Python.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>

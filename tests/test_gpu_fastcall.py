@@ -99,8 +99,8 @@ def test_same_results(monkeypatch, layout, rows, half):
 
 
 def test_same_refusals(monkeypatch):
-    """Arguments that are no plain dense tensors of the right size and type, ints or floats: the module leaves them alone, and
-    what the call does is what the Python code does."""
+    """Arguments that are no plain dense tensors of the right size and type, ints or floats, or a stream: the module leaves them alone (None).  Those that it takes
+    (`taken`) and those that it leaves do what the Python code does with them: the same error, or the same outputs."""
     import torch
     import paper_2511_04477_amd as spqt
     from paper_2511_04477_amd import binding
@@ -110,32 +110,44 @@ def test_same_refusals(monkeypatch):
     idx = torch.zeros(K, dtype=torch.int32, device="cuda")
     cnt = torch.zeros(1, dtype=torch.int32, device="cuda")
     y = torch.zeros(M, dtype=torch.float32, device="cuda")
-    fast, stream = binding._fast, torch.cuda.current_stream()
+    fast, stream, side = binding._fast, torch.cuda.current_stream(), torch.cuda.Stream()
     at = binding.lib().at
     gather, gemv = (x, 0.5, idx, cnt, None), (w, M, K, x, idx, cnt, y, ws, None, 128, 0, 0, 0)
     assert fast.gather(at["spqt_gather"], *gather) == 0 and fast.gemv(at["spqt_gemv_ex"], *gemv) == 0
+    torch.cuda.synchronize()
+    listed, outputs = (idx.clone(), cnt.clone()), (idx, cnt, y)
 
     def outcome(fn, args):
+        """What the call raises, or the outputs that it leaves behind."""
+        for t, v in zip(outputs, listed if fn is spqt.spqt_gemv else (idx.new_full((K,), -1), cnt.new_full((1,), -1))):
+            t.copy_(v)
+        y.fill_(7.0)
+        torch.cuda.synchronize()
         try:
             fn(*args)
             torch.cuda.synchronize()
-            return "taken"
+            return "done", [t.cpu().numpy().tobytes() for t in outputs]
         except Exception as e:
+            torch.cuda.synchronize()
             return type(e).__name__, str(e)
 
     wide = torch.zeros(K, 2, dtype=torch.float16, device="cuda")[:, 0]
-    for fn, f, name, args, changes in (
+    for fn, f, name, args, left, taken in (
             (spqt.spqt_gather, fast.gather, "spqt_gather", gather,
-             [(0, x.cpu()), (0, x.float()), (0, wide), (0, None), (0, x[:1000]), (1, 1), (1, "a"), (1, None), (2, idx[:100]), (2, idx.long()), (3, cnt[:0]),
-              (4, stream), (4, stream.cuda_stream), (0, torch.nn.Parameter(x, requires_grad=False)), (0, x.to_sparse()), (0, x.view(1, 1, K))]),
+             [(0, x.cpu()), (0, x.float()), (0, wide), (0, None), (1, 1), (1, "a"), (1, None), (2, idx[:100]), (2, idx.long()), (3, cnt[:0]), (4, stream), (4, side),
+              (4, stream.cuda_stream), (4, 0), (0, x.to_sparse()), (0, x.view(1, 1, K))],
+             [(0, x[:1000]), (0, torch.nn.Parameter(x, requires_grad=False)), (0, x.view(2, 512)), (1, float("nan")), (1, float("inf")), (4, None)]),
             (spqt.spqt_gemv, fast.gemv, "spqt_gemv_ex", gemv,
-             [(0, w[:-1]), (0, w.view(-1, 2)[:, 0]), (1, M + 1), (1, 512.0), (1, True), (1, 1 << 70), (2, 0), (2, 1000), (3, x[:512]), (3, x.view(2, 512)), (4, None),
-              (5, None), (6, y.double()), (6, y[:100]), (7, None), (7, ws[:300]), (8, stream), (9, 32), (9, 64), (10, -1), (10, 65), (11, 3), (12, 1 << 40)])):
-        for i, other in changes:
+             [(0, w[:-1]), (0, w.view(-1, 2)[:, 0]), (1, M + 1), (1, 512.0), (1, True), (1, 1 << 70), (2, 0), (2, 1000), (3, x[:512]), (3, x.view(2, 512)),
+              (5, None), (6, y.double()), (6, y[:100]), (8, stream), (8, side), (8, 0), (9, 32), (9, 64), (12, 1 << 40)],
+             [(4, None), (7, None), (7, ws[:300]), (10, -1), (10, 65), (11, 3), (12, 2)])):
+        for i, other, is_left in [(*c, True) for c in left] + [(*c, False) for c in taken]:
             changed = list(args)
             changed[i] = other
-            print(f"fastcall refusals {name} argument {i}", flush=True)
+            print(f"fastcall refusals {name} argument {i} {'left' if is_left else 'taken'}", flush=True)
             monkeypatch.setattr(binding, "_fast", None)
             want = outcome(fn, changed)
             monkeypatch.setattr(binding, "_fast", fast)
             assert outcome(fn, changed) == want, (name, i, other)
+            assert (f(at[name], *changed) is None) == is_left, (name, i, other)
+            torch.cuda.synchronize()
