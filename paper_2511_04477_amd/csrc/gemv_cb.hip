@@ -153,7 +153,7 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
             float sc[8], mn[8];
             if (FUSED && lane >= n) sv = u32x4{0u, 0u, 0u, 0u};      // an empty pass points at column 0, which may be dropped
             if (KQ) {
-                const float d = half_bits_to_float(sv.x & 0xFFFFu), dm = half_bits_to_float(sv.x >> 16);
+                const float d = half_bits_to_float(sv.x & 0xFFFFu), dm = lane < n ? half_bits_to_float(sv.x >> 16) : 0.0f;
                 const uint64_t lo = (uint64_t)sv.y | ((uint64_t)sv.z << 32);
                 const uint32_t hi = sv.w;
 #pragma unroll
@@ -190,14 +190,14 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
             }
             __builtin_amdgcn_wave_barrier();
         };
-        // Step u: 8 columns.  The bias sum takes the product itself, or x * minimum.
+        // Step u: 8 columns.  The bias sum takes the product itself, or x * minimum in one launch.
         auto step = [&](int u) {
             if (BATCH > 2) keep_order();     // x of several steps at once would not fit the registers
 #pragma unroll
             for (int b = 0; b < BATCH; ++b) {
                 const float xl = stage_xs[wave][b][u * 8 + cg][seg];
                 fma_step(w[u], xl, acc[b]);
-                bsum[b] += KQ ? stage_xm[wave][b][u * 8 + cg][seg] : xl;
+                if (!KQ || FUSED) bsum[b] += KQ ? stage_xm[wave][b][u * 8 + cg][seg] : xl;
             }
         };
         if (FUSED) {
@@ -218,15 +218,16 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
         //   dense, one row   14336 x 4096                  2.84e-7 / 2.36e-7   8.62 / 8.62     4096 x 14336   2.73e-7 / 2.28e-7   9.18 / 9.25
         //   list, 4 rows     14336 x 4096 at 60 %          2.64e-7 / 2.20e-7   18.75 / 18.76
         //   dense, 4 rows    4096 x 4096                   1.95e-7 / 1.48e-7   9.37 / 9.36
-        //   K-quant          14336 x 4096 at 50 %          1.24e-7 / 1.15e-7   9.95 / 9.88     4 rows at 60 %   1.36e-7 / 1.33e-7   19.8 / 20.0
+        //   K-quant          14336 x 4096 at 50 %          1.24e-7 / 1.15e-7   9.95 / 9.88     4 rows at 60 %   1.36e-7 / 1.33e-7   19.9 / 19.95
         // In one launch it is slower (K-quant 13824 x 5120 9.03 / 9.12), and the sums stay as they were.
         // Where colblock4_list_splits chose the launch shape (kLongSlicesBit), a slice well over two passes long takes the second pass so, too: where most columns are
         // kept, its four passes would be further off than the two of the slices that they replace (14336 x 4096 with S = 9, no pass centred / S = 4, one pass / S = 4,
         // two passes: all kept 2.18e-7 / 2.36e-7 / 2.00e-7, 80 % kept 2.00e-7 / 2.10e-7 / 1.75e-7; 12.8 / 11.65 / 11.71 us and 11.4 / 10.6 / 10.65).
         constexpr bool kCentred = !FUSED;
         constexpr bool kTwice = BATCH == 1 && !DENSE && !FUSED && !KQ;
-        // The products of the staged pass carry no bias: the sums are ahead of it by what its x adds up to.  (K-quant: what the steps of that pass count is
-        // dropped instead; a minimum may be infinite where the products are not, and taken off and added again it would be NaN.)
+        // The products of the staged pass carry no bias: the sums are ahead of it by what its x adds up to.  (K-quant: the minima of such a pass are not counted
+        // at all, those of the others where the pass is staged.  Counted by the steps of every pass and taken off for this one an infinite minimum would be NaN, and the
+        // steps' reads took as long or longer: list at 60 % 11008 x 4096 2 rows 11.45 / 11.29 us, 4096 x 4096 4 rows 12.62 / 12.35, dense 4096 x 4096 3 rows 8.70 / 8.42.)
         auto centre = [&](bool first_pass) {
 #pragma unroll
             for (int b = 0; b < BATCH; ++b) {
@@ -239,18 +240,19 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
                 for (int i = 0; i < 32; ++i) acc[b][i] = first_pass ? (i & 1 ? odd : even) : acc[b][i] + (i & 1 ? odd : even);
             }
         };
+        auto count_minima = [&]() {
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b) {
+                if (BATCH > 2) keep_order();
+#pragma unroll
+                for (int u = 0; u < 8; ++u) bsum[b] += stage_xm[wave][b][u * 8 + cg][seg];
+            }
+        };
         if constexpr (kCentred) {
-            if (KQ && lane >= n) sv = u32x4{0u, 0u, 0u, 0u};      // all 64 entries are counted: none of a column that is not the lane's
             stage();
             centre(true);
         }
-        const int first_end = pos;
-        auto drop_counted = [&]() {
-#pragma unroll
-            for (int b = 0; b < BATCH; ++b) bsum[b] = 0.0f;
-        };
         while (more(pos)) {
-            const bool first = KQ && kCentred && pos == first_end;
             if (!kCentred) stage();
             const bool whole = !FUSED || n > kPassCols / 2;
             pos = head(pos);
@@ -267,15 +269,14 @@ __global__ __launch_bounds__(WAVES * 64) void spqt_cb_gemv_kernel(
             keep_order();
             load_half(1);
             keep_order();
-            if (first) drop_counted();
             if (kCentred) stage();
+            if (KQ && kCentred) count_minima();
             if (kTwice && pos == second_end && end - pos > kPassCols / 2 && (M & kLongSlicesBit)) centre(false);
         }
         if (!kCentred) stage();
 #pragma unroll
         for (int u = 0; u < 8; ++u)
             if (u * 8 < n) step(u);
-        if (KQ && kCentred && pos == first_end) drop_counted();
     } else {
         outputs.read_now();
     }

@@ -469,10 +469,10 @@ def test_list_error_at_any_sparsity(gpu, sparsity, bound):
 
 
 @pytest.mark.parametrize("batch", [1, 3])
-@pytest.mark.parametrize("columns", [40, 128, 384])
-def test_cbk_infinite_minimum(gpu, batch, columns):
-    """The sums start at the minima of a slice's first pass; an infinite one (first column, its x of either sign) makes every output infinite, not NaN.
-    One wavefront; one pass, two and six."""
+@pytest.mark.parametrize("columns,at", [(40, 0), (128, 0), (384, 0), (101, 0), (101, 64)])
+def test_cbk_infinite_minimum(gpu, batch, columns, at):
+    """The sums start at the minima of a slice's first pass; an infinite one (first column of the first or of a short
+    second pass, its x of either sign) makes every output infinite, not NaN.  One wavefront; one pass, two and six."""
     torch, spqt, dev = gpu
     M, K = 512, 384
     r = np.random.default_rng(9800)
@@ -480,7 +480,7 @@ def test_cbk_infinite_minimum(gpu, batch, columns):
     head = chunks[:, :, :2048].reshape(M // 256, K // 128, 128, 16)
     head[..., :4] = r.uniform(0.001, 0.01, head.shape[:3] + (2,)).astype(np.float16).view(np.uint8)
     head[..., 4:] |= 0x41                       # no field is 0
-    head[:, 0, 0, 2:4] = np.frombuffer(np.float16(np.inf).tobytes(), np.uint8)
+    head[:, 0, at, 2:4] = np.frombuffer(np.float16(np.inf).tobytes(), np.uint8)
     chunks[:, :, :2048] = head.reshape(M // 256, K // 128, 2048)
     packed = torch.from_numpy(chunks.reshape(-1)).to(dev)
     ws = spqt.new_workspace(M, K, batch)
@@ -489,7 +489,7 @@ def test_cbk_infinite_minimum(gpu, batch, columns):
         x = x if batch > 1 else x[0].contiguous()
         idx = torch.arange(K, dtype=torch.int32, device=dev)
         cnt = torch.full((1,), columns, dtype=torch.int32, device=dev)
-        say(f"K-quant infinite minimum batch={batch} columns={columns} sign={sign}")
+        say(f"K-quant infinite minimum batch={batch} columns={columns} at={at} sign={sign}")
         y = torch.full((batch, M) if batch > 1 else (M,), float("nan"), dtype=torch.float32, device=dev)
         spqt.spqt_cbk_gemv(packed, M, K, x, idx, cnt, y, ws, splits=1, waves=1)
         torch.cuda.synchronize()
