@@ -302,7 +302,7 @@ __device__ __forceinline__ void combine_block_row(const float *red, int tid, con
     constexpr int kTogether = kPerThread < 2 ? kPerThread : 2;
     const int S = o.S;
     Word *slots = reinterpret_cast<Word *>(o.slots);    // [S][kUnits]; S - 1: handed over
-        for (int i0 = tid; kUnits == kThreads || i0 < kUnits; i0 += kTogether * kThreads) {
+    for (int i0 = tid; kUnits == kThreads || i0 < kUnits; i0 += kTogether * kThreads) {
         uint32_t at[kTogether];
         float sum[kTogether][kVals];
 #pragma unroll

@@ -101,7 +101,7 @@ __device__ __forceinline__ void load_columns(const uint8_t *base, uint32_t off, 
 // The matrix cores align products by the exponent FIELDS, so bits that a half has above its code are bits of precision lost in every product: codes sit as
 // high as one shift per two codes brings them.  That is by row, not only on the whole: error against 64-bit arithmetic of rows 0, 1, 2, 3 modulo 4,
 // dense 5120 x 5120, 1.7e-7 9.4e-8 1.7e-7 9.2e-8 with Laplace x, 5.5e-7 1.0e-7 5.4e-7 1.0e-7 with SiLU products.  (Other places for six instructions: at bits 6, 4, 2,
-// 6 with the bias at 2 2.6e-7 2.8e-7 5.4e-7 2.6e-7, at 7, 4, 3, 7 with SiLU products 1.1e-7 2.0e-7 5.4e-7 1.0e-7.  For seven, 7, 7, 3, 7, 1.1e-7 1.0e-7
+// 6 with the bias at 2 2.6e-7 2.8e-7 5.4e-7 2.6e-7 - on 1024 x 5120 rows 0 were closer so, 1.3e-7, now 1.7e-7 -, at 7, 4, 3, 7 with SiLU products 1.1e-7 2.0e-7 5.4e-7 1.0e-7.  For seven, 7, 7, 3, 7, 1.1e-7 1.0e-7
 // 5.4e-7 1.0e-7 and 0.5 to 1 % longer calls; for eight, all at bit 7, 1.0e-7 in every row and 1 to 3 %.)
 template <int Q>
 __device__ __forceinline__ void quarter_pass(const u32x2 (&w)[16], const ReadsX &rx, f32x4 (&d)[4]) {
